@@ -10,26 +10,25 @@
 //   * off[n+1] is the row capacity layout fixed at load time (OffT = int32
 //     or int64); deg[n] is the current row length (removals shrink rows in
 //     place, keeping them sorted).
-//   * The interaction matrix is stored sparse, one record per (vertex,
-//     neighbour community) in the row's own slot range [off[v], off[v] + ell):
-//     reckey[] holds the community (ascending within a vertex), recdat[] the
-//     first row position of that community's run, its length f and the weight
-//     w_v(c).
-//   * meta[v] = {deg, ell, p, q} of the last pass.  G' (the edges between
-//     communities) is implicit: v's foreign neighbours are the row positions
-//     outside [p, q), in ascending id order.
+//   * meta[v] = {deg, ell, p, q} of the last pass: v's foreign neighbours are
+//     the row positions outside [p, q), in ascending id order.
+//   * G' (the edges between communities) has compact slots: v's foreign
+//     entries own the slots [goff[v], goff[v + 1]) in row order (goff is the
+//     prefix of the load-time foreign degrees; removals only shrink the
+//     lists), and fcol[s] is the slot's neighbour.  Slots fit 32 bits.
+//   * The interaction matrix is stored sparse: a foreign community c of v is
+//     one run of v's slots, and the run's first slot s (its leader) holds the
+//     record prec[s] = {w_v(c), f, c}, written by v's row pass.  The own
+//     community's record is wown[v] and q - p.
 //   * Out-lists orient G': vertices are ranked by (load-time foreign degree,
 //     id), and out(v) lists v's foreign neighbours of higher rank.  Every
 //     triangle of G' is {u, x, y} with y in out(x) for exactly one ordering of
 //     its other two vertices, and the lists are short (a hub's foreign
 //     neighbours are mostly of lower rank).  Removals tombstone entries (~id).
-//   * Pair facts: every foreign row entry e = (w, u) gets prec[e], written by
-//     w's row pass: w_w(C(u)) and the run of C(u) in w's row.  The G' entries
-//     (u, w) of u have link slots [goff[u], goff[u + 1]) in foreign-list order
-//     (goff is the prefix of the load-time foreign degrees; removals only
-//     shrink the lists): plink[s] = the index of the reverse entry (w, u) and
-//     w's out-list range.  The score pass reads u's links as one contiguous
-//     stream and each pair's facts with one independent load.
+//   * Links: the slot s of (u, w) has plink[s] = the leader of C(u)'s run and
+//     the slot of u in w's list, and w's out-list range.  The score pass reads
+//     u's links as one contiguous stream and each pair's facts, the record at
+//     the leader, with one independent load.
 //   * Work is cut at load time into static tiles of consecutive vertices: row
 //     tiles bound the row capacity they cover, score tiles the number of
 //     foreign entries (removals only shrink both).  Vertices too large for a
@@ -123,53 +122,33 @@ enum KernelId {
     K_COUNT
 };
 
-struct __align__(16) RecDat {
-    int pos;   // first row position of the community's run
-    int f;     // run length = number of neighbours in the community
-    double w;  // w_v(community)
-};
-
 struct __align__(16) VMeta {
     int deg, ell, p, q;
 };
 
-// Everything a pass needs about a vertex, in one 64-byte card (one memory
-// line for a gathered vertex): the static row start, pair-slot start and
-// community, and the last pass's row facts, a_v and the first record keys
-// (INT_MAX past ell).
-struct __align__(64) VCard {
-    long long off;   // row start
-    long long goff;  // first pair slot
-    VMeta m;         // {deg, ell, p, q} of the last pass
-    int pad;
-    int lab;         // community
-    double a;        // cbrt(own-community weight) of the last pass
-    int key[4];      // first record keys of the last pass
-};
-
-// The facts of the pair (u, w) at w's row entry (w, u), written by w's row
-// pass: w_w(C(u)), the length f of C(u)'s run in w's row and the distance
-// from the entry back to the run's first entry.
+// The interaction-matrix record of a vertex v and a foreign community c, at
+// the leader slot of c's run in v's list: w_v(c), the run's length f (the
+// number of v's neighbours in c) and c.
 struct __align__(16) PairRec {
     double w;
     int f;
-    int back;
+    int c;
 };
 
-// An out-list entry x -> y: the indices of the row entries (x, y) in x's row
-// and (y, x) in y's row (a type-I hit reads the pair facts at both).
-struct __align__(16) OutEnt {
-    long long xy, yx;
+// An out-list entry x -> y: the leader slots of C(y)'s run in x's list and of
+// C(x)'s run in y's list (a type-I hit reads the records at both).
+struct __align__(8) OutEnt {
+    int xy, yx;
 };
 
-// A link slot (u, w): the index of the row entry (w, u) and w's out-list
-// range (tombstones included).
+// The link of the slot of (u, w): the leader slot of C(u)'s run in w's list,
+// the slot of (w, u), and w's out-list range (tombstones included).
 struct __align__(16) PairLink {
-    long long e;
+    int lead;
+    int slot;
     int oo;
     int on;
 };
-static_assert(sizeof(VCard) == 64, "one card per 64 bytes");
 
 // A row tile: vertices [v0, v1) whose rows occupy entries [e0, e0 + te).
 struct __align__(16) RowTile {
@@ -241,9 +220,10 @@ struct DeviceGraph {
     int2 *shub_chunk = nullptr;     // [chunks] (hub, chunk index within the hub)
     HubPart *hub_part = nullptr;    // [chunks] chunk partials
     int64_t *oo = nullptr;      // [n+1] out-list offsets
-    int64_t *goff = nullptr;    // [n+1] pair-slot offsets
-    PairRec *prec = nullptr;    // [nnz] pair facts at foreign row entries
-    PairLink *plink = nullptr;  // [link slots]
+    int32_t *goff = nullptr;    // [n+1] slot offsets of the foreign entries
+    int32_t *fcol = nullptr;    // [slots] foreign neighbours
+    PairRec *prec = nullptr;    // [slots] records at the leader slots
+    PairLink *plink = nullptr;  // [slots]
     int32_t *cstart = nullptr;  // [k+1] first internal id of each community
     unsigned long long *wpart = nullptr;  // [kWorkBlocks] partials of the on-demand W1 count
     // incremental re-score
@@ -252,7 +232,7 @@ struct DeviceGraph {
     int32_t *vscore = nullptr;              // [n] score tile block, or -1 - score hub index
     unsigned long long *wblk = nullptr;  // [64] per-workgroup maxima of k_wmax
     unsigned int *wticket = nullptr;     // k_wmax's finishing ticket (zero between passes)
-    OutEnt *oe = nullptr;         // [out-list entries] row entries of each out-list entry's edge
+    OutEnt *oe = nullptr;         // [out-list entries] leader slots of each out-list entry's edge
     uint32_t *hfilter = nullptr;  // [big hubs][kFilterWords] membership filter of each big hub's foreign neighbours
     uint8_t *rflag = nullptr, *cflag = nullptr, *hflag = nullptr;  // flags: row blocks, score-hub chunks, score hubs (whole)
     int32_t *elist = nullptr, *abin = nullptr;  // [n] changed rows; affected tile vertices by bin
@@ -274,9 +254,7 @@ struct DeviceGraph {
     double *bscores = nullptr;
     int64_t *bcounts = nullptr;             // [n_graphs]
     int32_t *outl = nullptr;    // [m'] out-lists: foreign neighbours of higher rank, ascending (removed: ~id)
-    int32_t *reckey = nullptr;  // [nnz] interaction-matrix record keys
-    RecDat *recdat = nullptr;   // [nnz] interaction-matrix record data
-    VCard *card = nullptr;      // [n]
+    VMeta *meta = nullptr;      // [n] row facts of the last pass
     double *wown = nullptr, *R = nullptr;
     double *av = nullptr;       // [n] a_v = cbrt(own-community weight) of the last pass
     double *raw = nullptr;      // [n] Eq. RSI sums before the w_max and d(d-1) division

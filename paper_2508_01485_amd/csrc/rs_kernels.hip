@@ -105,11 +105,9 @@ struct RowArgs {
     const RowTile *tiles;
     const int32_t *hubs;
     int n_tiles, n_hubs, tiles_per_xcd;
-    int32_t *reckey;
-    RecDat *recdat;
-    VCard *card;
-    const int64_t *goff;
-    PairRec *prec;     // pair facts at the foreign row entries, written by this pass
+    VMeta *meta;
+    const int32_t *goff;
+    PairRec *prec;     // records at the leader slots, written by this pass
     const int *blist;  // incremental pass: the listed blocks (k_rows_inc)
     double *wown, *R, *raw;
     double *av;  // [n] a_v = cbrt(own-community weight), dense for the score pass's run sums
@@ -128,29 +126,19 @@ struct RowAcc {
     unsigned long long nb, dp, ell, ellx;
 };
 
-// The vertex's row facts of this pass: its card (row facts, a_v, first four
-// record keys k4), own weight, and zero scores for a non-border vertex.
+// The vertex's row facts of this pass, its own weight and a_v, and zero
+// scores for a non-border vertex.
 template <typename OffT>
-__device__ __forceinline__ void finish_row(const RowArgs<OffT> &A, int v, int d, const RowResult &r, int4 k4,
-                                           long long off, long long goff, int lab, RowAcc &acc) {
+__device__ __forceinline__ void finish_row(const RowArgs<OffT> &A, int v, int d, const RowResult &r, RowAcc &acc) {
     const int fown = r.q - r.p;
     const int dprime = d - fown;
-    VCard c;  // written whole: one aligned 64-byte store, no partial lines
-    c.off = off;
-    c.goff = goff;
-    c.m.deg = d;
-    c.m.ell = r.ell;
-    c.m.p = r.p;
-    c.m.q = r.q;
-    c.pad = 0;
-    c.lab = lab;
-    c.a = cbrt(r.wown);
-    A.av[v] = c.a;
-    c.key[0] = k4.x;
-    c.key[1] = k4.y;
-    c.key[2] = k4.z;
-    c.key[3] = k4.w;
-    A.card[v] = c;
+    VMeta m;
+    m.deg = d;
+    m.ell = r.ell;
+    m.p = r.p;
+    m.q = r.q;
+    A.meta[v] = m;
+    A.av[v] = cbrt(r.wown);
     A.wown[v] = r.wown;
     acc.wmax = fmax(acc.wmax, r.lmax);
     acc.ell += (unsigned long long)r.ell;
@@ -227,7 +215,7 @@ static_assert(kRowTile % kBlock == 0 && kRowTile <= 65535 && kRowTileV % kBlock 
 // Streaming state of a hub row (one workgroup).
 struct HubSeg {
     int prev, next_prev;                     // label before the segment / of its last entry
-    int open_start, open_label, open_slot;   // run open at the segment boundary (open_start < 0: none)
+    int open_start, open_label;              // run open at the segment boundary (open_start < 0: none)
     int nruns;                               // runs started before the segment
     double red[kRowW];
     int ired[kRowW];
@@ -245,7 +233,8 @@ struct RowTileShared {
     int runlab[kRowTile];                // label of each run (-1: removed tail)
     double vX[kRowTileV];
     int vd[kRowTileV], vell[kRowTileV], vlab[kRowTileV];
-    unsigned short vrf[kRowTileV], vo[kRowTileV];
+    int vslot[kRowTileV];            // slot of a foreign entry below the own run, minus its tile-local entry
+    unsigned short vfo[kRowTileV];   // own run's length
 };
 
 __device__ __forceinline__ int run_index(const RowTileShared &S, int e) {
@@ -271,7 +260,7 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
         L[i] = e < TE ? A.clab[e0 + e] : -2;
     }
     int vo[kVU], vc[kVU], vdeg[kVU], vlab[kVU];
-    long long vgo[kVU];
+    int vgo[kVU];
 #pragma unroll
     for (int j = 0; j < kVU; ++j) {
         // a slot past the tile loads the tile's first vertex (tiles are never
@@ -359,50 +348,32 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
         S.vd[i] = d;
         S.vlab[i] = cv;
         S.vell[i] = ell;
-        S.vrf[i] = (unsigned short)rf;
-        S.vo[i] = (unsigned short)o;
+        S.vslot[i] = vgo[j] - o;
+        S.vfo[i] = (unsigned short)fown;
         RowResult res;
         res.ell = ell;
         res.p = below;
         res.q = below + fown;
         res.wown = fown > 0 ? weight_present_t(S.tab, d, X, ell, fown) : weight_absent_t(S.tab, d, X, ell);
         res.lmax = res.wown;
-        int4 k4;  // the first record keys: the labels of the first valid runs
-        k4.x = ell > 0 ? S.runlab[rf] : INT_MAX;
-        k4.y = ell > 1 ? S.runlab[rf + 1] : INT_MAX;
-        k4.z = ell > 2 ? S.runlab[rf + 2] : INT_MAX;
-        k4.w = ell > 3 ? S.runlab[rf + 3] : INT_MAX;
-        finish_row(A, v0 + i, d, res, k4, (long long)e0 + o, vgo[j], cv, acc);
+        finish_row(A, v0 + i, d, res, acc);
     }
     __syncthreads();
+    // a foreign run's record goes to its leader slot; the own community's
+    // weight is the vertex's own weight already
     for (int r = tid; r < total; r += kBlock) {
         const int lb = S.runlab[r];
         if (lb < 0) continue;
         const int i = S.runv[r];
-        const int f = (int)S.runpos[r + 1] - (int)S.runpos[r];
-        const double w = weight_present_t(S.tab, S.vd[i], S.vX[i], S.vell[i], f);
-        const int o = S.vo[i];
-        const OffT idx = e0 + (OffT)(o + (r - (int)S.vrf[i]));
-        A.reckey[idx] = lb;
-        RecDat rd;
-        rd.pos = (int)S.runpos[r] - o;
-        rd.f = f;
-        rd.w = w;
-        A.recdat[idx] = rd;
-        acc.wmax = fmax(acc.wmax, w);
-        // pair facts at the run's entries when it is another community's:
-        // entry (w, u) gets the record of C(u) in w's row (the weight computed
-        // once per run; neighbouring threads' runs are neighbouring entries)
-        if (lb != S.vlab[i]) {
-            const int p0 = (int)S.runpos[r];
-            PairRec pr;
-            pr.w = w;
-            pr.f = f;
-            for (int t = 0; t < f; ++t) {
-                pr.back = t;
-                A.prec[e0 + (OffT)(p0 + t)] = pr;
-            }
-        }
+        const int cv = S.vlab[i];
+        if (lb == cv) continue;
+        const int p0 = (int)S.runpos[r];
+        PairRec pr;
+        pr.f = (int)S.runpos[r + 1] - p0;
+        pr.w = weight_present_t(S.tab, S.vd[i], S.vX[i], S.vell[i], pr.f);
+        pr.c = lb;
+        A.prec[S.vslot[i] + p0 - (lb > cv ? (int)S.vfo[i] : 0)] = pr;
+        acc.wmax = fmax(acc.wmax, pr.w);
     }
 }
 
@@ -412,31 +383,32 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
 // (labels, run starts by ballot, runs closed flat over LDS), twice: the first
 // pass counts the runs, X and the own run, the second writes the weighted
 // records.  The run still open at a segment's end is carried to the next.
+struct HubTotals {
+    double X;
+    int ell, fown;  // (second pass)
+    int go;         // first slot
+};
 template <int PASS, typename OffT>
-__device__ __forceinline__ void hub_run(const RowArgs<OffT> &A, OffT rb, int d, int cv, double X, int ell, int label,
-                                        int start, int f, int slot, double &xpart, int &below, int &fown,
-                                        double &lmax) {
+__device__ __forceinline__ void hub_run(const RowArgs<OffT> &A, int d, int cv, const HubTotals &T, int label, int start,
+                                        int f, double &xpart, int &below, int &fown, double &lmax) {
     if (PASS == 1) {
         xpart += flogf(f);
         if (label == cv)
             fown = f;
         else if (label < cv)
             below += f;
-        A.reckey[rb + slot] = label;
-        RecDat rd;
-        rd.pos = start;
-        rd.f = f;
-        rd.w = 0.0;  // set by the second pass, once X and ell are known
-        A.recdat[rb + slot] = rd;
-    } else {
-        const double w = weight_present(d, X, ell, f);
-        A.recdat[rb + slot].w = w;
-        lmax = fmax(lmax, w);
+    } else if (label != cv) {
+        PairRec pr;
+        pr.w = weight_present(d, T.X, T.ell, f);
+        pr.f = f;
+        pr.c = label;
+        A.prec[T.go + start - (label > cv ? T.fown : 0)] = pr;
+        lmax = fmax(lmax, pr.w);
     }
 }
 
 template <int PASS, typename OffT>
-__device__ void hub_pass(const RowArgs<OffT> &A, RowTileShared &S, OffT rb, int d, int cv, double X, int ell,
+__device__ void hub_pass(const RowArgs<OffT> &A, RowTileShared &S, OffT rb, int d, int cv, const HubTotals &T,
                          double &xpart, int &below, int &fown, double &lmax) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     HubSeg &H = S.hub;
@@ -494,51 +466,23 @@ __device__ void hub_pass(const RowArgs<OffT> &A, RowTileShared &S, OffT rb, int 
         __syncthreads();
         const bool last = seg0 + TE >= d;
         const int nr0 = H.nruns;
-        if (PASS == 2) {
-            // pair facts at this segment's foreign entries: the entry's run
-            // (the one carried in, or the last run start at or before it)
-            // and that run's record from the first pass
-#pragma unroll
-            for (int i = 0; i < kRowU; ++i) {
-                const int e = wave * (kRowTile / kRowW) + i * 64 + lane;
-                if (e >= TE || L[i] < 0 || L[i] == cv) continue;
-                int lo = 0, hi = total;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if ((int)S.runpos[mid] <= e)
-                        lo = mid + 1;
-                    else
-                        hi = mid;
-                }
-                const int slot = lo == 0 ? H.open_slot : nr0 + lo - 1;
-                const RecDat rd = A.recdat[rb + slot];
-                PairRec pr;
-                pr.w = weight_present(d, X, ell, rd.f);
-                pr.f = rd.f;
-                pr.back = seg0 + e - rd.pos;
-                A.prec[rb + seg0 + e] = pr;
-            }
-        }
         // the run carried from the previous segment closes at this segment's
         // first run start (or at the row's end)
         if (tid == 0 && H.open_start >= 0 && (total > 0 || last)) {
             const int end = total > 0 ? seg0 + (int)S.runpos[0] : d;
-            hub_run<PASS, OffT>(A, rb, d, cv, X, ell, H.open_label, H.open_start, end - H.open_start, H.open_slot,
-                                xpart, below, fown, lmax);
+            hub_run<PASS, OffT>(A, d, cv, T, H.open_label, H.open_start, end - H.open_start, xpart, below, fown, lmax);
             H.open_start = -1;
         }
         const int closed = last ? total : total - 1;  // the segment's last run stays open unless the row ends
         for (int r = tid; r < closed; r += kBlock) {
             const int f = (int)S.runpos[r + 1] - (int)S.runpos[r];
-            hub_run<PASS, OffT>(A, rb, d, cv, X, ell, S.runlab[r], seg0 + (int)S.runpos[r], f, nr0 + r, xpart,
-                                below, fown, lmax);
+            hub_run<PASS, OffT>(A, d, cv, T, S.runlab[r], seg0 + (int)S.runpos[r], f, xpart, below, fown, lmax);
         }
         __syncthreads();
         if (tid == 0) {
             if (!last && total > 0) {
                 H.open_start = seg0 + (int)S.runpos[total - 1];
                 H.open_label = S.runlab[total - 1];
-                H.open_slot = nr0 + total - 1;
             }
             H.nruns = nr0 + total;
             H.prev = H.next_prev;
@@ -587,27 +531,23 @@ __device__ void hub_row(const RowArgs<OffT> &A, RowTileShared &S, int v, RowAcc 
     const int cv = A.lab[v];
     double xpart = 0.0, lmax = 0.0;
     int below = 0, fown = 0;
-    hub_pass<1, OffT>(A, S, rb, d, cv, 0.0, 0, xpart, below, fown, lmax);
-    const double X = block_sum_d(xpart, S.hub.red);
+    HubTotals T = {0.0, 0, 0, A.goff[v]};
+    hub_pass<1, OffT>(A, S, rb, d, cv, T, xpart, below, fown, lmax);
+    T.X = block_sum_d(xpart, S.hub.red);
     const int p = block_sum_i(below, S.hub.ired);
-    const int fo = block_sum_i(fown, S.hub.ired);  // one thread holds the own run's length
-    const int ell = S.hub.nruns;
+    T.fown = block_sum_i(fown, S.hub.ired);  // one thread holds the own run's length
+    T.ell = S.hub.nruns;
     __syncthreads();  // everyone has read pass 1's totals before pass 2 resets them
-    hub_pass<2, OffT>(A, S, rb, d, cv, X, ell, xpart, below, fown, lmax);
-    const double lm = block_max_d(lmax, S.hub.red);  // (its barriers order pass 2's record writes)
+    hub_pass<2, OffT>(A, S, rb, d, cv, T, xpart, below, fown, lmax);
+    const double lm = block_max_d(lmax, S.hub.red);
     if (threadIdx.x == 0) {
         RowResult r;
-        r.ell = ell;
+        r.ell = T.ell;
         r.p = p;
-        r.q = p + fo;
-        r.wown = fo > 0 ? weight_present(d, X, ell, fo) : weight_absent(d, X, ell);
+        r.q = p + T.fown;
+        r.wown = T.fown > 0 ? weight_present(d, T.X, T.ell, T.fown) : weight_absent(d, T.X, T.ell);
         r.lmax = fmax(lm, r.wown);
-        int4 k4;
-        k4.x = ell > 0 ? A.reckey[rb + 0] : INT_MAX;
-        k4.y = ell > 1 ? A.reckey[rb + 1] : INT_MAX;
-        k4.z = ell > 2 ? A.reckey[rb + 2] : INT_MAX;
-        k4.w = ell > 3 ? A.reckey[rb + 3] : INT_MAX;
-        finish_row(A, v, d, r, k4, (long long)rb, A.goff[v], cv, acc);
+        finish_row(A, v, d, r, acc);
     }
 }
 
@@ -783,10 +723,8 @@ __global__ __launch_bounds__(kBlock) void k_reduce_rows(const RowPart *part, int
 }
 
 // ============================================================ score pass
-template <typename OffT>
 struct ScoreArgs {
-    const OffT *off;
-    const int32_t *col, *lab;
+    const int32_t *goff, *fcol;  // slots of the foreign entries and their neighbours
     const int2 *tiles;
     const int32_t *hubs;
     int n_tiles, n_hubs, tiles_per_xcd;
@@ -796,14 +734,12 @@ struct ScoreArgs {
     HubPart *hub_part;
     const int32_t *outl;
     const int64_t *oo;      // out-list offsets
-    const int32_t *reckey;
-    const RecDat *recdat;
-    const VCard *card;
-    const PairRec *prec;    // pair facts at the foreign row entries, written by the row pass
+    const VMeta *meta;
+    const PairRec *prec;    // records at the leader slots, written by the row pass
     const uint32_t *hfilter;  // big hubs' neighbour filters (hub n_hubs_lds + i at i * kFilterWords)
-    const OutEnt *oe;         // each out-list entry's row entries (x, y) and (y, x)
+    const OutEnt *oe;         // each out-list entry's leader slots
     int n_hubs_lds;
-    const PairLink *plink;  // link slots: reverse entry and out-list range of each G' entry
+    const PairLink *plink;  // the links of the slots
     const double *av;       // [n] a_v of the row pass
     const int *blist;       // unused by the score kernels (the incremental lists are arguments)
     const unsigned long long *gwmax;  // batched graphs: w_max bits of each graph, else null
@@ -894,15 +830,14 @@ __device__ __forceinline__ bool out_has(const int32_t *outl, long long o0, long 
 }
 
 // The type-II terms of the pair (u, w), w a foreign neighbour of u (Lemma 2,
-// unnormalised weights), from the pair's facts at w's entry for u (W =
-// w_w(C(u)) and the run of C(u) in w's row): W^(2/3) times the sum of a_v
+// unnormalised weights), from w's record for C(u) (W = w_w(C(u)) and the run
+// of C(u) in w's list from its leader slot on): W^(2/3) times the sum of a_v
 // over the other members v of that run (v in C(u), v adjacent to w; counted
 // whether or not v ~ u), and the count f_w(C(u)) - 1.
-template <typename OffT>
-__device__ __forceinline__ double type2_pair(const ScoreArgs<OffT> &A, int u, const PairRec &pr, long long e) {
+__device__ __forceinline__ double type2_pair(const ScoreArgs &A, int u, const PairRec &pr, int lead) {
     if (pr.f <= 1) return 0.0;
     double S = 0.0;
-    const int32_t *run = A.col + (e - pr.back);
+    const int32_t *run = A.fcol + lead;
     for (int i = 0; i < pr.f; i += 8) {
         int x[8];
 #pragma unroll
@@ -922,8 +857,7 @@ __device__ __forceinline__ double score_value(double acc, int d, double wmax) {
     return (d >= 2 && wmax > 0.0) ? acc / wmax / (double)((long long)d * (d - 1)) : 0.0;
 }
 
-template <typename OffT>
-__device__ __forceinline__ void score_store(const ScoreArgs<OffT> &A, int u, int d, double acc, long long cI,
+__device__ __forceinline__ void score_store(const ScoreArgs &A, int u, int d, double acc, long long cI,
                                             long long cII, double wmax) {
     A.R[u] = score_value(acc, d, A.gwmax ? bitsd(A.gwmax[A.vgraph[u]]) : wmax);
     A.raw[u] = acc;
@@ -959,8 +893,7 @@ __device__ __forceinline__ int block_excl_scan(int x, int *ws, int &total) {
 // fixed tree order) goes to its slot; k_hub_sum adds the chunks of each hub in
 // chunk order once the score kernels are done.  The chunk's counts also go to
 // the block totals.
-template <typename OffT>
-__device__ void hub_chunk_store(const ScoreArgs<OffT> &A, const double *red, const long long (*ired)[kBlock / 64],
+__device__ void hub_chunk_store(const ScoreArgs &A, const double *red, const long long (*ired)[kBlock / 64],
                                 int hub, int chunk) {
     HubPart hp;
     hp.raw = 0.0;
@@ -983,8 +916,6 @@ struct TypeIShared {
     int ibeg[kBlock];      // first work item of each pair within its wavefront's list
     int ioo[kBlock];       // out-list start of each pair's w
     int pv[kBlock];        // u of each pair
-    int pcu[kBlock];       // C(u)
-    int pw[kBlock];        // w
     double pW[kBlock];     // w_w(C(u))
 };
 struct HitBuf {
@@ -1004,13 +935,13 @@ __device__ __forceinline__ void wave_sync() {
 
 // The terms of a wavefront's nb held hits (from slot h0), then each pair's
 // own lane adds its hits (a contiguous range of the list) in list order.
-template <class Edge, typename OffT>
-__device__ __forceinline__ void typeI_flush(const ScoreArgs<OffT> &A, const TypeIShared &T, HitBuf &H, const Edge &edge,
+template <class Edge>
+__device__ __forceinline__ void typeI_flush(const ScoreArgs &A, const TypeIShared &T, HitBuf &H, const Edge &edge,
                                             int h0, int nb, int lane, int me, bool mine, double &val, int &t1) {
     for (int h = lane; h < nb; h += 64) {
-        // the weights of the triangle {u, w, v} are the pair facts at its
-        // row entries: w_v(C(u)) at (v, u), w_w(C(v)) at (w, v), w_v(C(w))
-        // at (v, w) (the out-list entry w -> v holds the last two indices)
+        // the weights of the triangle {u, w, v}: w_v(C(u)), w_w(C(v)) and
+        // w_v(C(w)), each the record at a leader slot (the out-list entry
+        // w -> v holds the last two)
         const int q = H.hitp[h0 + h];
         const double W = T.pW[q];
         const OutEnt e = A.oe[H.hito[h0 + h]];
@@ -1052,10 +983,10 @@ __device__ __forceinline__ void typeI_flush(const ScoreArgs<OffT> &A, const Type
 //   cbrt(w_v(C(u)) w_w(C(v)) W) + cbrt(W w_v(C(w)) w_v(C(u))),  W = w_w(C(u)),
 // are evaluated, one lane per hit, and the pair's own lane adds them to its
 // sum in list order (so the sum's order is fixed).  `items` is the lane's
-// out-list length (0 without a pair), and T.ioo, T.pv, T.pcu, T.pw, T.pW hold
+// out-list length (0 without a pair), and T.ioo, T.pv, T.pW hold
 // the lane's pair; they must be visible block-wide (a barrier) before the call.
-template <class Edge, typename OffT>
-__device__ void typeI_scan(const ScoreArgs<OffT> &A, TypeIShared &T, HitBuf &H, int items, const Edge &edge,
+template <class Edge>
+__device__ void typeI_scan(const ScoreArgs &A, TypeIShared &T, HitBuf &H, int items, const Edge &edge,
                            double &val, int &t1) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int w0 = wave * 64;          // the wavefront's first pair
@@ -1139,8 +1070,7 @@ struct ScoreUnitSharedT {
     TypeIShared ti;
     union {  // three phases that never overlap
         struct {  // prologue: the tile's vertices
-            long long ou[kScoreTileV], go[kScoreTileV];  // row start and first pair slot
-            int cu[kScoreTileV], p[kScoreTileV], h[kScoreTileV];
+            int go[kScoreTileV];  // first slot
         } v;
         HitBuf hits;  // type-I scan
         struct {      // epilogue: the lanes' pair terms
@@ -1183,8 +1113,7 @@ struct TileEdge {
         code = k;  // (u, v) is the unit's pair k: its W is w_v(C(u))
         return k < S->pb[i + 1] && S->w[k] == y;
     }
-    template <typename OffT>
-    __device__ __forceinline__ double wvu(const ScoreArgs<OffT> &, const TypeIShared &T, int code) const {
+    __device__ __forceinline__ double wvu(const ScoreArgs &, const TypeIShared &T, int code) const {
         return T.pW[code];
     }
 };
@@ -1192,44 +1121,38 @@ struct HubListEdge {
     const int *w;
     int n;
     int cbase, ccnt;  // the chunk's pairs: list positions [cbase, cbase + ccnt)
-    long long go;     // the hub's first link slot
+    int go;           // the hub's first slot
     __device__ __forceinline__ bool operator()(int, int y, int &code) const {
         const int k = lds_lower(w, 0, n, y);
         code = k;  // (u, v) is the hub's pair k
         return k < n && w[k] == y;
     }
-    template <typename OffT>
-    __device__ __forceinline__ double wvu(const ScoreArgs<OffT> &A, const TypeIShared &T, int code) const {
+    __device__ __forceinline__ double wvu(const ScoreArgs &A, const TypeIShared &T, int code) const {
         if (code >= cbase && code < cbase + ccnt) return T.pW[code - cbase];
-        return A.prec[A.plink[go + code].e].w;
+        return A.prec[A.plink[go + code].lead].w;
     }
 };
 
 // vl: a unit of listed vertices vl[0, vn) (the incremental pass's rescored
 // vertices) instead of the tile idx.
-template <typename OffT, class SU>
-__device__ void score_unit(const ScoreArgs<OffT> &A, SU &S, bool hub_unit_arg, int idx, double wmax,
+template <class SU>
+__device__ void score_unit(const ScoreArgs &A, SU &S, bool hub_unit_arg, int idx, double wmax,
                            const int32_t *vl = nullptr, int vn = 0) {
     // a hub chunk needs room for the hub's whole foreign list
     const bool hub_unit = SU::kWords >= kHubList && hub_unit_arg;
     const int tid = threadIdx.x;
     // ---- prologue: lay out the unit's pairs
     int v0 = 0, nv = 0, total = 0, dp = 0, deg = 0, pb = 0;    // tile
-    int hub = 0, chunk = 0, hu = 0, hdp = 0, hcu = 0;  // hub chunk
-    long long hgo = 0;
+    int hub = 0, chunk = 0, hu = 0, hdp = 0, hgo = 0;  // hub chunk
     if (hub_unit) {
         const int2 hc = A.hub_chunk[idx];
         hub = hc.x;
         chunk = hc.y;
         hu = A.hubs[hub];
-        const VCard ch = A.card[hu];
-        const VMeta m = ch.m;
-        const long long ou = ch.off;
-        const int h = m.q - m.p;
-        hdp = m.deg - h;  // <= the load-time count, which fits kHubList
-        hcu = ch.lab;
-        hgo = ch.goff;
-        for (int j = tid; j < hdp; j += kBlock) S.w[j] = A.col[ou + (j < m.p ? j : j + h)];
+        const VMeta m = A.meta[hu];
+        hgo = A.goff[hu];
+        hdp = m.deg - (m.q - m.p);  // <= the load-time count, which fits kHubList
+        for (int j = tid; j < hdp; j += kBlock) S.w[j] = A.fcol[hgo + j];
         total = min(kBlock, max(0, hdp - chunk * kBlock));
         __syncthreads();
     } else {
@@ -1242,15 +1165,10 @@ __device__ void score_unit(const ScoreArgs<OffT> &A, SU &S, bool hub_unit_arg, i
         }
         if (tid < nv) {
             const int v = vl ? vl[tid] : v0 + tid;
-            const VCard cv = A.card[v];
-            const VMeta m = cv.m;
+            const VMeta m = A.meta[v];
             deg = m.deg;
             dp = m.deg - (m.q - m.p);
-            S.u.v.ou[tid] = cv.off;
-            S.u.v.go[tid] = cv.goff;
-            S.u.v.cu[tid] = cv.lab;
-            S.u.v.p[tid] = m.p;
-            S.u.v.h[tid] = m.q - m.p;
+            S.u.v.go[tid] = A.goff[v];
         }
         pb = block_excl_scan(dp, S.ws, total);
         if (tid < nv) {
@@ -1259,42 +1177,29 @@ __device__ void score_unit(const ScoreArgs<OffT> &A, SU &S, bool hub_unit_arg, i
         }
         if (tid == 0) S.pb[nv] = total;
         __syncthreads();
-        if (tid < total) {
-            const int i = S.pu[tid];
-            const int j = tid - S.pb[i];
-            S.w[tid] = A.col[S.u.v.ou[i] + (j < S.u.v.p[i] ? j : j + S.u.v.h[i])];
-        }
-        __syncthreads();
     }
     // ---- the lane's pair: type II
     const bool has = tid < total;
     double val = 0.0;
     int t2 = 0, t1 = 0, items = 0;
     if (has) {
-        int u, cu, w;
-        long long slot;
+        int u, slot;
         if (hub_unit) {
-            const int k = chunk * kBlock + tid;
             u = hu;
-            cu = hcu;
-            w = S.w[k];
-            slot = hgo + k;
+            slot = hgo + chunk * kBlock + tid;
         } else {
             const int i = S.pu[tid];
             u = vl ? vl[i] : v0 + i;
-            cu = S.u.v.cu[i];
-            w = S.w[tid];
             slot = S.u.v.go[i] + (tid - S.pb[i]);
+            S.w[tid] = A.fcol[slot];
         }
         const PairLink pl = A.plink[slot];
-        const PairRec pr = A.prec[pl.e];
-        val = type2_pair(A, u, pr, pl.e);
+        const PairRec pr = A.prec[pl.lead];
+        val = type2_pair(A, u, pr, pl.lead);
         t2 = pr.f - 1;
         items = pl.on;
         S.ti.ioo[tid] = pl.oo;
         S.ti.pv[tid] = u;
-        S.ti.pcu[tid] = cu;
-        S.ti.pw[tid] = w;
         S.ti.pW[tid] = pr.w;
     }
     // ---- type I (the hit lists overlay the prologue's vertex facts)
@@ -1383,23 +1288,17 @@ struct HubOutEdge {
         code = (int)(o << 1) | 1;
         return o >= 0;
     }
-    template <typename OffT>
-    __device__ __forceinline__ double wvu(const ScoreArgs<OffT> &A, const TypeIShared &, int code) const {
+    __device__ __forceinline__ double wvu(const ScoreArgs &A, const TypeIShared &, int code) const {
         const OutEnt e = A.oe[code >> 1];
         return A.prec[(code & 1) ? e.xy : e.yx].w;
     }
 };
 
-template <typename OffT>
-__device__ void score_hub_big(const ScoreArgs<OffT> &A, ScoreHubBigShared &S, int hub, int chunk, double wmax) {
+__device__ void score_hub_big(const ScoreArgs &A, ScoreHubBigShared &S, int hub, int chunk, double wmax) {
     const int tid = threadIdx.x;
     const int u = A.hubs[hub];
-    const VCard cu_ = A.card[u];
-    const VMeta m = cu_.m;
-    const long long ou = cu_.off;
-    const int h = m.q - m.p;
-    const int dp = m.deg - h;
-    const int cu = cu_.lab;
+    const VMeta m = A.meta[u];
+    const int dp = m.deg - (m.q - m.p);
     const long long uo0 = A.oo[u], uo1 = A.oo[u + 1];
     const int n_out = (int)(uo1 - uo0);
     const bool staged = n_out <= kHubOutStage;
@@ -1409,16 +1308,13 @@ __device__ void score_hub_big(const ScoreArgs<OffT> &A, ScoreHubBigShared &S, in
     double val = 0.0;
     int t2 = 0, t1 = 0, items = 0;
     if (k < dp) {
-        const int w = A.col[ou + (k < m.p ? k : k + h)];
-        const PairLink pl = A.plink[cu_.goff + k];
-        const PairRec pr = A.prec[pl.e];
-        val = type2_pair(A, u, pr, pl.e);
+        const PairLink pl = A.plink[A.goff[u] + k];
+        const PairRec pr = A.prec[pl.lead];
+        val = type2_pair(A, u, pr, pl.lead);
         t2 = pr.f - 1;
         items = pl.on;
         S.ti.ioo[tid] = pl.oo;
         S.ti.pv[tid] = u;
-        S.ti.pcu[tid] = cu;
-        S.ti.pw[tid] = w;
         S.ti.pW[tid] = pr.w;
     }
     HubOutEdge E;
@@ -1437,20 +1333,20 @@ __device__ void score_hub_big(const ScoreArgs<OffT> &A, ScoreHubBigShared &S, in
 }
 
 // Each big hub's neighbour filter from its current foreign list (after the
-// row pass: the card's own run [p, q)): built in LDS by one workgroup per
+// row pass): built in LDS by one workgroup per
 // hub, then written out whole.
-template <typename OffT>
-__global__ __launch_bounds__(kBlock) void k_hub_filters(const int32_t *hubs, int h0, const VCard *card,
-                                                        const int32_t *col, uint32_t *filters) {
+__global__ __launch_bounds__(kBlock) void k_hub_filters(const int32_t *hubs, int h0, const VMeta *meta,
+                                                        const int32_t *goff, const int32_t *fcol,
+                                                        uint32_t *filters) {
     __shared__ uint32_t f[kFilterWords];
     const int h = h0 + (int)blockIdx.x;
     for (int i = threadIdx.x; i < kFilterWords; i += kBlock) f[i] = 0u;
     __syncthreads();
-    const VCard c = card[hubs[h]];
-    const int hp = c.m.q - c.m.p;
-    const int dp = c.m.deg - hp;
+    const VMeta m = meta[hubs[h]];
+    const int go = goff[hubs[h]];
+    const int dp = m.deg - (m.q - m.p);
     for (int j = threadIdx.x; j < dp; j += kBlock) {
-        const uint32_t x = filter_hash(col[c.off + (j < c.m.p ? j : j + hp)]);
+        const uint32_t x = filter_hash(fcol[go + j]);
         atomicOr(&f[x >> 5], 1u << (x & 31));
     }
     __syncthreads();
@@ -1460,8 +1356,7 @@ __global__ __launch_bounds__(kBlock) void k_hub_filters(const int32_t *hubs, int
 
 // Algorithm 1 Step 3 (Eq. RSI) for every border vertex of the LDS-sized
 // score hubs (one chunk of 256 pairs per workgroup) ...
-template <typename OffT>
-__global__ __launch_bounds__(kBlock) void k_score_lds_hubs(ScoreArgs<OffT> A) {
+__global__ __launch_bounds__(kBlock) void k_score_lds_hubs(ScoreArgs A) {
     __shared__ ScoreUnitShared S;
     score_unit(A, S, true, (int)blockIdx.x, bitsd(A.ctr->wmax_bits));
 }
@@ -1469,8 +1364,7 @@ __global__ __launch_bounds__(kBlock) void k_score_lds_hubs(ScoreArgs<OffT> A) {
 // ... and of the score tiles (tile t of XCD x = t / per runs on a block of
 // that XCD: blocks are dealt to the XCDs round-robin, so consecutive tiles
 // share an L2).
-template <typename OffT>
-__global__ __launch_bounds__(kBlock) void k_score(ScoreArgs<OffT> A) {
+__global__ __launch_bounds__(kBlock) void k_score(ScoreArgs A) {
     __shared__ ScoreTileShared S;
     const int idx = tile_of_block((int)blockIdx.x, 0, A.tiles_per_xcd);
     if (idx < A.n_tiles) score_unit(A, S, false, idx, bitsd(A.ctr->wmax_bits));
@@ -1481,8 +1375,7 @@ __global__ __launch_bounds__(kBlock) void k_score(ScoreArgs<OffT> A) {
 // LDS hubs are few, where a launch of their own would end on one chunk's
 // latency with nothing beside it.
 constexpr int kSplitHubChunks = 4096;
-template <typename OffT>
-__global__ __launch_bounds__(kBlock) void k_score_all(ScoreArgs<OffT> A) {
+__global__ __launch_bounds__(kBlock) void k_score_all(ScoreArgs A) {
     __shared__ ScoreUnitShared S;
     const int b = (int)blockIdx.x;
     const bool hub_unit = b < A.n_chunks_lds;
@@ -1492,8 +1385,7 @@ __global__ __launch_bounds__(kBlock) void k_score_all(ScoreArgs<OffT> A) {
 
 // ... and of the hubs too large for LDS (chunks n_chunks_lds ...); partials
 // summed by k_hub_sum after the score kernels.
-template <typename OffT>
-__global__ __launch_bounds__(kBlock) void k_score_hub(ScoreArgs<OffT> A) {
+__global__ __launch_bounds__(kBlock) void k_score_hub(ScoreArgs A) {
     __shared__ ScoreHubBigShared S;
     const double wmax = bitsd(A.ctr->wmax_bits);
     const int b = (int)blockIdx.x;
@@ -1511,8 +1403,7 @@ __global__ __launch_bounds__(kBlock) void k_score_hub(ScoreArgs<OffT> A) {
 //      full pass, whose tiles run whole).
 // Every item runs as in the full launches; a unit's values are those of its
 // vertices' tiles (a vertex's sum does not depend on the unit's others).
-template <typename OffT>
-__global__ __launch_bounds__(kBlock) void k_score_inc(ScoreArgs<OffT> A, const int32_t *big, const int32_t *main_,
+__global__ __launch_bounds__(kBlock) void k_score_inc(ScoreArgs A, const int32_t *big, const int32_t *main_,
                                                       const int32_t *abin, const unsigned long long *ictr,
                                                       uint8_t *hflag, int grid_rows, int grid_score, int grid_main) {
     __shared__ union {
@@ -1567,7 +1458,7 @@ __global__ __launch_bounds__(kBlock) void k_score_inc(ScoreArgs<OffT> A, const i
 // sums chunks l, l + 64, ... in order, then a fixed shuffle tree).  A hub
 // whose foreign list became empty keeps the zeros the row pass wrote.
 __global__ __launch_bounds__(kBlock) void k_hub_sum(const int32_t *hubs, const int32_t *hub_first,
-                                                    const HubPart *hub_part, int n_hubs, const VCard *card,
+                                                    const HubPart *hub_part, int n_hubs, const VMeta *meta,
                                                     const DevCounters *ctr, const unsigned long long *gwmax,
                                                     const int32_t *vgraph, double *R, double *raw,
                                                     long long *tI, long long *tII) {
@@ -1591,7 +1482,7 @@ __global__ __launch_bounds__(kBlock) void k_hub_sum(const int32_t *hubs, const i
     }
     if (lane == 0) {
         const int u = hubs[hub];
-        const VMeta m = card[u].m;
+        const VMeta m = meta[u];
         if (m.deg - (m.q - m.p) > 0) {
             R[u] = score_value(acc, m.deg, bitsd(gwmax ? gwmax[vgraph[u]] : ctr->wmax_bits));
             raw[u] = acc;
@@ -1637,19 +1528,19 @@ __global__ __launch_bounds__(1024) void k_reduce_score(const long long *tI, cons
 // computed when a reader asks, from the last pass's row facts).  One
 // wavefront per vertex; per-block partials in wpart.
 template <typename OffT>
-__global__ __launch_bounds__(kBlock) void k_work_I(const OffT *off, const int32_t *col, const VCard *card, long long n,
+__global__ __launch_bounds__(kBlock) void k_work_I(const OffT *off, const int32_t *col, const VMeta *meta, long long n,
                                                    unsigned long long *wpart) {
     __shared__ unsigned long long s[kBlock / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     unsigned long long acc = 0;
     for (long long x = (long long)blockIdx.x * (kBlock / 64) + wave; x < n; x += (long long)gridDim.x * (kBlock / 64)) {
-        const VMeta m = card[x].m;
+        const VMeta m = meta[x];
         const int dpx = m.deg - (m.q - m.p);
         if (dpx == 0) continue;
         const OffT rb = off[x];
         for (int j = lane; j < m.deg; j += 64) {
             if (j >= m.p && j < m.q) continue;
-            const VMeta my = card[col[rb + j]].m;
+            const VMeta my = meta[col[rb + j]];
             acc += (unsigned long long)min(dpx, my.deg - (my.q - my.p));
         }
     }
@@ -1680,11 +1571,9 @@ __global__ __launch_bounds__(kBlock) void k_reduce_work(const unsigned long long
 }
 
 // ------------------------------------------------------------ link slots
-// For a row entry e = (x, y) with y foreign to x: plink[goff[x] + k] = {the
-// index of the entry (y, x), y's out-list range}, k = y's index among x's
-// foreign entries (x's row without its own-community id range).  Rows are
-// sorted, so positions are binary searches.  Run at load and after removals
-// (compaction shifts rows).
+// The link of the slot of (x, y): the leader of C(x)'s run and the slot of x
+// in y's list, and y's out-list range.  Run at load; after removals k_mark_link
+// rebuilds the links that moved.
 // Lower bounds (first position holding an id >= key) of N keys, key i in the
 // sorted row row[i][0, d[i]), found together: binary searches in lockstep,
 // each step one independent load per key still searching.  DEC: removed
@@ -1728,57 +1617,47 @@ template <typename OffT>
 struct LinkArgs {
     const OffT *off;
     const int32_t *deg, *col, *lab, *cstart;
-    const int64_t *goff, *oo;
+    const int32_t *goff, *fcol;
+    const int64_t *oo;
     PairLink *plink;
     const int32_t *outl;        // out-lists (tombstones complemented)
-    OutEnt *oe;                 // each out-list entry's row entries
+    OutEnt *oe;                 // each out-list entry's leader slots
     const unsigned int *vmark;  // after removals: kRowChanged marks the rows that changed
-    const VCard *card;          // the last pass's own-run bounds [p, q) of the unchanged rows
+    const VMeta *meta;          // the last pass's own-run bounds [p, q) of the unchanged rows
 };
 
-// The link of x's row entry j (if it is a current foreign entry).
-template <typename OffT>
-__device__ __forceinline__ void link_entry(const LinkArgs<OffT> &L, int x, int j) {
-    if (j >= L.deg[x]) return;  // removed tail
-    const int y = L.col[(long long)L.off[x] + j];
-    const int cx = L.lab[x];
-    if (L.lab[y] == cx) return;  // own community
-    // first position in a's row (length da) holding an id >= key
-    auto lower = [&](int a, int da, int key) {
-        const int32_t *row = L.col + L.off[a];
-        int l = 0, h = da;
-        while (l < h) {
-            const int mid = (l + h) >> 1;
-            if (row[mid] < key)
-                l = mid + 1;
-            else
-                h = mid;
-        }
-        return l;
-    };
-    const int dx = L.deg[x];
-    int kx = j;
-    if (y >= L.cstart[cx + 1]) kx -= lower(x, dx, L.cstart[cx + 1]) - lower(x, dx, L.cstart[cx]);
-    PairLink pl;
-    pl.e = (long long)L.off[y] + lower(y, L.deg[y], x);
-    pl.oo = (int)L.oo[y];
-    pl.on = (int)(L.oo[y + 1] - L.oo[y]);
-    L.plink[L.goff[x] + kx] = pl;
+// The last x in [0, n) with off[x] <= s.
+template <typename T>
+__device__ __forceinline__ int owner_of(const T *off, long long n, long long s) {
+    long long lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const long long mid = (lo + hi) >> 1;
+        if ((long long)off[mid] <= s)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    return (int)lo;
 }
 
-// Every entry (at load): the owning row is the last x with off[x] <= e.
+// Every slot's link (at load, when the lists are whole).
 template <typename OffT>
-__global__ __launch_bounds__(kBlock) void k_links(LinkArgs<OffT> L, long long n, long long nnz) {
-    for (long long e = (long long)blockIdx.x * kBlock + threadIdx.x; e < nnz; e += (long long)gridDim.x * kBlock) {
-        long long lo = 0, hi = n;
-        while (hi - lo > 1) {
-            const long long mid = (lo + hi) >> 1;
-            if ((long long)L.off[mid] <= e)
-                lo = mid;
-            else
-                hi = mid;
-        }
-        link_entry(L, (int)lo, (int)(e - (long long)L.off[lo]));
+__global__ __launch_bounds__(kBlock) void k_links(LinkArgs<OffT> L, long long n, long long slots) {
+    for (long long s = (long long)blockIdx.x * kBlock + threadIdx.x; s < slots; s += (long long)gridDim.x * kBlock) {
+        const int x = owner_of(L.goff, n, s);
+        const int y = L.fcol[s];
+        const int g0 = L.goff[y];
+        const int32_t *rows[2] = {L.fcol + g0, L.fcol + g0};
+        const int ds[2] = {L.goff[y + 1] - g0, L.goff[y + 1] - g0};
+        const int keys[2] = {L.cstart[L.lab[x]], x};
+        int k[2];
+        lower_n<2, false>(rows, ds, keys, k);
+        PairLink pl;
+        pl.lead = g0 + k[0];
+        pl.slot = g0 + k[1];
+        pl.oo = (int)L.oo[y];
+        pl.on = (int)(L.oo[y + 1] - L.oo[y]);
+        L.plink[s] = pl;
     }
 }
 
@@ -1794,7 +1673,8 @@ static LinkArgs<OffT> link_args(rs_graph *g) {
     L.goff = D.goff;
     L.oo = D.oo;
     L.vmark = D.vmark;
-    L.card = D.card;
+    L.fcol = D.fcol;
+    L.meta = D.meta;
     L.plink = D.plink;
     L.outl = D.outl;
     L.oe = D.oe;
@@ -1804,40 +1684,32 @@ static LinkArgs<OffT> link_args(rs_graph *g) {
 template <typename OffT>
 static rs_status links_t(rs_graph *g) {
     DeviceGraph &D = g->d;
-    if (D.nnz == 0) return RS_OK;
-    const long long grid = std::min<long long>((D.nnz + kBlock - 1) / kBlock, 65536);
-    hipLaunchKernelGGL(k_links<OffT>, dim3((int)grid), dim3(kBlock), 0, g->stream, link_args<OffT>(g),
-                       (long long)D.n, (long long)D.nnz);
+    const long long slots = 2 * g->n_out;  // each G' edge has one out-list entry and two slots
+    if (slots == 0) return RS_OK;
+    hipLaunchKernelGGL(k_links<OffT>, dim3(grid_for(slots, kBlock, 65536)), dim3(kBlock), 0, g->stream,
+                       link_args<OffT>(g), (long long)D.n, slots);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? RS_OK : hip_fail(e, "link-slot launch");
 }
 
 rs_status launch_links(rs_graph *g) { return g->d.off64 ? links_t<long long>(g) : links_t<int32_t>(g); }
 
-// Each out-list entry x -> y (at load): the indices of the row entries
-// (x, y) and (y, x); the owner x is the last with oo[x] <= o.
+// Each out-list entry x -> y (at load): the leader slots of C(y)'s run in x's
+// list and of C(x)'s run in y's list; the owner x is the last with oo[x] <= o.
 template <typename OffT>
 __global__ __launch_bounds__(kBlock) void k_out_entries(LinkArgs<OffT> L, long long n, long long n_out) {
     for (long long o = (long long)blockIdx.x * kBlock + threadIdx.x; o < n_out; o += (long long)gridDim.x * kBlock) {
-        long long lo = 0, hi = n;
-        while (hi - lo > 1) {
-            const long long mid = (lo + hi) >> 1;
-            if (L.oo[mid] <= o)
-                lo = mid;
-            else
-                hi = mid;
-        }
-        const int x = (int)lo;
+        const int x = owner_of(L.oo, n, o);
         const int y = out_id(L.outl[o]);
-        const long long xb = (long long)L.off[x], yb = (long long)L.off[y];
-        const int32_t *rows[2] = {L.col + xb, L.col + yb};
-        const int ds[2] = {L.deg[x], L.deg[y]};
-        const int keys[2] = {y, x};
+        const int xg = L.goff[x], yg = L.goff[y];
+        const int32_t *rows[2] = {L.fcol + xg, L.fcol + yg};
+        const int ds[2] = {L.goff[x + 1] - xg, L.goff[y + 1] - yg};
+        const int keys[2] = {L.cstart[L.lab[y]], L.cstart[L.lab[x]]};
         int k[2];
-        lower_n<2, true>(rows, ds, keys, k);
+        lower_n<2, false>(rows, ds, keys, k);
         OutEnt e;
-        e.xy = xb + k[0];
-        e.yx = yb + k[1];
+        e.xy = xg + k[0];
+        e.yx = yg + k[1];
         L.oe[o] = e;
     }
 }
@@ -1885,12 +1757,12 @@ __global__ void k_zero_u64(unsigned long long *p, int count) {
 // its raw sum (the same expression as the pass, so the bits equal a full
 // pass's).  Raw sums are 0 for vertices without foreign neighbours.
 __global__ __launch_bounds__(kBlock) void k_rescale(const unsigned long long *wmax_old, const DevCounters *ctr,
-                                                    const VCard *card, const double *raw, double *R, long long n) {
+                                                    const VMeta *meta, const double *raw, double *R, long long n) {
     const unsigned long long wb = ctr->wmax_bits;
     if (wb == *wmax_old) return;
     const double wmax = bitsd(wb);
     for (long long u = (long long)blockIdx.x * kBlock + threadIdx.x; u < n; u += (long long)gridDim.x * kBlock) {
-        const VMeta m = card[u].m;
+        const VMeta m = meta[u];
         R[u] = m.deg - (m.q - m.p) > 0 ? score_value(raw[u], m.deg, wmax) : 0.0;
     }
 }
@@ -1993,9 +1865,7 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
     A.n_tiles = g->n_rtiles;
     A.n_hubs = g->n_rhubs;
     A.tiles_per_xcd = (g->n_rtiles + 7) / 8;
-    A.reckey = D.reckey;
-    A.recdat = D.recdat;
-    A.card = D.card;
+    A.meta = D.meta;
     A.goff = D.goff;
     A.prec = D.prec;
     A.blist = inc ? D.rlist : nullptr;
@@ -2030,10 +1900,9 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
         timing_end(g, K_WMAX_GRAPHS, ev);
     }
 
-    ScoreArgs<OffT> S;
-    S.off = (const OffT *)D.off;
-    S.col = D.col;
-    S.lab = D.lab;
+    ScoreArgs S;
+    S.goff = D.goff;
+    S.fcol = D.fcol;
     S.tiles = D.stiles;
     S.hubs = D.shubs;
     S.n_tiles = g->n_stiles;
@@ -2046,9 +1915,7 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
     S.hub_part = D.hub_part;
     S.outl = D.outl;
     S.oo = D.oo;
-    S.reckey = D.reckey;
-    S.recdat = D.recdat;
-    S.card = D.card;
+    S.meta = D.meta;
     S.prec = D.prec;
     S.hfilter = D.hfilter;
     S.oe = D.oe;
@@ -2065,15 +1932,15 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
     const int n_big_hubs = g->n_shubs - g->n_shubs_lds;
     if (n_big_hubs > 0) {  // the big hubs' neighbour filters for the edge tests below
         timing_begin(g, K_HUB_FILTERS, &ev);
-        hipLaunchKernelGGL(k_hub_filters<OffT>, dim3(n_big_hubs), dim3(kBlock), 0, g->stream, D.shubs,
-                           g->n_shubs_lds, D.card, D.col, D.hfilter);
+        hipLaunchKernelGGL(k_hub_filters, dim3(n_big_hubs), dim3(kBlock), 0, g->stream, D.shubs, g->n_shubs_lds,
+                           D.meta, D.goff, D.fcol, D.hfilter);
         timing_end(g, K_HUB_FILTERS, ev);
     }
     const unsigned long long *ictr = D.ictr;
     if (inc) {
         S.blist = nullptr;
         timing_begin(g, K_SCORE, &ev);
-        hipLaunchKernelGGL(k_score_inc<OffT>, dim3(kIncGrid), dim3(kBlock), 0, g->stream, S, (const int32_t *)D.hlist,
+        hipLaunchKernelGGL(k_score_inc, dim3(kIncGrid), dim3(kBlock), 0, g->stream, S, (const int32_t *)D.hlist,
                            (const int32_t *)D.slist, (const int32_t *)D.abin, ictr, D.hflag, g->grid_rows,
                            g->grid_score, grid_main);
         timing_end(g, K_SCORE, ev);
@@ -2081,30 +1948,30 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
         if (n_big > 0) {
             S.blist = nullptr;
             timing_begin(g, K_SCORE_HUB, &ev);
-            hipLaunchKernelGGL(k_score_hub<OffT>, dim3(n_big), dim3(kBlock), 0, g->stream, S);
+            hipLaunchKernelGGL(k_score_hub, dim3(n_big), dim3(kBlock), 0, g->stream, S);
             timing_end(g, K_SCORE_HUB, ev);
         }
         S.blist = nullptr;
         const int grid_tiles = grid_main - g->n_schunks_lds;  // the tiles, rounded up to the 8 XCDs
         timing_begin(g, K_SCORE, &ev);
         if (g->n_schunks_lds >= kSplitHubChunks) {  // many LDS hubs: tiles with the smaller LDS form
-            hipLaunchKernelGGL(k_score_lds_hubs<OffT>, dim3(g->n_schunks_lds), dim3(kBlock), 0, g->stream, S);
-            if (grid_tiles > 0) hipLaunchKernelGGL(k_score<OffT>, dim3(grid_tiles), dim3(kBlock), 0, g->stream, S);
+            hipLaunchKernelGGL(k_score_lds_hubs, dim3(g->n_schunks_lds), dim3(kBlock), 0, g->stream, S);
+            if (grid_tiles > 0) hipLaunchKernelGGL(k_score, dim3(grid_tiles), dim3(kBlock), 0, g->stream, S);
         } else if (grid_main > 0) {
-            hipLaunchKernelGGL(k_score_all<OffT>, dim3(grid_main), dim3(kBlock), 0, g->stream, S);
+            hipLaunchKernelGGL(k_score_all, dim3(grid_main), dim3(kBlock), 0, g->stream, S);
         }
         timing_end(g, K_SCORE, ev);
     }
     if (g->n_shubs > 0) {
         timing_begin(g, K_HUB_SUM, &ev);
         hipLaunchKernelGGL(k_hub_sum, dim3((g->n_shubs + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0,
-                           g->stream, D.shubs, D.shub_first, D.hub_part, g->n_shubs, D.card, D.ctr, D.gwmax,
+                           g->stream, D.shubs, D.shub_first, D.hub_part, g->n_shubs, D.meta, D.ctr, D.gwmax,
                            D.vgraph, D.R, D.raw, D.tI, D.tII);
         timing_end(g, K_HUB_SUM, ev);
     }
     if (inc && D.n > 0)  // w_max moved: every score is rescaled from its raw sum
         hipLaunchKernelGGL(k_rescale, dim3(grid_for(D.n, kBlock, 4096)), dim3(kBlock), 0, g->stream,
-                           (const unsigned long long *)&D.ictr[kIcWmaxOld], D.ctr, D.card, D.raw, D.R, (long long)D.n);
+                           (const unsigned long long *)&D.ictr[kIcWmaxOld], D.ctr, D.meta, D.raw, D.R, (long long)D.n);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "score pass launch");
     return RS_OK;
@@ -2126,10 +1993,10 @@ rs_status launch_reduce_counts(rs_graph *g) {
     hipLaunchKernelGGL(k_reduce_score, dim3(1), dim3(1024), 0, g->stream, D.tI, D.tII, (long long)D.n, D.ctr);
     if (D.off64)
         hipLaunchKernelGGL(k_work_I<long long>, dim3(kWorkBlocks), dim3(kBlock), 0, g->stream,
-                           (const long long *)D.off, D.col, D.card, (long long)D.n, D.wpart);
+                           (const long long *)D.off, D.col, D.meta, (long long)D.n, D.wpart);
     else
         hipLaunchKernelGGL(k_work_I<int32_t>, dim3(kWorkBlocks), dim3(kBlock), 0, g->stream, (const int32_t *)D.off,
-                           D.col, D.card, (long long)D.n, D.wpart);
+                           D.col, D.meta, (long long)D.n, D.wpart);
     hipLaunchKernelGGL(k_reduce_work, dim3(1), dim3(kBlock), 0, g->stream, D.wpart, D.ctr);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? RS_OK : hip_fail(e, "reduce launch");
@@ -3404,10 +3271,12 @@ rs_status launch_remove_vertices(rs_graph *g, const int32_t *d_verts, int64_t nv
 // Compact the listed changed rows (removed entries are complemented, < 0):
 // one wavefront per row, kCompactGroups groups of 64 entries loaded at once
 // (a hub's long row takes one round trip per 1,024 entries), each group
-// packed by a ballot and prefix; the freed tail of the capacity is set to -1.
+// packed by a ballot and prefix (the foreign ones also into the row's slots);
+// the freed tail of the capacity is set to -1.
 constexpr int kCompactGroups = 16;
 template <typename OffT>
 __global__ __launch_bounds__(kBlock) void k_compact_rows(const OffT *off, int32_t *deg, int32_t *col, int32_t *clab,
+                                                         const int32_t *lab, const int32_t *goff, int32_t *fcol,
                                                          const int32_t *list, const unsigned long long *count) {
     const long long nl = (long long)*count;
     const int lane = threadIdx.x & 63;
@@ -3416,7 +3285,8 @@ __global__ __launch_bounds__(kBlock) void k_compact_rows(const OffT *off, int32_
         const int v = list[i];
         const long long rb = (long long)off[v];
         const int d = deg[v];
-        int w = 0;
+        const int cv = lab[v], go = goff[v];
+        int w = 0, wf = 0;
         for (int j0 = 0; j0 < d; j0 += 64 * kCompactGroups) {  // groups of 64 entries loaded at once
             int x[kCompactGroups], c[kCompactGroups];
 #pragma unroll
@@ -3427,13 +3297,16 @@ __global__ __launch_bounds__(kBlock) void k_compact_rows(const OffT *off, int32_
             }
 #pragma unroll
             for (int t = 0; t < kCompactGroups; ++t) {
-                const unsigned long long m = __ballot(x[t] >= 0);
+                const unsigned long long m = __ballot(x[t] >= 0), mf = __ballot(x[t] >= 0 && c[t] != cv);
+                const unsigned long long lt = (1ull << lane) - 1ull;
                 if (x[t] >= 0) {
-                    const long long to = rb + w + __popcll(m & ((1ull << lane) - 1ull));
+                    const long long to = rb + w + __popcll(m & lt);
                     col[to] = x[t];
                     clab[to] = c[t];
+                    if (c[t] != cv) fcol[go + wf + __popcll(mf & lt)] = x[t];
                 }
                 w += __popcll(m);
+                wf += __popcll(mf);
             }
         }
         for (int j = w + lane; j < d; j += 64) {
@@ -3483,7 +3356,7 @@ __device__ __forceinline__ void mark_run_member(const LinkArgs<OffT> &L, unsigne
         const int key[1] = {w};
         int k[1];
         lower_n<1, false>(row, d, key, k);
-        const VMeta m = L.card[x].m;
+        const VMeta m = L.meta[x];
         const int kx = k[0] < m.p ? k[0] : k[0] - (m.q - m.p);
         cflag[hub_first[-1 - sx] + kx / kScoreTileP] = 1;
     } else {
@@ -3513,9 +3386,8 @@ constexpr int kTriRow = 512;
 // After removals, one wavefront per chunk of 64 entries of a changed
 // (compacted) row v (chunks: k_row_chunks), for each entry (v, w) with w in
 // another community:
-// * links: v's link for the entry (the reverse entry and w's out-list), and
-//   the index of the entry (v, w), which moved with v's row, in w's link
-//   back to v;
+// * links: v's link for the entry, and the leader and slot in v's list, which
+//   moved with v's row, in w's link back to v;
 // * marks: v is affected whole.  The pairs whose terms read v's row are
 //   (a) (w, v) itself (w's pair facts, out-list scan, a-run),
 //   (b) (w, y) for each y adjacent to both, in a third community (the
@@ -3560,21 +3432,18 @@ __global__ __launch_bounds__(kBlock) void k_mark_link(LinkArgs<OffT> L, unsigned
             dw = L.deg[w];
             const int32_t *roww = L.col + wb;
             // in w's row: C(v)'s run [k[0], k[1]) and the entry (w, v) at
-            // k[2]; in v's row: v's own run [k[3], k[4])
-            const int32_t *rws[5] = {roww, roww, roww, L.col + rb, L.col + rb};
-            const int ds[5] = {dw, dw, dw, dv, dv};
-            const int keys[5] = {id0, id1, v, id0, id1};
-            int k[5];
-            lower_n<5, false>(rws, ds, keys, k);
+            // k[2]; in v's row: v's own run [k[3], k[4]) and the start of
+            // C(w)'s run at k[5]
+            const int32_t *rws[6] = {roww, roww, roww, L.col + rb, L.col + rb, L.col + rb};
+            const int ds[6] = {dw, dw, dw, dv, dv, dv};
+            const int keys[6] = {id0, id1, v, id0, id1, L.cstart[cw]};
+            int k[6];
+            lower_n<6, false>(rws, ds, keys, k);
             k0 = k[0];
             k1 = k[1];
-            const int pv = k[3], qv = k[4], ew = k[2];
-            PairLink pl;
-            pl.e = wb + ew;
-            pl.oo = (int)L.oo[w];
-            pl.on = (int)(L.oo[w + 1] - L.oo[w]);
-            L.plink[L.goff[v] + (j < pv ? j : j - (qv - pv))] = pl;
-            // w's own run is its card's when w's row did not change
+            const int ew = k[2], pv = k[3], hv = k[4] - k[3], lv = k[5];
+            const int gv = L.goff[v], gw = L.goff[w];
+            // w's own run is the last pass's when w's row did not change
             const bool wch = (L.vmark[w] & kRowChanged) != 0u;
             if (wch) {
                 const int32_t *rw2[2] = {roww, roww};
@@ -3585,16 +3454,27 @@ __global__ __launch_bounds__(kBlock) void k_mark_link(LinkArgs<OffT> L, unsigned
                 pw = pq[0];
                 qw = pq[1];
             } else {
-                const VMeta m = L.card[w].m;
+                const VMeta m = L.meta[w];
                 pw = m.p;
                 qw = m.q;
             }
+            // the slots of (v, w) and (w, v), and the leaders of C(w)'s run
+            // in v's list and of C(v)'s run in w's
             const int kw = ew < pw ? ew : ew - (qw - pw);
-            L.plink[L.goff[w] + kw].e = rb + j;
+            const int sv = gv + (j < pv ? j : j - hv), sw_ = gw + kw;
+            const int ldv = gv + (lv < pv ? lv : lv - hv), ldw = gw + (k0 < pw ? k0 : k0 - (qw - pw));
+            PairLink pl;
+            pl.lead = ldw;
+            pl.slot = sw_;
+            pl.oo = (int)L.oo[w];
+            pl.on = (int)(L.oo[w + 1] - L.oo[w]);
+            L.plink[sv] = pl;
+            L.plink[sw_].lead = ldv;
+            L.plink[sw_].slot = sv;
             {
                 // the out-list entry of {v, w} (in the list of the lower
-                // rank: load-time foreign degree, then id) gets both entries
-                const long long fv = L.goff[v + 1] - L.goff[v], fw = L.goff[w + 1] - L.goff[w];
+                // rank: load-time foreign degree, then id) gets both leaders
+                const int fv = L.goff[v + 1] - gv, fw = L.goff[w + 1] - gw;
                 const bool v_low = fv < fw || (fv == fw && v < w);
                 const int a = v_low ? v : w, bkey = v_low ? w : v;
                 const long long o0 = L.oo[a];
@@ -3605,8 +3485,8 @@ __global__ __launch_bounds__(kBlock) void k_mark_link(LinkArgs<OffT> L, unsigned
                 lower_n<1, true>(orow, od, okey, ok);
                 if (ok[0] < od[0] && L.outl[o0 + ok[0]] == bkey) {
                     OutEnt e;
-                    e.xy = v_low ? rb + j : wb + ew;
-                    e.yx = v_low ? wb + ew : rb + j;
+                    e.xy = v_low ? ldv : ldw;
+                    e.yx = v_low ? ldw : ldv;
                     L.oe[o0 + ok[0]] = e;
                 }
             }
@@ -3726,7 +3606,7 @@ __device__ __forceinline__ void load_marks(const unsigned int *vmark, long long 
 // ucnt[r * gridDim.x + range]: rows 0..kScoreBins-1 tile vertices per bin,
 // row kScoreBins affected vertices.
 __global__ __launch_bounds__(kBlock) void k_units_count(const unsigned int *vmark, const int32_t *vrowb,
-                                                        const int32_t *vscore, const int64_t *goff, long long n,
+                                                        const int32_t *vscore, const int32_t *goff, long long n,
                                                         uint8_t *rflag, uint8_t *hflag, int32_t *ucnt) {
     __shared__ int s_cnt[kUnitRows];
     if (threadIdx.x < kUnitRows) s_cnt[threadIdx.x] = 0;
@@ -3817,7 +3697,7 @@ __global__ __launch_bounds__(kBlock) void k_units_scan(int32_t *ucnt, int groups
 // a range and bin; a vertex's score does not depend on its unit); the marks
 // are cleared.
 __global__ __launch_bounds__(kBlock) void k_units_place(unsigned int *vmark, const int32_t *vscore,
-                                                        const int64_t *goff, long long n, const int32_t *ucnt,
+                                                        const int32_t *goff, long long n, const int32_t *ucnt,
                                                         int32_t *abin) {
     __shared__ int s_cur[kScoreBins];
     if (threadIdx.x < kScoreBins) s_cur[threadIdx.x] = ucnt[threadIdx.x * gridDim.x + blockIdx.x];
@@ -3885,7 +3765,7 @@ static rs_status incremental_marks_t(rs_graph *g) {
     const OffT *off = (const OffT *)D.off;
     const int gn = grid_for(D.n, kBlock, 1024);
     hipLaunchKernelGGL(k_compact_rows<OffT>, dim3(gn), dim3(kBlock), 0, g->stream, off, D.deg, D.col, D.clab,
-                       D.elist, &D.ictr[kIcChanged]);
+                       D.lab, D.goff, D.fcol, D.elist, &D.ictr[kIcChanged]);
     hipLaunchKernelGGL(k_row_chunks, dim3(gn), dim3(kBlock), 0, g->stream, D.deg, D.elist, &D.ictr[kIcChanged],
                        D.echunk, &D.ictr[kIcChunks]);
     hipLaunchKernelGGL(k_mark_link<OffT>, dim3(gn), dim3(kBlock), 0, g->stream, link_args<OffT>(g), D.vmark,

@@ -216,8 +216,8 @@ struct HostGraph : HostTiles {
     std::vector<int32_t> col;   // internal rows
     std::vector<int32_t> lab;   // internal community per internal vertex
     std::vector<int32_t> new2old, old2new, comm2orig;
-    std::vector<int64_t> oo, goff;
-    std::vector<int32_t> outl, cstart;
+    std::vector<int64_t> oo;
+    std::vector<int32_t> goff, fcol, outl, cstart;
 };
 
 // Greedy cut of the vertex sequence into tiles of consecutive vertices: a
@@ -415,9 +415,19 @@ static rs_status build_internal(int64_t n, int64_t nnz, const OffIn *off, const 
         });
         // link slots: u's foreign entries in row order (the links themselves
         // are built on the device)
-        H.goff.assign(n + 1, 0);
-        for (int64_t x = 0; x < n; ++x) H.goff[x + 1] = H.goff[x] + fgn[x];
         if (H.oo[n] > (int64_t)INT32_MAX) return fail(RS_ERR_RANGE, "out-lists exceed 32-bit offsets");
+        if (H.oo[n] >= (int64_t)1 << 30)
+            return fail(RS_ERR_RANGE, "more than 2^30 edges between communities (slots are 32-bit)");
+        H.goff.assign(n + 1, 0);
+        for (int64_t x = 0; x < n; ++x) H.goff[x + 1] = H.goff[x] + (int32_t)fgn[x];
+        H.fcol.resize(H.goff[n]);
+        parallel_for(n, 4096, [&](int64_t lo, int64_t hi) {
+            for (int64_t x = lo; x < hi; ++x) {
+                int32_t o = H.goff[x];
+                for (int64_t j = H.off[x]; j < H.off[x + 1]; ++j)
+                    if (foreign(x, H.col[j])) H.fcol[o++] = H.col[j];
+            }
+        });
         H.cstart.resize(k + 1);
         for (int64_t c = 0; c <= k; ++c) H.cstart[c] = (int32_t)start[c];
         cut_all(n, H.off, cap, fgn, vstart, Tiling(), H);
@@ -506,10 +516,9 @@ static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool 
     D.nnz = nnz;
     D.k = (int32_t)H.comm2orig.size();
     D.off64 = nnz > (int64_t)INT32_MAX || g->wide_offsets;
-    if (H.outl.size() >= ((size_t)1 << 30))
-        return fail(RS_ERR_RANGE, "more than 2^30 edges between communities (out-list positions are 30-bit in hit records)");
     g->n_out = (int64_t)H.outl.size();
     const size_t N = (size_t)std::max<int64_t>(n, 1), Z = (size_t)std::max<int64_t>(nnz, 1);
+    const size_t NX = std::max<size_t>((size_t)H.goff[n], 1);
     const size_t offb = D.off64 ? 8 : 4;
     struct Req {
         void **p;
@@ -523,9 +532,10 @@ static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool 
         {(void **)&D.new2old, 4 * N},
         {(void **)&D.alive, N},
         {(void **)&D.oo, 8 * (N + 1)},
-        {(void **)&D.goff, 8 * (N + 1)},
-        {(void **)&D.prec, sizeof(PairRec) * Z},
-        {(void **)&D.plink, sizeof(PairLink) * std::max<size_t>((size_t)H.goff[n], 1)},
+        {(void **)&D.goff, 4 * (N + 1)},
+        {(void **)&D.fcol, 4 * NX},
+        {(void **)&D.prec, sizeof(PairRec) * NX},
+        {(void **)&D.plink, sizeof(PairLink) * NX},
         {(void **)&D.cstart, 4 * H.cstart.size()},
         {(void **)&D.wpart, 8 * (size_t)kWorkBlocks},
         {(void **)&D.raw, 8 * N},
@@ -540,9 +550,7 @@ static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool 
         {(void **)&g->rem_cnt, 8 * 4},
         {(void **)&D.outl, 4 * std::max<size_t>(H.outl.size(), 1)},
         {(void **)&D.oe, sizeof(OutEnt) * std::max<size_t>(H.outl.size(), 1)},
-        {(void **)&D.reckey, 4 * Z},
-        {(void **)&D.recdat, sizeof(RecDat) * Z},
-        {(void **)&D.card, sizeof(VCard) * N},
+        {(void **)&D.meta, sizeof(VMeta) * N},
         {(void **)&D.wown, 8 * N},
         {(void **)&D.av, 8 * N},
         {(void **)&D.R, 8 * N},
@@ -595,23 +603,9 @@ static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool 
         if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
     };
     put(D.oo, H.oo.data(), 8 * H.oo.size());
-    put(D.goff, H.goff.data(), 8 * H.goff.size());
+    put(D.goff, H.goff.data(), 4 * H.goff.size());
+    put(D.fcol, H.fcol.data(), 4 * H.fcol.size());
     put(D.cstart, H.cstart.data(), 4 * H.cstart.size());
-    std::vector<VCard> cards;
-    try {
-        cards.resize(n);
-    } catch (const std::bad_alloc &) {
-        return fail(RS_ERR_NOMEM, "host allocation failed while building vertex cards");
-    }
-    for (int64_t v = 0; v < n; ++v) {
-        VCard &c = cards[v];
-        memset(&c, 0, sizeof(c));
-        c.off = H.off[v];
-        c.goff = H.goff[v];
-        c.lab = H.lab[v];
-    }
-    put(D.card, cards.data(), sizeof(VCard) * cards.size());
-    if (e == hipSuccess && n) e = hipStreamSynchronize(s);  // the host cards must outlive the copy
     put(D.outl, H.outl.data(), 4 * H.outl.size());
     if (e == hipSuccess) e = hipMemsetAsync(D.alive, 1, N, s);
     if (e == hipSuccess) e = hipMemsetAsync(D.vmark, 0, 4 * N, s);
@@ -755,14 +749,7 @@ template <class T>
 static hipError_t d2h(std::vector<T> &dst, const void *src, int64_t count);
 
 // The last pass's row facts {deg, ell, p, q} of every vertex (internal ids).
-static hipError_t read_meta(rs_graph *g, std::vector<VMeta> &meta) {
-    std::vector<VCard> cards;
-    const hipError_t e = d2h(cards, g->d.card, g->d.n);
-    if (e != hipSuccess) return e;
-    meta.resize(cards.size());
-    for (size_t v = 0; v < cards.size(); ++v) meta[v] = cards[v].m;
-    return hipSuccess;
-}
+static hipError_t read_meta(rs_graph *g, std::vector<VMeta> &meta) { return d2h(meta, g->d.meta, g->d.n); }
 
 template <class T>
 static hipError_t d2h(std::vector<T> &dst, const void *src, int64_t count) {
@@ -818,7 +805,8 @@ static rs_status retile(rs_graph *g, const Tiling &T) {
     const int64_t n = D.n;
     hipError_t e = hipStreamSynchronize(g->stream);
     if (e != hipSuccess) return hip_fail(e, "retile");
-    std::vector<int64_t> off, goff, cap, fgn;
+    std::vector<int64_t> off, cap, fgn;
+    std::vector<int32_t> goff;
     HostTiles X;
     try {
         off.resize(n + 1);
@@ -832,7 +820,7 @@ static rs_status retile(rs_graph *g, const Tiling &T) {
             e = hipMemcpy(o32.data(), D.off, 4 * (size_t)(n + 1), hipMemcpyDeviceToHost);
             for (int64_t v = 0; v <= n; ++v) off[v] = o32[v];
         }
-        if (e == hipSuccess) e = hipMemcpy(goff.data(), D.goff, 8 * (size_t)(n + 1), hipMemcpyDeviceToHost);
+        if (e == hipSuccess) e = hipMemcpy(goff.data(), D.goff, 4 * (size_t)(n + 1), hipMemcpyDeviceToHost);
         if (e != hipSuccess) return hip_fail(e, "retile: reading the capacity layout");
         for (int64_t v = 0; v < n; ++v) {
             cap[v] = off[v + 1] - off[v];
@@ -1471,28 +1459,41 @@ rs_status rs_read_rows(rs_graph *g, int64_t *row_off, int32_t *comm, int32_t *co
     const int64_t n = g->d.n;
     hipError_t e = hipStreamSynchronize(g->stream);
     std::vector<VMeta> meta;
-    std::vector<int64_t> off;
     if (e == hipSuccess) e = read_meta(g, meta);
-    if (e == hipSuccess) e = read_offsets(g, off);
     if (e != hipSuccess) return hip_fail(e, "row copy");
     row_off[0] = 0;
     for (int64_t v = 0; v < n; ++v) row_off[v + 1] = row_off[v] + meta[g->h_old2new[v]].ell;
     if (!comm && !count && !weight) return RS_OK;
-    std::vector<int32_t> key;
-    std::vector<RecDat> dat;
-    e = d2h(key, g->d.reckey, g->d.nnz);
-    if (e == hipSuccess) e = d2h(dat, g->d.recdat, g->d.nnz);
+    // a row's foreign records sit at the leader slots (a run's length leads
+    // to the next leader); the own community's goes in by its number
+    std::vector<int32_t> goff, lab;
+    std::vector<PairRec> rec;
+    std::vector<double> own;
+    e = d2h(goff, g->d.goff, n + 1);
+    if (e == hipSuccess) e = d2h(lab, g->d.lab, n);
+    if (e == hipSuccess) e = d2h(own, g->d.wown, n);
+    if (e == hipSuccess) e = d2h(rec, g->d.prec, n ? goff[n] : 0);
     if (e != hipSuccess) return hip_fail(e, "row copy");
     for (int64_t v = 0; v < n; ++v) {
         const int32_t x = g->h_old2new[v];
-        const int64_t rb = off[x];
         const VMeta &m = meta[x];
-        for (int32_t r = 0; r < m.ell; ++r) {
-            const int64_t o = row_off[v] + r;
-            if (comm) comm[o] = g->h_comm2orig[key[rb + r]];
-            if (count) count[o] = dat[rb + r].f;
-            if (weight) weight[o] = dat[rb + r].w;
+        int64_t o = row_off[v];
+        auto put = [&](int32_t c, int32_t f, double w) {
+            if (comm) comm[o] = g->h_comm2orig[c];
+            if (count) count[o] = f;
+            if (weight) weight[o] = w;
+            ++o;
+        };
+        bool own_due = m.q > m.p;
+        const int32_t s1 = goff[x] + m.deg - (m.q - m.p);
+        for (int32_t s = goff[x]; s < s1; s += rec[s].f) {
+            if (own_due && rec[s].c > lab[x]) {
+                put(lab[x], m.q - m.p, own[x]);
+                own_due = false;
+            }
+            put(rec[s].c, rec[s].f, rec[s].w);
         }
+        if (own_due) put(lab[x], m.q - m.p, own[x]);
     }
     return RS_OK;
 }
