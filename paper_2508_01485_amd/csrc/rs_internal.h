@@ -107,7 +107,7 @@ inline int tile_grid(int hubs, int tiles) { return hubs + 8 * ((tiles + 7) / 8);
 
 enum KernelId {
     K_ROWS = 0,
-    K_WMAX,
+    K_MID,
     K_SCORE_HUB,
     K_SCORE,
     K_TOPK_HIST,
@@ -117,8 +117,6 @@ enum KernelId {
     K_TOPK_RANK,
     K_HUB_SUM,
     K_TOPK_GRAPHS,
-    K_WMAX_GRAPHS,
-    K_HUB_FILTERS,
     K_COUNT
 };
 
@@ -128,7 +126,8 @@ struct __align__(16) VMeta {
 
 // The interaction-matrix record of a vertex v and a foreign community c, at
 // the leader slot of c's run in v's list: w_v(c), the run's length f (the
-// number of v's neighbours in c) and c.
+// number of v's neighbours in c) and c.  The run's other slots hold the same
+// w and c and, in the place of f, the negated distance to the leader.
 struct __align__(16) PairRec {
     double w;
     int f;
@@ -223,6 +222,7 @@ struct DeviceGraph {
     int32_t *goff = nullptr;    // [n+1] slot offsets of the foreign entries
     int32_t *fcol = nullptr;    // [slots] foreign neighbours
     PairRec *prec = nullptr;    // [slots] records at the leader slots
+    double *val2 = nullptr;     // [slots] type-II value of each run member (runs longer than one; full passes)
     PairLink *plink = nullptr;  // [slots]
     int32_t *cstart = nullptr;  // [k+1] first internal id of each community
     unsigned long long *wpart = nullptr;  // [kWorkBlocks] partials of the on-demand W1 count
@@ -230,8 +230,8 @@ struct DeviceGraph {
     unsigned int *vmark = nullptr;          // [n] kRowChanged | kAffected
     int32_t *vrowb = nullptr;               // [n] row block of each vertex
     int32_t *vscore = nullptr;              // [n] score tile block, or -1 - score hub index
-    unsigned long long *wblk = nullptr;  // [64] per-workgroup maxima of k_wmax
-    unsigned int *wticket = nullptr;     // k_wmax's finishing ticket (zero between passes)
+    unsigned long long *wblk = nullptr;  // [64] per-workgroup maxima of k_mid
+    unsigned int *wticket = nullptr;     // k_mid's finishing ticket (zero between passes)
     OutEnt *oe = nullptr;         // [out-list entries] leader slots of each out-list entry's edge
     uint32_t *hfilter = nullptr;  // [big hubs][kFilterWords] membership filter of each big hub's foreign neighbours
     uint8_t *rflag = nullptr, *cflag = nullptr, *hflag = nullptr;  // flags: row blocks, score-hub chunks, score hubs (whole)
@@ -308,6 +308,7 @@ struct rs_graph {
     int n_schunks_lds = 0;               // chunks of hubs whose foreign list fits in LDS (listed first)
     int n_shubs_lds = 0;                 // those hubs (the big hubs follow)
     int64_t n_out = 0;                   // out-list entries (G' edges)
+    bool type2_by_slot = false;          // full passes compute the type-II values by slot (k_mid)
     int grid_rows = 0, grid_score = 0;   // hubs first, then the tiles in XCD-major order
     std::vector<int32_t> h_new2old, h_old2new, h_comm2orig;
     rs::DeviceGraph d;
@@ -365,7 +366,7 @@ rs_status launch_remove_edges(rs_graph *g, const int32_t *d_src, const int32_t *
                               unsigned long long *d_removed);
 rs_status launch_remove_vertices(rs_graph *g, const int32_t *d_verts, int64_t nv,
                                  unsigned long long *d_removed_edges);
-rs_status launch_links(rs_graph *g);
+rs_status launch_links(rs_graph *g, unsigned long long *d_run_walk);
 rs_status launch_col_labels(rs_graph *g);
 rs_status launch_out_entries(rs_graph *g);
 rs_status launch_incremental_marks(rs_graph *g);

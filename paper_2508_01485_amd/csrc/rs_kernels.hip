@@ -113,7 +113,7 @@ struct RowArgs {
     double *av;  // [n] a_v = cbrt(own-community weight), dense for the score pass's run sums
     long long *tI, *tII;
     RowPart *part;
-    unsigned long long *wmax_part;  // [grid] w_max bits of each block (dense copy for k_wmax)
+    unsigned long long *wmax_part;  // [grid] w_max bits of each block (dense copy for k_mid)
 };
 
 struct RowResult {
@@ -372,7 +372,13 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
         pr.f = (int)S.runpos[r + 1] - p0;
         pr.w = weight_present_t(S.tab, S.vd[i], S.vX[i], S.vell[i], pr.f);
         pr.c = lb;
-        A.prec[S.vslot[i] + p0 - (lb > cv ? (int)S.vfo[i] : 0)] = pr;
+        const int s = S.vslot[i] + p0 - (lb > cv ? (int)S.vfo[i] : 0);
+        const int f = pr.f;
+        A.prec[s] = pr;
+        for (int t = 1; t < f; ++t) {
+            pr.f = -t;
+            A.prec[s + t] = pr;
+        }
         acc.wmax = fmax(acc.wmax, pr.w);
     }
 }
@@ -402,7 +408,12 @@ __device__ __forceinline__ void hub_run(const RowArgs<OffT> &A, int d, int cv, c
         pr.w = weight_present(d, T.X, T.ell, f);
         pr.f = f;
         pr.c = label;
-        A.prec[T.go + start - (label > cv ? T.fown : 0)] = pr;
+        const int s = T.go + start - (label > cv ? T.fown : 0);
+        A.prec[s] = pr;
+        for (int t = 1; t < f; ++t) {
+            pr.f = -t;
+            A.prec[s + t] = pr;
+        }
         lmax = fmax(lmax, pr.w);
     }
 }
@@ -656,26 +667,26 @@ __global__ __launch_bounds__(kBlock) void k_rows_inc(RowArgs<OffT> A, const unsi
     }
 }
 
-// w_max of a pass from the dense per-block maxima of the row kernel: up to
-// kWmaxBlocks workgroups of 1,024 threads each take a contiguous slice
+// w_max of a pass from the dense per-block maxima of the row kernel (part of
+// k_mid): up to kWmaxBlocks workgroups of 1,024 threads each take a contiguous slice
 // (eight loads per thread in flight together) and store its maximum; the
 // workgroup that finishes last (a ticket) takes the maximum of those and
 // resets the ticket.  A maximum does not depend on the order, so the bits are
 // those of a single workgroup's.  The other row totals are reduced only when
 // a reader asks for them.
 constexpr int kWmaxBlocks = 64;
-__global__ __launch_bounds__(1024) void k_wmax(const unsigned long long *wpart, int np, unsigned long long *wblk,
-                                               unsigned int *ticket, DevCounters *c) {
-    __shared__ unsigned long long s[16];
-    __shared__ bool last;
-    const int per = (np + gridDim.x - 1) / gridDim.x;
-    const int lo = blockIdx.x * per, hi = min(np, lo + per);
+constexpr int kMidThreads = 1024;
+__device__ __forceinline__ void reduce_wmax(const unsigned long long *wpart, int np, int block, int blocks,
+                                            unsigned long long *wblk, unsigned int *ticket, DevCounters *c) {
+    __shared__ unsigned long long s[kMidThreads / 64];
+    const int per = (np + blocks - 1) / blocks;
+    const int lo = block * per, hi = min(np, lo + per);
     unsigned long long w = 0;
-    for (int i0 = lo + threadIdx.x; i0 < hi; i0 += 8 * 1024) {
+    for (int i0 = lo + threadIdx.x; i0 < hi; i0 += 8 * kMidThreads) {
         unsigned long long q[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const int i = i0 + j * 1024;
+            const int i = i0 + j * kMidThreads;
             q[j] = i < hi ? wpart[i] : 0ull;
         }
 #pragma unroll
@@ -686,18 +697,19 @@ __global__ __launch_bounds__(1024) void k_wmax(const unsigned long long *wpart, 
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long m = 0;
-        for (int i = 0; i < 16; ++i) m = max(m, s[i]);
-        wblk[blockIdx.x] = m;
-        __threadfence();
-        last = atomicAdd(ticket, 1u) == gridDim.x - 1;
-    }
-    __syncthreads();
-    if (last && threadIdx.x == 0) {
-        __threadfence();
-        unsigned long long m = 0;
-        for (unsigned int i = 0; i < gridDim.x; ++i) m = max(m, ((volatile unsigned long long *)wblk)[i]);
-        c->wmax_bits = m;
-        *ticket = 0u;
+        for (int i = 0; i < kMidThreads / 64; ++i) m = max(m, s[i]);
+        bool last = true;
+        if (blocks > 1) {
+            wblk[block] = m;
+            __threadfence();
+            last = atomicAdd(ticket, 1u) == (unsigned int)blocks - 1u;
+            if (last) {
+                __threadfence();
+                for (int i = 0; i < blocks; ++i) m = max(m, ((volatile unsigned long long *)wblk)[i]);
+                *ticket = 0u;
+            }
+        }
+        if (last) c->wmax_bits = m;
     }
 }
 
@@ -705,12 +717,9 @@ __global__ __launch_bounds__(1024) void k_wmax(const unsigned long long *wpart, 
 // blocks (row tiles never span two graphs), one wavefront per graph.  The
 // block values are fp64 bits maximised as integers, as for the whole-graph
 // w_max, so a graph's w_max has the bits it has when the graph is alone.
-__global__ __launch_bounds__(kBlock) void k_wmax_graphs(const unsigned long long *wpart, const int32_t *gblk_off,
-                                                        const int32_t *gblk, int n_graphs,
-                                                        unsigned long long *gwmax) {
-    const int gi = (int)blockIdx.x * (kBlock / 64) + (int)(threadIdx.x >> 6);
+__device__ __forceinline__ void reduce_wmax_graph(const unsigned long long *wpart, const int32_t *gblk_off,
+                                                  const int32_t *gblk, int gi, unsigned long long *gwmax) {
     const int lane = threadIdx.x & 63;
-    if (gi >= n_graphs) return;  // whole wavefronts leave; no barrier follows
     unsigned long long m = 0;
     for (int i = gblk_off[gi] + lane; i < gblk_off[gi + 1]; i += 64) m = max(m, wpart[gblk[i]]);
     for (int o = 32; o > 0; o >>= 1) m = max(m, (unsigned long long)__shfl_xor(m, o));
@@ -741,7 +750,7 @@ struct ScoreArgs {
     int n_hubs_lds;
     const PairLink *plink;  // the links of the slots
     const double *av;       // [n] a_v of the row pass
-    const int *blist;       // unused by the score kernels (the incremental lists are arguments)
+    const double *val2;     // the slots' type-II values (k_mid), or null: each pair sums its run
     const unsigned long long *gwmax;  // batched graphs: w_max bits of each graph, else null
     const int32_t *vgraph;            // batched graphs: graph of each vertex
     double *R, *raw;
@@ -834,8 +843,11 @@ __device__ __forceinline__ bool out_has(const int32_t *outl, long long o0, long 
 // of C(u) in w's list from its leader slot on): W^(2/3) times the sum of a_v
 // over the other members v of that run (v in C(u), v adjacent to w; counted
 // whether or not v ~ u), and the count f_w(C(u)) - 1.
-__device__ __forceinline__ double type2_pair(const ScoreArgs &A, int u, const PairRec &pr, int lead) {
+// val2 holds the same sums, in the same order, when k_mid computed them.
+__device__ __forceinline__ double type2_pair(const ScoreArgs &A, int u, const PairRec &pr, const PairLink &pl) {
     if (pr.f <= 1) return 0.0;
+    if (A.val2) return A.val2[pl.slot];
+    const int lead = pl.lead;
     double S = 0.0;
     const int32_t *run = A.fcol + lead;
     for (int i = 0; i < pr.f; i += 8) {
@@ -1195,7 +1207,7 @@ __device__ void score_unit(const ScoreArgs &A, SU &S, bool hub_unit_arg, int idx
         }
         const PairLink pl = A.plink[slot];
         const PairRec pr = A.prec[pl.lead];
-        val = type2_pair(A, u, pr, pl.lead);
+        val = type2_pair(A, u, pr, pl);
         t2 = pr.f - 1;
         items = pl.on;
         S.ti.ioo[tid] = pl.oo;
@@ -1310,7 +1322,7 @@ __device__ void score_hub_big(const ScoreArgs &A, ScoreHubBigShared &S, int hub,
     if (k < dp) {
         const PairLink pl = A.plink[A.goff[u] + k];
         const PairRec pr = A.prec[pl.lead];
-        val = type2_pair(A, u, pr, pl.lead);
+        val = type2_pair(A, u, pr, pl);
         t2 = pr.f - 1;
         items = pl.on;
         S.ti.ioo[tid] = pl.oo;
@@ -1333,25 +1345,148 @@ __device__ void score_hub_big(const ScoreArgs &A, ScoreHubBigShared &S, int hub,
 }
 
 // Each big hub's neighbour filter from its current foreign list (after the
-// row pass): built in LDS by one workgroup per
-// hub, then written out whole.
-__global__ __launch_bounds__(kBlock) void k_hub_filters(const int32_t *hubs, int h0, const VMeta *meta,
-                                                        const int32_t *goff, const int32_t *fcol,
-                                                        uint32_t *filters) {
-    __shared__ uint32_t f[kFilterWords];
-    const int h = h0 + (int)blockIdx.x;
-    for (int i = threadIdx.x; i < kFilterWords; i += kBlock) f[i] = 0u;
-    __syncthreads();
-    const VMeta m = meta[hubs[h]];
-    const int go = goff[hubs[h]];
+// row pass): built in LDS by one workgroup per hub, kFiltPer neighbours per
+// thread loaded together, then written out whole.
+constexpr int kFiltPer = 8;
+__device__ __forceinline__ void build_filter(uint32_t *f, const VMeta *meta, const int32_t *goff, const int32_t *fcol,
+                                             int hub, uint32_t *out) {
+    for (int i = threadIdx.x; i < kFilterWords; i += kMidThreads) f[i] = 0u;
+    const VMeta m = meta[hub];
+    const int go = goff[hub];
     const int dp = m.deg - (m.q - m.p);
-    for (int j = threadIdx.x; j < dp; j += kBlock) {
-        const uint32_t x = filter_hash(fcol[go + j]);
-        atomicOr(&f[x >> 5], 1u << (x & 31));
+    __syncthreads();
+    for (int j0 = threadIdx.x; j0 < dp; j0 += kFiltPer * kMidThreads) {
+        int y[kFiltPer];
+#pragma unroll
+        for (int t = 0; t < kFiltPer; ++t) y[t] = fcol[go + min(j0 + t * kMidThreads, dp - 1)];  // (repeats set a bit again)
+#pragma unroll
+        for (int t = 0; t < kFiltPer; ++t) {
+            const uint32_t x = filter_hash(y[t]);
+            atomicOr(&f[x >> 5], 1u << (x & 31));
+        }
     }
     __syncthreads();
-    uint32_t *out = filters + (size_t)blockIdx.x * kFilterWords;
-    for (int i = threadIdx.x; i < kFilterWords; i += kBlock) out[i] = f[i];
+    for (int i = threadIdx.x; i < kFilterWords; i += kMidThreads) out[i] = f[i];
+}
+
+// Type-II values by slot: for a run of w's list longer than one (the members
+// of one community c adjacent to w), every member x gets
+//   w_w(c)^(2/3) * (the sum of a_v over the run's other members v),
+// the type-II terms of the pair (x, w) (Lemma 2), so the score pass reads one
+// value where it would walk the run: a hub's run of hundreds of members is
+// walked by each of its members, by one lane each, and at n = 3 million, mean
+// degree 30, those walks (43 M gathers for 13.7 M pairs) held the score
+// kernel at 2.0 ms.  Here each a_v is gathered once, into LDS, and a member
+// sums the run from there, in run order (the order of type2_pair, so the bits
+// are the same).  A workgroup takes kT2Tile consecutive slots and stages them
+// with the rest of the runs cut at both ends; runs too long for the window
+// are summed from memory.
+constexpr int kT2Per = 2;
+constexpr int kT2Tile = kT2Per * kMidThreads;
+constexpr int kT2Win = 4096;  // staged a_v (32 KB, the size of a filter)
+__device__ __forceinline__ void type2_tile(double *s_a, const PairRec *prec, const int32_t *fcol, const double *av,
+                                           double *val2, int slots, int tile) {
+    const int s0 = tile * kT2Tile, s1 = min(slots, s0 + kT2Tile);
+    // slots beyond a list that removals shrank hold the runs of an earlier
+    // pass: their values are never read, and their runs stay in range
+    PairRec rec[kT2Per];
+    int lead[kT2Per], f[kT2Per];
+#pragma unroll
+    for (int j = 0; j < kT2Per; ++j) rec[j] = prec[min(s0 + (int)threadIdx.x + j * kMidThreads, s1 - 1)];
+    const PairRec r0 = prec[s0], r1 = prec[s1 - 1];
+    const int l1 = r1.f < 0 ? s1 - 1 + r1.f : s1 - 1;
+    const int e1 = l1 + max(1, prec[l1].f);
+    // the window: from the leader of the first slot's run to the end of the
+    // last slot's, as far as it holds them
+    const int lo = r0.f < 0 ? max(s0 + r0.f, s0 - (kT2Win - kT2Tile) / 2) : s0;
+    const int hi = min(lo + kT2Win, min(slots, max(s1, e1)));
+#pragma unroll
+    for (int j = 0; j < kT2Per; ++j) {
+        const int s = s0 + (int)threadIdx.x + j * kMidThreads;
+        lead[j] = rec[j].f < 0 ? s + rec[j].f : s;
+        f[j] = s < s1 ? (rec[j].f < 0 ? prec[lead[j]].f : rec[j].f) : 0;
+        if (f[j] > 1) s_a[s - lo] = av[fcol[s]];
+    }
+    for (int s = lo + (int)threadIdx.x; s < s0; s += kMidThreads) s_a[s - lo] = av[fcol[s]];
+    for (int s = s1 + (int)threadIdx.x; s < hi; s += kMidThreads) s_a[s - lo] = av[fcol[s]];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kT2Per; ++j) {
+        if (f[j] <= 1) continue;
+        const int s = s0 + (int)threadIdx.x + j * kMidThreads;
+        const int b = lead[j], e = lead[j] + f[j];
+        double S = 0.0;
+        if (b >= lo && e <= hi) {
+            for (int i = b; i < e; i += 8) {
+                double x[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) x[t] = i + t < e && i + t != s ? s_a[min(i + t, e - 1) - lo] : 0.0;
+#pragma unroll
+                for (int t = 0; t < 8; ++t) S += x[t];
+            }
+        } else {
+            for (int i = b; i < e; i += 16) {
+                int y[16];
+#pragma unroll
+                for (int t = 0; t < 16; ++t) y[t] = fcol[min(i + t, e - 1)];
+                double x[16];
+#pragma unroll
+                for (int t = 0; t < 16; ++t) x[t] = av[y[t]];
+#pragma unroll
+                for (int t = 0; t < 16; ++t) S += i + t < e && i + t != s ? x[t] : 0.0;
+            }
+        }
+        const double c1 = cbrt(rec[j].w);
+        val2[s] = c1 * c1 * S;
+    }
+}
+
+// Everything between the row pass and the score pass, in one launch whose
+// parts do not depend on each other: w_max (n_wmax workgroups), each graph's
+// w_max of a batch (one wavefront per graph), the big hubs' filters (one
+// workgroup each) and the type-II values (n_t2 tiles; 0 when the pairs sum
+// their runs themselves).
+struct MidArgs {
+    const unsigned long long *wpart;
+    int n_parts, n_wmax;
+    unsigned long long *wblk;
+    unsigned int *wticket;
+    DevCounters *ctr;
+    const int32_t *gblk_off, *gblk;
+    int n_graphs;
+    unsigned long long *gwmax;
+    const int32_t *big_hubs;
+    int n_filters;
+    uint32_t *filters;
+    const VMeta *meta;
+    const int32_t *goff, *fcol;
+    const PairRec *prec;
+    const double *av;
+    double *val2;
+    int slots, n_t2;
+};
+constexpr int kMidGraphs = kMidThreads / 64;  // graphs per workgroup
+__global__ __launch_bounds__(kMidThreads) void k_mid(MidArgs M) {
+    __shared__ __align__(16) unsigned char buf[4 * kFilterWords];
+    static_assert(sizeof(buf) == 8 * kT2Win, "a filter and a type-II window share the LDS");
+    int b = (int)blockIdx.x;
+    if (b < M.n_wmax) {
+        reduce_wmax(M.wpart, M.n_parts, b, M.n_wmax, M.wblk, M.wticket, M.ctr);
+        return;
+    }
+    b -= M.n_wmax;
+    if (b < M.n_filters) {
+        build_filter((uint32_t *)buf, M.meta, M.goff, M.fcol, M.big_hubs[b], M.filters + (size_t)b * kFilterWords);
+        return;
+    }
+    b -= M.n_filters;
+    if (b < M.n_t2) {
+        type2_tile((double *)buf, M.prec, M.fcol, M.av, M.val2, M.slots, b);
+        return;
+    }
+    b -= M.n_t2;
+    const int gi = b * kMidGraphs + (int)(threadIdx.x >> 6);
+    if (gi < M.n_graphs) reduce_wmax_graph(M.wpart, M.gblk_off, M.gblk, gi, M.gwmax);
 }
 
 // Algorithm 1 Step 3 (Eq. RSI) for every border vertex of the LDS-sized
@@ -1640,9 +1775,13 @@ __device__ __forceinline__ int owner_of(const T *off, long long n, long long s) 
     return (int)lo;
 }
 
-// Every slot's link (at load, when the lists are whole).
+// Every slot's link (at load, when the lists are whole).  run_walk[0] gets
+// the sum of the slots' distances to their leaders: half the steps in which
+// the pairs would walk each other's runs.
 template <typename OffT>
-__global__ __launch_bounds__(kBlock) void k_links(LinkArgs<OffT> L, long long n, long long slots) {
+__global__ __launch_bounds__(kBlock) void k_links(LinkArgs<OffT> L, long long n, long long slots,
+                                                  unsigned long long *run_walk) {
+    unsigned long long walk = 0;
     for (long long s = (long long)blockIdx.x * kBlock + threadIdx.x; s < slots; s += (long long)gridDim.x * kBlock) {
         const int x = owner_of(L.goff, n, s);
         const int y = L.fcol[s];
@@ -1658,6 +1797,16 @@ __global__ __launch_bounds__(kBlock) void k_links(LinkArgs<OffT> L, long long n,
         pl.oo = (int)L.oo[y];
         pl.on = (int)(L.oo[y + 1] - L.oo[y]);
         L.plink[s] = pl;
+        walk += (unsigned long long)(k[1] - k[0]);
+    }
+    __shared__ unsigned long long s_w[kBlock / 64];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) walk += __shfl_xor(walk, o);
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = walk;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < kBlock / 64; ++i) walk += s_w[i];
+        if (walk) atomicAdd(run_walk, walk);
     }
 }
 
@@ -1682,17 +1831,19 @@ static LinkArgs<OffT> link_args(rs_graph *g) {
 }
 
 template <typename OffT>
-static rs_status links_t(rs_graph *g) {
+static rs_status links_t(rs_graph *g, unsigned long long *run_walk) {
     DeviceGraph &D = g->d;
     const long long slots = 2 * g->n_out;  // each G' edge has one out-list entry and two slots
     if (slots == 0) return RS_OK;
-    hipLaunchKernelGGL(k_links<OffT>, dim3(grid_for(slots, kBlock, 65536)), dim3(kBlock), 0, g->stream,
-                       link_args<OffT>(g), (long long)D.n, slots);
+    hipLaunchKernelGGL(k_links<OffT>, dim3(grid_for(slots, kBlock, 4096)), dim3(kBlock), 0, g->stream,
+                       link_args<OffT>(g), (long long)D.n, slots, run_walk);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? RS_OK : hip_fail(e, "link-slot launch");
 }
 
-rs_status launch_links(rs_graph *g) { return g->d.off64 ? links_t<long long>(g) : links_t<int32_t>(g); }
+rs_status launch_links(rs_graph *g, unsigned long long *d_run_walk) {
+    return g->d.off64 ? links_t<long long>(g, d_run_walk) : links_t<int32_t>(g, d_run_walk);
+}
 
 // Each out-list entry x -> y (at load): the leader slots of C(y)'s run in x's
 // list and of C(x)'s run in y's list; the owner x is the last with oo[x] <= o.
@@ -1889,16 +2040,35 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
         hipLaunchKernelGGL(k_rows<OffT>, dim3(g->grid_rows), dim3(kBlock), 0, g->stream, A);
         timing_end(g, K_ROWS, ev);
     }
-    timing_begin(g, K_WMAX, &ev);
-    hipLaunchKernelGGL(k_wmax, dim3(std::max(1, std::min(kWmaxBlocks, (g->grid_rows + 8191) / 8192))), dim3(1024), 0,
-                       g->stream, D.wmax_part, g->grid_rows, D.wblk, D.wticket, D.ctr);
-    timing_end(g, K_WMAX, ev);
-    if (g->n_graphs > 0) {
-        timing_begin(g, K_WMAX_GRAPHS, &ev);
-        hipLaunchKernelGGL(k_wmax_graphs, dim3((g->n_graphs + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0,
-                           g->stream, D.wmax_part, D.gblk_off, D.gblk, g->n_graphs, D.gwmax);
-        timing_end(g, K_WMAX_GRAPHS, ev);
-    }
+    const int n_big_hubs = g->n_shubs - g->n_shubs_lds;
+    const long long slots = 2 * g->n_out;
+    const bool by_slot = !inc && g->type2_by_slot;
+    MidArgs M;
+    M.wpart = D.wmax_part;
+    M.n_parts = g->grid_rows;
+    M.n_wmax = std::max(1, std::min(kWmaxBlocks, (g->grid_rows + 8191) / 8192));
+    M.wblk = D.wblk;
+    M.wticket = D.wticket;
+    M.ctr = D.ctr;
+    M.gblk_off = D.gblk_off;
+    M.gblk = D.gblk;
+    M.n_graphs = g->n_graphs;
+    M.gwmax = D.gwmax;
+    M.big_hubs = D.shubs + g->n_shubs_lds;
+    M.n_filters = n_big_hubs;
+    M.filters = D.hfilter;
+    M.meta = D.meta;
+    M.goff = D.goff;
+    M.fcol = D.fcol;
+    M.prec = D.prec;
+    M.av = D.av;
+    M.val2 = D.val2;
+    M.slots = (int)slots;
+    M.n_t2 = by_slot ? (int)((slots + kT2Tile - 1) / kT2Tile) : 0;
+    timing_begin(g, K_MID, &ev);
+    hipLaunchKernelGGL(k_mid, dim3(M.n_wmax + M.n_filters + M.n_t2 + (M.n_graphs + kMidGraphs - 1) / kMidGraphs),
+                       dim3(kMidThreads), 0, g->stream, M);
+    timing_end(g, K_MID, ev);
 
     ScoreArgs S;
     S.goff = D.goff;
@@ -1922,6 +2092,7 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
     S.n_hubs_lds = g->n_shubs_lds;
     S.plink = D.plink;
     S.av = D.av;
+    S.val2 = by_slot ? D.val2 : nullptr;
     S.R = D.R;
     S.raw = D.raw;
     S.gwmax = g->n_graphs > 0 ? D.gwmax : nullptr;
@@ -1929,16 +2100,8 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
     S.tI = D.tI;
     S.tII = D.tII;
     S.ctr = D.ctr;
-    const int n_big_hubs = g->n_shubs - g->n_shubs_lds;
-    if (n_big_hubs > 0) {  // the big hubs' neighbour filters for the edge tests below
-        timing_begin(g, K_HUB_FILTERS, &ev);
-        hipLaunchKernelGGL(k_hub_filters, dim3(n_big_hubs), dim3(kBlock), 0, g->stream, D.shubs, g->n_shubs_lds,
-                           D.meta, D.goff, D.fcol, D.hfilter);
-        timing_end(g, K_HUB_FILTERS, ev);
-    }
     const unsigned long long *ictr = D.ictr;
     if (inc) {
-        S.blist = nullptr;
         timing_begin(g, K_SCORE, &ev);
         hipLaunchKernelGGL(k_score_inc, dim3(kIncGrid), dim3(kBlock), 0, g->stream, S, (const int32_t *)D.hlist,
                            (const int32_t *)D.slist, (const int32_t *)D.abin, ictr, D.hflag, g->grid_rows,
@@ -1946,12 +2109,10 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
         timing_end(g, K_SCORE, ev);
     } else {
         if (n_big > 0) {
-            S.blist = nullptr;
-            timing_begin(g, K_SCORE_HUB, &ev);
+                timing_begin(g, K_SCORE_HUB, &ev);
             hipLaunchKernelGGL(k_score_hub, dim3(n_big), dim3(kBlock), 0, g->stream, S);
             timing_end(g, K_SCORE_HUB, ev);
         }
-        S.blist = nullptr;
         const int grid_tiles = grid_main - g->n_schunks_lds;  // the tiles, rounded up to the 8 XCDs
         timing_begin(g, K_SCORE, &ev);
         if (g->n_schunks_lds >= kSplitHubChunks) {  // many LDS hubs: tiles with the smaller LDS form

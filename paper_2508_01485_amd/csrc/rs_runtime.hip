@@ -535,6 +535,7 @@ static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool 
         {(void **)&D.goff, 4 * (N + 1)},
         {(void **)&D.fcol, 4 * NX},
         {(void **)&D.prec, sizeof(PairRec) * NX},
+        {(void **)&D.val2, 8 * NX},
         {(void **)&D.plink, sizeof(PairLink) * NX},
         {(void **)&D.cstart, 4 * H.cstart.size()},
         {(void **)&D.wpart, 8 * (size_t)kWorkBlocks},
@@ -621,12 +622,24 @@ static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool 
     if (e != hipSuccess) return hip_fail(e, "graph upload");
     const rs_status lst = launch_col_labels(g);  // each entry's neighbour community
     if (lst != RS_OK) return lst;
-    const rs_status rst = launch_links(g);  // each G' entry's reverse entry and out-list range
+    unsigned long long walk = 0;
+    rs_status rst = launch_zero_u64(g, D.scratch_u, 1);
+    if (rst == RS_OK) rst = launch_links(g, D.scratch_u);
     if (rst != RS_OK) return rst;
+    e = hipMemcpyAsync(&walk, D.scratch_u, 8, hipMemcpyDeviceToHost, s);
+    if (e != hipSuccess) return hip_fail(e, "run lengths");
     const rs_status ost = launch_out_entries(g);  // each out-list entry's two row entries
     if (ost != RS_OK) return ost;
     e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "pair-slot map");
+    // The type-II values by slot cost each slot some 7 to 11 ps (its record
+    // and neighbour read once more); the pairs walking the runs themselves
+    // cost 14 to 41 ps a step.  With half the steps at 0.07 and 0.16 of the
+    // slots (n = 1 M, mean degree 20; 128 graphs of 200 to 50,000 vertices)
+    // the walks are faster (302 against 316 us a pass; 522 against 567), at
+    // 1.06 and 1.21 (n = 3 M, mean degree 30; n = 150 K, mean degree 71) the
+    // values by slot (1,818 against 2,675 us; 686 against 776).
+    g->type2_by_slot = 4 * walk >= (unsigned long long)H.goff[n];
     if (keep) {
         try {
             g->h_new2old = H.new2old;
@@ -1533,8 +1546,8 @@ rs_status rs_read_gprime(rs_graph *g, int64_t *goff, int32_t *gcol) {
 }
 
 static const char *kKernelNames[K_COUNT] = {
-    "k_rows", "k_wmax", "k_score_hub", "k_score", "k_topk_hist", "k_topk_find", "k_topk_collect", "k_tie_rank", "k_final_order",
-    "k_hub_sum", "k_topk_graphs", "k_wmax_graphs", "k_hub_filters"};
+    "k_rows", "k_mid", "k_score_hub", "k_score", "k_topk_hist", "k_topk_find", "k_topk_collect", "k_tie_rank", "k_final_order",
+    "k_hub_sum", "k_topk_graphs"};
 
 const char *rs_kernel_name(int32_t id) { return (id >= 0 && id < K_COUNT) ? kKernelNames[id] : nullptr; }
 
