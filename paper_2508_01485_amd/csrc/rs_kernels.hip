@@ -232,13 +232,56 @@ struct RowTileShared {
     unsigned short runv[kRowTile];       // tile-local vertex of each run
     int runlab[kRowTile];                // label of each run (-1: removed tail)
     double vX[kRowTileV];
-    int vd[kRowTileV], vell[kRowTileV], vlab[kRowTileV];
-    int vslot[kRowTileV];            // slot of a foreign entry below the own run, minus its tile-local entry
-    unsigned short vfo[kRowTileV];   // own run's length
+    unsigned int vde[kRowTileV];     // degree and ell (16 bits each)
+    short vslot[kRowTileV];          // tile slot of a foreign entry below the own community, minus its tile-local entry
+    unsigned short vrun[kRowTileV];  // first run not below the own community, and kOwnRun when that is the own one
 };
+constexpr int kOwnRun = 0x8000;
+// A workgroup takes 26.9 KB, so six share a CU (with the facts unpacked, five).
+static_assert(6 * sizeof(RowTileShared) <= 160 * 1024, "six row workgroups per CU");
 
 __device__ __forceinline__ int run_index(const RowTileShared &S, int e) {
     return S.mbase[e >> 6] + __popcll(S.mask[e >> 6] & ((1ull << (e & 63)) - 1ull));
+}
+
+// A wavefront's walk over the runs [rf, re) of one vertex (64 at a time), for
+// rows with more than kWalkRuns runs, where one lane's walk keeps the other 63
+// waiting.  X adds the runs in order, as the single lane does: a run of
+// length one adds zero, so only the longer ones take a step each.  Labels
+// ascend, so the runs below the own community are counted.  The totals go to
+// the lane that owns the vertex.
+constexpr int kWalkRuns = 20;
+__device__ __forceinline__ double lane_value(double x, int l) {
+    const unsigned long long b = dbits(x);
+    const unsigned int lo = __builtin_amdgcn_readlane((int)(unsigned int)b, l);
+    const unsigned int hi = __builtin_amdgcn_readlane((int)(unsigned int)(b >> 32), l);
+    return bitsd(((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ void wave_walk(RowTileShared &S, int rf, int re, int cv, int i, int lane, bool mine,
+                                          double &X, int &ell, int &nbelow, bool &own) {
+    double x = 0.0;
+    int n = 0, nb = 0;
+    bool o = false;
+    for (int r0 = rf; r0 < re; r0 += 64) {
+        const int r = r0 + lane;
+        int lb = -1, f = 0;
+        if (r < re) {
+            lb = S.runlab[r];
+            f = lb < 0 ? 0 : (int)S.runpos[r + 1] - (int)S.runpos[r];  // (a removed tail is the last run)
+            S.runv[r] = (unsigned short)i;
+        }
+        const double t = flogf_t(S.tab, f);
+        for (unsigned long long m = __ballot(f > 1); m; m &= m - 1ull) x += lane_value(t, __ffsll((long long)m) - 1);
+        n += __popcll(__ballot(f > 0));
+        nb += __popcll(__ballot(f > 0 && lb < cv));
+        o |= __any(f > 0 && lb == cv);
+    }
+    if (mine) {
+        X = x;
+        ell = n;
+        nbelow = nb;
+        own = o;
+    }
 }
 
 template <typename OffT>
@@ -249,6 +292,7 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
     const int v0 = tl.v0, nv = tl.v1 - tl.v0;
     const OffT e0 = (OffT)tl.e0;
     const int TE = tl.te;
+    const int go0 = A.goff[v0];
     for (int x = tid; x < kRowTile / 32; x += kBlock) S.bm[x] = 0u;
     // the tile's entries and the facts of this thread's vertices, all
     // independent loads issued together (the tables are filled while they
@@ -322,34 +366,44 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kVU; ++j) {
+        if (__ballot(tid + j * kBlock < nv) == 0ull) break;  // no vertex in this wavefront
         const int i = tid + j * kBlock;
-        if (i >= nv) continue;
-        const int o = vo[j], c = vc[j], d = vdeg[j], cv = vlab[j];
+        const bool in = i < nv;
+        const int o = vo[j], c = in ? vc[j] : 0, d = vdeg[j], cv = vlab[j];
         int rf = 0, re = 0;
         if (c > 0) {
             rf = run_index(S, o);
             re = o + c >= TE ? total : run_index(S, o + c);
         }
         double X = 0.0;
-        int ell = 0, fown = 0, below = 0;
-        for (int r = rf; r < re; ++r) {
-            const int lb = S.runlab[r];
-            if (lb < 0) break;
-            const int f = (int)S.runpos[r + 1] - (int)S.runpos[r];
-            X += flogf_t(S.tab, f);
-            ++ell;
-            S.runv[r] = (unsigned short)i;
-            if (lb == cv)
-                fown = f;
-            else if (lb < cv)
-                below += f;
+        int ell = 0, nbelow = 0;
+        bool own = false;
+        if (re - rf <= kWalkRuns) {
+            for (int r = rf; r < re; ++r) {
+                const int lb = S.runlab[r];
+                if (lb < 0) break;
+                const int f = (int)S.runpos[r + 1] - (int)S.runpos[r];
+                if (f > 1) X += flogf_t(S.tab, f);
+                ++ell;
+                S.runv[r] = (unsigned short)i;
+                nbelow += (int)(lb < cv);
+                own |= lb == cv;
+            }
         }
+        for (unsigned long long pend = __ballot(re - rf > kWalkRuns); pend; pend &= pend - 1ull) {
+            const int l = __ffsll((long long)pend) - 1;
+            wave_walk(S, __builtin_amdgcn_readlane(rf, l), __builtin_amdgcn_readlane(re, l),
+                      __builtin_amdgcn_readlane(cv, l), __builtin_amdgcn_readlane(i, l), lane, lane == l, X, ell,
+                      nbelow, own);
+        }
+        if (!in) continue;
+        // the runs below the own community come first
+        const int below = c > 0 ? (int)S.runpos[rf + nbelow] - o : 0;
+        const int fown = own ? (int)S.runpos[rf + nbelow + 1] - (int)S.runpos[rf + nbelow] : 0;
         S.vX[i] = X;
-        S.vd[i] = d;
-        S.vlab[i] = cv;
-        S.vell[i] = ell;
-        S.vslot[i] = vgo[j] - o;
-        S.vfo[i] = (unsigned short)fown;
+        S.vde[i] = (unsigned int)d | (unsigned int)ell << 16;
+        S.vslot[i] = (short)(vgo[j] - go0 - o);
+        S.vrun[i] = (unsigned short)((rf + nbelow) | (own ? kOwnRun : 0));
         RowResult res;
         res.ell = ell;
         res.p = below;
@@ -365,14 +419,17 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
         const int lb = S.runlab[r];
         if (lb < 0) continue;
         const int i = S.runv[r];
-        const int cv = S.vlab[i];
-        if (lb == cv) continue;
+        const int vr = S.vrun[i] & (kOwnRun - 1);
+        const bool own = (S.vrun[i] & kOwnRun) != 0;
+        if (own && r == vr) continue;
         const int p0 = (int)S.runpos[r];
+        const unsigned int de = S.vde[i];
         PairRec pr;
         pr.f = (int)S.runpos[r + 1] - p0;
-        pr.w = weight_present_t(S.tab, S.vd[i], S.vX[i], S.vell[i], pr.f);
+        pr.w = weight_present_t(S.tab, (int)(de & 0xffffu), S.vX[i], (int)(de >> 16), pr.f);
         pr.c = lb;
-        const int s = S.vslot[i] + p0 - (lb > cv ? (int)S.vfo[i] : 0);
+        const int fo = own && r > vr ? (int)S.runpos[vr + 1] - (int)S.runpos[vr] : 0;
+        const int s = go0 + S.vslot[i] + p0 - fo;
         const int f = pr.f;
         A.prec[s] = pr;
         for (int t = 1; t < f; ++t) {
