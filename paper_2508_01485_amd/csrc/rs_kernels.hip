@@ -108,6 +108,7 @@ struct RowArgs {
     VMeta *meta;
     const int32_t *goff;
     PairRec *prec;     // records at the leader slots, written by this pass
+    double *val2;      // scratch of the hub rows here
     const int *blist;  // incremental pass: the listed blocks (k_rows_inc)
     double *wown, *R, *raw;
     double *av;  // [n] a_v = cbrt(own-community weight), dense for the score pass's run sums
@@ -217,6 +218,7 @@ struct HubSeg {
     int prev, next_prev;                     // label before the segment / of its last entry
     int open_start, open_label;              // run open at the segment boundary (open_start < 0: none)
     int nruns;                               // runs started before the segment
+    int own;                                 // 1 once the own community's run has started
     double red[kRowW];
     int ired[kRowW];
 };
@@ -441,73 +443,60 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
 }
 
 // ------------------------------------------------------------ hub rows
-// A vertex whose row capacity exceeds kRowTile gets a workgroup: its row is
-// streamed in segments of kRowTile entries with the tile's flat machinery
-// (labels, run starts by ballot, runs closed flat over LDS), twice: the first
-// pass counts the runs, X and the own run, the second writes the weighted
-// records.  The run still open at a segment's end is carried to the next.
-struct HubTotals {
-    double X;
-    int ell, fown;  // (second pass)
-    int go;         // first slot
+// A vertex whose row capacity exceeds kRowTile gets a workgroup.  Its row is
+// streamed once in segments of kRowTile entries with the tile's flat machinery
+// (labels, run starts by ballot, runs closed flat over LDS; the next segment's
+// labels are in flight meanwhile): this counts the runs, X and the own run and
+// lists the foreign runs' starts.  The run still open at a segment's end is
+// carried to the next.  The records are then computed flat over the list.
+// Streaming the row a second time for the records, with one thread writing
+// all slots of a run, took a hub of 46,000 neighbours 660 us, longer than all
+// row tiles of n = 3 million.
+struct HubRun {
+    int start;  // row position
+    int label;
 };
-template <int PASS, typename OffT>
-__device__ __forceinline__ void hub_run(const RowArgs<OffT> &A, int d, int cv, const HubTotals &T, int label, int start,
-                                        int f, double &xpart, int &below, int &fown, double &lmax) {
-    if (PASS == 1) {
-        xpart += flogf(f);
-        if (label == cv)
-            fown = f;
-        else if (label < cv)
-            below += f;
-    } else if (label != cv) {
-        PairRec pr;
-        pr.w = weight_present(d, T.X, T.ell, f);
-        pr.f = f;
-        pr.c = label;
-        const int s = T.go + start - (label > cv ? T.fown : 0);
-        A.prec[s] = pr;
-        for (int t = 1; t < f; ++t) {
-            pr.f = -t;
-            A.prec[s + t] = pr;
-        }
-        lmax = fmax(lmax, pr.w);
-    }
-}
-
-template <int PASS, typename OffT>
-__device__ void hub_pass(const RowArgs<OffT> &A, RowTileShared &S, OffT rb, int d, int cv, const HubTotals &T,
-                         double &xpart, int &below, int &fown, double &lmax) {
+template <typename OffT>
+__device__ void hub_stream(const RowArgs<OffT> &A, RowTileShared &S, OffT rb, int d, int cv, HubRun *list,
+                           double &xpart, int &below, int &fown) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     HubSeg &H = S.hub;
     if (tid == 0) {
         H.prev = INT_MIN;
         H.open_start = -1;
         H.nruns = 0;
+        H.own = 0;
     }
+    auto close = [&](int label, int f) {
+        xpart += flogf(f);
+        if (label == cv)
+            fown = f;
+        else if (label < cv)
+            below += f;
+    };
+    const int e0 = wave * (kRowTile / kRowW) + lane;
+    int L[kRowU];
+#pragma unroll
+    for (int i = 0; i < kRowU; ++i) L[i] = A.clab[rb + min(e0 + i * 64, max(d - 1, 0))];
     for (int seg0 = 0; seg0 < d; seg0 += kRowTile) {
         const int TE = min(kRowTile, d - seg0);
-        int L[kRowU];
+        int next[kRowU];
 #pragma unroll
-        for (int i = 0; i < kRowU; ++i) {
-            const int e = wave * (kRowTile / kRowW) + i * 64 + lane;
-            L[i] = e < TE ? A.clab[rb + seg0 + e] : -2;
-        }
+        for (int i = 0; i < kRowU; ++i) next[i] = A.clab[rb + min(seg0 + kRowTile + e0 + i * 64, d - 1)];
         __syncthreads();  // the previous segment is done with S
         if (lane == 63) S.wlast[wave] = L[kRowU - 1];
 #pragma unroll
         for (int i = 0; i < kRowU; ++i)
-            if (wave * (kRowTile / kRowW) + i * 64 + lane == TE - 1) H.next_prev = L[i];
+            if (e0 + i * 64 == TE - 1) H.next_prev = L[i];
         __syncthreads();
         unsigned long long m[kRowU];
         int cnt = 0;
 #pragma unroll
         for (int i = 0; i < kRowU; ++i) {
-            const int e = wave * (kRowTile / kRowW) + i * 64 + lane;
             int lp = __shfl_up(L[i], 1);
             const int carry = i > 0 ? __shfl(L[i > 0 ? i - 1 : 0], 63) : (wave > 0 ? S.wlast[wave > 0 ? wave - 1 : 0] : H.prev);
             if (lane == 0) lp = carry;
-            m[i] = __ballot(e < TE && L[i] != lp);
+            m[i] = __ballot(e0 + i * 64 < TE && L[i] != lp);
             cnt += __popcll(m[i]);
         }
         if (lane == 0) S.wcnt[wave] = cnt;
@@ -522,11 +511,11 @@ __device__ void hub_pass(const RowArgs<OffT> &A, RowTileShared &S, OffT rb, int 
         const unsigned long long lt = (1ull << lane) - 1ull;
 #pragma unroll
         for (int i = 0; i < kRowU; ++i) {
-            const int e = wave * (kRowTile / kRowW) + i * 64 + lane;
             if ((m[i] >> lane) & 1ull) {
                 const int r = base + __popcll(m[i] & lt);
-                S.runpos[r] = (unsigned short)e;
+                S.runpos[r] = (unsigned short)(e0 + i * 64);
                 S.runlab[r] = L[i];
+                if (L[i] == cv) H.own = 1;
             }
             base += __popcll(m[i]);
         }
@@ -538,13 +527,14 @@ __device__ void hub_pass(const RowArgs<OffT> &A, RowTileShared &S, OffT rb, int 
         // first run start (or at the row's end)
         if (tid == 0 && H.open_start >= 0 && (total > 0 || last)) {
             const int end = total > 0 ? seg0 + (int)S.runpos[0] : d;
-            hub_run<PASS, OffT>(A, d, cv, T, H.open_label, H.open_start, end - H.open_start, xpart, below, fown, lmax);
+            close(H.open_label, end - H.open_start);
             H.open_start = -1;
         }
         const int closed = last ? total : total - 1;  // the segment's last run stays open unless the row ends
-        for (int r = tid; r < closed; r += kBlock) {
-            const int f = (int)S.runpos[r + 1] - (int)S.runpos[r];
-            hub_run<PASS, OffT>(A, d, cv, T, S.runlab[r], seg0 + (int)S.runpos[r], f, xpart, below, fown, lmax);
+        for (int r = tid; r < total; r += kBlock) {
+            const int lb = S.runlab[r], p0 = (int)S.runpos[r];
+            if (r < closed) close(lb, (int)S.runpos[r + 1] - p0);
+            if (lb != cv) list[nr0 + r - (lb > cv ? H.own : 0)] = HubRun{seg0 + p0, lb};
         }
         __syncthreads();
         if (tid == 0) {
@@ -555,6 +545,8 @@ __device__ void hub_pass(const RowArgs<OffT> &A, RowTileShared &S, OffT rb, int 
             H.nruns = nr0 + total;
             H.prev = H.next_prev;
         }
+#pragma unroll
+        for (int i = 0; i < kRowU; ++i) L[i] = next[i];
     }
     __syncthreads();
 }
@@ -599,21 +591,50 @@ __device__ void hub_row(const RowArgs<OffT> &A, RowTileShared &S, int v, RowAcc 
     const int cv = A.lab[v];
     double xpart = 0.0, lmax = 0.0;
     int below = 0, fown = 0;
-    HubTotals T = {0.0, 0, 0, A.goff[v]};
-    hub_pass<1, OffT>(A, S, rb, d, cv, T, xpart, below, fown, lmax);
-    T.X = block_sum_d(xpart, S.hub.red);
+    const int go = A.goff[v];
+    HubRun *list = (HubRun *)(A.val2 + go);  // the type-II values are written after this pass
+    hub_stream(A, S, rb, d, cv, list, xpart, below, fown);
+    const double X = block_sum_d(xpart, S.hub.red);
     const int p = block_sum_i(below, S.hub.ired);
-    T.fown = block_sum_i(fown, S.hub.ired);  // one thread holds the own run's length
-    T.ell = S.hub.nruns;
-    __syncthreads();  // everyone has read pass 1's totals before pass 2 resets them
-    hub_pass<2, OffT>(A, S, rb, d, cv, T, xpart, below, fown, lmax);
+    const int fo = block_sum_i(fown, S.hub.ired);  // one thread holds the own run's length
+    const int ell = S.hub.nruns;
+    const int nf = ell - (fo > 0 ? 1 : 0);
+    const int lane = threadIdx.x & 63;
+    for (int r0 = (int)threadIdx.x - lane; r0 < nf; r0 += kBlock) {
+        const int r = r0 + lane;
+        PairRec pr = {0.0, 0, 0};
+        int s = 0;
+        if (r < nf) {
+            const HubRun h = list[r];
+            int end = r + 1 < nf ? list[r + 1].start : d;
+            if (h.start < p) end = min(end, p);  // the own run lies between
+            pr.f = end - h.start;
+            pr.c = h.label;
+            pr.w = weight_present(d, X, ell, pr.f);
+            s = go + h.start - (h.label > cv ? fo : 0);
+            A.prec[s] = pr;
+            lmax = fmax(lmax, pr.w);
+        }
+        // the other slots of the lanes' runs, one run at a time
+        for (unsigned long long m = __ballot(pr.f > 1); m; m &= m - 1ull) {
+            const int l = __ffsll((long long)m) - 1;
+            const int f = __builtin_amdgcn_readlane(pr.f, l), s0 = __builtin_amdgcn_readlane(s, l);
+            PairRec q;
+            q.w = lane_value(pr.w, l);
+            q.c = __builtin_amdgcn_readlane(pr.c, l);
+            for (int t = 1 + lane; t < f; t += 64) {
+                q.f = -t;
+                A.prec[s0 + t] = q;
+            }
+        }
+    }
     const double lm = block_max_d(lmax, S.hub.red);
     if (threadIdx.x == 0) {
         RowResult r;
-        r.ell = T.ell;
+        r.ell = ell;
         r.p = p;
-        r.q = p + T.fown;
-        r.wown = T.fown > 0 ? weight_present(d, T.X, T.ell, T.fown) : weight_absent(d, T.X, T.ell);
+        r.q = p + fo;
+        r.wown = fo > 0 ? weight_present(d, X, ell, fo) : weight_absent(d, X, ell);
         r.lmax = fmax(lm, r.wown);
         finish_row(A, v, d, r, acc);
     }
@@ -2076,6 +2097,7 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
     A.meta = D.meta;
     A.goff = D.goff;
     A.prec = D.prec;
+    A.val2 = D.val2;
     A.blist = inc ? D.rlist : nullptr;
     A.wown = D.wown;
     A.av = D.av;
