@@ -696,7 +696,7 @@ __device__ void reduce_row_parts(const RowPart *part, int np, DevCounters *c) {
 
 // Algorithm 1 Steps 1-2 for every vertex: hub rows first, then the tiles.
 template <typename OffT>
-__global__ __launch_bounds__(kBlock) void k_rows(RowArgs<OffT> A) {
+__global__ __launch_bounds__(kBlock, 6) void k_rows(RowArgs<OffT> A) {
     __shared__ RowTileShared S;
     RowAcc acc = {0.0, 0, 0, 0, 0};
     const int b = (int)blockIdx.x;
@@ -997,23 +997,39 @@ __device__ void hub_chunk_store(const ScoreArgs &A, const double *red, const lon
     A.hub_part[A.hub_first[hub] + chunk] = hp;
 }
 
-// Per-pair facts of a unit's type-I scan, and the hits found so far.
-constexpr int kScanR = 2;                  // work items per lane per round
-constexpr int kWaveHitCap = 192;           // hits a wavefront holds before evaluating them
+// A unit's type-I scan (below): the pairs with a non-empty out-list, in pair
+// order per wavefront, the start bits of the items at hand, and the items that
+// may close a triangle.
+constexpr int kScanR = 2;             // work items per lane per round
+constexpr int kScanSpan = 2048;       // items whose start bits are held at once
+constexpr int kWaveHitCap = 192;      // candidates a wavefront holds before testing them
 constexpr int kHitCap = kWaveHitCap * (kBlock / 64);
-static_assert(kWaveHitCap >= 64 * kScanR, "a round's hits always fit after a flush");
+static_assert(kWaveHitCap >= 64 * kScanR, "a round's candidates always fit after a flush");
+static_assert(kScanSpan % (64 * kScanR) == 0 && kScanSpan / 32 == 64, "whole rounds, one start word per lane");
+struct OwnEnt {
+    int delta;          // out-list start of the pair's w minus the pair's first item
+    int pair;           // index in the unit
+    unsigned int salt;  // the pair's part of the filter hash
+    int pad;
+};
 struct TypeIShared {
-    int ibeg[kBlock];      // first work item of each pair within its wavefront's list
-    int ioo[kBlock];       // out-list start of each pair's w
-    int pv[kBlock];        // u of each pair
-    double pW[kBlock];     // w_w(C(u))
+    OwnEnt own[kBlock];                             // per wavefront: its non-empty pairs
+    unsigned int start[kBlock / 64][kScanSpan / 32];
+    double pW[kBlock];                              // w_w(C(u)) of each pair
+};
+// A candidate (item), later a hit, later the hit's two ordered triads.
+union HitSlot {
+    struct {
+        int op;    // out-list position of v (the entry w -> v)
+        int code;  // v; for a hit, where the edge test found (u, v)
+    } c;
+    double v;
 };
 struct HitBuf {
-    int hitp[kHitCap];     // pair of each hit (per wavefront: ascending)
-    int hitc[kHitCap];     // where the edge test found (u, v): the edge test's code
-    int hito[kHitCap];     // the out-list position of v (the entry w -> v)
-    double hitv[kHitCap];  // the hit's two ordered triads
+    HitSlot s[kHitCap];
+    unsigned char p[kHitCap];  // pair (per wavefront: ascending)
 };
+static_assert(kBlock <= 256, "a pair index fits a byte");
 
 // Lanes of one wavefront exchange data through LDS: the writes must be
 // complete and visible before other lanes read them.
@@ -1023,35 +1039,62 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The terms of a wavefront's nb held hits (from slot h0), then each pair's
-// own lane adds its hits (a contiguous range of the list) in list order.
+// The exact edge test of a wavefront's nb held candidates (from slot h0): the
+// hits move up, in order; returns their number.
+template <class Edge>
+__device__ __forceinline__ int typeI_test(HitBuf &H, const Edge &edge, int h0, int nb, int lane) {
+    int kept = 0;
+    for (int b0 = 0; b0 < nb; b0 += 64) {
+        const int h = h0 + b0 + lane;
+        int p = 0, op = 0, code = 0;
+        bool hit = false;
+        if (b0 + lane < nb) {
+            p = H.p[h];
+            op = H.s[h].c.op;
+            hit = edge(p, H.s[h].c.code, code);
+        }
+        const unsigned long long m = __ballot(hit);
+        wave_sync();
+        if (hit) {
+            const int s = h0 + kept + __popcll(m & ((1ull << lane) - 1ull));
+            H.p[s] = (unsigned char)p;
+            H.s[s].c.op = op;
+            H.s[s].c.code = code;
+        }
+        kept += __popcll(m);
+    }
+    wave_sync();
+    return kept;
+}
+
+// The terms of a wavefront's nb hits (from slot h0), then each pair's own lane
+// adds its hits (a contiguous range of the list) in list order.
 template <class Edge>
 __device__ __forceinline__ void typeI_flush(const ScoreArgs &A, const TypeIShared &T, HitBuf &H, const Edge &edge,
                                             int h0, int nb, int lane, int me, bool mine, double &val, int &t1) {
-    for (int h = lane; h < nb; h += 64) {
+    for (int h = h0 + lane; h < h0 + nb; h += 64) {
         // the weights of the triangle {u, w, v}: w_v(C(u)), w_w(C(v)) and
         // w_v(C(w)), each the record at a leader slot (the out-list entry
         // w -> v holds the last two)
-        const int q = H.hitp[h0 + h];
-        const double W = T.pW[q];
-        const OutEnt e = A.oe[H.hito[h0 + h]];
+        const double W = T.pW[H.p[h]];
+        const OutEnt e = A.oe[H.s[h].c.op];
         const double w_wv = A.prec[e.xy].w;
         const double w_vw = A.prec[e.yx].w;
-        const double w_vu = edge.wvu(A, T, H.hitc[h0 + h]);
-        H.hitv[h0 + h] = cbrt(w_vu * w_wv * W) + cbrt(W * w_vw * w_vu);
+        const double w_vu = edge.wvu(A, T, H.s[h].c.code);
+        H.s[h].v = cbrt(w_vu * w_wv * W) + cbrt(W * w_vw * w_vu);
     }
     wave_sync();
     if (mine) {
         int a = 0, b = nb;
         while (a < b) {
             const int mid = (a + b) >> 1;
-            if (H.hitp[h0 + mid] < me)
+            if ((int)H.p[h0 + mid] < me)
                 a = mid + 1;
             else
                 b = mid;
         }
-        for (int h = a; h < nb && H.hitp[h0 + h] == me; ++h) {
-            val += H.hitv[h0 + h];
+        for (int h = a; h < nb && (int)H.p[h0 + h] == me; ++h) {
+            val += H.s[h0 + h].v;
             t1 += 2;
         }
     }
@@ -1062,76 +1105,133 @@ __device__ __forceinline__ void typeI_flush(const ScoreArgs &A, const TypeIShare
 // C(u): the triangles of G').  The pair (u, w) finds the triangles {u, w, v}
 // with v in out(w) (each triangle at u is found by exactly one of its two
 // pairs).  Every position of every pair's out-list is one work item.  Each
-// wavefront works through the items of its own 64 pairs, kScanR items per
-// lane per round with their loads in flight together (consecutive lanes read
-// consecutive entries of one list, and no lane scans a long list alone); the
-// wavefronts of the block do not wait for each other.  A live entry v with
-// edge(p, v) closes a triangle.  Hits are appended in item order, so each
-// pair's hits stay contiguous and in out-list order; when the wavefront's
-// list is nearly full (and at the end) every held hit's two ordered triads
-// (w, v) and (v, w),
+// wavefront works through the items of its own 64 pairs, 64 items at a time
+// (consecutive lanes read consecutive entries of one list, and no lane scans a
+// long list alone), kScanR such groups with their loads in flight together;
+// the wavefronts of the block do not wait for each other.  The kernel is bound
+// by instructions issued and by the latency of the out-list reads (at n =
+// 150 K, mean degree 71, 54 M items, half of the VALU's cycles), so an item
+// takes few of both:
+//   * its pair is found from one 64-bit word of start bits (a bit per item at
+//     which a pair's list starts) by a count of the bits below the lane, where
+//     a binary search of the pairs took six dependent LDS reads;
+//   * a hashed filter of the unit's (u, v) pairs rejects nearly every
+//     non-edge with one LDS read (the big hubs' filters are in memory), where
+//     each item searched u's list; the few candidates are searched 64 at a
+//     time.
+// Candidates, and then hits, stay in item order, so each pair's hits are
+// contiguous and in out-list order; every hit's two ordered triads (w, v) and
+// (v, w),
 //   cbrt(w_v(C(u)) w_w(C(v)) W) + cbrt(W w_v(C(w)) w_v(C(u))),  W = w_w(C(u)),
 // are evaluated, one lane per hit, and the pair's own lane adds them to its
 // sum in list order (so the sum's order is fixed).  `items` is the lane's
-// out-list length (0 without a pair), and T.ioo, T.pv, T.pW hold
-// the lane's pair; they must be visible block-wide (a barrier) before the call.
+// out-list length (0 without a pair), `oo` its start and `salt` its part of
+// the hash; T.pW and the edge test's lists must be visible block-wide (a
+// barrier) before the call.
 template <class Edge>
-__device__ void typeI_scan(const ScoreArgs &A, TypeIShared &T, HitBuf &H, int items, const Edge &edge,
-                           double &val, int &t1) {
+__device__ void typeI_scan(const ScoreArgs &A, TypeIShared &T, HitBuf &H, int items, int oo, unsigned int salt,
+                           const Edge &edge, double &val, int &t1) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int w0 = wave * 64;          // the wavefront's first pair
-    const int h0 = wave * kWaveHitCap;  // and its hit slots
+    const int w0 = wave * 64;           // the wavefront's first pair
+    const int h0 = wave * kWaveHitCap;  // and its candidate slots
     int incl = items;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const int y = __shfl_up(incl, o);
         if (lane >= o) incl += y;
     }
-    const int total = __shfl(incl, 63);
-    T.ibeg[tid] = incl - items;
-    wave_sync();
-    int nb = 0;  // held hits of this wavefront
-    for (int base = 0; base < total; base += 64 * kScanR) {
-        int y[kScanR], p[kScanR], op[kScanR];
-#pragma unroll
-        for (int r = 0; r < kScanR; ++r) {
-            const int i = base + r * 64 + lane;
-            p[r] = w0;
-            y[r] = -1;
-            op[r] = 0;
-            if (i < total) {
-                int lo = 0, hi = 64;  // the last pair of the wavefront whose first item is <= i
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (T.ibeg[w0 + mid] <= i)
-                        lo = mid;
-                    else
-                        hi = mid;
-                }
-                p[r] = w0 + lo;
-                op[r] = T.ioo[w0 + lo] + (i - T.ibeg[w0 + lo]);
-                y[r] = A.outl[op[r]];
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < kScanR; ++r) {
-            int code = 0;
-            const bool hit = y[r] >= 0 && y[r] != T.pv[p[r]] && edge(p[r], y[r], code);
-            const unsigned long long m = __ballot(hit);
-            if (hit) {
-                const int s = nb + __popcll(m & ((1ull << lane) - 1ull));
-                H.hitp[h0 + s] = p[r];
-                H.hitc[h0 + s] = code;
-                H.hito[h0 + s] = op[r];
-            }
-            nb += __popcll(m);
-        }
-        if (nb > kWaveHitCap - 64 * kScanR || (base + 64 * kScanR >= total && nb > 0)) {
-            wave_sync();
-            typeI_flush(A, T, H, edge, h0, nb, lane, tid, items > 0, val, t1);
-            nb = 0;
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    if (total == 0) return;
+    const int first = incl - items;
+    {
+        const unsigned long long m = __ballot(items > 0);
+        if (items > 0) {
+            OwnEnt e;
+            e.delta = oo - first;
+            e.pair = tid;
+            e.salt = salt;
+            e.pad = 0;
+            T.own[w0 + __popcll(m & ((1ull << lane) - 1ull))] = e;
         }
     }
+    int nb = 0;    // held candidates of this wavefront
+    int seen = 0;  // pairs whose lists start before the group at hand
+    for (int sb = 0; sb < total; sb += kScanSpan) {
+        T.start[wave][lane] = 0u;
+        wave_sync();
+        if (items > 0 && first >= sb && first < sb + kScanSpan)
+            atomicOr(&T.start[wave][(first - sb) >> 5], 1u << ((first - sb) & 31));
+        wave_sync();
+        const int se = min(total, sb + kScanSpan);
+        for (int base = sb; base < se; base += 64 * kScanR) {
+            int y[kScanR], op[kScanR], p[kScanR];
+            unsigned int salts[kScanR];
+#pragma unroll
+            for (int r = 0; r < kScanR; ++r) {
+                const int b = base + 64 * r;
+                y[r] = -1;
+                op[r] = p[r] = 0;
+                salts[r] = 0u;
+                if (b < se) {  // (uniform)
+                    const unsigned int m0 = T.start[wave][(b - sb) >> 5], m1 = T.start[wave][((b - sb) >> 5) + 1];
+                    const unsigned int lo = __builtin_amdgcn_readfirstlane((int)m0);
+                    const unsigned int hi = __builtin_amdgcn_readfirstlane((int)m1);
+                    const unsigned int mine = ((lane < 32 ? lo : hi) >> (lane & 31)) & 1u;
+                    const int rank =
+                        seen + (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u)) + (int)mine - 1;
+                    seen += __popc(lo) + __popc(hi);
+                    const OwnEnt e = T.own[w0 + rank];
+                    p[r] = e.pair;
+                    salts[r] = e.salt;
+                    // (past the last item: the last one again, skipped below)
+                    op[r] = e.delta + min(b + lane, total - 1);
+                    y[r] = A.outl[op[r]];
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < kScanR; ++r) {
+                if (base + 64 * r >= se) break;
+                const bool cand = base + 64 * r + lane < total && y[r] >= 0 && edge.maybe(salts[r], y[r]);
+                const unsigned long long m = __ballot(cand);
+                if (!m) continue;
+                if (cand) {
+                    const int s = h0 + nb + __popcll(m & ((1ull << lane) - 1ull));
+                    H.p[s] = (unsigned char)p[r];
+                    H.s[s].c.op = op[r];
+                    H.s[s].c.code = y[r];
+                }
+                nb += __popcll(m);
+            }
+            if (nb > kWaveHitCap - 64 * kScanR) {
+                wave_sync();
+                nb = typeI_test(H, edge, h0, nb, lane);
+                typeI_flush(A, T, H, edge, h0, nb, lane, tid, items > 0, val, t1);
+                nb = 0;
+            }
+        }
+    }
+    if (nb > 0) {
+        wave_sync();
+        nb = typeI_test(H, edge, h0, nb, lane);
+        if (nb > 0) typeI_flush(A, T, H, edge, h0, nb, lane, tid, items > 0, val, t1);
+    }
+}
+
+// Filter of a unit's (u, v) pairs in LDS: 256 pairs (an LDS hub: up to 1,024)
+// in 16,384 bits, so 1.6 % (6 %) of the non-edges pass.
+constexpr int kUnitFilterBits = 14;
+constexpr int kUnitFilterWords = (1 << kUnitFilterBits) / 32;
+__device__ __forceinline__ unsigned int unit_salt(int i) { return (unsigned int)i * 0x85EBCA6Bu; }
+__device__ __forceinline__ unsigned int unit_hash(unsigned int salt, int y) {
+    return ((unsigned int)y * 2654435761u + salt) >> (32 - kUnitFilterBits);
+}
+__device__ __forceinline__ void unit_filter_set(unsigned int *f, unsigned int salt, int y) {
+    const unsigned int h = unit_hash(salt, y);
+    atomicOr(&f[h >> 5], 1u << (h & 31));
+}
+__device__ __forceinline__ bool unit_filter_has(const unsigned int *f, unsigned int salt, int y) {
+    const unsigned int h = unit_hash(salt, y);
+    return (f[h >> 5] >> (h & 31)) & 1u;
 }
 
 // ------------------------------------------------------------ score units
@@ -1145,32 +1245,26 @@ __device__ void typeI_scan(const ScoreArgs &A, TypeIShared &T, HitBuf &H, int it
 // fixed order).
 static_assert(kScoreTileV == kBlock && kScoreTileP == kBlock, "score unit size: one vertex and one pair per thread");
 
-// A score unit's LDS: kW foreign neighbours (a tile's at most kScoreTileP,
-// an LDS hub's at most kHubList); tiles launch with the smaller form, which
-// leaves room for one more workgroup per CU.
-template <int kW>
-struct ScoreUnitSharedT {
-    static constexpr int kWords = kW;
-    int w[kW];                       // foreign neighbours
+// A score unit's LDS: 27.5 KB would hold five workgroups on a CU, this form
+// holds seven (a candidate takes nine bytes).
+struct ScoreUnitShared {
+    int w[kHubList];                 // foreign neighbours (a tile's at most kScoreTileP, an LDS hub's at most kHubList)
     int pb[kScoreTileV + 1];         // tile: first pair of each vertex
     unsigned short pu[kScoreTileP];  // tile: vertex of each pair
     int ws[kBlock / 64];
     double red[kBlock / 64];
     long long ired[2][kBlock / 64];
+    unsigned int filt[kUnitFilterWords];
     TypeIShared ti;
     union {  // three phases that never overlap
-        struct {  // prologue: the tile's vertices
-            int go[kScoreTileV];  // first slot
-        } v;
-        HitBuf hits;  // type-I scan
-        struct {      // epilogue: the lanes' pair terms
+        int go[kScoreTileV];  // prologue: first slot of each of the tile's vertices
+        HitBuf hits;          // type-I scan
+        struct {              // epilogue: the lanes' pair terms
             double val[kBlock];
             int t2[kBlock], t1[kBlock];
         } e;
     } u;
 };
-using ScoreUnitShared = ScoreUnitSharedT<kHubList>;
-using ScoreTileShared = ScoreUnitSharedT<kScoreTileP>;
 
 // A hub chunk's partial: block tree sum of the lanes' terms (thread 0 gets it).
 __device__ __forceinline__ void chunk_tree(double x, long long y1, long long y2, double *red,
@@ -1191,12 +1285,11 @@ __device__ __forceinline__ void chunk_tree(double x, long long y1, long long y2,
 }
 
 // Edge tests of a unit's type-I scan: u's foreign list is in LDS (a tile
-// vertex's slice, or a hub's whole list).
-template <class SU>
-// Each also gives a code for its hits, from which wvu() reads w_v(C(u)),
-// the pair fact at the row entry (v, u).
+// vertex's slice, or a hub's whole list).  Each also gives a code for its
+// hits, from which wvu() reads w_v(C(u)), the record of C(u) in v's list.
 struct TileEdge {
-    const SU *S;
+    const ScoreUnitShared *S;
+    __device__ __forceinline__ bool maybe(unsigned int salt, int y) const { return unit_filter_has(S->filt, salt, y); }
     __device__ __forceinline__ bool operator()(int p, int y, int &code) const {
         const int i = S->pu[p];
         const int k = lds_lower(S->w, S->pb[i], S->pb[i + 1], y);
@@ -1208,14 +1301,15 @@ struct TileEdge {
     }
 };
 struct HubListEdge {
-    const int *w;
+    const ScoreUnitShared *S;
     int n;
     int cbase, ccnt;  // the chunk's pairs: list positions [cbase, cbase + ccnt)
     int go;           // the hub's first slot
+    __device__ __forceinline__ bool maybe(unsigned int salt, int y) const { return unit_filter_has(S->filt, salt, y); }
     __device__ __forceinline__ bool operator()(int, int y, int &code) const {
-        const int k = lds_lower(w, 0, n, y);
+        const int k = lds_lower(S->w, 0, n, y);
         code = k;  // (u, v) is the hub's pair k
-        return k < n && w[k] == y;
+        return k < n && S->w[k] == y;
     }
     __device__ __forceinline__ double wvu(const ScoreArgs &A, const TypeIShared &T, int code) const {
         if (code >= cbase && code < cbase + ccnt) return T.pW[code - cbase];
@@ -1225,12 +1319,10 @@ struct HubListEdge {
 
 // vl: a unit of listed vertices vl[0, vn) (the incremental pass's rescored
 // vertices) instead of the tile idx.
-template <class SU>
-__device__ void score_unit(const ScoreArgs &A, SU &S, bool hub_unit_arg, int idx, double wmax,
+__device__ void score_unit(const ScoreArgs &A, ScoreUnitShared &S, bool hub_unit, int idx, double wmax,
                            const int32_t *vl = nullptr, int vn = 0) {
-    // a hub chunk needs room for the hub's whole foreign list
-    const bool hub_unit = SU::kWords >= kHubList && hub_unit_arg;
     const int tid = threadIdx.x;
+    for (int i = tid; i < kUnitFilterWords; i += kBlock) S.filt[i] = 0u;
     // ---- prologue: lay out the unit's pairs
     int v0 = 0, nv = 0, total = 0, dp = 0, deg = 0, pb = 0;    // tile
     int hub = 0, chunk = 0, hu = 0, hdp = 0, hgo = 0;  // hub chunk
@@ -1242,9 +1334,13 @@ __device__ void score_unit(const ScoreArgs &A, SU &S, bool hub_unit_arg, int idx
         const VMeta m = A.meta[hu];
         hgo = A.goff[hu];
         hdp = m.deg - (m.q - m.p);  // <= the load-time count, which fits kHubList
-        for (int j = tid; j < hdp; j += kBlock) S.w[j] = A.fcol[hgo + j];
+        __syncthreads();  // the cleared filter
+        for (int j = tid; j < hdp; j += kBlock) {
+            const int w = A.fcol[hgo + j];
+            S.w[j] = w;
+            unit_filter_set(S.filt, 0u, w);
+        }
         total = min(kBlock, max(0, hdp - chunk * kBlock));
-        __syncthreads();
     } else {
         if (vl) {
             nv = vn;
@@ -1258,7 +1354,7 @@ __device__ void score_unit(const ScoreArgs &A, SU &S, bool hub_unit_arg, int idx
             const VMeta m = A.meta[v];
             deg = m.deg;
             dp = m.deg - (m.q - m.p);
-            S.u.v.go[tid] = A.goff[v];
+            S.u.go[tid] = A.goff[v];
         }
         pb = block_excl_scan(dp, S.ws, total);
         if (tid < nv) {
@@ -1271,7 +1367,8 @@ __device__ void score_unit(const ScoreArgs &A, SU &S, bool hub_unit_arg, int idx
     // ---- the lane's pair: type II
     const bool has = tid < total;
     double val = 0.0;
-    int t2 = 0, t1 = 0, items = 0;
+    int t2 = 0, t1 = 0, items = 0, oo = 0;
+    unsigned int salt = 0u;
     if (has) {
         int u, slot;
         if (hub_unit) {
@@ -1280,32 +1377,34 @@ __device__ void score_unit(const ScoreArgs &A, SU &S, bool hub_unit_arg, int idx
         } else {
             const int i = S.pu[tid];
             u = vl ? vl[i] : v0 + i;
-            slot = S.u.v.go[i] + (tid - S.pb[i]);
-            S.w[tid] = A.fcol[slot];
+            slot = S.u.go[i] + (tid - S.pb[i]);
+            const int w = A.fcol[slot];
+            S.w[tid] = w;
+            salt = unit_salt(i);
+            unit_filter_set(S.filt, salt, w);
         }
         const PairLink pl = A.plink[slot];
         const PairRec pr = A.prec[pl.lead];
         val = type2_pair(A, u, pr, pl);
         t2 = pr.f - 1;
         items = pl.on;
-        S.ti.ioo[tid] = pl.oo;
-        S.ti.pv[tid] = u;
+        oo = pl.oo;
         S.ti.pW[tid] = pr.w;
     }
-    // ---- type I (the hit lists overlay the prologue's vertex facts)
+    // ---- type I (the candidate lists overlay the prologue's slots)
     __syncthreads();
     if (hub_unit) {
         HubListEdge E;
-        E.w = S.w;
+        E.S = &S;
         E.n = hdp;
         E.cbase = chunk * kBlock;
         E.ccnt = total;
         E.go = hgo;
-        typeI_scan(A, S.ti, S.u.hits, items, E, val, t1);
+        typeI_scan(A, S.ti, S.u.hits, items, oo, salt, E, val, t1);
     } else {
-        TileEdge<SU> E;
+        TileEdge E;
         E.S = &S;
-        typeI_scan(A, S.ti, S.u.hits, items, E, val, t1);
+        typeI_scan(A, S.ti, S.u.hits, items, oo, salt, E, val, t1);
     }
     // ---- epilogue: sums in a fixed order (its terms overlay the hit lists)
     __syncthreads();
@@ -1358,11 +1457,13 @@ struct HubOutEdge {
     long long uo0, uo1;    // out(u) in HBM
     const uint32_t *filt;  // u's neighbour filter
     int u;
+    __device__ __forceinline__ bool maybe(unsigned int, int y) const {
+        const uint32_t h = filter_hash(y);
+        return (filt[h >> 5] >> (h & 31)) & 1u;
+    }
     // code: the out-list position of the edge, times two, plus 1 when it is
     // the entry v -> u (else u -> v)
     __device__ __forceinline__ bool operator()(int, int y, int &code) const {
-        const uint32_t h = filter_hash(y);
-        if (!((filt[h >> 5] >> (h & 31)) & 1u)) return false;
         long long o = -1;
         if (stage) {
             const int k = lds_find_out(stage, n_stage, y);
@@ -1396,15 +1497,14 @@ __device__ void score_hub_big(const ScoreArgs &A, ScoreHubBigShared &S, int hub,
         for (int j = tid; j < n_out; j += kBlock) S.outu[j] = A.outl[uo0 + j];
     const int k = chunk * kScoreTileP + tid;
     double val = 0.0;
-    int t2 = 0, t1 = 0, items = 0;
+    int t2 = 0, t1 = 0, items = 0, oo = 0;
     if (k < dp) {
         const PairLink pl = A.plink[A.goff[u] + k];
         const PairRec pr = A.prec[pl.lead];
         val = type2_pair(A, u, pr, pl);
         t2 = pr.f - 1;
         items = pl.on;
-        S.ti.ioo[tid] = pl.oo;
-        S.ti.pv[tid] = u;
+        oo = pl.oo;
         S.ti.pW[tid] = pr.w;
     }
     HubOutEdge E;
@@ -1417,7 +1517,7 @@ __device__ void score_hub_big(const ScoreArgs &A, ScoreHubBigShared &S, int hub,
     E.filt = A.hfilter + (size_t)(hub - A.n_hubs_lds) * kFilterWords;
     E.u = u;
     __syncthreads();  // the staged out-list
-    typeI_scan(A, S.ti, S.hits, items, E, val, t1);
+    typeI_scan(A, S.ti, S.hits, items, oo, 0u, E, val, t1);
     chunk_tree(val, t1, t2, S.red, S.ired);
     if (tid == 0) hub_chunk_store(A, S.red, S.ired, hub, chunk);
 }
@@ -1567,43 +1667,32 @@ __global__ __launch_bounds__(kMidThreads) void k_mid(MidArgs M) {
     if (gi < M.n_graphs) reduce_wmax_graph(M.wpart, M.gblk_off, M.gblk, gi, M.gwmax);
 }
 
-// Algorithm 1 Step 3 (Eq. RSI) for every border vertex of the LDS-sized
-// score hubs (one chunk of 256 pairs per workgroup) ...
-__global__ __launch_bounds__(kBlock) void k_score_lds_hubs(ScoreArgs A) {
-    __shared__ ScoreUnitShared S;
-    score_unit(A, S, true, (int)blockIdx.x, bitsd(A.ctr->wmax_bits));
-}
+union ScoreShared {
+    ScoreUnitShared u;
+    ScoreHubBigShared h;
+};
+static_assert(7 * sizeof(ScoreShared) <= 160 * 1024, "seven score workgroups per CU");
 
-// ... and of the score tiles (tile t of XCD x = t / per runs on a block of
-// that XCD: blocks are dealt to the XCDs round-robin, so consecutive tiles
-// share an L2).
-__global__ __launch_bounds__(kBlock) void k_score(ScoreArgs A) {
-    __shared__ ScoreTileShared S;
-    const int idx = tile_of_block((int)blockIdx.x, 0, A.tiles_per_xcd);
-    if (idx < A.n_tiles) score_unit(A, S, false, idx, bitsd(A.ctr->wmax_bits));
-}
-
-// Both in one launch (the LDS hubs' chunks first, so they start early, then
-// the tiles), with the larger LDS form for every workgroup: used when the
-// LDS hubs are few, where a launch of their own would end on one chunk's
-// latency with nothing beside it.
-constexpr int kSplitHubChunks = 4096;
-__global__ __launch_bounds__(kBlock) void k_score_all(ScoreArgs A) {
-    __shared__ ScoreUnitShared S;
-    const int b = (int)blockIdx.x;
+// Algorithm 1 Step 3 (Eq. RSI) for every border vertex, in one launch: the
+// chunks of the hubs too large for LDS first (the longest units), then the
+// LDS hubs' chunks, then the tiles (tile t of XCD x = t / per runs on a block
+// of that XCD: blocks are dealt to the XCDs round-robin, so consecutive tiles
+// share an L2).  Hub partials are summed by k_hub_sum.  Launches of their own
+// for the hubs ended on one chunk's latency with nothing beside it.
+__global__ __launch_bounds__(kBlock, 7) void k_score(ScoreArgs A) {
+    __shared__ ScoreShared S;
+    const int n_big = A.n_chunks - A.n_chunks_lds;
+    const double wmax = bitsd(A.ctr->wmax_bits);
+    int b = (int)blockIdx.x;
+    if (b < n_big) {
+        const int2 hc = A.hub_chunk[A.n_chunks_lds + b];
+        score_hub_big(A, S.h, hc.x, hc.y, wmax);
+        return;
+    }
+    b -= n_big;
     const bool hub_unit = b < A.n_chunks_lds;
     const int idx = hub_unit ? b : tile_of_block(b, A.n_chunks_lds, A.tiles_per_xcd);
-    if (hub_unit || idx < A.n_tiles) score_unit(A, S, hub_unit, idx, bitsd(A.ctr->wmax_bits));
-}
-
-// ... and of the hubs too large for LDS (chunks n_chunks_lds ...); partials
-// summed by k_hub_sum after the score kernels.
-__global__ __launch_bounds__(kBlock) void k_score_hub(ScoreArgs A) {
-    __shared__ ScoreHubBigShared S;
-    const double wmax = bitsd(A.ctr->wmax_bits);
-    const int b = (int)blockIdx.x;
-    const int2 hc = A.hub_chunk[A.n_chunks_lds + b];
-    score_hub_big(A, S, hc.x, hc.y, wmax);
+    if (hub_unit || idx < A.n_tiles) score_unit(A, S.u, hub_unit, idx, wmax);
 }
 
 // The incremental pass's score work in one launch (the parts are
@@ -1619,10 +1708,7 @@ __global__ __launch_bounds__(kBlock) void k_score_hub(ScoreArgs A) {
 __global__ __launch_bounds__(kBlock) void k_score_inc(ScoreArgs A, const int32_t *big, const int32_t *main_,
                                                       const int32_t *abin, const unsigned long long *ictr,
                                                       uint8_t *hflag, int grid_rows, int grid_score, int grid_main) {
-    __shared__ union {
-        ScoreUnitShared u;
-        ScoreHubBigShared h;
-    } S;
+    __shared__ ScoreShared S;
     // the whole-hub flags of the marks were turned into lists: clear them
     for (int h = blockIdx.x * kBlock + threadIdx.x; h < A.n_hubs; h += gridDim.x * kBlock) hflag[h] = 0;
     const double wmax = bitsd(A.ctr->wmax_bits);
@@ -2187,19 +2273,8 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
                            g->grid_score, grid_main);
         timing_end(g, K_SCORE, ev);
     } else {
-        if (n_big > 0) {
-                timing_begin(g, K_SCORE_HUB, &ev);
-            hipLaunchKernelGGL(k_score_hub, dim3(n_big), dim3(kBlock), 0, g->stream, S);
-            timing_end(g, K_SCORE_HUB, ev);
-        }
-        const int grid_tiles = grid_main - g->n_schunks_lds;  // the tiles, rounded up to the 8 XCDs
         timing_begin(g, K_SCORE, &ev);
-        if (g->n_schunks_lds >= kSplitHubChunks) {  // many LDS hubs: tiles with the smaller LDS form
-            hipLaunchKernelGGL(k_score_lds_hubs, dim3(g->n_schunks_lds), dim3(kBlock), 0, g->stream, S);
-            if (grid_tiles > 0) hipLaunchKernelGGL(k_score, dim3(grid_tiles), dim3(kBlock), 0, g->stream, S);
-        } else if (grid_main > 0) {
-            hipLaunchKernelGGL(k_score_all, dim3(grid_main), dim3(kBlock), 0, g->stream, S);
-        }
+        if (g->grid_score > 0) hipLaunchKernelGGL(k_score, dim3(g->grid_score), dim3(kBlock), 0, g->stream, S);
         timing_end(g, K_SCORE, ev);
     }
     if (g->n_shubs > 0) {
