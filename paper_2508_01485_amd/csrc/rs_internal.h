@@ -214,6 +214,7 @@ struct DeviceGraph {
     RowTile *rtiles = nullptr;  // row tiles
     int32_t *rhubs = nullptr;   // vertices whose row capacity exceeds kRowTile
     int2 *stiles = nullptr;     // score tiles
+    uint8_t *sown = nullptr;    // [slots] a tile vertex's slots: its index in the tile
     int32_t *shubs = nullptr;   // vertices with more than kScoreTileP foreign entries
     int32_t *shub_first = nullptr;  // [hubs + 1] first chunk of each score hub
     int2 *shub_chunk = nullptr;     // [chunks] (hub, chunk index within the hub)
@@ -368,6 +369,7 @@ rs_status launch_remove_vertices(rs_graph *g, const int32_t *d_verts, int64_t nv
                                  unsigned long long *d_removed_edges);
 rs_status launch_links(rs_graph *g, unsigned long long *d_run_walk);
 rs_status launch_col_labels(rs_graph *g);
+rs_status launch_slot_owners(rs_graph *g);
 rs_status launch_out_entries(rs_graph *g);
 rs_status launch_incremental_marks(rs_graph *g);
 rs_status launch_topk_graphs(rs_graph *g, int64_t k, int32_t *d_ids, double *d_scores, int64_t *d_counts);

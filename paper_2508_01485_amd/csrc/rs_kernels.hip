@@ -812,6 +812,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_rows(const RowPart *part, int
 // ============================================================ score pass
 struct ScoreArgs {
     const int32_t *goff, *fcol;  // slots of the foreign entries and their neighbours
+    const uint8_t *sown;         // a tile slot's vertex (index in the tile)
     const int2 *tiles;
     const int32_t *hubs;
     int n_tiles, n_hubs, tiles_per_xcd;
@@ -1039,12 +1040,12 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The exact edge test of a wavefront's nb held candidates (from slot h0): the
-// hits move up, in order; returns their number.
+// The exact edge test of a wavefront's held candidates [nt, nb) (from slot
+// h0; the first nt are hits already): the hits move up, in order; returns the
+// number of hits.
 template <class Edge>
-__device__ __forceinline__ int typeI_test(HitBuf &H, const Edge &edge, int h0, int nb, int lane) {
-    int kept = 0;
-    for (int b0 = 0; b0 < nb; b0 += 64) {
+__device__ __forceinline__ int typeI_test(HitBuf &H, const Edge &edge, int h0, int nt, int nb, int lane) {
+    for (int b0 = nt; b0 < nb; b0 += 64) {
         const int h = h0 + b0 + lane;
         int p = 0, op = 0, code = 0;
         bool hit = false;
@@ -1056,22 +1057,23 @@ __device__ __forceinline__ int typeI_test(HitBuf &H, const Edge &edge, int h0, i
         const unsigned long long m = __ballot(hit);
         wave_sync();
         if (hit) {
-            const int s = h0 + kept + __popcll(m & ((1ull << lane) - 1ull));
+            const int s = h0 + nt + __popcll(m & ((1ull << lane) - 1ull));
             H.p[s] = (unsigned char)p;
             H.s[s].c.op = op;
             H.s[s].c.code = code;
         }
-        kept += __popcll(m);
+        nt += __popcll(m);
     }
     wave_sync();
-    return kept;
+    return nt;
 }
 
 // The terms of a wavefront's nb hits (from slot h0), then each pair's own lane
 // adds its hits (a contiguous range of the list) in list order.
 template <class Edge>
 __device__ __forceinline__ void typeI_flush(const ScoreArgs &A, const TypeIShared &T, HitBuf &H, const Edge &edge,
-                                            int h0, int nb, int lane, int me, bool mine, double &val, int &t1) {
+                                            int h0, int nb, int lane, int me, bool mine, bool mem, double &val,
+                                            int &t1) {
     for (int h = h0 + lane; h < h0 + nb; h += 64) {
         // the weights of the triangle {u, w, v}: w_v(C(u)), w_w(C(v)) and
         // w_v(C(w)), each the record at a leader slot (the out-list entry
@@ -1080,7 +1082,7 @@ __device__ __forceinline__ void typeI_flush(const ScoreArgs &A, const TypeIShare
         const OutEnt e = A.oe[H.s[h].c.op];
         const double w_wv = A.prec[e.xy].w;
         const double w_vw = A.prec[e.yx].w;
-        const double w_vu = edge.wvu(A, T, H.s[h].c.code);
+        const double w_vu = edge.wvu(A, T, H.s[h].c.code, mem);
         H.s[h].v = cbrt(w_vu * w_wv * W) + cbrt(W * w_vw * w_vu);
     }
     wave_sync();
@@ -1124,13 +1126,21 @@ __device__ __forceinline__ void typeI_flush(const ScoreArgs &A, const TypeIShare
 // (v, w),
 //   cbrt(w_v(C(u)) w_w(C(v)) W) + cbrt(W w_v(C(w)) w_v(C(u))),  W = w_w(C(u)),
 // are evaluated, one lane per hit, and the pair's own lane adds them to its
-// sum in list order (so the sum's order is fixed).  `items` is the lane's
-// out-list length (0 without a pair), `oo` its start and `salt` its part of
-// the hash; T.pW and the edge test's lists must be visible block-wide (a
-// barrier) before the call.
-template <class Edge>
-__device__ void typeI_scan(const ScoreArgs &A, TypeIShared &T, HitBuf &H, int items, int oo, unsigned int salt,
-                           const Edge &edge, double &val, int &t1) {
+// sum, after the type-II terms, in list order (so the sum's order is fixed).
+// `items` is the lane's out-list length (0 without a pair), `oo` its start and
+// `salt` its part of the hash; the edge test's lists must be visible
+// block-wide (a barrier) before the call.
+//
+// The pair's own facts are not needed before the hits are evaluated, so their
+// loads are in flight during the scan: settle(), called once, waits for them
+// and stores T.pW.  At the scan's end every wavefront passes one barrier of
+// the block (kBlockW: hits read other wavefronts' T.pW), then evaluates its
+// hits; a wavefront whose list fills up before evaluates what it holds at
+// once, reading other wavefronts' weights from memory.
+template <bool kBlockW, class Edge, class Settle>
+__device__ __forceinline__ void typeI_scan(const ScoreArgs &A, TypeIShared &T, HitBuf &H, int items, int oo,
+                                           unsigned int salt, const Edge &edge, const Settle &settle, double &val,
+                                           int &t1) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int w0 = wave * 64;           // the wavefront's first pair
     const int h0 = wave * kWaveHitCap;  // and its candidate slots
@@ -1141,7 +1151,6 @@ __device__ void typeI_scan(const ScoreArgs &A, TypeIShared &T, HitBuf &H, int it
         if (lane >= o) incl += y;
     }
     const int total = __builtin_amdgcn_readlane(incl, 63);
-    if (total == 0) return;
     const int first = incl - items;
     {
         const unsigned long long m = __ballot(items > 0);
@@ -1154,16 +1163,20 @@ __device__ void typeI_scan(const ScoreArgs &A, TypeIShared &T, HitBuf &H, int it
             T.own[w0 + __popcll(m & ((1ull << lane) - 1ull))] = e;
         }
     }
-    int nb = 0;    // held candidates of this wavefront
-    int seen = 0;  // pairs whose lists start before the group at hand
-    for (int sb = 0; sb < total; sb += kScanSpan) {
-        T.start[wave][lane] = 0u;
-        wave_sync();
-        if (items > 0 && first >= sb && first < sb + kScanSpan)
-            atomicOr(&T.start[wave][(first - sb) >> 5], 1u << ((first - sb) & 31));
-        wave_sync();
-        const int se = min(total, sb + kScanSpan);
-        for (int base = sb; base < se; base += 64 * kScanR) {
+    int nb = 0, nt = 0;  // held candidates of this wavefront, the first nt of them hits
+    int seen = 0;        // pairs whose lists start before the group at hand
+    int base = 0;
+    bool settled = false;
+    for (;;) {
+        while (base < total && nb <= kWaveHitCap - 64 * kScanR) {
+            const int sb = base & ~(kScanSpan - 1);
+            if (base == sb) {  // the next span's start bits
+                T.start[wave][lane] = 0u;
+                wave_sync();
+                if (items > 0 && first >= sb && first < sb + kScanSpan)
+                    atomicOr(&T.start[wave][(first - sb) >> 5], 1u << ((first - sb) & 31));
+                wave_sync();
+            }
             int y[kScanR], op[kScanR], p[kScanR];
             unsigned int salts[kScanR];
 #pragma unroll
@@ -1172,7 +1185,7 @@ __device__ void typeI_scan(const ScoreArgs &A, TypeIShared &T, HitBuf &H, int it
                 y[r] = -1;
                 op[r] = p[r] = 0;
                 salts[r] = 0u;
-                if (b < se) {  // (uniform)
+                if (b < total) {  // (uniform)
                     const unsigned int m0 = T.start[wave][(b - sb) >> 5], m1 = T.start[wave][((b - sb) >> 5) + 1];
                     const unsigned int lo = __builtin_amdgcn_readfirstlane((int)m0);
                     const unsigned int hi = __builtin_amdgcn_readfirstlane((int)m1);
@@ -1190,7 +1203,7 @@ __device__ void typeI_scan(const ScoreArgs &A, TypeIShared &T, HitBuf &H, int it
             }
 #pragma unroll
             for (int r = 0; r < kScanR; ++r) {
-                if (base + 64 * r >= se) break;
+                if (base + 64 * r >= total) break;
                 const bool cand = base + 64 * r + lane < total && y[r] >= 0 && edge.maybe(salts[r], y[r]);
                 const unsigned long long m = __ballot(cand);
                 if (!m) continue;
@@ -1202,18 +1215,23 @@ __device__ void typeI_scan(const ScoreArgs &A, TypeIShared &T, HitBuf &H, int it
                 }
                 nb += __popcll(m);
             }
-            if (nb > kWaveHitCap - 64 * kScanR) {
-                wave_sync();
-                nb = typeI_test(H, edge, h0, nb, lane);
-                typeI_flush(A, T, H, edge, h0, nb, lane, tid, items > 0, val, t1);
-                nb = 0;
-            }
+            base += 64 * kScanR;
         }
-    }
-    if (nb > 0) {
+        const bool end = base >= total;
         wave_sync();
-        nb = typeI_test(H, edge, h0, nb, lane);
-        if (nb > 0) typeI_flush(A, T, H, edge, h0, nb, lane, tid, items > 0, val, t1);
+        nt = nb = typeI_test(H, edge, h0, nt, nb, lane);
+        if (!end && nb <= kWaveHitCap - 64 * kScanR) continue;
+        if (!settled) {
+            settle();
+            settled = true;
+        }
+        if (end && kBlockW)
+            __syncthreads();  // once per wavefront
+        else
+            wave_sync();
+        if (nb > 0) typeI_flush(A, T, H, edge, h0, nb, lane, tid, items > 0, !end, val, t1);
+        if (end) return;
+        nb = nt = 0;
     }
 }
 
@@ -1249,8 +1267,8 @@ static_assert(kScoreTileV == kBlock && kScoreTileP == kBlock, "score unit size: 
 // holds seven (a candidate takes nine bytes).
 struct ScoreUnitShared {
     int w[kHubList];                 // foreign neighbours (a tile's at most kScoreTileP, an LDS hub's at most kHubList)
-    int pb[kScoreTileV + 1];         // tile: first pair of each vertex
-    unsigned short pu[kScoreTileP];  // tile: vertex of each pair
+    unsigned short pb[kScoreTileV], pe[kScoreTileV];  // tile: pairs of each vertex
+    unsigned char pu[kScoreTileP];                     // tile: vertex of each pair
     int ws[kBlock / 64];
     double red[kBlock / 64];
     long long ired[2][kBlock / 64];
@@ -1260,9 +1278,9 @@ struct ScoreUnitShared {
         int go[kScoreTileV];  // prologue: first slot of each of the tile's vertices
         HitBuf hits;          // type-I scan
         struct {              // epilogue: the lanes' pair terms
-            double val[kBlock];
-            int t2[kBlock], t1[kBlock];
-        } e;
+            double val;
+            int t2, t1;
+        } e[kBlock];
     } u;
 };
 
@@ -1284,48 +1302,54 @@ __device__ __forceinline__ void chunk_tree(double x, long long y1, long long y2,
     __syncthreads();
 }
 
-// Edge tests of a unit's type-I scan: u's foreign list is in LDS (a tile
-// vertex's slice, or a hub's whole list).  Each also gives a code for its
-// hits, from which wvu() reads w_v(C(u)), the record of C(u) in v's list.
-struct TileEdge {
+// The edge test of a unit's type-I scan: u's foreign list is in LDS (a tile
+// vertex's slice, or a hub's whole list, whose chunk's pairs are the list's
+// positions [cbase, cbase + kBlock)).  It also gives a code for its hits, v's
+// position, from which wvu() reads w_v(C(u)), the record of C(u) in v's list:
+// it is the W of the pair (u, v), in T.pW when the unit has that pair, else
+// (or with mem, where T.pW may not be whole) in memory.
+struct UnitEdge {
     const ScoreUnitShared *S;
+    int cbase;
+    int slot0;          // slot of position 0
+    const int32_t *vl;  // listed vertices (their slots are not consecutive), or null
     __device__ __forceinline__ bool maybe(unsigned int salt, int y) const { return unit_filter_has(S->filt, salt, y); }
     __device__ __forceinline__ bool operator()(int p, int y, int &code) const {
-        const int i = S->pu[p];
-        const int k = lds_lower(S->w, S->pb[i], S->pb[i + 1], y);
-        code = k;  // (u, v) is the unit's pair k: its W is w_v(C(u))
-        return k < S->pb[i + 1] && S->w[k] == y;
+        const int i = S->pu[p], e = S->pe[i];
+        const int k = lds_lower(S->w, S->pb[i], e, y);
+        code = k;
+        return k < e && S->w[k] == y;
     }
-    __device__ __forceinline__ double wvu(const ScoreArgs &, const TypeIShared &T, int code) const {
-        return T.pW[code];
-    }
-};
-struct HubListEdge {
-    const ScoreUnitShared *S;
-    int n;
-    int cbase, ccnt;  // the chunk's pairs: list positions [cbase, cbase + ccnt)
-    int go;           // the hub's first slot
-    __device__ __forceinline__ bool maybe(unsigned int salt, int y) const { return unit_filter_has(S->filt, salt, y); }
-    __device__ __forceinline__ bool operator()(int, int y, int &code) const {
-        const int k = lds_lower(S->w, 0, n, y);
-        code = k;  // (u, v) is the hub's pair k
-        return k < n && S->w[k] == y;
-    }
-    __device__ __forceinline__ double wvu(const ScoreArgs &A, const TypeIShared &T, int code) const {
-        if (code >= cbase && code < cbase + ccnt) return T.pW[code - cbase];
-        return A.prec[A.plink[go + code].lead].w;
+    __device__ __forceinline__ double wvu(const ScoreArgs &A, const TypeIShared &T, int code, bool mem) const {
+        if (!mem && (unsigned int)(code - cbase) < (unsigned int)kBlock) return T.pW[code - cbase];
+        int s = slot0 + code;
+        if (vl) {
+            const int i = S->pu[code];
+            s = A.goff[vl[i]] + (code - S->pb[i]);
+        }
+        return A.prec[A.plink[s].lead].w;
     }
 };
 
 // vl: a unit of listed vertices vl[0, vn) (the incremental pass's rescored
 // vertices) instead of the tile idx.
+//
+// A workgroup spends its time in a chain of dependent reads (some 20 us at n =
+// 3 million, mean degree 30, with six of them on a CU), so the chain is kept
+// short: a tile's lanes take its slots as they lie (a slot's vertex is a byte
+// fixed with the schedule; slots that removals freed idle), so the links, the
+// neighbours and the vertices' row facts are read together, and the pairs'
+// records while the type-I scan runs.
 __device__ void score_unit(const ScoreArgs &A, ScoreUnitShared &S, bool hub_unit, int idx, double wmax,
                            const int32_t *vl = nullptr, int vn = 0) {
     const int tid = threadIdx.x;
     for (int i = tid; i < kUnitFilterWords; i += kBlock) S.filt[i] = 0u;
-    // ---- prologue: lay out the unit's pairs
-    int v0 = 0, nv = 0, total = 0, dp = 0, deg = 0, pb = 0;    // tile
+    int v0 = 0, nv = 0, dp = 0, deg = 0, pb = 0;       // tile
     int hub = 0, chunk = 0, hu = 0, hdp = 0, hgo = 0;  // hub chunk
+    int total = 0;                                     // hub chunk, listed vertices: pairs
+    int slot = 0, s0 = 0, w = 0, own = 0;
+    bool in = false, has = false;
+    PairLink pl = {};
     if (hub_unit) {
         const int2 hc = A.hub_chunk[idx];
         hub = hc.x;
@@ -1334,99 +1358,122 @@ __device__ void score_unit(const ScoreArgs &A, ScoreUnitShared &S, bool hub_unit
         const VMeta m = A.meta[hu];
         hgo = A.goff[hu];
         hdp = m.deg - (m.q - m.p);  // <= the load-time count, which fits kHubList
+        total = min(kBlock, max(0, hdp - chunk * kBlock));
+        has = tid < total;
+        if (has) {
+            slot = hgo + chunk * kBlock + tid;
+            pl = A.plink[slot];
+        }
         __syncthreads();  // the cleared filter
         for (int j = tid; j < hdp; j += kBlock) {
-            const int w = A.fcol[hgo + j];
-            S.w[j] = w;
-            unit_filter_set(S.filt, 0u, w);
+            const int x = A.fcol[hgo + j];
+            S.w[j] = x;
+            unit_filter_set(S.filt, unit_salt(0), x);
         }
-        total = min(kBlock, max(0, hdp - chunk * kBlock));
+        S.pu[tid] = 0;  // one vertex, whose pairs are the whole list
+        if (tid == 0) {
+            S.pb[0] = 0;
+            S.pe[0] = (unsigned short)hdp;
+        }
+        __syncthreads();
     } else {
         if (vl) {
+            if (tid < vn) {
+                const int v = vl[tid];
+                const VMeta m = A.meta[v];
+                deg = m.deg;
+                dp = m.deg - (m.q - m.p);
+                S.u.go[tid] = A.goff[v];
+            }
             nv = vn;
+            pb = block_excl_scan(dp, S.ws, total);  // (its barrier: the cleared filter)
+            if (tid < nv)
+                for (int q = pb; q < pb + dp; ++q) S.pu[q] = (unsigned char)tid;
+            if (tid < nv) {
+                S.pb[tid] = (unsigned short)pb;
+                S.pe[tid] = (unsigned short)(pb + dp);
+            }
+            __syncthreads();
+            in = tid < total;
+            if (in) {
+                own = S.pu[tid];
+                slot = S.u.go[own] + (tid - S.pb[own]);
+                pl = A.plink[slot];
+                w = A.fcol[slot];
+            }
         } else {
             const int2 tl = A.tiles[idx];
             v0 = tl.x;
             nv = tl.y - tl.x;
-        }
-        if (tid < nv) {
-            const int v = vl ? vl[tid] : v0 + tid;
-            const VMeta m = A.meta[v];
-            deg = m.deg;
-            dp = m.deg - (m.q - m.p);
-            S.u.go[tid] = A.goff[v];
-        }
-        pb = block_excl_scan(dp, S.ws, total);
-        if (tid < nv) {
-            S.pb[tid] = pb;
-            for (int k = pb; k < pb + dp; ++k) S.pu[k] = (unsigned short)tid;
-        }
-        if (tid == 0) S.pb[nv] = total;
-        __syncthreads();
-    }
-    // ---- the lane's pair: type II
-    const bool has = tid < total;
-    double val = 0.0;
-    int t2 = 0, t1 = 0, items = 0, oo = 0;
-    unsigned int salt = 0u;
-    if (has) {
-        int u, slot;
-        if (hub_unit) {
-            u = hu;
-            slot = hgo + chunk * kBlock + tid;
-        } else {
-            const int i = S.pu[tid];
-            u = vl ? vl[i] : v0 + i;
-            slot = S.u.go[i] + (tid - S.pb[i]);
-            const int w = A.fcol[slot];
-            S.w[tid] = w;
-            salt = unit_salt(i);
-            unit_filter_set(S.filt, salt, w);
-        }
-        const PairLink pl = A.plink[slot];
-        const PairRec pr = A.prec[pl.lead];
-        val = type2_pair(A, u, pr, pl);
-        t2 = pr.f - 1;
-        items = pl.on;
-        oo = pl.oo;
-        S.ti.pW[tid] = pr.w;
-    }
-    // ---- type I (the candidate lists overlay the prologue's slots)
-    __syncthreads();
-    if (hub_unit) {
-        HubListEdge E;
-        E.S = &S;
-        E.n = hdp;
-        E.cbase = chunk * kBlock;
-        E.ccnt = total;
-        E.go = hgo;
-        typeI_scan(A, S.ti, S.u.hits, items, oo, salt, E, val, t1);
-    } else {
-        TileEdge E;
-        E.S = &S;
-        typeI_scan(A, S.ti, S.u.hits, items, oo, salt, E, val, t1);
-    }
-    // ---- epilogue: sums in a fixed order (its terms overlay the hit lists)
-    __syncthreads();
-    if (!hub_unit) {
-        S.u.e.val[tid] = val;
-        S.u.e.t2[tid] = t2;
-        S.u.e.t1[tid] = t1;
-        __syncthreads();
-        if (tid < nv && dp > 0) {
-            double acc = 0.0;
-            long long c1 = 0, c2 = 0;
-            for (int q = pb; q < pb + dp; ++q) {
-                acc += S.u.e.val[q];
-                c2 += S.u.e.t2[q];
-                c1 += S.u.e.t1[q];
+            const int s1 = A.goff[tl.y];
+            s0 = A.goff[tl.x];
+            in = tid < s1 - s0;
+            if (in) {
+                slot = s0 + tid;
+                pl = A.plink[slot];
+                w = A.fcol[slot];
+                own = A.sown[slot];
             }
-            score_store(A, vl ? vl[tid] : v0 + tid, deg, acc, c1, c2, wmax);
+            if (tid < nv) {
+                const VMeta m = A.meta[v0 + tid];
+                pb = A.goff[v0 + tid] - s0;
+                deg = m.deg;
+                dp = m.deg - (m.q - m.p);
+                S.pb[tid] = (unsigned short)pb;
+                S.pe[tid] = (unsigned short)(pb + dp);
+            }
+            __syncthreads();  // the cleared filter
+            if (in) S.pu[tid] = (unsigned char)own;
         }
+        if (in) {
+            has = tid < (int)S.pe[own];
+            S.w[tid] = w;
+            if (has) unit_filter_set(S.filt, unit_salt(own), w);
+        }
+        __syncthreads();
+    }
+    // ---- the lane's pair: its record is read while the type-I scan runs
+    PairRec pr = {};
+    if (has) pr = A.prec[pl.lead];
+    const int items = has ? pl.on : 0;
+    double val = 0.0;
+    int t2 = 0, t1 = 0;
+    auto settle = [&]() {
+        if (has) {
+            val = type2_pair(A, hub_unit ? hu : vl ? vl[own] : v0 + own, pr, pl);
+            t2 = pr.f - 1;
+            S.ti.pW[tid] = pr.w;
+        }
+    };
+    // ---- type I (the candidate lists overlay the prologue's slots)
+    UnitEdge E;
+    E.S = &S;
+    E.cbase = hub_unit ? chunk * kBlock : 0;
+    E.slot0 = hub_unit ? hgo : s0;
+    E.vl = vl;
+    typeI_scan<true>(A, S.ti, S.u.hits, items, pl.oo, unit_salt(own), E, settle, val, t1);
+    if (hub_unit) {
+        chunk_tree(val, t1, t2, S.red, S.ired);
+        if (tid == 0) hub_chunk_store(A, S.red, S.ired, hub, chunk);
         return;
     }
-    chunk_tree(val, t1, t2, S.red, S.ired);
-    if (tid == 0) hub_chunk_store(A, S.red, S.ired, hub, chunk);
+    // ---- epilogue: each vertex adds its pairs in order (the terms overlay the hit lists)
+    __syncthreads();
+    S.u.e[tid].val = val;
+    S.u.e[tid].t2 = t2;
+    S.u.e[tid].t1 = t1;
+    __syncthreads();
+    if (tid < nv && dp > 0) {
+        double acc = 0.0;
+        long long c1 = 0, c2 = 0;
+#pragma unroll 4
+        for (int q = pb; q < pb + dp; ++q) {
+            acc += S.u.e[q].val;
+            c2 += S.u.e[q].t2;
+            c1 += S.u.e[q].t1;
+        }
+        score_store(A, vl ? vl[tid] : v0 + tid, deg, acc, c1, c2, wmax);
+    }
 }
 
 // A hub whose foreign list exceeds kHubList: u's list stays in HBM.  The
@@ -1479,7 +1526,7 @@ struct HubOutEdge {
         code = (int)(o << 1) | 1;
         return o >= 0;
     }
-    __device__ __forceinline__ double wvu(const ScoreArgs &A, const TypeIShared &, int code) const {
+    __device__ __forceinline__ double wvu(const ScoreArgs &A, const TypeIShared &, int code, bool) const {
         const OutEnt e = A.oe[code >> 1];
         return A.prec[(code & 1) ? e.xy : e.yx].w;
     }
@@ -1496,17 +1543,23 @@ __device__ void score_hub_big(const ScoreArgs &A, ScoreHubBigShared &S, int hub,
     if (staged)
         for (int j = tid; j < n_out; j += kBlock) S.outu[j] = A.outl[uo0 + j];
     const int k = chunk * kScoreTileP + tid;
-    double val = 0.0;
-    int t2 = 0, t1 = 0, items = 0, oo = 0;
-    if (k < dp) {
-        const PairLink pl = A.plink[A.goff[u] + k];
-        const PairRec pr = A.prec[pl.lead];
-        val = type2_pair(A, u, pr, pl);
-        t2 = pr.f - 1;
-        items = pl.on;
-        oo = pl.oo;
-        S.ti.pW[tid] = pr.w;
+    const bool has = k < dp;
+    PairLink pl = {};
+    PairRec pr = {};
+    if (has) {
+        pl = A.plink[A.goff[u] + k];
+        pr = A.prec[pl.lead];
     }
+    const int items = has ? pl.on : 0;
+    double val = 0.0;
+    int t2 = 0, t1 = 0;
+    auto settle = [&]() {
+        if (has) {
+            val = type2_pair(A, u, pr, pl);
+            t2 = pr.f - 1;
+            S.ti.pW[tid] = pr.w;
+        }
+    };
     HubOutEdge E;
     E.stage = staged ? S.outu : nullptr;
     E.n_stage = n_out;
@@ -1517,7 +1570,7 @@ __device__ void score_hub_big(const ScoreArgs &A, ScoreHubBigShared &S, int hub,
     E.filt = A.hfilter + (size_t)(hub - A.n_hubs_lds) * kFilterWords;
     E.u = u;
     __syncthreads();  // the staged out-list
-    typeI_scan(A, S.ti, S.hits, items, oo, 0u, E, val, t1);
+    typeI_scan<false>(A, S.ti, S.hits, items, pl.oo, 0u, E, settle, val, t1);
     chunk_tree(val, t1, t2, S.red, S.ired);
     if (tid == 0) hub_chunk_store(A, S.red, S.ired, hub, chunk);
 }
@@ -1671,7 +1724,10 @@ union ScoreShared {
     ScoreUnitShared u;
     ScoreHubBigShared h;
 };
-static_assert(7 * sizeof(ScoreShared) <= 160 * 1024, "seven score workgroups per CU");
+// Six workgroups share a CU: with registers for seven the compiler spills 33 of
+// them (n = 3 million, mean degree 30: 1,413 against 1,362 us a pass; 128
+// graphs: 435 against 443).
+static_assert(7 * sizeof(ScoreShared) <= 160 * 1024, "LDS for seven score workgroups per CU");
 
 // Algorithm 1 Step 3 (Eq. RSI) for every border vertex, in one launch: the
 // chunks of the hubs too large for LDS first (the longest units), then the
@@ -1679,7 +1735,7 @@ static_assert(7 * sizeof(ScoreShared) <= 160 * 1024, "seven score workgroups per
 // of that XCD: blocks are dealt to the XCDs round-robin, so consecutive tiles
 // share an L2).  Hub partials are summed by k_hub_sum.  Launches of their own
 // for the hubs ended on one chunk's latency with nothing beside it.
-__global__ __launch_bounds__(kBlock, 7) void k_score(ScoreArgs A) {
+__global__ __launch_bounds__(kBlock, 6) void k_score(ScoreArgs A) {
     __shared__ ScoreShared S;
     const int n_big = A.n_chunks - A.n_chunks_lds;
     const double wmax = bitsd(A.ctr->wmax_bits);
@@ -2009,6 +2065,26 @@ rs_status launch_links(rs_graph *g, unsigned long long *d_run_walk) {
     return g->d.off64 ? links_t<long long>(g, d_run_walk) : links_t<int32_t>(g, d_run_walk);
 }
 
+// The tile vertices' slots: each one's vertex, as its index in its score tile
+// (with the schedule; a wavefront per tile vertex range).
+__global__ __launch_bounds__(kBlock) void k_slot_owners(const int2 *tiles, int n_tiles, const int32_t *goff,
+                                                        uint8_t *sown) {
+    for (int t = (int)blockIdx.x; t < n_tiles; t += (int)gridDim.x) {
+        const int2 tl = tiles[t];
+        const int v = tl.x + (int)threadIdx.x;
+        if (v < tl.y)
+            for (int s = goff[v]; s < goff[v + 1]; ++s) sown[s] = (uint8_t)threadIdx.x;
+    }
+}
+
+rs_status launch_slot_owners(rs_graph *g) {
+    if (g->n_stiles == 0) return RS_OK;
+    hipLaunchKernelGGL(k_slot_owners, dim3(std::min(g->n_stiles, 1 << 20)), dim3(kBlock), 0, g->stream, g->d.stiles,
+                       g->n_stiles, g->d.goff, g->d.sown);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? RS_OK : hip_fail(e, "slot owner launch");
+}
+
 // Each out-list entry x -> y (at load): the leader slots of C(y)'s run in x's
 // list and of C(x)'s run in y's list; the owner x is the last with oo[x] <= o.
 template <typename OffT>
@@ -2238,6 +2314,7 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
     ScoreArgs S;
     S.goff = D.goff;
     S.fcol = D.fcol;
+    S.sown = D.sown;
     S.tiles = D.stiles;
     S.hubs = D.shubs;
     S.n_tiles = g->n_stiles;

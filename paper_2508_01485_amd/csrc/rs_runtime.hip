@@ -448,7 +448,7 @@ static rs_status upload_tiles(rs_graph *g, const HostTiles &H) {
                             (void **)&D.shub_first, (void **)&D.shub_chunk, (void **)&D.hub_part,
                             (void **)&D.rflag, (void **)&D.cflag, (void **)&D.hflag, (void **)&D.rlist,
                             (void **)&D.slist, (void **)&D.hlist, (void **)&D.part_rows, (void **)&D.wmax_part,
-                            (void **)&D.vrowb, (void **)&D.vscore, (void **)&D.hfilter};
+                            (void **)&D.vrowb, (void **)&D.vscore, (void **)&D.hfilter, (void **)&D.sown};
     for (void **p : tile_arrays) dev_free(g, p);
     const size_t N = (size_t)std::max<int64_t>(D.n, 1);
     g->n_rtiles = (int)H.rtiles.size();
@@ -485,6 +485,7 @@ static rs_status upload_tiles(rs_graph *g, const HostTiles &H) {
         {(void **)&D.wmax_part, 8 * gr},
         {(void **)&D.vrowb, 4 * N},
         {(void **)&D.vscore, 4 * N},
+        {(void **)&D.sown, (size_t)std::max<int64_t>(2 * g->n_out, 1)},
         {(void **)&D.hfilter, 4 * (size_t)kFilterWords * std::max<size_t>(H.shubs.size() - H.n_hubs_lds, 1)},
     };
     for (auto &r : reqs) {
@@ -507,7 +508,7 @@ static rs_status upload_tiles(rs_graph *g, const HostTiles &H) {
     if (e == hipSuccess) e = hipMemsetAsync(D.rflag, 0, gr, s);
     if (e == hipSuccess) e = hipMemsetAsync(D.cflag, 0, nch, s);
     if (e == hipSuccess) e = hipMemsetAsync(D.hflag, 0, nsh, s);
-    return e == hipSuccess ? RS_OK : hip_fail(e, "schedule upload");
+    return e == hipSuccess ? launch_slot_owners(g) : hip_fail(e, "schedule upload");
 }
 
 static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool keep = false) {
