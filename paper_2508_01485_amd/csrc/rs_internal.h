@@ -320,8 +320,9 @@ struct rs_graph {
     std::vector<int64_t> h_vstart;
     std::vector<int32_t> h_gblk_off, h_gblk;
     int32_t n_segs = 0;       // batched top-k segments (0: the one-wavefront-per-graph form)
-    int32_t *reach_comp = nullptr, *reach_src = nullptr;  // reachable-community buffers (first use)
-    unsigned int *reach_bits = nullptr, *reach_flag = nullptr, *reach_hflag = nullptr;
+    int32_t *reach_comp = nullptr;                        // reachable-community buffers (first use)
+    unsigned int *reach_bits = nullptr;
+    long long *reach_cnt = nullptr, *reach_host = nullptr;  // counts, then sources; the same, pinned
     std::vector<std::pair<void *, size_t>> allocations;  // device buffers and their sizes
     rs::Tiling tiling;
     // pinned host buffer of the common top-k path: [flag | ids | scores]
@@ -379,13 +380,13 @@ struct Prebuilt;
 rs_status prebuild_graph(const rs_csr *csr, Prebuilt **out);
 rs_status load_prebuilt(Prebuilt *P, void *hip_stream, rs_graph **out);
 void free_prebuilt(Prebuilt *P);
+// counts[i] of source d_src[i] (internal ids; ns <= kMaxReachSources), with
+// comp [n], bits [ns * words] as scratch.
 rs_status launch_reach(rs_graph *g, const int32_t *d_src, int ns, int32_t *comp, unsigned int *bits, int words,
-                       unsigned int *d_changed, unsigned int *h_changed);
+                       long long *d_counts);
 rs_status launch_zero_u64(rs_graph *g, unsigned long long *p, int count);
 // The device address of this library's static scratch array on `device`
-// (taken once per device with hipGetSymbolAddress), and the per-source
-// bit counts of reach bitmaps.
+// (taken once per device with hipGetSymbolAddress).
 rs_status static_scratch(int device, void **out);
-rs_status launch_reach_counts(rs_graph *g, const unsigned int *bits, int ns, int words, long long *d_counts);
 
 }  // namespace rs

@@ -4206,107 +4206,267 @@ rs_status launch_zero_u64(rs_graph *g, unsigned long long *p, int count) {
 
 // ============================================================ reachable communities
 // For the absolute AWCC of the robustness experiments (Section VII-B): the
-// connected components of the current graph by hooking and pointer jumping
-// (labels only decrease along parent links, so no cycle can form), then, for
-// each source, the communities of the other members of its component.
-__global__ __launch_bounds__(kBlock) void k_cc_init(int32_t *comp, long long n) {
-    for (long long v = (long long)blockIdx.x * kBlock + threadIdx.x; v < n; v += (long long)gridDim.x * kBlock)
-        comp[v] = (int32_t)v;
+// connected components of the current graph, then, for each source, the
+// communities of the other members of its component.
+//
+// Components are a union-find over the live edges, with no rounds to
+// convergence and no host check: parents only ever decrease (comp[v] <= v, so no
+// cycle can form), an edge hooks the larger of its two roots under the smaller
+// with a compare-and-swap, and a failed one goes on from the value it met, a
+// smaller id.  (Rounds of hooking and pointer jumping, with a thread walking
+// each row, took four sweeps of 37 to 740 us at n = 10^5 and a host wait per
+// four rounds.)  Parents may be read from a cache that another XCD's swap has
+// made stale, and path stores may land late: a value once above v stays an
+// ancestor of v, only roots are swapped, and no store makes a root, so a stale
+// value costs a failed swap and nothing else.
+__device__ __forceinline__ int32_t cc_load(const int32_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void cc_store(int32_t *p, int32_t x) {
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Hook the root of the larger label under the smaller one across every live
-// edge; comp[] holds roots here (the jump kernel ran before).
-template <typename OffT>
-__global__ __launch_bounds__(kBlock) void k_cc_hook(const OffT *off, const int32_t *deg, const int32_t *col,
-                                                    int32_t *comp, long long n, unsigned int *changed) {
-    for (long long v = (long long)blockIdx.x * kBlock + threadIdx.x; v < n; v += (long long)gridDim.x * kBlock) {
-        const long long rb = (long long)off[v];
-        const int d = deg[v];
-        bool hooked = false;
-        for (int j = 0; j < d; ++j) {
-            const int32_t x = col[rb + j];
-            if (x < 0) continue;  // (rows are compacted after removals; defensive)
-            const int32_t cu = comp[x], cv = comp[v];
-            if (cu < cv) {
-                atomicMin(&comp[cv], cu);
-                hooked = true;
-            }
+// The root above v; every second vertex of the path is pointed at its
+// grandparent on the way.
+__device__ __forceinline__ int32_t cc_find(int32_t *comp, int32_t v) {
+    int32_t prev = v, p = cc_load(&comp[v]);
+    if (p == v) return v;
+    for (;;) {
+        const int32_t next = cc_load(&comp[p]);
+        if (next == p) return p;
+        cc_store(&comp[prev], next);
+        prev = p;
+        p = next;
+    }
+}
+
+__device__ __forceinline__ void cc_unite(int32_t *comp, int32_t u, int32_t v) {
+    int32_t a = cc_find(comp, u), b = cc_find(comp, v);
+    while (a != b) {
+        if (a < b) {
+            const int32_t t = a;
+            a = b;
+            b = t;
         }
-        if (hooked) *changed = 1u;
+        const int32_t old = atomicCAS(&comp[a], a, b);  // a is the larger root
+        if (old == a) return;
+        a = cc_find(comp, old);  // a was hooked meanwhile: old < a
+    }
+}
+
+// Every vertex starts under its smallest neighbour, if that is smaller.  Also
+// clears the community bitmaps (n_bits words).
+template <typename OffT>
+__global__ __launch_bounds__(kBlock) void k_cc_init(const OffT *off, const int32_t *deg, const int32_t *col,
+                                                    int32_t *comp, long long n, unsigned int *bits,
+                                                    long long n_bits) {
+    for (long long w = (long long)blockIdx.x * kBlock + threadIdx.x; w < n_bits; w += (long long)gridDim.x * kBlock)
+        bits[w] = 0u;
+    for (long long v = (long long)blockIdx.x * kBlock + threadIdx.x; v < n; v += (long long)gridDim.x * kBlock) {
+        const int32_t x = deg[v] > 0 ? col[off[v]] : (int32_t)v;
+        comp[v] = x >= 0 && x < (int32_t)v ? x : (int32_t)v;  // (rows are compacted after removals: x < 0 is defensive)
+    }
+}
+
+// One sweep over the edges, each from its larger end (a row's entries below the
+// vertex).  A wavefront takes the rows of 64 vertices, flattened over its
+// lanes.  kUnite: the ends are united.  Else, with comp[] flat (roots), the
+// larger root takes the smaller as its parent if that is less than what it
+// has: a round of this joins most trees with two reads an edge, and after
+// kCcRounds of them (each flattened) the uniting sweep meets the same root
+// twice at nearly every edge.  Uniting from the start, where trees grow deep
+// while every lane climbs them, took 200 to 350 us at n = 10^5 with 4.6 edges
+// left a vertex (whole queries: one round 97 us, two 108, three 118).
+constexpr int kCcRounds = 1;
+template <bool kUnite, typename OffT>
+__global__ __launch_bounds__(kBlock) void k_cc_hook(const OffT *off, const int32_t *deg, const int32_t *col,
+                                                    int32_t *comp, long long n) {
+    __shared__ int s_pre[kBlock / 64][64];
+    __shared__ long long s_rb[kBlock / 64][64];
+    const int lane = threadIdx.x & 63;
+    int *pre = s_pre[threadIdx.x >> 6];
+    long long *row = s_rb[threadIdx.x >> 6];
+    auto join = [&](int32_t x, int32_t v) {
+        if (x < 0 || x >= v) return;
+        if (kUnite) {
+            cc_unite(comp, x, v);
+        } else {
+            int32_t a = cc_load(&comp[x]), b = cc_load(&comp[v]);
+            if (a == b) return;
+            if (a < b) {
+                const int32_t t = a;
+                a = b;
+                b = t;
+            }
+            if (b < cc_load(&comp[a])) atomicMin(&comp[a], b);
+        }
+    };
+    for (long long v0 = (long long)blockIdx.x * kBlock + (threadIdx.x & ~63); v0 < n;
+         v0 += (long long)gridDim.x * kBlock) {
+        const long long v = v0 + lane;
+        int cnt = 0;
+        long long rb = 0;
+        if (v < n) {
+            rb = (long long)off[v];
+            cnt = deg[v];
+        }
+        long long incl = cnt;  // (rows of hubs: the 64 may hold more than 2^31 entries)
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const long long y = __shfl_up(incl, o);
+            if (lane >= o) incl += y;
+        }
+        const long long total = __shfl(incl, 63);
+        if (total <= (long long)INT_MAX) {
+            pre[lane] = (int)incl;
+            row[lane] = rb;
+            wave_sync();
+            for (int g0 = 0; g0 < (int)total; g0 += 64) {
+                const int g = g0 + lane;
+                if (g < (int)total) {
+                    int j;
+                    const int l = flat_owner(pre, g, j);
+                    join(col[row[l] + j], (int32_t)(v0 + l));
+                }
+            }
+            wave_sync();
+        } else {
+            for (int j = 0; j < cnt; ++j) join(col[rb + j], (int32_t)v);
+        }
     }
 }
 
 // Point every vertex at its root.
-__global__ __launch_bounds__(kBlock) void k_cc_jump(int32_t *comp, long long n) {
+__global__ __launch_bounds__(kBlock) void k_cc_flatten(int32_t *comp, long long n) {
     for (long long v = (long long)blockIdx.x * kBlock + threadIdx.x; v < n; v += (long long)gridDim.x * kBlock) {
-        int32_t c = comp[v];
-        while (comp[c] != c) c = comp[c];
-        comp[v] = c;
+        int32_t c = cc_load(&comp[v]);
+        for (;;) {
+            const int32_t p = cc_load(&comp[c]);
+            if (p == c) break;
+            c = p;
+        }
+        cc_store(&comp[v], c);
     }
 }
 
-// bits[i][c] = 1 when some vertex other than source i lies in source i's
-// component and belongs to community c.
-__global__ __launch_bounds__(kBlock) void k_reach_bits(const int32_t *comp, const int32_t *lab, long long n,
-                                                       const int32_t *src, int ns, int words, unsigned int *bits) {
-    __shared__ int32_t s_c[kMaxReachSources], s_v[kMaxReachSources];
-    for (int i = threadIdx.x; i < ns; i += kBlock) {
-        s_v[i] = src[i];
-        s_c[i] = comp[src[i]];
+// What is kept of a source until its count is known: the first source of the
+// same component, whose bitmap serves the whole component, and whether
+// another member shares the source's community.
+struct ReachSource {
+    int32_t group;
+    unsigned int other;
+};
+static_assert(sizeof(ReachSource) == sizeof(long long), "the counts replace the sources' facts");
+
+// One workgroup: the root of each source's component is marked with the first
+// of its sources to get there (comp[root] = ~i), and the sources get their
+// groups.
+__global__ __launch_bounds__(kMaxReachSources) void k_reach_groups(int32_t *comp, const int32_t *src, int ns,
+                                                                   ReachSource *out) {
+    const int i = threadIdx.x;
+    if (i < ns) {
+        const int32_t c = cc_load(&comp[src[i]]);
+        if (c >= 0) atomicCAS(&comp[c], c, ~i);
     }
     __syncthreads();
-    for (long long v = (long long)blockIdx.x * kBlock + threadIdx.x; v < n; v += (long long)gridDim.x * kBlock) {
-        const int32_t c = comp[v];
-        const int32_t l = lab[v];
-        const unsigned int bit = 1u << (l & 31);
-        for (int i = 0; i < ns; ++i)
-            if (s_c[i] == c && s_v[i] != (int32_t)v) {
-                unsigned int *w = &bits[(long long)i * words + (l >> 5)];
-                if (!(__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit))
-                    atomicOr(w, bit);  // most members find their community's bit already set
-            }
+    if (i < ns) {  // (the swaps act in memory: read past the caches)
+        const int32_t c = __hip_atomic_load(&comp[src[i]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int32_t g = c < 0 ? c : __hip_atomic_load(&comp[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        out[i].group = ~g;
+        out[i].other = 0u;
     }
 }
 
-__global__ void k_zero_u32(unsigned int *p, long long count) {
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (long long)gridDim.x * blockDim.x)
-        p[i] = 0u;
+// Each member of a marked component sets its community's bit in the
+// component's bitmap (in LDS when all bitmaps fit, added to the global ones at
+// the end; most members find their bit set already), and tells the sources of
+// the same component and community that they are not alone.
+constexpr int kReachWords = 8192;
+__global__ __launch_bounds__(kBlock) void k_reach_bits(const int32_t *comp, const int32_t *lab, long long n,
+                                                       const int32_t *src, int ns, int words, ReachSource *rs,
+                                                       unsigned int *bits) {
+    __shared__ int32_t s_g[kMaxReachSources], s_v[kMaxReachSources], s_l[kMaxReachSources];
+    __shared__ unsigned int s_other[kMaxReachSources], s_bits[kReachWords];
+    const bool local = (long long)ns * words <= kReachWords;
+    for (int i = threadIdx.x; i < ns; i += kBlock) {
+        s_g[i] = rs[i].group;
+        s_v[i] = src[i];
+        s_l[i] = lab[src[i]];
+        s_other[i] = 0u;
+    }
+    if (local)
+        for (int i = threadIdx.x; i < ns * words; i += kBlock) s_bits[i] = 0u;
+    __syncthreads();
+    for (long long v = (long long)blockIdx.x * kBlock + threadIdx.x; v < n; v += (long long)gridDim.x * kBlock) {
+        int32_t g = comp[v];
+        const int32_t l = lab[v];
+        if (g >= 0) g = comp[g];
+        if (g >= 0) continue;  // no source in this component
+        g = ~g;
+        const unsigned int bit = 1u << (l & 31);
+        const long long at = (long long)g * words + (l >> 5);
+        if (local) {
+            if (!(s_bits[at] & bit)) atomicOr(&s_bits[at], bit);
+        } else if (!(__hip_atomic_load(&bits[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit)) {
+            atomicOr(&bits[at], bit);
+        }
+        for (int i = 0; i < ns; ++i)
+            if (s_g[i] == g && s_l[i] == l && s_v[i] != (int32_t)v) s_other[i] = 1u;
+    }
+    __syncthreads();
+    if (local)
+        for (int i = threadIdx.x; i < ns * words; i += kBlock)
+            if (s_bits[i]) atomicOr(&bits[i], s_bits[i]);
+    for (int i = threadIdx.x; i < ns; i += kBlock)
+        if (s_other[i]) atomicOr(&rs[i].other, 1u);
+}
+
+// counts[i] (in the place of rs[i]) = the bits of source i's component, less
+// its own community's when no other member has it (one wavefront per source).
+__global__ __launch_bounds__(kBlock) void k_reach_counts(const unsigned int *bits, int ns, int words,
+                                                         ReachSource *rs) {
+    const int i = (int)blockIdx.x * (kBlock / 64) + (int)(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (i >= ns) return;
+    const ReachSource s = rs[i];
+    int c = 0;
+    for (int w = lane; w < words; w += 64) c += __popc(bits[(long long)s.group * words + w]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+    if (lane == 0) ((long long *)rs)[i] = (long long)c - (s.other ? 0 : 1);
 }
 
 template <typename OffT>
-static rs_status components_t(rs_graph *g, int32_t *comp, unsigned int *d_changed, unsigned int *h_changed) {
+static void components_t(rs_graph *g, int32_t *comp, unsigned int *bits, long long n_bits) {
     DeviceGraph &D = g->d;
     const int grid = grid_for(D.n, kBlock, 8192);
-    hipLaunchKernelGGL(k_cc_init, dim3(grid), dim3(kBlock), 0, g->stream, comp, (long long)D.n);
-    // rounds go in groups of four between host checks; the flag tells
-    // whether the group's last round hooked anything (rounds after
-    // convergence change nothing)
-    for (int it = 0; it < 512; it += 4) {
-        for (int q = 0; q < 4; ++q) {
-            hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, g->stream, d_changed, 1ll);
-            hipLaunchKernelGGL(k_cc_hook<OffT>, dim3(grid), dim3(kBlock), 0, g->stream, (const OffT *)D.off, D.deg,
-                               D.col, comp, (long long)D.n, d_changed);
-            hipLaunchKernelGGL(k_cc_jump, dim3(grid), dim3(kBlock), 0, g->stream, comp, (long long)D.n);
-        }
-        hipError_t e = hipMemcpyAsync(h_changed, d_changed, sizeof(unsigned int), hipMemcpyDeviceToHost, g->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
-        if (e != hipSuccess) return hip_fail(e, "components");
-        if (*h_changed == 0u) return RS_OK;
+    hipLaunchKernelGGL(k_cc_init<OffT>, dim3(grid), dim3(kBlock), 0, g->stream, (const OffT *)D.off, D.deg, D.col,
+                       comp, (long long)D.n, bits, n_bits);
+    hipLaunchKernelGGL(k_cc_flatten, dim3(grid), dim3(kBlock), 0, g->stream, comp, (long long)D.n);
+    for (int i = 0; i <= kCcRounds; ++i) {
+        if (i < kCcRounds)
+            hipLaunchKernelGGL((k_cc_hook<false, OffT>), dim3(grid), dim3(kBlock), 0, g->stream, (const OffT *)D.off,
+                               D.deg, D.col, comp, (long long)D.n);
+        else
+            hipLaunchKernelGGL((k_cc_hook<true, OffT>), dim3(grid), dim3(kBlock), 0, g->stream, (const OffT *)D.off,
+                               D.deg, D.col, comp, (long long)D.n);
+        hipLaunchKernelGGL(k_cc_flatten, dim3(grid), dim3(kBlock), 0, g->stream, comp, (long long)D.n);
     }
-    return fail(RS_ERR_STATE, "components did not converge");
 }
 
 rs_status launch_reach(rs_graph *g, const int32_t *d_src, int ns, int32_t *comp, unsigned int *bits, int words,
-                       unsigned int *d_changed, unsigned int *h_changed) {
+                       long long *d_counts) {
     DeviceGraph &D = g->d;
-    rs_status st = D.off64 ? components_t<long long>(g, comp, d_changed, h_changed)
-                           : components_t<int32_t>(g, comp, d_changed, h_changed);
-    if (st != RS_OK) return st;
-    const int grid = grid_for(D.n, kBlock, 8192);
-    hipLaunchKernelGGL(k_zero_u32, dim3(grid_for((long long)ns * words, kBlock, 1024)), dim3(kBlock), 0, g->stream,
-                       bits, (long long)ns * words);
-    hipLaunchKernelGGL(k_reach_bits, dim3(grid), dim3(kBlock), 0, g->stream, comp, D.lab, (long long)D.n, d_src, ns,
-                       words, bits);
+    if (D.off64)
+        components_t<long long>(g, comp, bits, (long long)ns * words);
+    else
+        components_t<int32_t>(g, comp, bits, (long long)ns * words);
+    ReachSource *rs = (ReachSource *)d_counts;
+    hipLaunchKernelGGL(k_reach_groups, dim3(1), dim3(kMaxReachSources), 0, g->stream, comp, d_src, ns, rs);
+    hipLaunchKernelGGL(k_reach_bits, dim3(grid_for(D.n, 2 * kBlock, 1024)), dim3(kBlock), 0, g->stream, comp, D.lab,
+                       (long long)D.n, d_src, ns, words, rs, bits);
+    hipLaunchKernelGGL(k_reach_counts, dim3((ns + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0, g->stream,
+                       bits, ns, words, rs);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? RS_OK : hip_fail(e, "reach launch");
 }
@@ -4339,27 +4499,6 @@ rs_status static_scratch(int device, void **out) {
     }
     *out = g_scratch_ptr[device];
     return RS_OK;
-}
-
-// counts[i] = the bits set in source i's community bitmap (one wavefront per
-// source).
-__global__ __launch_bounds__(kBlock) void k_reach_counts(const unsigned int *bits, int ns, int words,
-                                                         long long *counts) {
-    const int i = (int)blockIdx.x * (kBlock / 64) + (int)(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (i >= ns) return;
-    long long c = 0;
-    for (int w = lane; w < words; w += 64) c += __popc(bits[(long long)i * words + w]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-    if (lane == 0) counts[i] = c;
-}
-
-rs_status launch_reach_counts(rs_graph *g, const unsigned int *bits, int ns, int words, long long *d_counts) {
-    hipLaunchKernelGGL(k_reach_counts, dim3((ns + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0, g->stream,
-                       bits, ns, words, d_counts);
-    const hipError_t e = hipGetLastError();
-    return e == hipSuccess ? RS_OK : hip_fail(e, "reach counts launch");
 }
 
 }  // namespace rs

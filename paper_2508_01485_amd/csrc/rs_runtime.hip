@@ -100,10 +100,10 @@ static void release(rs_graph *g) {
     if (g->rem_cnt_host) (void)hipHostFree(g->rem_cnt_host);
     if (g->rem_ev) (void)hipEventDestroy(g->rem_ev);
     g->rem_ev = nullptr;
-    if (g->reach_hflag) (void)hipHostFree(g->reach_hflag);
-    g->reach_hflag = nullptr;
-    g->reach_comp = g->reach_src = nullptr;
-    g->reach_bits = g->reach_flag = nullptr;
+    if (g->reach_host) (void)hipHostFree(g->reach_host);
+    g->reach_host = g->reach_cnt = nullptr;
+    g->reach_comp = nullptr;
+    g->reach_bits = nullptr;
     g->rem_buf = g->rem_host = nullptr;
     g->rem_cnt_host = nullptr;
     g->rem_cap = g->rem_host_cap = 0;
@@ -1235,53 +1235,44 @@ rs_status rs_reachable_communities(rs_graph *g, int64_t n_sources, const int32_t
         return fail(RS_ERR_ARG, "n_sources must be 0.." + std::to_string(kMaxReachSources));
     if (n_sources > 0 && (!sources || !counts)) return fail(RS_ERR_ARG, "sources or counts is NULL");
     const int64_t n = g->d.n;
-    std::vector<int32_t> src((size_t)n_sources);
-    for (int64_t i = 0; i < n_sources; ++i) {
+    for (int64_t i = 0; i < n_sources; ++i)
         if (sources[i] < 0 || sources[i] >= n) return fail(RS_ERR_RANGE, "source id out of range");
-        src[i] = g->h_old2new[sources[i]];
-    }
     if (n_sources == 0) return RS_OK;
     const int words = std::max(1, (int)((g->d.k + 31) / 32));
-    const size_t nb = 4 * (size_t)n_sources * words;
     // buffers kept by the handle from the first call (sized for the largest
     // source count, 1,024)
     hipError_t e = hipSuccess;
+    const size_t cap = 12 * (size_t)kMaxReachSources;  // counts and sources
     if (!g->reach_comp) {
-        const size_t cap_bits = 4 * (size_t)kMaxReachSources * words;
         e = dev_alloc(g, (void **)&g->reach_comp, 4 * (size_t)std::max<int64_t>(n, 1));
-        if (e == hipSuccess) e = dev_alloc(g, (void **)&g->reach_src, 4 * (size_t)kMaxReachSources);
-        if (e == hipSuccess) e = dev_alloc(g, (void **)&g->reach_bits, cap_bits);
-        if (e == hipSuccess) e = dev_alloc(g, (void **)&g->reach_flag, sizeof(unsigned int));
-        if (e == hipSuccess) e = hipHostMalloc((void **)&g->reach_hflag, sizeof(unsigned int), hipHostMallocDefault);
+        if (e == hipSuccess) e = dev_alloc(g, (void **)&g->reach_bits, 4 * (size_t)kMaxReachSources * words);
+        if (e == hipSuccess) e = dev_alloc(g, (void **)&g->reach_cnt, cap);
+        if (e == hipSuccess && !g->reach_host) e = hipHostMalloc((void **)&g->reach_host, cap, hipHostMallocDefault);
         if (e != hipSuccess) {
             g->reach_comp = nullptr;  // (device buffers stay tracked and are freed with the handle)
             return hip_fail(e, "reach buffers");
         }
     }
-    e = hipMemcpyAsync(g->reach_src, src.data(), 4 * (size_t)n_sources, hipMemcpyHostToDevice, g->stream);
+    int32_t *src = (int32_t *)(g->reach_host + kMaxReachSources);
+    int32_t *d_src = (int32_t *)(g->reach_cnt + kMaxReachSources);
+    for (int64_t i = 0; i < n_sources; ++i) src[i] = g->h_old2new[sources[i]];
+    e = hipMemcpyAsync(d_src, src, 4 * (size_t)n_sources, hipMemcpyHostToDevice, g->stream);
     rs_status st = e == hipSuccess ? RS_OK : hip_fail(e, "reach upload");
-    if (st == RS_OK)
-        st = launch_reach(g, g->reach_src, (int)n_sources, g->reach_comp, g->reach_bits, words, g->reach_flag,
-                          g->reach_hflag);
-    std::vector<unsigned int> hb;
+    if (st == RS_OK) st = launch_reach(g, d_src, (int)n_sources, g->reach_comp, g->reach_bits, words, g->reach_cnt);
     if (st == RS_OK) {
-        hb.resize(nb / 4);
-        e = hipMemcpyAsync(hb.data(), g->reach_bits, nb, hipMemcpyDeviceToHost, g->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
+        e = hipMemcpyAsync(g->reach_host, g->reach_cnt, 8 * (size_t)n_sources, hipMemcpyDeviceToHost, g->stream);
         if (e != hipSuccess) st = hip_fail(e, "reach copy");
     }
+    e = hipStreamSynchronize(g->stream);  // (on an error too: the upload reads the pinned sources)
+    if (st == RS_OK && e != hipSuccess) st = hip_fail(e, "reach copy");
     if (st == RS_OK)
-        for (int64_t i = 0; i < n_sources; ++i) {
-            int64_t c = 0;
-            for (int w = 0; w < words; ++w) c += __builtin_popcount(hb[(size_t)i * words + w]);
-            counts[i] = c;
-        }
+        for (int64_t i = 0; i < n_sources; ++i) counts[i] = g->reach_host[i];
     return st;
 }
 
 // Scratch layout of rs_reachable_communities_static (offsets from the
-// device's static array, each 256-byte aligned): the hook flag, the counts,
-// the sources, the community bitmaps, the component labels.
+// device's static array, each 256-byte aligned): the counts, the sources, the
+// community bitmaps, the component labels.
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 rs_status rs_reachable_communities_static(rs_graph *g, int64_t n_sources, const int32_t *sources, int64_t *counts) {
@@ -1310,16 +1301,13 @@ rs_status rs_reachable_communities_static(rs_graph *g, int64_t n_sources, const 
     rs_status st = static_scratch(g->device, &base);
     if (st != RS_OK) return st;
     char *b = (char *)base;
-    unsigned int *d_flag = (unsigned int *)b;
     long long *d_cnt = (long long *)(b + o_cnt);
     int32_t *d_src = (int32_t *)(b + o_src);
     unsigned int *d_bits = (unsigned int *)(b + o_bits);
     int32_t *d_comp = (int32_t *)(b + o_comp);
     hipError_t e = hipMemcpyAsync(d_src, src, 4 * (size_t)n_sources, hipMemcpyHostToDevice, g->stream);
     if (e != hipSuccess) return hip_fail(e, "reach upload");
-    unsigned int h_flag = 0;  // written by the component rounds' flag copies
-    st = launch_reach(g, d_src, (int)n_sources, d_comp, d_bits, words, d_flag, &h_flag);
-    if (st == RS_OK) st = launch_reach_counts(g, d_bits, (int)n_sources, words, d_cnt);
+    st = launch_reach(g, d_src, (int)n_sources, d_comp, d_bits, words, d_cnt);
     if (st == RS_OK) {
         e = hipMemcpyAsync(counts, d_cnt, 8 * (size_t)n_sources, hipMemcpyDeviceToHost, g->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
