@@ -732,8 +732,7 @@ def main():
     torch.cuda.synchronize()
     t_total = time.perf_counter() - t_start
     # per-kernel durations: the same steps again with HIP events recorded by
-    # the library around every launch on the graph's stream (eager launches;
-    # the timed steps above replay captured HIP graphs)
+    # the library around every launch on the graph's stream
     rs.rs_set_timing(h, True)
     rs.rs_read_timings(h)  # reset
     for _ in range(args.steps):

@@ -89,7 +89,6 @@ static void dev_free(rs_graph *g, void **p) {
 static void release(rs_graph *g) {
     if (!g) return;
     if (g->stream) (void)hipStreamSynchronize(g->stream);
-    release_replays(g);
     for (auto &a : g->allocations) (void)hipFree(a.first);
     g->allocations.clear();
     if (g->hpin) (void)hipHostFree(g->hpin);
@@ -735,7 +734,6 @@ rs_status load_prebuilt(Prebuilt *P, void *hip_stream, rs_graph **out) {
     rs_graph *g = new (std::nothrow) rs_graph();
     if (!g) return fail(RS_ERR_NOMEM, "handle allocation failed");
     g->stream = (hipStream_t)hip_stream;
-    if (const char *gv = std::getenv("RS_GRAPHS")) g->graphs_off = gv[0] == '0';
     hipError_t e = hipGetDevice(&g->device);
     rs_status st = e == hipSuccess ? RS_OK : hip_fail(e, "hipGetDevice");
     if (st == RS_OK && !g->stream) {
@@ -812,8 +810,8 @@ static Tiling to_tiling(const rs_tiling *t) {
 // Re-cut the schedule of a resident graph for the tiling T.  The cut needs
 // each vertex's row capacity and load-time foreign degree, which the device
 // keeps as the capacity layout and the pair-slot offsets; the tiles are cut
-// on the host and the schedule's arrays replaced.  Captured replays are
-// dropped (their grids change), and the graph must be scored again.
+// on the host and the schedule's arrays replaced, and the graph must be scored
+// again.
 static rs_status retile(rs_graph *g, const Tiling &T) {
     DeviceGraph &D = g->d;
     const int64_t n = D.n;
@@ -844,7 +842,6 @@ static rs_status retile(rs_graph *g, const Tiling &T) {
     } catch (const std::bad_alloc &) {
         return fail(RS_ERR_NOMEM, "host allocation failed while cutting tiles");
     }
-    release_replays(g);
     rs_status st = upload_tiles(g, X);
     if (st == RS_OK && g->n_graphs > 0) {  // a batch's row blocks of each graph
         dev_free(g, (void **)&D.gblk_off);
@@ -905,7 +902,6 @@ static rs_status load_graph(const rs_csr *csr, void *hip_stream, uint32_t flags,
     if (!g) return fail(RS_ERR_NOMEM, "handle allocation failed");
     g->stream = (hipStream_t)hip_stream;  // NULL: created after validation
     g->wide_offsets = (flags & RS_LOAD_WIDE_OFFSETS) != 0;
-    if (const char *gv = std::getenv("RS_GRAPHS")) g->graphs_off = gv[0] == '0';
     if (vstart) {
         g->n_graphs = n_graphs;
         g->h_vstart.assign(vstart, vstart + n_graphs + 1);
@@ -1353,7 +1349,7 @@ rs_status rs_autotune(rs_graph *g, int32_t n_cand, const rs_tiling *cand, int32_
     int32_t b = -1;
     for (int32_t i = 0; i < n_cand && st == RS_OK; ++i) {
         st = retile(g, to_tiling(&cand[i]));
-        if (st == RS_OK) st = launch_score_pass(g);  // warm-up (and the replay's capture)
+        if (st == RS_OK) st = launch_score_pass(g);  // warm-up
         if (st != RS_OK) break;
         e = hipEventRecord(e0, g->stream);
         for (int32_t r = 0; r < reps && st == RS_OK && e == hipSuccess; ++r) st = launch_score_pass(g);
@@ -1552,7 +1548,6 @@ rs_status rs_read_timings(rs_graph *g, int32_t cap, double *ms, int64_t *launche
     if (!g) return fail(RS_ERR_ARG, "graph is NULL");
     hipError_t e = hipStreamSynchronize(g->stream);
     if (e != hipSuccess) return hip_fail(e, "timing sync");
-    drain_replays(g);
     for (auto &pe : g->timing.pending) {
         float t = 0.f;
         if (hipEventElapsedTime(&t, pe.second.first, pe.second.second) == hipSuccess) {
