@@ -251,9 +251,7 @@ struct DeviceGraph {
     unsigned long long *c_hi = nullptr;     // [segments * kBatchK] segment top-k keys (score bits)
     unsigned int *c_lo = nullptr;           // [segments * kBatchK] segment top-k keys (low words)
     int32_t *c_cnt = nullptr;               // [segments] keys per segment list
-    int32_t *bids = nullptr;                // [n_graphs * kBatchK] per-graph top-k
-    double *bscores = nullptr;
-    int64_t *bcounts = nullptr;             // [n_graphs]
+    char *bout = nullptr;                   // per-graph top-k of up to kBatchK: counts | scores | ids
     int32_t *outl = nullptr;    // [m'] out-lists: foreign neighbours of higher rank, ascending (removed: ~id)
     VMeta *meta = nullptr;      // [n] row facts of the last pass
     double *wown = nullptr, *R = nullptr;
@@ -306,6 +304,8 @@ struct rs_graph {
     std::vector<int64_t> h_vstart;
     std::vector<int32_t> h_gblk_off, h_gblk;
     int32_t n_segs = 0;       // batched top-k segments (0: the one-wavefront-per-graph form)
+    int32_t n_graphs_seg = 0; // graphs with segments
+    char *bpin = nullptr;     // pinned copy of the per-graph top-k
     int32_t *reach_comp = nullptr;                        // reachable-community buffers (first use)
     unsigned int *reach_bits = nullptr;
     long long *reach_cnt = nullptr, *reach_host = nullptr;  // counts, then sources; the same, pinned

@@ -3287,97 +3287,199 @@ __global__ __launch_bounds__(64) void k_topk_graphs(const double *R, const int32
 
 // Segmented form, for batches whose graphs have at most 64 segments of
 // kSegKeys = 64 * kTopkGU vertices: one wavefront per segment holds its keys
-// in registers (kTopkGU per lane) and takes out the segment's top-k by k
-// rounds of a wavefront maximum over the lanes' best remaining keys; then one
-// wavefront per graph merges the graph's segment lists (one per lane, staged
-// in its LDS column) by k rounds over the list heads.  The latency of a
-// graph is then that of one segment plus one merge, whatever its size.
+// in registers (kTopkGU per lane) and takes out the segment's top-k; one
+// wavefront per graph merges the lists of a graph of several segments.  Both
+// find a key that at least k keys reach, keep the keys that reach it (some k
+// to 2k of them) and place each by counting the larger ones: keys are unique.
+// (k rounds of a wavefront maximum took a segment 23 us for k = 7 and 57 us for
+// k = 20; the placing takes one pass whatever k is.)
 constexpr int kSegKeys = 64 * kTopkGU;
 static_assert(kSegKeys == kSegVerts, "a segment is one key per lane and register slot");
+constexpr int kSegCand = kTopkGU * kBatchK;  // candidates: the keys of at most k lanes
+
+__device__ __forceinline__ unsigned long long lane_u64(unsigned long long x, int l) {
+    return ((unsigned long long)(unsigned int)__builtin_amdgcn_readlane((int)(x >> 32), l) << 32) |
+           (unsigned int)__builtin_amdgcn_readlane((int)x, l);
+}
+
+// The k-th largest of the lanes' keys (f: the lane has one); false when fewer
+// than k lanes have keys.
+__device__ __forceinline__ bool lane_kth(bool f, unsigned long long h, unsigned int l, int k, unsigned long long &kh,
+                                         unsigned int &kl) {
+    const unsigned long long full = __ballot(f);
+    if (__popcll(full) < k) return false;
+    int rank = 0;
+    for (unsigned long long m = full; m; m &= m - 1ull) {
+        const int s = __ffsll((long long)m) - 1;
+        rank += key_gt(lane_u64(h, s), (unsigned int)__builtin_amdgcn_readlane((int)l, s), h, l) ? 1 : 0;
+    }
+    const unsigned long long at = __ballot(f && rank == k - 1);  // (one lane: keys are unique)
+    const int s = __ffsll((long long)at) - 1;
+    kh = lane_u64(h, s);
+    kl = (unsigned int)__builtin_amdgcn_readlane((int)l, s);
+    return true;
+}
+
+// Place the n candidates of a wavefront's list: emit(rank, hi, lo) for the k
+// largest.
+template <class Emit>
+__device__ __forceinline__ void place_candidates(const unsigned long long *ch, const unsigned int *cl, int n, int k,
+                                                 const Emit &emit) {
+    for (int i = threadIdx.x & 63; i < n; i += 64) {
+        const unsigned long long h = ch[i];
+        const unsigned int l = cl[i];
+        int rank = 0;
+        int t = 0;
+        for (; t + 8 <= n; t += 8) {  // eight reads in flight together
+            unsigned long long th[8];
+            unsigned int tl[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                th[j] = ch[t + j];
+                tl[j] = cl[t + j];
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) rank += key_gt(th[j], tl[j], h, l) ? 1 : 0;
+        }
+        for (; t < n; ++t) rank += key_gt(ch[t], cl[t], h, l) ? 1 : 0;
+        if (rank < k) emit(rank, h, l);
+    }
+}
 
 __global__ __launch_bounds__(kBlock) void k_topk_seg(const double *R, const int32_t *new2old, const uint8_t *alive,
                                                      const int64_t *vstart, const int32_t *seg_g,
                                                      const int32_t *sfirst, int n_segs, int k,
-                                                     unsigned long long *c_hi, unsigned int *c_lo, int32_t *c_cnt) {
+                                                     unsigned long long *c_hi, unsigned int *c_lo, int32_t *c_cnt,
+                                                     int32_t *ids, double *scores, int64_t *counts) {
+    __shared__ unsigned long long s_h[kBlock / 64][kSegCand];
+    __shared__ unsigned int s_l[kBlock / 64][kSegCand];
     const int seg = (int)blockIdx.x * (kBlock / 64) + (int)(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (seg >= n_segs) return;  // whole wavefronts leave; no barrier follows
+    unsigned long long *ch = s_h[threadIdx.x >> 6];
+    unsigned int *cl = s_l[threadIdx.x >> 6];
     const int gi = seg_g[seg];
+    const int sf = sfirst[gi];
+    const bool whole = sfirst[gi + 1] - sf == 1;  // the graph's only segment: its lists are the graph's
     const long long gv0 = vstart[gi];
-    const long long s0 = gv0 + (long long)(seg - sfirst[gi]) * kSegKeys;
+    const long long s0 = gv0 + (long long)(seg - sf) * kSegKeys;
     const long long s1 = min(s0 + (long long)kSegKeys, (long long)vstart[gi + 1]);
-    unsigned long long hi[kTopkGU];
-    unsigned int lo[kTopkGU];
+    unsigned long long hi[kTopkGU], bh = 0ull;
+    unsigned int lo[kTopkGU], bl = 0u;
     unsigned int valid = 0u;
+    if (s1 > s0) {
+        double sc[kTopkGU];
+        unsigned int al[kTopkGU], id[kTopkGU];
 #pragma unroll
-    for (int j = 0; j < kTopkGU; ++j) {
-        const long long v = s0 + 64 * j + lane;
-        hi[j] = 0ull;
-        lo[j] = 0u;
-        if (v < s1 && alive[v]) {
-            hi[j] = score_bits(R[v]);
-            lo[j] = 0xffffffffu - (unsigned int)(new2old[v] - (int)gv0);
-            valid |= 1u << j;
+        for (int j = 0; j < kTopkGU; ++j) {  // (slots past the segment load its last vertex, and are skipped)
+            const long long v = min(s0 + 64 * j + lane, s1 - 1);
+            sc[j] = R[v];
+            al[j] = alive[v];
+            id[j] = (unsigned int)new2old[v];
         }
-    }
-    int r = 0;
-#pragma unroll 1
-    for (; r < k; ++r) {
-        bool f = false;
-        unsigned long long bh = 0ull;
-        unsigned int bl = 0u;
-        int bj = 0;
 #pragma unroll
         for (int j = 0; j < kTopkGU; ++j) {
-            const bool ok = ((valid >> j) & 1u) != 0u;
-            const bool better = ok && (!f || key_gt(hi[j], lo[j], bh, bl));
-            bh = better ? hi[j] : bh;
-            bl = better ? lo[j] : bl;
-            bj = better ? j : bj;
-            f = f || ok;
-        }
-        int who = lane;
-        wave_max_key(f, bh, bl, who);
-        if (!f) break;  // the segment has fewer live vertices than k (uniform)
-        if (lane == who) valid &= ~(1u << bj);
-        if (lane == 0) {
-            c_hi[(long long)seg * k + r] = bh;
-            c_lo[(long long)seg * k + r] = bl;
+            hi[j] = score_bits(sc[j]);
+            lo[j] = 0xffffffffu - (id[j] - (unsigned int)gv0);
+            const bool ok = s0 + 64 * j + lane < s1 && al[j];
+            valid |= (ok ? 1u : 0u) << j;
+            if (ok && ((valid & ((1u << j) - 1u)) == 0u || key_gt(hi[j], lo[j], bh, bl))) {
+                bh = hi[j];
+                bl = lo[j];
+            }
         }
     }
-    if (lane == 0) c_cnt[seg] = r;
+    unsigned long long kh = 0ull;
+    unsigned int kl = 0u;
+    const bool bound = lane_kth(valid != 0u, bh, bl, k, kh, kl);
+    int n = 0;  // at most kTopkGU * k: a lane with a candidate is one of the k, or there are fewer than k lanes
+#pragma unroll
+    for (int j = 0; j < kTopkGU; ++j) {
+        const bool c = ((valid >> j) & 1u) && !(bound && key_gt(kh, kl, hi[j], lo[j]));
+        const unsigned long long m = __ballot(c);
+        if (c) {
+            const int i = n + __popcll(m & ((1ull << lane) - 1ull));
+            ch[i] = hi[j];
+            cl[i] = lo[j];
+        }
+        n += __popcll(m);
+    }
+    wave_sync();
+    place_candidates(ch, cl, n, k, [&](int rank, unsigned long long h, unsigned int l) {
+        if (whole) {
+            ids[(long long)gi * k + rank] = (int32_t)(0xffffffffu - l);
+            scores[(long long)gi * k + rank] = __longlong_as_double((long long)h);
+        } else {
+            c_hi[(long long)seg * k + rank] = h;
+            c_lo[(long long)seg * k + rank] = l;
+        }
+    });
+    if (lane == 0) {
+        if (whole)
+            counts[gi] = min(n, k);
+        else
+            c_cnt[seg] = min(n, k);
+    }
 }
 
+constexpr int kMergePer = 8;  // keys per lane per step, loads in flight together
 __global__ __launch_bounds__(64) void k_topk_merge(const unsigned long long *c_hi, const unsigned int *c_lo,
                                                    const int32_t *c_cnt, const int32_t *sfirst, int n_graphs, int k,
                                                    int32_t *ids, double *scores, int64_t *counts) {
-    extern __shared__ unsigned long long topk_lds[];  // [k][64] score bits, then [k][64] low keys
-    unsigned long long *lhi = topk_lds;
-    unsigned int *llo = (unsigned int *)(topk_lds + 64 * k);
+    extern __shared__ unsigned long long topk_lds[];  // [64 k] score bits, then [64 k] low keys
+    unsigned long long *ch = topk_lds;
+    unsigned int *cl = (unsigned int *)(topk_lds + 64 * k);
     const int lane = threadIdx.x;
     for (int gi = blockIdx.x; gi < n_graphs; gi += gridDim.x) {
         const int sa = sfirst[gi], ns = sfirst[gi + 1] - sa;  // ns <= 64
+        if (ns == 1) continue;  // (k_topk_seg wrote it)
         const int cnt = lane < ns ? c_cnt[sa + lane] : 0;
-        for (int r = 0; r < cnt; ++r) {
-            lhi[64 * r + lane] = c_hi[(long long)(sa + lane) * k + r];
-            llo[64 * r + lane] = c_lo[(long long)(sa + lane) * k + r];
-        }
-        int ptr = 0, taken = 0;
-        for (int r = 0; r < k; ++r) {
-            bool f = ptr < cnt;
-            unsigned long long hh = f ? lhi[64 * ptr + lane] : 0ull;
-            unsigned int hl = f ? llo[64 * ptr + lane] : 0u;
-            int who = lane;
-            wave_max_key(f, hh, hl, who);
-            if (!f) break;
-            if (lane == who) ++ptr;
-            if (lane == 0) {
-                ids[(long long)gi * k + r] = (int32_t)(0xffffffffu - hl);
-                scores[(long long)gi * k + r] = __longlong_as_double((long long)hh);
+        // a key that k keys reach: lane S l + s samples list l at depth
+        // (s + 1) step - 1, so each sample stands for step keys, and the
+        // ceil(k / step)-th largest sample is reached by k (with k lists or
+        // more, the samples are the heads)
+        unsigned long long kh = 0ull;
+        unsigned int kl = 0u;
+        const int S = ns >= k || ns < 1 ? 1 : 64 / ns, step = ns >= k ? 1 : (k + S - 1) / S;
+        const int sl = lane / S, depth = (lane % S + 1) * step - 1;
+        const int scnt = __shfl(cnt, min(sl, 63));
+        const bool sample = sl < ns && depth < scnt;
+        const long long sat = (long long)(sa + sl) * k + depth;
+        const bool bound = lane_kth(sample, sample ? c_hi[sat] : 0ull, sample ? c_lo[sat] : 0u, (k + step - 1) / step,
+                                    kh, kl);
+        int n = 0;
+        const int total = ns * k;
+        const long long base = (long long)sa * k;
+        for (int i0 = 0; i0 < total; i0 += 64 * kMergePer) {  // the graph's lists lie together
+            unsigned long long h[kMergePer];
+            unsigned int l[kMergePer];
+#pragma unroll
+            for (int j = 0; j < kMergePer; ++j) {
+                const long long i = base + min(i0 + 64 * j + lane, total - 1);
+                h[j] = c_hi[i];
+                l[j] = c_lo[i];
             }
-            ++taken;
+#pragma unroll
+            for (int j = 0; j < kMergePer; ++j) {
+                const int i = i0 + 64 * j + lane, li = min(i / k, 63);
+                const int have = __shfl(cnt, li);
+                const bool c = i < total && i - li * k < have && !(bound && key_gt(kh, kl, h[j], l[j]));
+                const unsigned long long m = __ballot(c);
+                if (c) {
+                    const int q = n + __popcll(m & ((1ull << lane) - 1ull));
+                    ch[q] = h[j];
+                    cl[q] = l[j];
+                }
+                n += __popcll(m);
+            }
         }
-        if (lane == 0) counts[gi] = taken;
+        wave_sync();
+        place_candidates(ch, cl, n, k, [&](int rank, unsigned long long h, unsigned int l) {
+            ids[(long long)gi * k + rank] = (int32_t)(0xffffffffu - l);
+            scores[(long long)gi * k + rank] = __longlong_as_double((long long)h);
+        });
+        if (lane == 0) counts[gi] = min(n, k);
+        wave_sync();  // the next graph's candidates
     }
 }
 
@@ -3389,8 +3491,9 @@ rs_status launch_topk_graphs(rs_graph *g, int64_t k, int32_t *d_ids, double *d_s
     if (g->n_segs > 0) {
         hipLaunchKernelGGL(k_topk_seg, dim3((g->n_segs + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0,
                            g->stream, D.R, D.new2old, D.alive, D.vstart, D.seg_g, D.sfirst, g->n_segs, (int)k,
-                           D.c_hi, D.c_lo, D.c_cnt);
-        hipLaunchKernelGGL(k_topk_merge, dim3(grid_for(g->n_graphs, 1, 1 << 20)), dim3(64), (size_t)(12 * 64 * k),
+                           D.c_hi, D.c_lo, D.c_cnt, d_ids, d_scores, d_counts);
+        if (g->n_segs > g->n_graphs_seg || g->n_graphs > g->n_graphs_seg) // several segments, or none
+            hipLaunchKernelGGL(k_topk_merge, dim3(grid_for(g->n_graphs, 1, 1 << 20)), dim3(64), (size_t)(12 * 64 * k),
                            g->stream, D.c_hi, D.c_lo, D.c_cnt, D.sfirst, g->n_graphs, (int)k, d_ids, d_scores,
                            d_counts);
     } else {

@@ -94,6 +94,8 @@ static void release(rs_graph *g) {
     if (g->hpin) (void)hipHostFree(g->hpin);
     g->hpin = nullptr;
     g->hpin_cap = 0;
+    if (g->bpin) (void)hipHostFree(g->bpin);
+    g->bpin = nullptr;
     if (g->rem_buf) (void)hipFree(g->rem_buf);
     if (g->rem_host) (void)hipHostFree(g->rem_host);
     if (g->rem_cnt_host) (void)hipHostFree(g->rem_cnt_host);
@@ -923,6 +925,9 @@ rs_status rs_load_graph(const rs_csr *csr, void *hip_stream, uint32_t flags, rs_
     return load_graph(csr, hip_stream, flags, nullptr, 0, out);
 }
 
+// Bytes of a batch's top-k block: counts, scores, ids.
+static size_t batch_out_bytes(size_t graphs, size_t k) { return 8 * graphs + 12 * graphs * k; }
+
 rs_status rs_load_batch(int32_t n_graphs, const int64_t *vertex_offsets, const rs_csr *csr, void *hip_stream,
                         uint32_t flags, rs_graph **out) {
     clear_error();
@@ -992,9 +997,7 @@ rs_status rs_load_batch(int32_t n_graphs, const int64_t *vertex_offsets, const r
         {(void **)&D.gblk_off, 4 * (G + 1)},
         {(void **)&D.gorder, 4 * G},
         {(void **)&D.gblk, 4 * std::max<size_t>(g->h_gblk.size(), 1)},
-        {(void **)&D.bids, 4 * G * kBatchK},
-        {(void **)&D.bscores, 8 * G * kBatchK},
-        {(void **)&D.bcounts, 8 * G},
+        {(void **)&D.bout, batch_out_bytes(G, kBatchK)},
     };
     hipError_t e = hipSuccess;
     for (auto &r : reqs) {
@@ -1014,6 +1017,7 @@ rs_status rs_load_batch(int32_t n_graphs, const int64_t *vertex_offsets, const r
             const int64_t ns = (vertex_offsets[i + 1] - vertex_offsets[i] + kSegVerts - 1) / kSegVerts;
             for (int64_t j = 0; j < ns; ++j) seg_g.push_back((int32_t)i);
             sfirst[i + 1] = (int32_t)seg_g.size();
+            if (ns > 0) ++g->n_graphs_seg;
         }
     }
     const size_t S = seg_g.size();
@@ -1062,14 +1066,31 @@ rs_status rs_topk_batch(rs_graph *g, int64_t k, int32_t *ids, double *scores, in
     if (g->n_graphs <= 0) return fail(RS_ERR_STATE, "not a batch");
     if (k < 1 || k > kBatchK) return fail(RS_ERR_ARG, "k must be 1.." + std::to_string(kBatchK));
     if (!g->scored) return fail(RS_ERR_STATE, "rs_topk_batch before rs_score");
-    rs_status st = launch_topk_graphs(g, k, g->d.bids, g->d.bscores, g->d.bcounts);
+    const size_t G = (size_t)g->n_graphs, bytes = batch_out_bytes(G, (size_t)k);
+    if (!g->bpin) {
+        const hipError_t ea = hipHostMalloc((void **)&g->bpin, batch_out_bytes(G, kBatchK), hipHostMallocDefault);
+        if (ea != hipSuccess) {
+            g->bpin = nullptr;
+            return hip_fail(ea, "pinned batched top-k buffer");
+        }
+    }
+    // one block and one copy: counts, scores, ids
+    char *o = g->d.bout;
+    const size_t o_sc = 8 * G, o_id = o_sc + 8 * G * (size_t)k;
+    rs_status st = launch_topk_graphs(g, k, (int32_t *)(o + o_id), (double *)(o + o_sc), (int64_t *)o);
     if (st != RS_OK) return st;
-    const size_t G = (size_t)g->n_graphs;
-    hipError_t e = hipMemcpyAsync(ids, g->d.bids, 4 * G * (size_t)k, hipMemcpyDeviceToHost, g->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(scores, g->d.bscores, 8 * G * (size_t)k, hipMemcpyDeviceToHost, g->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(counts, g->d.bcounts, 8 * G, hipMemcpyDeviceToHost, g->stream);
+    hipError_t e = hipMemcpyAsync(g->bpin, o, bytes, hipMemcpyDeviceToHost, g->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
-    return e == hipSuccess ? RS_OK : hip_fail(e, "batched top-k copy");
+    if (e != hipSuccess) return hip_fail(e, "batched top-k copy");
+    memcpy(counts, g->bpin, 8 * G);
+    memcpy(scores, g->bpin + o_sc, 8 * G * (size_t)k);
+    memcpy(ids, g->bpin + o_id, 4 * G * (size_t)k);
+    for (size_t i = 0; i < G; ++i)  // a graph with fewer live vertices than k
+        for (int64_t j = counts[i]; j < k; ++j) {
+            ids[i * (size_t)k + j] = 0;
+            scores[i * (size_t)k + j] = 0.0;
+        }
+    return RS_OK;
 }
 
 void rs_free_graph(rs_graph *g) {

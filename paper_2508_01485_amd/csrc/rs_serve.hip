@@ -66,9 +66,9 @@ int64_t estimate_bytes(int64_t n, int64_t nnz) {
 }
 
 // Device bytes a resident graph is charged with.  The runtime hands out device
-// memory in chunks of 2 MiB and keeps more of it for the graph's stream and
-// captured launch sequences: free device memory falls by 4.2 to 6.3 MB for
-// each graph whose own buffers hold 1.6 to 3.0 MB.
+// memory in chunks of 2 MiB and takes more for streams (25 MB and more with some
+// of the first): forty graphs whose own buffers hold 1.6 to 3.0 MB took 7.2 MB
+// of free device memory each.
 int64_t charged_bytes(const rs_graph *h) {
     constexpr int64_t kChunk = 2 << 20;
     return (h->dev_bytes + kChunk - 1) / kChunk * kChunk + kChunk;
