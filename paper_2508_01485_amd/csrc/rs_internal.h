@@ -311,6 +311,9 @@ struct rs_graph {
     long long *reach_cnt = nullptr, *reach_host = nullptr;  // counts, then sources; the same, pinned
     std::vector<std::pair<void *, size_t>> allocations;  // device buffers and their sizes
     rs::Tiling tiling;
+    // pinned staging of the readers' results (first use)
+    char *read_host = nullptr;
+    size_t read_cap = 0;
     // pinned host buffer of the common top-k path: [flag | ids | scores]
     void *hpin = nullptr;
     int64_t hpin_cap = 0;
@@ -358,6 +361,13 @@ rs_status launch_out_entries(rs_graph *g);
 rs_status launch_incremental_marks(rs_graph *g);
 rs_status launch_topk_graphs(rs_graph *g, int64_t k, int32_t *d_ids, double *d_scores, int64_t *d_counts);
 rs_status launch_gather_scores(rs_graph *g, double *d_out, int raw);
+// Device arrays in caller order; null: not wanted.
+struct VertexOut {
+    int32_t *border, *ell, *dprime;
+    long long *tI, *tII;
+    double *w_own;
+};
+rs_status launch_gather_counts(rs_graph *g, const VertexOut &out);
 // Host-built graphs kept for reloads (the request server).
 struct Prebuilt;
 rs_status prebuild_graph(const rs_csr *csr, Prebuilt **out);

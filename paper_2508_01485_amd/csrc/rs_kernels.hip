@@ -4222,6 +4222,31 @@ rs_status launch_gather_scores(rs_graph *g, double *d_out, int raw) {
     return e == hipSuccess ? RS_OK : hip_fail(e, "gather launch");
 }
 
+// The per-vertex results in caller order (any array may be null).  A vertex
+// without foreign neighbours counts no triads.
+__global__ __launch_bounds__(kBlock) void k_gather_counts(const VMeta *meta, const long long *tI, const long long *tII,
+                                                          const double *wown, const int32_t *new2old, long long n,
+                                                          VertexOut out) {
+    for (long long v = (long long)blockIdx.x * kBlock + threadIdx.x; v < n; v += (long long)gridDim.x * kBlock) {
+        const VMeta m = meta[v];
+        const int x = new2old[v], dp = m.deg - (m.q - m.p);
+        if (out.border) out.border[x] = dp > 0 ? 1 : 0;
+        if (out.ell) out.ell[x] = m.ell;
+        if (out.dprime) out.dprime[x] = dp;
+        if (out.tI) out.tI[x] = dp > 0 ? tI[v] : 0;
+        if (out.tII) out.tII[x] = dp > 0 ? tII[v] : 0;
+        if (out.w_own) out.w_own[x] = wown[v];
+    }
+}
+
+rs_status launch_gather_counts(rs_graph *g, const VertexOut &out) {
+    DeviceGraph &D = g->d;
+    hipLaunchKernelGGL(k_gather_counts, dim3(grid_for(D.n, kBlock, 8192)), dim3(kBlock), 0, g->stream, D.meta, D.tI,
+                       D.tII, D.wown, D.new2old, (long long)D.n, out);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? RS_OK : hip_fail(e, "gather launch");
+}
+
 rs_status launch_zero_u64(rs_graph *g, unsigned long long *p, int count) {
     hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, g->stream, p, count);
     const hipError_t e = hipGetLastError();
