@@ -310,6 +310,8 @@ struct rs_graph {
     unsigned int *reach_bits = nullptr;
     long long *reach_cnt = nullptr, *reach_host = nullptr;  // counts, then sources; the same, pinned
     std::vector<std::pair<void *, size_t>> allocations;  // device buffers and their sizes
+    long long n_requests = 0;                            // buffers asked for so far
+    void *tile_slab = nullptr;                           // the schedule's arrays
     rs::Tiling tiling;
     // pinned staging of the readers' results (first use)
     char *read_host = nullptr;

@@ -64,19 +64,43 @@ static void parallel_for(int64_t n, int64_t grain, F &&f) {
 
 // ------------------------------------------------------------ allocation
 // Optional fault injection for tests of the error paths: RS_FAULT_ALLOC=N
-// makes the N-th device allocation of every rs_load_graph call fail.
-static hipError_t dev_alloc(rs_graph *g, void **p, size_t bytes) {
-    *p = nullptr;
-    const long long idx = (long long)g->allocations.size() + 1;
-    if (const char *f = std::getenv("RS_FAULT_ALLOC")) {
-        if (std::atoll(f) == idx) return hipErrorOutOfMemory;
+// makes the N-th buffer asked for by every rs_load_graph call fail.
+struct DevReq {
+    void **p;
+    size_t bytes;
+};
+// Buffers that live and die together share one device allocation (its base in
+// *slab, if wanted): a graph's sixty buffers cost 75 us each to free and 20 us
+// to allocate one by one.
+static hipError_t dev_alloc_group(rs_graph *g, const DevReq *reqs, size_t n, void **slab = nullptr) {
+    constexpr size_t kAlign = 256;
+    const char *f = std::getenv("RS_FAULT_ALLOC");
+    size_t total = 0;
+    for (size_t i = 0; i < n; ++i) {
+        *reqs[i].p = nullptr;
+        total += (std::max<size_t>(reqs[i].bytes, 16) + kAlign - 1) / kAlign * kAlign;
+        if (f && std::atoll(f) == ++g->n_requests) return hipErrorOutOfMemory;
     }
-    hipError_t e = hipMalloc(p, bytes ? bytes : 16);
-    if (e == hipSuccess) {
-        g->allocations.push_back({*p, bytes ? bytes : 16});
-        g->dev_bytes += (int64_t)(bytes ? bytes : 16);
+    char *base = nullptr;
+    const hipError_t e = hipMalloc((void **)&base, total);
+    if (e != hipSuccess) return e;
+    try {
+        g->allocations.push_back({base, total});
+    } catch (...) {
+        (void)hipFree(base);
+        return hipErrorOutOfMemory;
+    }
+    g->dev_bytes += (int64_t)total;
+    if (slab) *slab = base;
+    for (size_t i = 0; i < n; ++i) {
+        *reqs[i].p = base;
+        base += (std::max<size_t>(reqs[i].bytes, 16) + kAlign - 1) / kAlign * kAlign;
     }
     return e;
+}
+static hipError_t dev_alloc(rs_graph *g, void **p, size_t bytes) {
+    const DevReq r = {p, bytes};
+    return dev_alloc_group(g, &r, 1);
 }
 
 // Free one buffer of the graph (the stream must be idle).
@@ -454,12 +478,7 @@ static rs_status build_internal(int64_t n, int64_t nnz, const OffIn *off, const 
 // the copies queued on the graph's stream.
 static rs_status upload_tiles(rs_graph *g, const HostTiles &H) {
     DeviceGraph &D = g->d;
-    void **tile_arrays[] = {(void **)&D.rtiles, (void **)&D.rhubs, (void **)&D.stiles, (void **)&D.shubs,
-                            (void **)&D.shub_first, (void **)&D.shub_chunk, (void **)&D.hub_part,
-                            (void **)&D.rflag, (void **)&D.cflag, (void **)&D.hflag, (void **)&D.rlist,
-                            (void **)&D.slist, (void **)&D.hlist, (void **)&D.part_rows, (void **)&D.wmax_part,
-                            (void **)&D.vrowb, (void **)&D.vscore, (void **)&D.hfilter, (void **)&D.sown};
-    for (void **p : tile_arrays) dev_free(g, p);
+    dev_free(g, &g->tile_slab);
     const size_t N = (size_t)std::max<int64_t>(D.n, 1);
     g->n_rtiles = (int)H.rtiles.size();
     g->n_rhubs = (int)H.rhubs.size();
@@ -474,10 +493,7 @@ static rs_status upload_tiles(rs_graph *g, const HostTiles &H) {
     const size_t nrt = std::max<size_t>(H.rtiles.size(), 1), nrh = std::max<size_t>(H.rhubs.size(), 1);
     const size_t nst = std::max<size_t>(H.stiles.size(), 1), nsh = std::max<size_t>(H.shubs.size(), 1);
     const size_t gr = (size_t)std::max(g->grid_rows, 1), gs = (size_t)std::max(g->grid_score, 1);
-    struct Req {
-        void **p;
-        size_t bytes;
-    } reqs[] = {
+    const DevReq reqs[] = {
         {(void **)&D.rtiles, sizeof(RowTile) * nrt},
         {(void **)&D.rhubs, 4 * nrh},
         {(void **)&D.stiles, sizeof(int2) * nst},
@@ -498,12 +514,9 @@ static rs_status upload_tiles(rs_graph *g, const HostTiles &H) {
         {(void **)&D.sown, (size_t)std::max<int64_t>(2 * g->n_out, 1)},
         {(void **)&D.hfilter, 4 * (size_t)kFilterWords * std::max<size_t>(H.shubs.size() - H.n_hubs_lds, 1)},
     };
-    for (auto &r : reqs) {
-        hipError_t e = dev_alloc(g, r.p, r.bytes);
-        if (e != hipSuccess) return hip_fail(e, "device allocation");
-    }
+    hipError_t e = dev_alloc_group(g, reqs, sizeof(reqs) / sizeof(reqs[0]), &g->tile_slab);
+    if (e != hipSuccess) return hip_fail(e, "device allocation");
     hipStream_t s = g->stream;
-    hipError_t e = hipSuccess;
     auto put = [&](void *dst, const void *src, size_t bytes) {
         if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
     };
@@ -531,10 +544,7 @@ static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool 
     const size_t N = (size_t)std::max<int64_t>(n, 1), Z = (size_t)std::max<int64_t>(nnz, 1);
     const size_t NX = std::max<size_t>((size_t)H.goff[n], 1);
     const size_t offb = D.off64 ? 8 : 4;
-    struct Req {
-        void **p;
-        size_t bytes;
-    } reqs[] = {
+    const DevReq reqs[] = {
         {&D.off, offb * (N + 1)},
         {(void **)&D.deg, 4 * N},
         {(void **)&D.col, 4 * Z},
@@ -581,21 +591,9 @@ static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool 
         {(void **)&D.tblk, 16 + 16 * N},
         {(void **)&D.scratch_u, 8 * 8},
     };
-    for (auto &r : reqs) {
-        hipError_t e = dev_alloc(g, r.p, r.bytes);
-        if (e != hipSuccess) return hip_fail(e, "device allocation");
-    }
     {
-        const hipError_t eh = hipHostMalloc((void **)&g->rem_cnt_host, 8 * (4 + (size_t)kIcCount), hipHostMallocDefault);
-        if (eh != hipSuccess) {
-            g->rem_cnt_host = nullptr;
-            return hip_fail(eh, "pinned counters");
-        }
-        const hipError_t ee = hipEventCreateWithFlags(&g->rem_ev, hipEventDisableTiming);
-        if (ee != hipSuccess) {
-            g->rem_ev = nullptr;
-            return hip_fail(ee, "removal event");
-        }
+        const hipError_t ea = dev_alloc_group(g, reqs, sizeof(reqs) / sizeof(reqs[0]));
+        if (ea != hipSuccess) return hip_fail(ea, "device allocation");
     }
     std::vector<int32_t> off32, deg(n);
     for (int64_t v = 0; v < n; ++v) deg[v] = (int32_t)(H.off[v + 1] - H.off[v]);
@@ -1064,23 +1062,17 @@ rs_status rs_load_batch(int32_t n_graphs, const int64_t *vertex_offsets, const r
     for (int32_t gi = 0; gi < n_graphs; ++gi)
         for (int64_t v = vertex_offsets[gi]; v < vertex_offsets[gi + 1]; ++v) vg[v] = gi;
     const size_t N = (size_t)std::max<int64_t>(n, 1), G = (size_t)n_graphs;
-    struct Req {
-        void **p;
-        size_t bytes;
-    } reqs[] = {
+    const DevReq reqs[] = {
         {(void **)&D.vstart, 8 * (G + 1)},
         {(void **)&D.vgraph, 4 * N},
         {(void **)&D.gwmax, 8 * G},
-        {(void **)&D.gblk_off, 4 * (G + 1)},
         {(void **)&D.gorder, 4 * G},
-        {(void **)&D.gblk, 4 * std::max<size_t>(g->h_gblk.size(), 1)},
         {(void **)&D.bout, batch_out_bytes(G, kBatchK)},
     };
-    hipError_t e = hipSuccess;
-    for (auto &r : reqs) {
-        e = dev_alloc(g, r.p, r.bytes);
-        if (e != hipSuccess) break;
-    }
+    hipError_t e = dev_alloc_group(g, reqs, sizeof(reqs) / sizeof(reqs[0]));
+    // (replaced when the schedule is cut again)
+    if (e == hipSuccess) e = dev_alloc(g, (void **)&D.gblk_off, 4 * (G + 1));
+    if (e == hipSuccess) e = dev_alloc(g, (void **)&D.gblk, 4 * std::max<size_t>(g->h_gblk.size(), 1));
     if (e == hipSuccess) e = hipMemcpyAsync(D.vstart, vertex_offsets, 8 * (G + 1), hipMemcpyHostToDevice, g->stream);
     if (e == hipSuccess && n) e = hipMemcpyAsync(D.vgraph, vg.data(), 4 * n, hipMemcpyHostToDevice, g->stream);
     if (e == hipSuccess)
@@ -1099,20 +1091,14 @@ rs_status rs_load_batch(int32_t n_graphs, const int64_t *vertex_offsets, const r
     }
     const size_t S = seg_g.size();
     if (e == hipSuccess && S > 0) {
-        struct Req2 {
-            void **p;
-            size_t bytes;
-        } more[] = {
+        const DevReq more[] = {
             {(void **)&D.seg_g, 4 * S},
             {(void **)&D.sfirst, 4 * (G + 1)},
             {(void **)&D.c_hi, 8 * S * kBatchK},
             {(void **)&D.c_lo, 4 * S * kBatchK},
             {(void **)&D.c_cnt, 4 * S},
         };
-        for (auto &r : more) {
-            e = dev_alloc(g, r.p, r.bytes);
-            if (e != hipSuccess) break;
-        }
+        e = dev_alloc_group(g, more, sizeof(more) / sizeof(more[0]));
         if (e == hipSuccess) e = hipMemcpyAsync(D.seg_g, seg_g.data(), 4 * S, hipMemcpyHostToDevice, g->stream);
         if (e == hipSuccess) e = hipMemcpyAsync(D.sfirst, sfirst.data(), 4 * (G + 1), hipMemcpyHostToDevice, g->stream);
         if (e == hipSuccess) g->n_segs = (int32_t)S;
@@ -1229,6 +1215,20 @@ rs_status rs_apply_removals(rs_graph *g, const rs_removals *b, rs_removal_result
     std::sort(vs.begin(), vs.end());
     vs.erase(std::unique(vs.begin(), vs.end()), vs.end());
     const int64_t m = b->n_edges, nv = (int64_t)vs.size();
+    if (!g->rem_cnt_host) {  // (a graph that never loses an edge does without)
+        const hipError_t eh = hipHostMalloc((void **)&g->rem_cnt_host, 8 * (4 + (size_t)kIcCount), hipHostMallocDefault);
+        if (eh != hipSuccess) {
+            g->rem_cnt_host = nullptr;
+            return hip_fail(eh, "pinned counters");
+        }
+    }
+    if (!g->rem_ev) {
+        const hipError_t ee = hipEventCreateWithFlags(&g->rem_ev, hipEventDisableTiming);
+        if (ee != hipSuccess) {
+            g->rem_ev = nullptr;
+            return hip_fail(ee, "removal event");
+        }
+    }
     const int64_t need = std::max<int64_t>(2 * m + nv, 1);
     // staging kept between calls: grown (never shrunk) before anything is mutated
     if (need > g->rem_cap || need > g->rem_host_cap) {
