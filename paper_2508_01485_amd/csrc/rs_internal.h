@@ -356,6 +356,24 @@ rs_status launch_remove_edges(rs_graph *g, const int32_t *d_src, const int32_t *
                               unsigned long long *d_removed);
 rs_status launch_remove_vertices(rs_graph *g, const int32_t *d_verts, int64_t nv,
                                  unsigned long long *d_removed_edges);
+// Loading on the device: the caller's CSR in device memory and scratch.
+struct LoadArgs {
+    const void *off;  // [n+1] row offsets
+    int offset_bytes;
+    const int32_t *col;  // [nnz]
+    int2 *map;           // [n] internal id and community of each caller id
+    int32_t *fgn;        // [n] foreign degree of each vertex (out)
+    unsigned int *bad;   // not zero: the rows are not those of a simple undirected graph
+    const int32_t *hubs; // internal ids of the vertices with more than load_hub_row() entries
+    int n_hubs;
+};
+int load_hub_row();
+// Fills deg, col, clab and fgn from off, new2old and lab, and checks the rows.
+rs_status launch_load_rows(rs_graph *g, const LoadArgs &L);
+// Fills fcol, oo and outl from goff and the rows; count [n] and sums
+// [prefix_blocks(n)] are scratch.
+int prefix_blocks(int64_t n);
+rs_status launch_load_slots(rs_graph *g, int32_t *count, long long *sums);
 rs_status launch_links(rs_graph *g, unsigned long long *d_run_walk);
 rs_status launch_col_labels(rs_graph *g);
 rs_status launch_slot_owners(rs_graph *g);

@@ -1968,6 +1968,369 @@ __device__ __forceinline__ void lower_n(const int32_t *const *row, const int *d,
     for (int i = 0; i < N; ++i) pos[i] = lo[i];
 }
 
+// ============================================================ load
+// A graph's device form from the caller's CSR (large graphs; the host builds
+// the small ones and those that fail a check here, to say what is wrong): the
+// host renumbers the vertices, the device checks the rows, renumbers and sorts
+// them, lists the foreign entries and orients G'.
+// n = 200,000 with 3.7 M entries: rows 410 us, hub rows 75, symmetry 201, slots
+// 34 + 66, all bound by the latency of dependent loads (5 in a row per vertex);
+// load, pass, top-k and free in 3.9 ms, 26.7 with the host's build.
+
+// Each caller id's internal id and community.
+__global__ __launch_bounds__(kBlock) void k_load_map(const int32_t *new2old, const int32_t *lab, long long n,
+                                                     int2 *map) {
+    for (long long v = (long long)blockIdx.x * kBlock + threadIdx.x; v < n; v += (long long)gridDim.x * kBlock)
+        map[new2old[v]] = make_int2((int)v, lab[v]);
+}
+
+// The rows of up to kLoadRow entries, one wavefront per row: check each entry
+// (an id in range, no self-loop, the row ascending), renumber it, and write it
+// at its rank among the row's new ids (counted: the ids are distinct, or the
+// graph is refused).  An entry in a bad row is clamped, so everything stays in
+// range; *bad tells.  Also each vertex's row length and foreign degree.
+constexpr int kLoadRow = 1024;
+template <typename OffIn, typename OffT>
+__global__ __launch_bounds__(kBlock) void k_load_rows(const OffIn *off_in, const int32_t *col_in,
+                                                      const int32_t *new2old, const int2 *map, long long n,
+                                                      const OffT *off, int32_t *col, int32_t *clab, int32_t *deg,
+                                                      int32_t *fgn, unsigned int *bad) {
+    __shared__ __align__(16) int s_id[kBlock / 64][kLoadRow];
+    int *ids = s_id[threadIdx.x >> 6];
+    const int lane = threadIdx.x & 63;
+    for (long long x = ((long long)blockIdx.x * kBlock + threadIdx.x) >> 6; x < n;
+         x += ((long long)gridDim.x * kBlock) >> 6) {
+        const int u = new2old[x];
+        const long long b = (long long)off_in[u];
+        const int d = (int)((long long)off_in[u + 1] - b);
+        if (lane == 0) deg[x] = d;
+        if (d > kLoadRow) continue;  // (k_load_hubs)
+        const int cu = map[u].y;
+        const long long o = (long long)off[x];
+        unsigned int wrong = 0u;
+        int foreign = 0;
+        if (d <= 64) {
+            int v = lane < d ? col_in[b + lane] : INT_MAX;
+            const int prev = __shfl_up(v, 1);
+            if (lane < d) {
+                wrong = (v < 0 || v >= n || v == u || (lane > 0 && prev >= v)) ? 1u : 0u;
+                v = min(max(v, 0), (int)(n - 1));
+            }
+            int2 m = make_int2(INT_MAX, cu);
+            if (lane < d) m = map[v];
+            int rank = 0;
+            for (int j = 0; j < d; ++j) rank += __builtin_amdgcn_readlane(m.x, j) < m.x ? 1 : 0;
+            if (lane < d) {
+                col[o + rank] = m.x;
+                clab[o + rank] = m.y;
+            }
+            foreign = __popcll(__ballot(m.y != cu));
+        } else {
+            for (int t = lane; t < ((d + 3) & ~3); t += 64) {
+                int id = INT_MAX;  // (padding of the last four)
+                if (t < d) {
+                    int v = col_in[b + t];
+                    if (v < 0 || v >= n || v == u || (t > 0 && col_in[b + t - 1] >= v)) wrong = 1u;
+                    id = map[min(max(v, 0), (int)(n - 1))].x;
+                }
+                ids[t] = id;
+            }
+            wave_sync();
+            for (int t0 = 0; t0 < d; t0 += 64) {
+                const int t = t0 + lane;
+                const int id = t < d ? ids[t] : INT_MAX;
+                int rank = 0;
+                for (int j = 0; j < d; j += 4) {
+                    const int4 q = *(const int4 *)&ids[j];
+                    rank += (q.x < id) + (q.y < id) + (q.z < id) + (q.w < id);
+                }
+                int c = cu;
+                if (t < d) {
+                    c = map[new2old[id]].y;
+                    col[o + rank] = id;
+                    clab[o + rank] = c;
+                }
+                foreign += __popcll(__ballot(c != cu));
+            }
+            wave_sync();  // the next row's ids
+        }
+        if (lane == 0) fgn[x] = foreign;
+        if (__any(wrong != 0u) && lane == 0) atomicOr(bad, 1u);
+    }
+}
+
+// A longer row, one workgroup each (hubs: internal ids): its new ids are set as
+// bits of a range of 2^20 ids at a time and read back in order.
+constexpr int kLoadBits = 1 << 20;
+constexpr int kLoadWords = kLoadBits / 32 / 1024;  // words per thread
+template <typename OffIn, typename OffT>
+__global__ __launch_bounds__(1024) void k_load_hubs(const OffIn *off_in, const int32_t *col_in,
+                                                    const int32_t *new2old, const int2 *map, const int32_t *lab,
+                                                    long long n, const int32_t *hubs, const OffT *off, int32_t *col,
+                                                    int32_t *clab, int32_t *fgn, unsigned int *bad) {
+    __shared__ unsigned int s_bits[kLoadBits / 32];
+    __shared__ int s_w[16], s_f;
+    const int x = hubs[blockIdx.x];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int u = new2old[x], cu = lab[x];
+    const long long b = (long long)off_in[u], o = (long long)off[x];
+    const int d = (int)((long long)off_in[u + 1] - b);
+    if (tid == 0) s_f = 0;
+    int done = 0, foreign = 0;
+    unsigned int wrong = 0u;
+    for (long long r0 = 0; r0 < n; r0 += kLoadBits) {
+        for (int i = tid; i < kLoadBits / 32; i += 1024) s_bits[i] = 0u;
+        __syncthreads();
+        for (int t = tid; t < d; t += 1024) {
+            const int v = col_in[b + t];
+            if (r0 == 0 && (v < 0 || v >= n || v == u || (t > 0 && col_in[b + t - 1] >= v))) wrong = 1u;
+            const long long id = (long long)map[min(max(v, 0), (int)(n - 1))].x - r0;
+            if (id >= 0 && id < kLoadBits) atomicOr(&s_bits[id >> 5], 1u << (id & 31));
+        }
+        __syncthreads();
+        unsigned int w[kLoadWords];
+        int cnt = 0;
+#pragma unroll
+        for (int j = 0; j < kLoadWords; ++j) {
+            w[j] = s_bits[tid * kLoadWords + j];
+            cnt += __popc(w[j]);
+        }
+        int incl = cnt;
+#pragma unroll
+        for (int q = 1; q < 64; q <<= 1) {
+            const int y = __shfl_up(incl, q);
+            if (lane >= q) incl += y;
+        }
+        if (lane == 63) s_w[wave] = incl;
+        __syncthreads();
+        int at = done + incl - cnt;
+        for (int q = 0; q < 16; ++q) {
+            if (q < wave) at += s_w[q];
+            done += s_w[q];
+        }
+#pragma unroll
+        for (int j = 0; j < kLoadWords; ++j) {
+            for (unsigned int m = w[j]; m; m &= m - 1u) {
+                const int id = (int)(r0 + 32ll * (tid * kLoadWords + j) + (__ffs((int)m) - 1));
+                const int c = lab[id];
+                col[o + at] = id;
+                clab[o + at] = c;
+                foreign += c != cu ? 1 : 0;
+                ++at;
+            }
+        }
+        __syncthreads();  // s_bits, s_w
+    }
+    // (a bad row may hold an id twice: the places left take its own id)
+    for (int t = done + tid; t < d; t += 1024) {
+        col[o + t] = x;
+        clab[o + t] = cu;
+    }
+    if (foreign) atomicAdd(&s_f, foreign);
+    if (wrong || (tid == 0 && done != d)) atomicOr(bad, 1u);
+    __syncthreads();
+    if (tid == 0) fgn[x] = s_f;
+}
+
+// Symmetry: every entry (x, y) has its (y, x).  A wavefront takes the rows of 64
+// vertices, flattened over its lanes.  Not after a bad row (bit 0 of *bad, set
+// by the launches before this one): places of its ids may be unwritten.
+template <typename OffT>
+__global__ __launch_bounds__(kBlock) void k_load_symmetric(const OffT *off, const int32_t *col, long long n,
+                                                           unsigned int *bad) {
+    __shared__ long long s_end[kBlock / 64][64];
+    long long *end = s_end[threadIdx.x >> 6];
+    const int lane = threadIdx.x & 63;
+    if (*bad & 1u) return;
+    for (long long v0 = (long long)blockIdx.x * kBlock + (threadIdx.x & ~63); v0 < n;
+         v0 += (long long)gridDim.x * kBlock) {
+        const long long first = (long long)off[v0], last = (long long)off[min(v0 + 64, n)];
+        end[lane] = (long long)off[min(v0 + lane + 1, n)];
+        wave_sync();
+        unsigned int wrong = 0u;
+        for (long long e = first + lane; e < last; e += 64) {
+            int lo = 0, hi = 63;  // the row: the first whose end is beyond e
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (end[mid] > e)
+                    hi = mid;
+                else
+                    lo = mid + 1;
+            }
+            const int x = (int)(v0 + lo);
+            const int y = col[e];
+            const long long yb = (long long)off[y];
+            const int32_t *row[1] = {col + yb};
+            const int d[1] = {(int)((long long)off[y + 1] - yb)};
+            const int key[1] = {x};
+            int p[1];
+            lower_n<1, false>(row, d, key, p);
+            if (p[0] >= d[0] || row[0][p[0]] != x) wrong = 1u;
+        }
+        if (__any(wrong != 0u) && lane == 0) atomicOr(bad, 2u);
+        wave_sync();  // the next rows' ends
+    }
+}
+
+// The foreign entries into their slots, in row order, and the number of those
+// of higher rank (foreign degree, id) per vertex (count: out-list lengths), or,
+// with oo, those entries into the out-lists.  One wavefront per row.
+template <typename OffT>
+__global__ __launch_bounds__(kBlock) void k_load_slots(const OffT *off, const int32_t *col, const int32_t *clab,
+                                                       const int32_t *lab, const int32_t *goff, long long n,
+                                                       int32_t *fcol, int32_t *count, const int64_t *oo,
+                                                       int32_t *outl) {
+    const int lane = threadIdx.x & 63;
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    for (long long x = ((long long)blockIdx.x * kBlock + threadIdx.x) >> 6; x < n;
+         x += ((long long)gridDim.x * kBlock) >> 6) {
+        const int go = goff[x], f = goff[x + 1] - go;
+        int higher = 0;
+        if (!oo) {
+            const long long b = (long long)off[x], e = (long long)off[x + 1];
+            const int cx = lab[x];
+            int at = go;
+            for (long long j0 = b; j0 < e && at < go + f; j0 += 64) {
+                const long long j = j0 + lane;
+                const bool in = j < e && clab[j < e ? j : b] != cx;
+                const int y = in ? col[j] : 0;
+                const int g = in ? goff[y + 1] - goff[y] : 0;
+                const unsigned long long m = __ballot(in);
+                if (in) fcol[at + __popcll(m & lt)] = y;
+                at += __popcll(m);
+                higher += __popcll(__ballot(in && (g > f || (g == f && y > (int)x))));
+            }
+            if (lane == 0) count[x] = higher;
+        } else {
+            for (int j0 = 0; j0 < f; j0 += 64) {
+                const bool in = j0 + lane < f;
+                const int y = in ? fcol[go + j0 + lane] : 0;
+                const int g = in ? goff[y + 1] - goff[y] : 0;
+                const bool up = in && (g > f || (g == f && y > (int)x));
+                const unsigned long long m = __ballot(up);
+                if (up) outl[oo[x] + higher + __popcll(m & lt)] = y;
+                higher += __popcll(m);
+            }
+        }
+    }
+}
+
+// Exclusive prefix of n counts into out[0..n], in blocks of kPrefixBlock: the
+// blocks' sums, their prefix by one workgroup, and each block's own.
+constexpr int kPrefixBlock = 2048;
+int prefix_blocks(int64_t n) { return (int)((n + kPrefixBlock - 1) / kPrefixBlock); }
+
+__device__ __forceinline__ long long block_prefix(long long x, long long *ws, int waves, long long &total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    long long incl = x;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const long long y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
+    }
+    if (lane == 63) ws[wave] = incl;
+    __syncthreads();
+    long long before = 0;
+    total = 0;
+    for (int w = 0; w < waves; ++w) {
+        if (w < wave) before += ws[w];
+        total += ws[w];
+    }
+    __syncthreads();
+    return before + incl - x;
+}
+
+__global__ __launch_bounds__(kBlock) void k_prefix_sums(const int32_t *count, long long n, long long *sums) {
+    __shared__ long long ws[kBlock / 64];
+    long long s = 0, total;
+    for (int j = 0; j < kPrefixBlock / kBlock; ++j) {
+        const long long i = (long long)blockIdx.x * kPrefixBlock + j * kBlock + threadIdx.x;
+        s += i < n ? count[i] : 0;
+    }
+    (void)block_prefix(s, ws, kBlock / 64, total);
+    if (threadIdx.x == 0) sums[blockIdx.x] = total;
+}
+
+__global__ __launch_bounds__(1024) void k_prefix_top(long long *sums, int blocks) {
+    __shared__ long long ws[16];
+    long long base = 0;
+    for (int i0 = 0; i0 < blocks; i0 += 1024) {
+        const int i = i0 + (int)threadIdx.x;
+        const long long x = i < blocks ? sums[i] : 0;
+        long long total;
+        const long long p = block_prefix(x, ws, 16, total);
+        if (i < blocks) sums[i] = base + p;
+        base += total;
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_prefix_out(const int32_t *count, long long n, const long long *sums,
+                                                       int64_t *out) {
+    __shared__ long long ws[kBlock / 64];
+    long long base = sums[blockIdx.x];
+    for (int j = 0; j < kPrefixBlock / kBlock; ++j) {
+        const long long i = (long long)blockIdx.x * kPrefixBlock + j * kBlock + threadIdx.x;
+        const long long x = i < n ? count[i] : 0;
+        long long total;
+        const long long p = block_prefix(x, ws, kBlock / 64, total);
+        if (i < n) out[i] = base + p;
+        if (i == n - 1) out[n] = base + p + x;
+        base += total;
+    }
+}
+
+template <typename OffIn, typename OffT>
+static void load_rows_t(rs_graph *g, const LoadArgs &L) {
+    DeviceGraph &D = g->d;
+    const long long n = D.n;
+    hipLaunchKernelGGL(k_load_map, dim3(grid_for(n, kBlock, 8192)), dim3(kBlock), 0, g->stream, D.new2old, D.lab, n,
+                       L.map);
+    hipLaunchKernelGGL((k_load_rows<OffIn, OffT>), dim3(grid_for(n, kBlock / 64, 16384)), dim3(kBlock), 0, g->stream,
+                       (const OffIn *)L.off, L.col, D.new2old, L.map, n, (const OffT *)D.off, D.col, D.clab, D.deg,
+                       L.fgn, L.bad);
+    if (L.n_hubs > 0)
+        hipLaunchKernelGGL((k_load_hubs<OffIn, OffT>), dim3(L.n_hubs), dim3(1024), 0, g->stream, (const OffIn *)L.off,
+                           L.col, D.new2old, L.map, D.lab, n, L.hubs, (const OffT *)D.off, D.col, D.clab, L.fgn,
+                           L.bad);
+    hipLaunchKernelGGL(k_load_symmetric<OffT>, dim3(grid_for(n, kBlock, 8192)), dim3(kBlock), 0, g->stream,
+                       (const OffT *)D.off, D.col, n, L.bad);
+}
+
+int load_hub_row() { return kLoadRow; }
+
+rs_status launch_load_rows(rs_graph *g, const LoadArgs &L) {
+    const bool w = L.offset_bytes == 8;
+    if (g->d.off64)
+        w ? load_rows_t<int64_t, long long>(g, L) : load_rows_t<int32_t, long long>(g, L);
+    else
+        w ? load_rows_t<int64_t, int32_t>(g, L) : load_rows_t<int32_t, int32_t>(g, L);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? RS_OK : hip_fail(e, "row load launch");
+}
+
+template <typename OffT>
+static void load_slots_t(rs_graph *g, int32_t *count, long long *sums) {
+    DeviceGraph &D = g->d;
+    const long long n = D.n;
+    const int grid = grid_for(n, kBlock / 64, 16384), nb = prefix_blocks(n);
+    hipLaunchKernelGGL(k_load_slots<OffT>, dim3(grid), dim3(kBlock), 0, g->stream, (const OffT *)D.off, D.col, D.clab,
+                       D.lab, D.goff, n, D.fcol, count, (const int64_t *)nullptr, (int32_t *)nullptr);
+    hipLaunchKernelGGL(k_prefix_sums, dim3(nb), dim3(kBlock), 0, g->stream, count, n, sums);
+    hipLaunchKernelGGL(k_prefix_top, dim3(1), dim3(1024), 0, g->stream, sums, nb);
+    hipLaunchKernelGGL(k_prefix_out, dim3(nb), dim3(kBlock), 0, g->stream, count, n, sums, D.oo);
+    hipLaunchKernelGGL(k_load_slots<OffT>, dim3(grid), dim3(kBlock), 0, g->stream, (const OffT *)D.off, D.col, D.clab,
+                       D.lab, D.goff, n, D.fcol, (int32_t *)nullptr, (const int64_t *)D.oo, D.outl);
+}
+
+rs_status launch_load_slots(rs_graph *g, int32_t *count, long long *sums) {
+    if (g->d.off64)
+        load_slots_t<long long>(g, count, sums);
+    else
+        load_slots_t<int32_t>(g, count, sums);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? RS_OK : hip_fail(e, "slot load launch");
+}
+
 template <typename OffT>
 struct LinkArgs {
     const OffT *off;

@@ -471,7 +471,6 @@ static rs_status build_internal(int64_t n, int64_t nnz, const OffIn *off, const 
     return RS_OK;
 }
 
-// keep: H stays intact for later uploads (its host maps are copied, not moved)
 // Allocate and fill the schedule's device arrays, freeing any earlier
 // ones: tiles and hubs, the per-block partials, the incremental re-score's
 // unit flags and lists, and each vertex's row block and score unit.  Leaves
@@ -534,15 +533,15 @@ static rs_status upload_tiles(rs_graph *g, const HostTiles &H) {
     return e == hipSuccess ? launch_slot_owners(g) : hip_fail(e, "schedule upload");
 }
 
-static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool keep = false) {
+// The graph's device arrays: those sized by its vertices and entries, cleared
+// where a pass expects it, and those sized by its slots (2 n_out).
+static rs_status alloc_vertices(rs_graph *g, int64_t n, int64_t nnz, int64_t k) {
     DeviceGraph &D = g->d;
     D.n = n;
     D.nnz = nnz;
-    D.k = (int32_t)H.comm2orig.size();
+    D.k = (int32_t)k;
     D.off64 = nnz > (int64_t)INT32_MAX || g->wide_offsets;
-    g->n_out = (int64_t)H.outl.size();
     const size_t N = (size_t)std::max<int64_t>(n, 1), Z = (size_t)std::max<int64_t>(nnz, 1);
-    const size_t NX = std::max<size_t>((size_t)H.goff[n], 1);
     const size_t offb = D.off64 ? 8 : 4;
     const DevReq reqs[] = {
         {&D.off, offb * (N + 1)},
@@ -554,11 +553,7 @@ static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool 
         {(void **)&D.alive, N},
         {(void **)&D.oo, 8 * (N + 1)},
         {(void **)&D.goff, 4 * (N + 1)},
-        {(void **)&D.fcol, 4 * NX},
-        {(void **)&D.prec, sizeof(PairRec) * NX},
-        {(void **)&D.val2, 8 * NX},
-        {(void **)&D.plink, sizeof(PairLink) * NX},
-        {(void **)&D.cstart, 4 * H.cstart.size()},
+        {(void **)&D.cstart, 4 * ((size_t)D.k + 1)},
         {(void **)&D.wpart, 8 * (size_t)kWorkBlocks},
         {(void **)&D.raw, 8 * N},
         {(void **)&D.vmark, 4 * N},
@@ -570,8 +565,6 @@ static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool 
         {(void **)&D.wblk, 8 * 64},
         {(void **)&D.wticket, 8},
         {(void **)&g->rem_cnt, 8 * 4},
-        {(void **)&D.outl, 4 * std::max<size_t>(H.outl.size(), 1)},
-        {(void **)&D.oe, sizeof(OutEnt) * std::max<size_t>(H.outl.size(), 1)},
         {(void **)&D.meta, sizeof(VMeta) * N},
         {(void **)&D.wown, 8 * N},
         {(void **)&D.av, 8 * N},
@@ -591,55 +584,60 @@ static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool 
         {(void **)&D.tblk, 16 + 16 * N},
         {(void **)&D.scratch_u, 8 * 8},
     };
-    {
-        const hipError_t ea = dev_alloc_group(g, reqs, sizeof(reqs) / sizeof(reqs[0]));
-        if (ea != hipSuccess) return hip_fail(ea, "device allocation");
-    }
-    std::vector<int32_t> off32, deg(n);
-    for (int64_t v = 0; v < n; ++v) deg[v] = (int32_t)(H.off[v + 1] - H.off[v]);
-    const void *offsrc = H.off.data();
-    if (!D.off64) {
-        off32.resize(n + 1);
-        for (int64_t v = 0; v <= n; ++v) off32[v] = (int32_t)H.off[v];
-        offsrc = off32.data();
-    }
+    hipError_t e = dev_alloc_group(g, reqs, sizeof(reqs) / sizeof(reqs[0]));
+    if (e != hipSuccess) return hip_fail(e, "device allocation");
     hipStream_t s = g->stream;
-    hipError_t e = hipMemcpyAsync(D.off, offsrc, offb * (n + 1), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && n) e = hipMemcpyAsync(D.deg, deg.data(), 4 * n, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && nnz) e = hipMemcpyAsync(D.col, H.col.data(), 4 * nnz, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && n) e = hipMemcpyAsync(D.lab, H.lab.data(), 4 * n, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && n) e = hipMemcpyAsync(D.new2old, H.new2old.data(), 4 * n, hipMemcpyHostToDevice, s);
-    auto put = [&](void *dst, const void *src, size_t bytes) {
-        if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
-    };
-    put(D.oo, H.oo.data(), 8 * H.oo.size());
-    put(D.goff, H.goff.data(), 4 * H.goff.size());
-    put(D.fcol, H.fcol.data(), 4 * H.fcol.size());
-    put(D.cstart, H.cstart.data(), 4 * H.cstart.size());
-    put(D.outl, H.outl.data(), 4 * H.outl.size());
-    if (e == hipSuccess) e = hipMemsetAsync(D.alive, 1, N, s);
+    e = hipMemsetAsync(D.alive, 1, N, s);
     if (e == hipSuccess) e = hipMemsetAsync(D.vmark, 0, 4 * N, s);
     if (e == hipSuccess) e = hipMemsetAsync(D.thist, 0, 4 * (size_t)kTopkBins, s);
     if (e == hipSuccess) e = hipMemsetAsync(D.thist_c, 0, 4 * 256, s);
     if (e == hipSuccess) e = hipMemsetAsync(D.ctr, 0, sizeof(DevCounters), s);
     if (e == hipSuccess) e = hipMemsetAsync(D.wticket, 0, 8, s);
     if (e == hipSuccess) e = hipMemsetAsync(D.tstate, 0, sizeof(TopkState), s);
-    if (e != hipSuccess) return hip_fail(e, "graph upload");
-    const rs_status tst = upload_tiles(g, H);
-    if (tst != RS_OK) return tst;
-    e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(e, "graph upload");
-    const rs_status lst = launch_col_labels(g);  // each entry's neighbour community
-    if (lst != RS_OK) return lst;
+    return e == hipSuccess ? RS_OK : hip_fail(e, "graph upload");
+}
+
+static rs_status alloc_slots(rs_graph *g, int64_t n_out) {
+    DeviceGraph &D = g->d;
+    g->n_out = n_out;
+    const size_t NX = std::max<size_t>(2 * (size_t)n_out, 1), NO = std::max<size_t>((size_t)n_out, 1);
+    const DevReq reqs[] = {
+        {(void **)&D.fcol, 4 * NX},
+        {(void **)&D.prec, sizeof(PairRec) * NX},
+        {(void **)&D.val2, 8 * NX},
+        {(void **)&D.plink, sizeof(PairLink) * NX},
+        {(void **)&D.outl, 4 * NO},
+        {(void **)&D.oe, sizeof(OutEnt) * NO},
+    };
+    const hipError_t e = dev_alloc_group(g, reqs, sizeof(reqs) / sizeof(reqs[0]));
+    return e == hipSuccess ? RS_OK : hip_fail(e, "device allocation");
+}
+
+// The row offsets in the device's width.
+static hipError_t put_offsets(rs_graph *g, const std::vector<int64_t> &off, std::vector<int32_t> &off32) {
+    const size_t n1 = off.size();
+    if (g->d.off64) return hipMemcpyAsync(g->d.off, off.data(), 8 * n1, hipMemcpyHostToDevice, g->stream);
+    off32.resize(n1);
+    parallel_for((int64_t)n1, 1 << 18, [&](int64_t lo, int64_t hi) {
+        for (int64_t v = lo; v < hi; ++v) off32[v] = (int32_t)off[v];
+    });
+    return hipMemcpyAsync(g->d.off, off32.data(), 4 * n1, hipMemcpyHostToDevice, g->stream);
+}
+
+// What follows once the rows, slots and out-lists are in place: the schedule
+// (cut in H), the links and the out-list entries' leaders.
+static rs_status finish_load(rs_graph *g, const HostGraph &H) {
+    DeviceGraph &D = g->d;
+    rs_status st = upload_tiles(g, H);
+    if (st == RS_OK) st = launch_zero_u64(g, D.scratch_u, 1);
+    if (st == RS_OK) st = launch_links(g, D.scratch_u);
+    if (st != RS_OK) return st;
     unsigned long long walk = 0;
-    rs_status rst = launch_zero_u64(g, D.scratch_u, 1);
-    if (rst == RS_OK) rst = launch_links(g, D.scratch_u);
-    if (rst != RS_OK) return rst;
-    e = hipMemcpyAsync(&walk, D.scratch_u, 8, hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) return hip_fail(e, "run lengths");
-    const rs_status ost = launch_out_entries(g);  // each out-list entry's two row entries
-    if (ost != RS_OK) return ost;
-    e = hipStreamSynchronize(s);
+    hipError_t e = hipMemcpyAsync(&walk, D.scratch_u, 8, hipMemcpyDeviceToHost, g->stream);
+    if (e == hipSuccess) st = launch_out_entries(g);
+    const hipError_t es = hipStreamSynchronize(g->stream);  // (on an error too: walk is this frame's)
+    if (st != RS_OK) return st;
+    if (e == hipSuccess) e = es;
     if (e != hipSuccess) return hip_fail(e, "pair-slot map");
     // The type-II values by slot cost each slot some 7 to 11 ps (its record
     // and neighbour read once more); the pairs walking the runs themselves
@@ -648,7 +646,44 @@ static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool 
     // the walks are faster (302 against 316 us a pass; 522 against 567), at
     // 1.06 and 1.21 (n = 3 M, mean degree 30; n = 150 K, mean degree 71) the
     // values by slot (1,818 against 2,675 us; 686 against 776).
-    g->type2_by_slot = 4 * walk >= (unsigned long long)H.goff[n];
+    g->type2_by_slot = 4 * walk >= 2 * (unsigned long long)g->n_out;
+    g->n_alive = D.n;
+    return RS_OK;
+}
+
+// keep: H stays intact for later uploads (its host maps are copied, not moved)
+static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool keep = false) {
+    DeviceGraph &D = g->d;
+    rs_status st = alloc_vertices(g, n, nnz, (int64_t)H.comm2orig.size());
+    if (st == RS_OK) st = alloc_slots(g, (int64_t)H.outl.size());
+    if (st != RS_OK) return st;
+    std::vector<int32_t> off32, deg;
+    hipError_t e;
+    try {
+        deg.resize(n);
+        for (int64_t v = 0; v < n; ++v) deg[v] = (int32_t)(H.off[v + 1] - H.off[v]);
+        e = put_offsets(g, H.off, off32);
+    } catch (const std::bad_alloc &) {
+        return fail(RS_ERR_NOMEM, "host staging of the upload");
+    }
+    auto put = [&](void *dst, const void *src, size_t bytes) {
+        if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, g->stream);
+    };
+    put(D.deg, deg.data(), 4 * (size_t)n);
+    put(D.col, H.col.data(), 4 * (size_t)nnz);
+    put(D.lab, H.lab.data(), 4 * (size_t)n);
+    put(D.new2old, H.new2old.data(), 4 * (size_t)n);
+    put(D.oo, H.oo.data(), 8 * H.oo.size());
+    put(D.goff, H.goff.data(), 4 * H.goff.size());
+    put(D.fcol, H.fcol.data(), 4 * H.fcol.size());
+    put(D.cstart, H.cstart.data(), 4 * H.cstart.size());
+    put(D.outl, H.outl.data(), 4 * H.outl.size());
+    const hipError_t es = hipStreamSynchronize(g->stream);  // (on an error too: the staging is this frame's)
+    if (e == hipSuccess) e = es;
+    if (e != hipSuccess) return hip_fail(e, "graph upload");
+    st = launch_col_labels(g);  // each entry's neighbour community
+    if (st == RS_OK) st = finish_load(g, H);
+    if (st != RS_OK) return st;
     if (keep) {
         try {
             g->h_new2old = H.new2old;
@@ -662,13 +697,282 @@ static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool 
         g->h_old2new.swap(H.old2new);
         g->h_comm2orig.swap(H.comm2orig);
     }
-    g->n_alive = n;
+    return RS_OK;
+}
+
+// ------------------------------------------------------------ load on the device
+// The vertices' renumbering: communities by ascending label, a stable counting
+// sort of the vertices by community (in chunks, one thread each, when there are
+// enough vertices for the communities), and the internal row offsets.
+// False: a negative label, bad offsets or a row that no simple graph has (the
+// host's checks say which).
+template <class OffIn>
+static bool renumber(int64_t n, int64_t nnz, const OffIn *off, const int32_t *lab, HostGraph &H,
+                     std::vector<int64_t> &cap) {
+    std::atomic<bool> ok{(int64_t)off[0] == 0 && (int64_t)off[n] == nnz};
+    std::atomic<int32_t> top{0};
+    parallel_for(n, 1 << 16, [&](int64_t lo, int64_t hi) {
+        int32_t m = 0;
+        bool good = true;
+        for (int64_t v = lo; v < hi; ++v) {
+            const int64_t len = (int64_t)off[v + 1] - (int64_t)off[v];
+            good = good && lab[v] >= 0 && len >= 0 && len < n;
+            m = std::max(m, lab[v]);
+        }
+        if (!good) ok.store(false);
+        int32_t t = top.load();
+        while (m > t && !top.compare_exchange_weak(t, m)) {
+        }
+    });
+    if (!ok.load()) return false;
+    // communities: labels up to a few times n are counted, others sorted
+    const int64_t span = (int64_t)top.load() + 1;
+    std::vector<int32_t> rank, cid;
+    const bool dense = span <= 4 * n + 65536;
+    if (dense) {
+        rank.assign(span, 0);
+        for (int64_t v = 0; v < n; ++v) rank[lab[v]] = 1;
+        for (int64_t c = 0, r = 0; c < span; ++c) {
+            if (!rank[c]) continue;
+            H.comm2orig.push_back((int32_t)c);
+            rank[c] = (int32_t)r++;
+        }
+    } else {
+        H.comm2orig.assign(lab, lab + n);
+        std::sort(H.comm2orig.begin(), H.comm2orig.end());
+        H.comm2orig.erase(std::unique(H.comm2orig.begin(), H.comm2orig.end()), H.comm2orig.end());
+    }
+    const int64_t k = (int64_t)H.comm2orig.size();
+    const int64_t T = n >= (1 << 17) && k <= (1 << 16) ? 8 : 1, per = (n + T - 1) / T;
+    cid.resize(n);
+    std::vector<int64_t> at((size_t)(T * k), 0);  // [chunk][community]: counts, then places
+    parallel_for(T, 1, [&](int64_t t0, int64_t t1) {
+        for (int64_t t = t0; t < t1; ++t) {
+            int64_t *c = at.data() + t * k;
+            for (int64_t v = t * per; v < std::min(n, (t + 1) * per); ++v) {
+                cid[v] = dense ? rank[lab[v]]
+                               : (int32_t)(std::lower_bound(H.comm2orig.begin(), H.comm2orig.end(), lab[v]) -
+                                           H.comm2orig.begin());
+                ++c[cid[v]];
+            }
+        }
+    });
+    H.cstart.resize(k + 1);
+    int64_t s = 0;
+    for (int64_t c = 0; c < k; ++c) {
+        H.cstart[c] = (int32_t)s;
+        for (int64_t t = 0; t < T; ++t) {
+            const int64_t x = at[t * k + c];
+            at[t * k + c] = s;
+            s += x;
+        }
+    }
+    H.cstart[k] = (int32_t)s;
+    H.new2old.resize(n);
+    H.old2new.resize(n);
+    H.lab.resize(n);
+    cap.resize(n);
+    parallel_for(T, 1, [&](int64_t t0, int64_t t1) {
+        for (int64_t t = t0; t < t1; ++t) {
+            int64_t *c = at.data() + t * k;
+            for (int64_t v = t * per; v < std::min(n, (t + 1) * per); ++v) {
+                const int64_t x = c[cid[v]]++;
+                H.new2old[x] = (int32_t)v;
+                H.old2new[v] = (int32_t)x;
+                H.lab[x] = cid[v];
+                cap[x] = (int64_t)off[v + 1] - (int64_t)off[v];
+            }
+        }
+    });
+    H.off.resize(n + 1);
+    H.off[0] = 0;
+    for (int64_t x = 0; x < n; ++x) H.off[x + 1] = H.off[x] + cap[x];
+    return true;
+}
+
+// Graphs from this many entries on are built on the device, where the host
+// would sort a row at a time and look up every entry's reverse: 1.6 against
+// 8.1 ms with 1.8 M entries (n = 100,000), 10 against 94 ms with 18 M, 0.40
+// against 1.7 ms with 62,000.  The device's way costs 0.35 ms of launches and
+// waits at the least, what the host takes for some 8,000 entries (7,700: 0.32
+// ms; 15,000: 0.71 ms).
+constexpr int64_t kDeviceLoadMin = 1 << 13;
+
+// *done: the graph is loaded.  Not done with RS_OK: something is wrong with
+// the graph or the device, and the host's path tells what.
+template <class OffIn>
+static rs_status load_on_device(const rs_csr *csr, rs_graph *g, bool *done) {
+    *done = false;
+    const int64_t n = csr->n, nnz = csr->nnz;
+    hipStream_t s = g->stream;
+    std::vector<OffIn> h_off;
+    std::vector<int32_t> h_lab;
+    const OffIn *off = (const OffIn *)csr->row_offsets;
+    const int32_t *lab = csr->labels;
+    if (csr->on_device) {
+        h_off.resize(n + 1);
+        h_lab.resize(n);
+        hipError_t e = hipMemcpy(h_off.data(), off, sizeof(OffIn) * (n + 1), hipMemcpyDeviceToHost);
+        if (e == hipSuccess) e = hipMemcpy(h_lab.data(), lab, 4 * n, hipMemcpyDeviceToHost);
+        if (e != hipSuccess) return hip_fail(e, "copying the device-resident input graph");
+        off = h_off.data();
+        lab = h_lab.data();
+    }
+    HostGraph H;  // (these outlive the copies: the scratch's end waits for the stream)
+    std::vector<int64_t> cap, fgn;
+    std::vector<int32_t> off32, f32, hubs;
+    // scratch of the load, one allocation
+    const size_t b_off = csr->on_device ? 0 : sizeof(OffIn) * (n + 1), b_col = csr->on_device ? 0 : 4 * (size_t)nnz;
+    const size_t sizes[] = {b_off, b_col, 8 * (size_t)n, 4 * (size_t)n, 8 * (size_t)prefix_blocks(n), 16,
+                            4 * (size_t)(nnz / load_hub_row() + 1)};
+    size_t at[8] = {0};
+    for (int i = 0; i < 7; ++i) at[i + 1] = at[i] + (sizes[i] + 255) / 256 * 256;
+    struct Scratch {
+        char *p = nullptr;
+        hipStream_t s;
+        ~Scratch() {
+            if (p) {
+                (void)hipStreamSynchronize(s);
+                (void)hipFree(p);
+            }
+        }
+    } tmp;
+    tmp.s = s;
+    hipError_t e = hipMalloc((void **)&tmp.p, at[7]);
+    if (e != hipSuccess) {
+        tmp.p = nullptr;
+        return hip_fail(e, "load scratch");
+    }
+    LoadArgs L;
+    L.offset_bytes = (int)sizeof(OffIn);
+    L.off = csr->on_device ? csr->row_offsets : tmp.p + at[0];
+    L.col = csr->on_device ? csr->col : (const int32_t *)(tmp.p + at[1]);
+    L.map = (int2 *)(tmp.p + at[2]);
+    L.fgn = (int32_t *)(tmp.p + at[3]);
+    long long *sums = (long long *)(tmp.p + at[4]);
+    L.bad = (unsigned int *)(tmp.p + at[5]);
+    L.hubs = (const int32_t *)(tmp.p + at[6]);
+    // the columns travel while the host renumbers the vertices
+    hipError_t ec = hipSuccess;
+    std::thread copier;
+    if (!csr->on_device) {
+        const int dev = g->device;
+        auto copy = [&, dev]() {
+            ec = hipSetDevice(dev);
+            if (ec == hipSuccess) ec = hipMemcpyAsync((void *)L.off, csr->row_offsets, b_off, hipMemcpyHostToDevice, s);
+            if (ec == hipSuccess) ec = hipMemcpyAsync((void *)L.col, csr->col, b_col, hipMemcpyHostToDevice, s);
+        };
+        try {
+            copier = std::thread(copy);
+        } catch (...) {
+            copy();
+        }
+    }
+    struct Join {
+        std::thread &t;
+        ~Join() {
+            if (t.joinable()) t.join();
+        }
+    } join{copier};
+    const bool good = renumber<OffIn>(n, nnz, off, lab, H, cap);
+    for (int64_t x = 0; good && x < n; ++x)
+        if (cap[x] > load_hub_row()) hubs.push_back((int32_t)x);
+    if (copier.joinable()) copier.join();
+    if (ec != hipSuccess) return hip_fail(ec, "graph upload");
+    if (!good) return RS_OK;
+    L.n_hubs = (int)hubs.size();
+    rs_status st = alloc_vertices(g, n, nnz, (int64_t)H.comm2orig.size());
+    if (st != RS_OK) return st;
+    DeviceGraph &D = g->d;
+    e = put_offsets(g, H.off, off32);
+    auto put = [&](void *dst, const void *src, size_t bytes) {
+        if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+    };
+    put(D.lab, H.lab.data(), 4 * (size_t)n);
+    put(D.new2old, H.new2old.data(), 4 * (size_t)n);
+    put(D.cstart, H.cstart.data(), 4 * H.cstart.size());
+    put((void *)L.hubs, hubs.data(), 4 * hubs.size());
+    if (e == hipSuccess) e = hipMemsetAsync(L.bad, 0, 16, s);
+    if (e == hipSuccess) st = launch_load_rows(g, L);
+    unsigned int bad = 0;
+    f32.resize(n);
+    if (e == hipSuccess && st == RS_OK) e = hipMemcpyAsync(f32.data(), L.fgn, 4 * (size_t)n, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess && st == RS_OK) e = hipMemcpyAsync(&bad, L.bad, 4, hipMemcpyDeviceToHost, s);
+    const hipError_t es = hipStreamSynchronize(s);  // (on an error too: the staging is this frame's)
+    if (st != RS_OK) return st;
+    if (e == hipSuccess) e = es;
+    if (e != hipSuccess) return hip_fail(e, "graph upload");
+    if (bad) return RS_OK;
+    int64_t slots = 0;
+    fgn.resize(n);
+    H.goff.resize(n + 1);
+    for (int64_t x = 0; x < n; ++x) {
+        H.goff[x] = (int32_t)slots;
+        fgn[x] = f32[x];
+        slots += f32[x];
+        if (slots >= (int64_t)1 << 31)
+            return fail(RS_ERR_RANGE, "more than 2^30 edges between communities (slots are 32-bit)");
+    }
+    H.goff[n] = (int32_t)slots;
+    st = alloc_slots(g, slots / 2);
+    if (st != RS_OK) return st;
+    e = hipMemcpyAsync(D.goff, H.goff.data(), 4 * H.goff.size(), hipMemcpyHostToDevice, s);
+    if (e != hipSuccess) return hip_fail(e, "graph upload");
+    st = launch_load_slots(g, L.fgn, sums);  // (the foreign degrees are in goff now)
+    if (st != RS_OK) return st;
+    cut_all(n, H.off, cap, fgn, g->h_vstart, Tiling(), H);
+    g->h_gblk_off.swap(H.gblk_off);
+    g->h_gblk.swap(H.gblk);
+    st = finish_load(g, H);
+    if (st != RS_OK) return st;
+    g->h_new2old.swap(H.new2old);
+    g->h_old2new.swap(H.old2new);
+    g->h_comm2orig.swap(H.comm2orig);
+    *done = true;
+    return RS_OK;
+}
+
+// The current device, and a stream of the graph's own if the caller gave none.
+static rs_status take_stream(rs_graph *g) {
+    hipError_t e = hipGetDevice(&g->device);
+    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+    if (!g->stream) {
+        e = hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking);
+        if (e != hipSuccess) {
+            g->stream = nullptr;
+            return hip_fail(e, "hipStreamCreate");
+        }
+        g->own_stream = true;
+    }
     return RS_OK;
 }
 
 template <class OffIn>
 static rs_status load_t(const rs_csr *csr, rs_graph *g) {
     const int64_t n = csr->n, nnz = csr->nnz;
+    if (nnz >= kDeviceLoadMin) {
+        bool done = false;
+        rs_status st = take_stream(g);
+        if (st == RS_OK) {
+            try {
+                st = load_on_device<OffIn>(csr, g, &done);
+            } catch (const std::bad_alloc &) {
+                st = fail(RS_ERR_NOMEM, "host allocation failed while renumbering the graph");
+            }
+        }
+        if (done) return RS_OK;
+        // the checks below tell what is wrong with the graph or the device (or,
+        // where only the load's scratch was too much, the host builds the graph)
+        if (g->stream) (void)hipStreamSynchronize(g->stream);
+        for (auto &a : g->allocations) (void)hipFree(a.first);
+        g->allocations.clear();
+        g->d = DeviceGraph();
+        g->dev_bytes = 0;
+        g->n_requests = 0;
+        g->tile_slab = nullptr;
+        g->rem_cnt = nullptr;
+        clear_error();
+    }
     const OffIn *off = (const OffIn *)csr->row_offsets;
     const int32_t *col = csr->col, *lab = csr->labels;
     std::vector<OffIn> h_off;
@@ -696,13 +1000,8 @@ static rs_status load_t(const rs_csr *csr, rs_graph *g) {
     if (st != RS_OK) return st;
     g->h_gblk_off.swap(H.gblk_off);
     g->h_gblk.swap(H.gblk);
-    hipError_t e = hipGetDevice(&g->device);
-    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-    if (!g->stream) {
-        e = hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking);
-        if (e != hipSuccess) return hip_fail(e, "hipStreamCreate");
-        g->own_stream = true;
-    }
+    st = take_stream(g);
+    if (st != RS_OK) return st;
     return upload(g, H, n, nnz);
 }
 
