@@ -93,12 +93,19 @@ constexpr int kScoreBins = 9;
 // The units are found over contiguous vertex ranges, one per workgroup (at
 // most kUnitGroups), each counting its tile vertices per bin and its
 // affected vertices (kUnitRows counts per range).
-constexpr int kUnitGroups = 1024;
+constexpr int kUnitGroups = 512;
 constexpr int kUnitRows = kScoreBins + 1;
 enum IncCounter {
-    kIcChanged = 0, kIcLinkRows, kIcRows, kIcMain, kIcBig, kIcAffected, kIcWmaxOld, kIcChunks, kIcAList,
-    kIcBins,  // kScoreBins counts
-    kIcCount = kIcBins + kScoreBins
+    kIcChanged = 0, kIcRows, kIcMain, kIcBig, kIcWmaxOld, kIcChunks,
+    kIcBins,                          // kScoreBins counts
+    kIcEdges = kIcBins + kScoreBins,  // listed edges removed
+    kIcVertexEdges,                   // edges removed with their vertices
+    kIcVertices,                      // vertices removed
+    kIcCount
+};
+// What rs_apply_removals reports, written by the device into pinned memory.
+struct RemovalCounts {
+    unsigned long long edges, vertex_edges, vertices, affected;
 };
 
 // Grid of a tiled launch: one workgroup per hub, then the tiles rounded up to
@@ -237,10 +244,11 @@ struct DeviceGraph {
     uint32_t *hfilter = nullptr;  // [big hubs][kFilterWords] membership filter of each big hub's foreign neighbours
     uint8_t *rflag = nullptr, *cflag = nullptr, *hflag = nullptr;  // flags: row blocks, score-hub chunks, score hubs (whole)
     int32_t *elist = nullptr, *abin = nullptr;  // [n] changed rows; affected tile vertices by bin
-    int32_t *ucnt = nullptr;                    // [kUnitRows * kUnitGroups] per-range counts, then slots
+    int32_t *ucnt = nullptr;                    // [kUnitRows * kUnitGroups] affected vertices per bin and range
     int2 *echunk = nullptr;                 // [n + nnz / 64] chunks of 64 entries of the changed rows
     int32_t *rlist = nullptr, *slist = nullptr, *hlist = nullptr; // block lists
-    unsigned long long *ictr = nullptr;     // [kIcCount]
+    unsigned long long *ictr = nullptr;     // [kIcCount] this re-score's counters, zero when it starts
+    unsigned long long *ictr_next = nullptr;  // [kIcCount] the next one's
     // batched graphs (a disjoint union of n_graphs graphs, each a contiguous id range)
     int64_t *vstart = nullptr;              // [n_graphs + 1] first vertex of each graph
     int32_t *vgraph = nullptr;              // [n] graph of each vertex
@@ -325,8 +333,8 @@ struct rs_graph {
     int64_t rem_cap = 0;
     int32_t *rem_host = nullptr;
     int64_t rem_host_cap = 0;
-    unsigned long long *rem_cnt = nullptr;       // device [4]: edges removed, -, edges of removed vertices, vertices
-    unsigned long long *rem_cnt_host = nullptr;  // pinned [4 + kIcCount]
+    rs::RemovalCounts *rem_cnt_host = nullptr;       // pinned
+    bool ictr_dirty = false;                     // a re-score failed on its way: both counters need clearing
     hipEvent_t rem_ev = nullptr;                 // the removal counts have reached rem_cnt_host
 };
 
@@ -352,10 +360,10 @@ rs_status launch_score_pass(rs_graph *g);
 rs_status launch_score_incremental(rs_graph *g);
 rs_status launch_topk(rs_graph *g, int64_t k, int32_t *ids, double *scores, int64_t *count);
 rs_status launch_reduce_counts(rs_graph *g);
-rs_status launch_remove_edges(rs_graph *g, const int32_t *d_src, const int32_t *d_dst, int64_t m,
-                              unsigned long long *d_removed);
-rs_status launch_remove_vertices(rs_graph *g, const int32_t *d_verts, int64_t nv,
-                                 unsigned long long *d_removed_edges);
+// The listed edges and vertices (device or pinned memory) are removed in one
+// launch: no listed edge may touch a listed vertex.
+rs_status launch_remove(rs_graph *g, const int32_t *src, const int32_t *dst, int64_t m, const int32_t *verts,
+                        int64_t nv);
 // Loading on the device: the caller's CSR in device memory and scratch.
 struct LoadArgs {
     const void *off;  // [n+1] row offsets

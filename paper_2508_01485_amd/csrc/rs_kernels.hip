@@ -1812,19 +1812,26 @@ __global__ __launch_bounds__(kBlock) void k_score_inc(ScoreArgs A, const int32_t
 // Each hub's score from its chunk partials (one wavefront per hub: lane l
 // sums chunks l, l + 64, ... in order, then a fixed shuffle tree).  A hub
 // whose foreign list became empty keeps the zeros the row pass wrote.
-__global__ __launch_bounds__(kBlock) void k_hub_sum(const int32_t *hubs, const int32_t *hub_first,
-                                                    const HubPart *hub_part, int n_hubs, const VMeta *meta,
-                                                    const DevCounters *ctr, const unsigned long long *gwmax,
-                                                    const int32_t *vgraph, double *R, double *raw,
-                                                    long long *tI, long long *tII) {
+struct HubSumArgs {
+    const int32_t *hubs, *hub_first;
+    const HubPart *hub_part;
+    int n_hubs;
+    const VMeta *meta;
+    const DevCounters *ctr;
+    const unsigned long long *gwmax;
+    const int32_t *vgraph;
+    double *R, *raw;
+    long long *tI, *tII;
+};
+__device__ __forceinline__ void hub_sum(const HubSumArgs &A) {
     const int hub = (int)blockIdx.x * (kBlock / 64) + (int)(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (hub >= n_hubs) return;
-    const int first = hub_first[hub], nch = hub_first[hub + 1] - first;
+    if (hub >= A.n_hubs) return;
+    const int first = A.hub_first[hub], nch = A.hub_first[hub + 1] - first;
     double acc = 0.0;
     long long c1 = 0, c2 = 0;
     for (int c = lane; c < nch; c += 64) {
-        const HubPart q = hub_part[first + c];
+        const HubPart q = A.hub_part[first + c];
         acc += q.raw;
         c1 += q.tI;
         c2 += q.tII;
@@ -1836,16 +1843,18 @@ __global__ __launch_bounds__(kBlock) void k_hub_sum(const int32_t *hubs, const i
         c2 += __shfl_xor(c2, o);
     }
     if (lane == 0) {
-        const int u = hubs[hub];
-        const VMeta m = meta[u];
+        const int u = A.hubs[hub];
+        const VMeta m = A.meta[u];
         if (m.deg - (m.q - m.p) > 0) {
-            R[u] = score_value(acc, m.deg, bitsd(gwmax ? gwmax[vgraph[u]] : ctr->wmax_bits));
-            raw[u] = acc;
-            tI[u] = c1;
-            tII[u] = c2;
+            A.R[u] = score_value(acc, m.deg, bitsd(A.gwmax ? A.gwmax[A.vgraph[u]] : A.ctr->wmax_bits));
+            A.raw[u] = acc;
+            A.tI[u] = c1;
+            A.tII[u] = c2;
         }
     }
 }
+
+__global__ __launch_bounds__(kBlock) void k_hub_sum(HubSumArgs A) { hub_sum(A); }
 
 // The pass's triad totals from the per-vertex counts (read on demand: the
 // incremental pass reruns vertices in units of its own, so per-workgroup
@@ -2507,17 +2516,24 @@ __global__ void k_zero_u64(unsigned long long *p, int count) {
     for (int i = threadIdx.x; i < count; i += blockDim.x) p[i] = 0ull;
 }
 
-// After an incremental pass: when w_max changed, every R is recomputed from
-// its raw sum (the same expression as the pass, so the bits equal a full
-// pass's).  Raw sums are 0 for vertices without foreign neighbours.
-__global__ __launch_bounds__(kBlock) void k_rescale(const unsigned long long *wmax_old, const DevCounters *ctr,
-                                                    const VMeta *meta, const double *raw, double *R, long long n) {
-    const unsigned long long wb = ctr->wmax_bits;
+// The end of an incremental pass: the hubs' sums (the first sum_blocks
+// workgroups) and, when w_max changed, every other R recomputed from its raw
+// sum (the same expression as the pass, so the bits equal a full pass's).
+// Raw sums are 0 for vertices without foreign neighbours.
+__global__ __launch_bounds__(kBlock) void k_inc_scores(HubSumArgs A, int sum_blocks, const int32_t *vscore,
+                                                       const unsigned long long *wmax_old, long long n) {
+    if ((int)blockIdx.x < sum_blocks) {
+        hub_sum(A);
+        return;
+    }
+    const unsigned long long wb = A.ctr->wmax_bits;
     if (wb == *wmax_old) return;
     const double wmax = bitsd(wb);
-    for (long long u = (long long)blockIdx.x * kBlock + threadIdx.x; u < n; u += (long long)gridDim.x * kBlock) {
-        const VMeta m = meta[u];
-        R[u] = m.deg - (m.q - m.p) > 0 ? score_value(raw[u], m.deg, wmax) : 0.0;
+    for (long long u = (long long)((int)blockIdx.x - sum_blocks) * kBlock + threadIdx.x; u < n;
+         u += (long long)((int)gridDim.x - sum_blocks) * kBlock) {
+        if (vscore[u] < 0) continue;  // a hub
+        const VMeta m = A.meta[u];
+        A.R[u] = m.deg - (m.q - m.p) > 0 ? score_value(A.raw[u], m.deg, wmax) : 0.0;
     }
 }
 
@@ -2639,16 +2655,29 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
         if (g->grid_score > 0) hipLaunchKernelGGL(k_score, dim3(g->grid_score), dim3(kBlock), 0, g->stream, S);
         timing_end(g, K_SCORE, ev);
     }
-    if (g->n_shubs > 0) {
-        timing_begin(g, K_HUB_SUM, &ev);
-        hipLaunchKernelGGL(k_hub_sum, dim3((g->n_shubs + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0,
-                           g->stream, D.shubs, D.shub_first, D.hub_part, g->n_shubs, D.meta, D.ctr, D.gwmax,
-                           D.vgraph, D.R, D.raw, D.tI, D.tII);
-        timing_end(g, K_HUB_SUM, ev);
-    }
-    if (inc && D.n > 0)  // w_max moved: every score is rescaled from its raw sum
-        hipLaunchKernelGGL(k_rescale, dim3(grid_for(D.n, kBlock, 4096)), dim3(kBlock), 0, g->stream,
-                           (const unsigned long long *)&D.ictr[kIcWmaxOld], D.ctr, D.meta, D.raw, D.R, (long long)D.n);
+    HubSumArgs U;
+    U.hubs = D.shubs;
+    U.hub_first = D.shub_first;
+    U.hub_part = D.hub_part;
+    U.n_hubs = g->n_shubs;
+    U.meta = D.meta;
+    U.ctr = D.ctr;
+    U.gwmax = D.gwmax;
+    U.vgraph = D.vgraph;
+    U.R = D.R;
+    U.raw = D.raw;
+    U.tI = D.tI;
+    U.tII = D.tII;
+    const int sum_blocks = (g->n_shubs + kBlock / 64 - 1) / (kBlock / 64);
+    const bool sums = sum_blocks > 0;
+    if (sums) timing_begin(g, K_HUB_SUM, &ev);
+    if (inc && D.n > 0)
+        hipLaunchKernelGGL(k_inc_scores, dim3(sum_blocks + grid_for(D.n, kBlock, 4096)), dim3(kBlock), 0, g->stream, U,
+                           sum_blocks, (const int32_t *)D.vscore, (const unsigned long long *)&D.ictr[kIcWmaxOld],
+                           (long long)D.n);
+    else if (sums)
+        hipLaunchKernelGGL(k_hub_sum, dim3(sum_blocks), dim3(kBlock), 0, g->stream, U);
+    if (sums) timing_end(g, K_HUB_SUM, ev);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "score pass launch");
     return RS_OK;
@@ -3923,71 +3952,93 @@ __device__ __forceinline__ int delete_edge(const OffT *off, const int32_t *deg, 
     return 1;
 }
 
+// What the removals append to: the changed rows and, one by one, their chunks
+// of 64 entries (row's list index, chunk), at least one per row.  The chunks
+// count the row's length before; those beyond its new end are empty.
+struct ChangedRows {
+    const int32_t *deg;
+    int32_t *list;
+    int2 *chunks;
+    unsigned long long *ictr;
+};
+
 // The rows first marked changed by a wavefront's lanes, appended to the list
-// of changed rows (any order; one atomic per wavefront).  All lanes call it.
-__device__ __forceinline__ void append_changed(int x, bool nx, int y, bool ny, int32_t *list,
-                                               unsigned long long *count) {
+// of changed rows with their chunks (any order; one atomic per wavefront for
+// each).  All lanes call it.
+__device__ __forceinline__ void append_changed(int x, bool nx, int y, bool ny, const ChangedRows &C) {
     const int lane = (int)__lane_id();
     const unsigned long long mx = __ballot(nx), my = __ballot(ny);
     const int tot = __popcll(mx) + __popcll(my);
     if (tot == 0) return;
-    unsigned long long first = 0;
-    if (lane == 0) first = atomicAdd(count, (unsigned long long)tot);
-    first = __shfl(first, 0);
-    const unsigned long long below = (1ull << lane) - 1ull;
-    if (nx) list[first + __popcll(mx & below)] = x;
-    if (ny) list[first + __popcll(mx) + __popcll(my & below)] = y;
-}
-
-template <typename OffT>
-__global__ void k_remove_edges(const OffT *off, const int32_t *deg, int32_t *col, OutLists O, const int32_t *src,
-                               const int32_t *dst, long long m, unsigned long long *removed, int32_t *changed,
-                               unsigned long long *n_changed) {
-    const int lane = (int)__lane_id();
-    unsigned long long cnt = 0;
-    for (long long base = (long long)blockIdx.x * blockDim.x + threadIdx.x - lane; base < m;
-         base += (long long)gridDim.x * blockDim.x) {
-        const long long i = base + lane;
-        int a = 0, b = 0;
-        bool nx = false, ny = false;
-        if (i < m) {
-            a = src[i];
-            b = dst[i];
-            if (a != b) cnt += (unsigned long long)delete_edge(off, deg, col, O, a, b, nx, ny);
-        }
-        append_changed(min(a, b), nx, max(a, b), ny, changed, n_changed);
+    const int cx = nx ? max(1, (C.deg[x] + 63) >> 6) : 0, cy = ny ? max(1, (C.deg[y] + 63) >> 6) : 0;
+    int incl = cx + cy;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o);
+        if (lane >= o) incl += t;
     }
-    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
-    if (lane == 0 && cnt) atomicAdd(removed, cnt);
+    unsigned long long first = 0, chunk = 0;
+    if (lane == 63) {
+        first = atomicAdd(&C.ictr[kIcChanged], (unsigned long long)tot);
+        chunk = atomicAdd(&C.ictr[kIcChunks], (unsigned long long)incl);
+    }
+    first = __shfl(first, 63);
+    chunk = __shfl(chunk, 63) + (unsigned long long)(incl - cx - cy);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const long long ix = (long long)first + __popcll(mx & below);
+    const long long iy = (long long)first + __popcll(mx) + __popcll(my & below);
+    if (nx) C.list[ix] = x;
+    if (ny) C.list[iy] = y;
+    for (int c = 0; c < cx; ++c) C.chunks[chunk + c] = make_int2((int)ix, c);
+    for (int c = 0; c < cy; ++c) C.chunks[chunk + cx + c] = make_int2((int)iy, c);
 }
 
-// One wavefront per removed vertex: delete every incident edge, then mark the
-// vertex dead.  removed[0] counts edges, removed[1] newly dead vertices.
+// The first edge_blocks workgroups take the listed edges, a lane each; the
+// others the listed vertices, a wavefront each: delete every incident edge,
+// then mark the vertex dead.
 template <typename OffT>
-__global__ void k_remove_vertices(const OffT *off, const int32_t *deg, int32_t *col, OutLists O, uint8_t *alive,
-                                  const int32_t *verts, long long nv, unsigned long long *removed, int32_t *changed,
-                                  unsigned long long *n_changed) {
-    const long long wave = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const long long nwave = ((long long)gridDim.x * blockDim.x) >> 6;
+__global__ __launch_bounds__(256) void k_remove(const OffT *off, int32_t *col, OutLists O, uint8_t *alive,
+                                                ChangedRows C, const int32_t *src, const int32_t *dst, long long m,
+                                                int edge_blocks, const int32_t *verts, long long nv) {
     const int lane = (int)__lane_id();
+    if ((int)blockIdx.x < edge_blocks) {
+        unsigned long long cnt = 0;
+        for (long long base = (long long)blockIdx.x * blockDim.x + threadIdx.x - lane; base < m;
+             base += (long long)edge_blocks * blockDim.x) {
+            const long long i = base + lane;
+            int a = 0, b = 0;
+            bool nx = false, ny = false;
+            if (i < m) {
+                a = src[i];
+                b = dst[i];
+                if (a != b) cnt += (unsigned long long)delete_edge(off, C.deg, col, O, a, b, nx, ny);
+            }
+            append_changed(min(a, b), nx, max(a, b), ny, C);
+        }
+        for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
+        if (lane == 0 && cnt) atomicAdd(&C.ictr[kIcEdges], cnt);
+        return;
+    }
+    const long long wave = ((long long)((int)blockIdx.x - edge_blocks) * blockDim.x + threadIdx.x) >> 6;
+    const long long nwave = ((long long)((int)gridDim.x - edge_blocks) * blockDim.x) >> 6;
     for (long long i = wave; i < nv; i += nwave) {
         const int x = verts[i];
         const long long rb = (long long)off[x];
-        const int d = deg[x];
+        const int d = C.deg[x];
         unsigned long long cnt = 0;
         for (int j0 = 0; j0 < d; j0 += 64) {
             const int j = j0 + lane;
             const int y = j < d ? col[rb + j] : -1;
             bool nx = false, ny = false;
-            if (y >= 0) cnt += (unsigned long long)delete_edge(off, deg, col, O, x, y, nx, ny);
-            append_changed(min(x, y), nx, max(x, y), ny, changed, n_changed);
+            if (y >= 0) cnt += (unsigned long long)delete_edge(off, C.deg, col, O, x, y, nx, ny);
+            append_changed(min(x, y), nx, max(x, y), ny, C);
         }
         for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
         if (lane == 0) {
-            if (cnt) atomicAdd(&removed[0], cnt);
+            if (cnt) atomicAdd(&C.ictr[kIcVertexEdges], cnt);
             if (alive[x]) {
                 alive[x] = 0;
-                atomicAdd(&removed[1], 1ull);
+                atomicAdd(&C.ictr[kIcVertices], 1ull);
             }
         }
     }
@@ -4002,37 +4053,21 @@ static OutLists out_lists(rs_graph *g) {
     return O;
 }
 
-rs_status launch_remove_edges(rs_graph *g, const int32_t *d_src, const int32_t *d_dst, int64_t m,
-                              unsigned long long *d_removed) {
-    if (m <= 0) return RS_OK;
-    const int grid = grid_for(m, 256, 4096);
-    if (g->d.off64)
-        hipLaunchKernelGGL(k_remove_edges<long long>, dim3(grid), dim3(256), 0, g->stream,
-                           (const long long *)g->d.off, g->d.deg, g->d.col, out_lists(g), d_src, d_dst, (long long)m,
-                           d_removed, g->d.elist, &g->d.ictr[kIcChanged]);
+rs_status launch_remove(rs_graph *g, const int32_t *src, const int32_t *dst, int64_t m, const int32_t *verts,
+                        int64_t nv) {
+    DeviceGraph &D = g->d;
+    const int eb = m > 0 ? grid_for(m, 256, 4096) : 0, vb = nv > 0 ? grid_for(nv, 4, 4096) : 0;
+    if (eb + vb == 0) return RS_OK;
+    const ChangedRows C = {D.deg, D.elist, D.echunk, D.ictr};
+    if (D.off64)
+        hipLaunchKernelGGL(k_remove<long long>, dim3(eb + vb), dim3(256), 0, g->stream, (const long long *)D.off,
+                           D.col, out_lists(g), D.alive, C, src, dst, (long long)m, eb, verts, (long long)nv);
     else
-        hipLaunchKernelGGL(k_remove_edges<int32_t>, dim3(grid), dim3(256), 0, g->stream, (const int32_t *)g->d.off,
-                           g->d.deg, g->d.col, out_lists(g), d_src, d_dst, (long long)m, d_removed, g->d.elist,
-                           &g->d.ictr[kIcChanged]);
+        hipLaunchKernelGGL(k_remove<int32_t>, dim3(eb + vb), dim3(256), 0, g->stream, (const int32_t *)D.off, D.col,
+                           out_lists(g), D.alive, C, src, dst, (long long)m, eb, verts, (long long)nv);
     const hipError_t e = hipGetLastError();
-    return e == hipSuccess ? RS_OK : hip_fail(e, "remove edges launch");
+    return e == hipSuccess ? RS_OK : hip_fail(e, "removal launch");
 }
-
-rs_status launch_remove_vertices(rs_graph *g, const int32_t *d_verts, int64_t nv, unsigned long long *d_removed) {
-    if (nv <= 0) return RS_OK;
-    const int grid = grid_for(nv, 4, 4096);
-    if (g->d.off64)
-        hipLaunchKernelGGL(k_remove_vertices<long long>, dim3(grid), dim3(256), 0, g->stream,
-                           (const long long *)g->d.off, g->d.deg, g->d.col, out_lists(g), g->d.alive, d_verts,
-                           (long long)nv, d_removed, g->d.elist, &g->d.ictr[kIcChanged]);
-    else
-        hipLaunchKernelGGL(k_remove_vertices<int32_t>, dim3(grid), dim3(256), 0, g->stream, (const int32_t *)g->d.off,
-                           g->d.deg, g->d.col, out_lists(g), g->d.alive, d_verts, (long long)nv, d_removed,
-                           g->d.elist, &g->d.ictr[kIcChanged]);
-    const hipError_t e = hipGetLastError();
-    return e == hipSuccess ? RS_OK : hip_fail(e, "remove vertices launch");
-}
-
 
 // ------------------------------------------------------------ incremental re-score
 // After a removal batch only some results change.  With E the vertices whose
@@ -4096,31 +4131,6 @@ __global__ __launch_bounds__(kBlock) void k_compact_rows(const OffT *off, int32_
     }
 }
 
-// The listed (changed, compacted) rows cut into chunks of 64 entries, at
-// least one per row: (row's list index, chunk).  One slot per wavefront in
-// the chunk counter (a wavefront prefix orders its lanes' chunks).
-__global__ __launch_bounds__(kBlock) void k_row_chunks(const int32_t *deg, const int32_t *list,
-                                                       const unsigned long long *count, int2 *chunks,
-                                                       unsigned long long *n_chunks) {
-    const long long nl = (long long)*count;
-    const int lane = threadIdx.x & 63;
-    for (long long base = (long long)blockIdx.x * kBlock + (threadIdx.x & ~63); base < nl;
-         base += (long long)gridDim.x * kBlock) {
-        const long long i = base + lane;
-        const int nc = i < nl ? max(1, (deg[list[i]] + 63) >> 6) : 0;
-        int incl = nc;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int t = __shfl_up(incl, o);
-            if (lane >= o) incl += t;
-        }
-        unsigned long long first = 0;
-        if (lane == 63) first = atomicAdd(n_chunks, (unsigned long long)incl);
-        first = __shfl(first, 63);
-        for (int c = 0; c < nc; ++c) chunks[first + (incl - nc) + c] = make_int2((int)i, c);
-    }
-}
-
 // The marks of the pair (x, w) of a member x of C(v) in the row of v's
 // foreign neighbour w (the pair sums a_v): a score hub whose row did not
 // change flags the chunk holding the pair (w's place in x's foreign list);
@@ -4163,7 +4173,7 @@ __device__ __forceinline__ int flat_owner(const int *pre, int g, int &idx) {
 constexpr int kTriRow = 512;
 
 // After removals, one wavefront per chunk of 64 entries of a changed
-// (compacted) row v (chunks: k_row_chunks), for each entry (v, w) with w in
+// (compacted) row v (chunks: append_changed), for each entry (v, w) with w in
 // another community:
 // * links: v's link for the entry, and the leader and slot in v's list, which
 //   moved with v's row, in w's link back to v;
@@ -4351,20 +4361,20 @@ __global__ __launch_bounds__(kBlock) void k_mark_link(LinkArgs<OffT> L, unsigned
 // all chunks of its score hub; an affected tile vertex is placed in abin,
 // grouped by the bin of its load-time foreign degree (units of rescored
 // vertices are built per pass, so scattered affected vertices do not rerun
-// whole tiles).  Three steps over contiguous vertex ranges, one range per
+// whole tiles).  Two launches over contiguous vertex ranges, one range per
 // workgroup, so that no counter in global memory is shared: count per range
-// and bin (LDS atomics), an exclusive scan of the counts bin after bin (one
-// workgroup), and placement at the scanned offsets.  The scan also counts the
-// affected vertices and keeps w_max before the pass; placement clears the
-// marks.
+// and bin (LDS atomics), then each range sums the counts before its own
+// (18 KB a workgroup, from the L2; a launch of its own for the sums took 8 us
+// and a gap) and places its vertices there.  Placement clears the marks, and
+// beside it other workgroups turn the flags into lists.
 __device__ __forceinline__ int score_bin(long long fgn) {
     int b = 0;
     while (b < kScoreBins - 1 && (1ll << b) < fgn) ++b;
     return b;
 }
 
-__device__ __forceinline__ void unit_range(long long n, long long &lo, long long &hi) {
-    const long long per = ((n + gridDim.x - 1) / gridDim.x + 63) & ~63ll;
+__device__ __forceinline__ void unit_range(long long n, int groups, long long &lo, long long &hi) {
+    const long long per = ((n + groups - 1) / groups + 63) & ~63ll;
     lo = min(n, (long long)blockIdx.x * per);
     hi = min(n, lo + per);
 }
@@ -4382,7 +4392,7 @@ __device__ __forceinline__ void load_marks(const unsigned int *vmark, long long 
     }
 }
 
-// ucnt[r * gridDim.x + range]: rows 0..kScoreBins-1 tile vertices per bin,
+// ucnt[r * kUnitGroups + range]: rows 0..kScoreBins-1 tile vertices per bin,
 // row kScoreBins affected vertices.
 __global__ __launch_bounds__(kBlock) void k_units_count(const unsigned int *vmark, const int32_t *vrowb,
                                                         const int32_t *vscore, const int32_t *goff, long long n,
@@ -4391,7 +4401,7 @@ __global__ __launch_bounds__(kBlock) void k_units_count(const unsigned int *vmar
     if (threadIdx.x < kUnitRows) s_cnt[threadIdx.x] = 0;
     __syncthreads();
     long long lo, hi;
-    unit_range(n, lo, hi);
+    unit_range(n, (int)gridDim.x, lo, hi);
     int aff = 0;
     for (long long v0 = lo + threadIdx.x; v0 < hi; v0 += (long long)kMarkPer * kBlock) {
         unsigned int mk[kMarkPer];
@@ -4414,75 +4424,122 @@ __global__ __launch_bounds__(kBlock) void k_units_count(const unsigned int *vmar
     }
     if (aff) atomicAdd(&s_cnt[kScoreBins], aff);
     __syncthreads();
-    if (threadIdx.x < kUnitRows) ucnt[threadIdx.x * gridDim.x + blockIdx.x] = s_cnt[threadIdx.x];
+    if (threadIdx.x < kUnitRows) ucnt[threadIdx.x * kUnitGroups + blockIdx.x] = s_cnt[threadIdx.x];
 }
 
-// One workgroup: each bin's per-range counts become the ranges' first slots
-// in abin (bins in order); bin totals, the listed total and the affected
-// count go to the counters.  Thread t holds ranges 4t..4t+3 of every row
-// (all loads issued at once), and one block scan serves all bins.
-static_assert(kUnitGroups == 4 * kBlock, "k_units_scan holds four ranges per thread");
-__global__ __launch_bounds__(kBlock) void k_units_scan(int32_t *ucnt, int groups, unsigned long long *ictr,
-                                                       const DevCounters *ctr) {
-    __shared__ int ws[kUnitRows][kBlock / 64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int j0 = 4 * threadIdx.x;
-    int x[kUnitRows][4], incl[kUnitRows];
-#pragma unroll
-    for (int r = 0; r < kUnitRows; ++r) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) x[r][i] = j0 + i < groups ? ucnt[r * groups + j0 + i] : 0;
-    }
-#pragma unroll
-    for (int r = 0; r < kUnitRows; ++r) {
-        int t = x[r][0] + x[r][1] + x[r][2] + x[r][3];
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(t, o);
-            if (lane >= o) t += y;
+// Append the lanes' values whose pred holds to list (one atomic per
+// wavefront; all lanes call it).
+__device__ __forceinline__ void wave_append(bool pred, int val, int32_t *list, unsigned long long *count) {
+    const int lane = threadIdx.x & 63;
+    const unsigned long long m = __ballot(pred);
+    if (!m) return;
+    unsigned long long first = 0;
+    if (lane == 0) first = atomicAdd(count, (unsigned long long)__popcll(m));
+    first = __shfl(first, 0);
+    if (pred) list[first + __popcll(m & ((1ull << lane) - 1ull))] = val;
+}
+
+// The flags' part of k_units_place.
+struct UnitLists {
+    uint8_t *rflag, *cflag;
+    const uint8_t *hflag;
+    const int2 *hub_chunk;
+    int n_rows, n_chunks, n_chunks_lds;
+    int32_t *rlist, *slist, *hlist;
+};
+
+// Flags -> the incremental launches' lists (indices of the full launches):
+// the flagged row blocks, and the score-hub chunks to rerun, each chunk of a
+// hub flagged whole and each chunk flagged by itself (the main list takes
+// the LDS-hub chunks, the big list the others).  Clears the row and chunk
+// flags; the hub flags are cleared by the score pass that follows.
+__device__ __forceinline__ void unit_lists(const UnitLists &U, int block, int blocks, unsigned long long *ictr) {
+    const int lane = threadIdx.x & 63;
+    const int top = max(U.n_rows, U.n_chunks);
+    for (int base = block * kBlock + (threadIdx.x & ~63); base < top; base += blocks * kBlock) {
+        const int i = base + lane;
+        const bool r = i < U.n_rows && U.rflag[i] != 0;
+        if (r) U.rflag[i] = 0;
+        bool c = false;
+        if (i < U.n_chunks) {
+            const bool own = U.cflag[i] != 0;
+            if (own) U.cflag[i] = 0;
+            c = own || U.hflag[U.hub_chunk[i].x] != 0;
         }
-        incl[r] = t;
-        if (lane == 63) ws[r][wave] = t;
-    }
-    __syncthreads();
-    int base = 0;
-#pragma unroll
-    for (int r = 0; r < kScoreBins; ++r) {
-        int before = 0, total = 0;
-#pragma unroll
-        for (int w = 0; w < kBlock / 64; ++w) {
-            if (w < wave) before += ws[r][w];
-            total += ws[r][w];
-        }
-        int pos = base + before + incl[r] - (x[r][0] + x[r][1] + x[r][2] + x[r][3]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (j0 + i < groups) ucnt[r * groups + j0 + i] = pos;
-            pos += x[r][i];
-        }
-        if (threadIdx.x == 0) ictr[kIcBins + r] = (unsigned long long)total;
-        base += total;
-    }
-    if (threadIdx.x == 0) {
-        long long aff = 0;
-        for (int w = 0; w < kBlock / 64; ++w) aff += ws[kScoreBins][w];
-        ictr[kIcAffected] = (unsigned long long)aff;
-        ictr[kIcAList] = (unsigned long long)base;
-        ictr[kIcWmaxOld] = ctr->wmax_bits;
+        wave_append(r, i, U.rlist, &ictr[kIcRows]);
+        wave_append(c && i < U.n_chunks_lds, i, U.slist, &ictr[kIcMain]);
+        wave_append(c && i >= U.n_chunks_lds, i - U.n_chunks_lds, U.hlist, &ictr[kIcBig]);
     }
 }
 
-// Each range's affected tile vertices to their bins' slots (any order inside
-// a range and bin; a vertex's score does not depend on its unit); the marks
-// are cleared.
+// The first `groups` workgroups place their range's affected tile vertices in
+// their bins (any order inside a range and bin; a vertex's score does not
+// depend on its unit) and clear the marks; the others make the lists.  The
+// first workgroup also leaves the bins' totals and w_max before the pass in
+// the counters, what the host reports in pinned memory, and the next
+// re-score's counters cleared.
+static_assert(kUnitGroups == 2 * kBlock, "k_units_place sums two ranges per thread");
 __global__ __launch_bounds__(kBlock) void k_units_place(unsigned int *vmark, const int32_t *vscore,
                                                         const int32_t *goff, long long n, const int32_t *ucnt,
-                                                        int32_t *abin) {
+                                                        int groups, int32_t *abin, UnitLists U,
+                                                        unsigned long long *ictr, unsigned long long *ictr_next,
+                                                        const DevCounters *ctr, RemovalCounts *host) {
+    if ((int)blockIdx.x >= groups) {
+        unit_lists(U, (int)blockIdx.x - groups, (int)gridDim.x - groups, ictr);
+        return;
+    }
     __shared__ int s_cur[kScoreBins];
-    if (threadIdx.x < kScoreBins) s_cur[threadIdx.x] = ucnt[threadIdx.x * gridDim.x + blockIdx.x];
+    __shared__ int s_sum[kUnitRows][2][kBlock / 64];  // before this range; of all ranges
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    {
+        int2 x[kUnitRows];
+        const int j = 2 * (int)threadIdx.x;
+#pragma unroll
+        for (int r = 0; r < kUnitRows; ++r) {
+            x[r] = *(const int2 *)&ucnt[r * kUnitGroups + j];
+            if (j >= groups) x[r].x = 0;
+            if (j + 1 >= groups) x[r].y = 0;
+        }
+#pragma unroll
+        for (int r = 0; r < kUnitRows; ++r) {
+            int all = x[r].x + x[r].y;
+            int before = (j < (int)blockIdx.x ? x[r].x : 0) + (j + 1 < (int)blockIdx.x ? x[r].y : 0);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                all += __shfl_xor(all, o);
+                before += __shfl_xor(before, o);
+            }
+            if (lane == 0) {
+                s_sum[r][0][wave] = before;
+                s_sum[r][1][wave] = all;
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < kUnitRows) {
+        const int r = threadIdx.x;
+        int at = 0, total = 0;
+        for (int q = 0; q <= r; ++q) {
+            at += total;
+            total = 0;
+            for (int w = 0; w < kBlock / 64; ++w) total += s_sum[q][1][w];
+        }
+        for (int w = 0; w < kBlock / 64; ++w) at += s_sum[r][0][w];
+        if (r < kScoreBins) s_cur[r] = at;
+        if (blockIdx.x == 0 && r < kScoreBins) ictr[kIcBins + r] = (unsigned long long)total;
+        if (blockIdx.x == 0 && r == kScoreBins) {
+            ictr[kIcWmaxOld] = ctr->wmax_bits;
+            host->edges = ictr[kIcEdges];
+            host->vertex_edges = ictr[kIcVertexEdges];
+            host->vertices = ictr[kIcVertices];
+            host->affected = (unsigned long long)total;
+            __threadfence_system();
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x < kIcCount) ictr_next[threadIdx.x] = 0ull;
     __syncthreads();
     long long lo, hi;
-    unit_range(n, lo, hi);
+    unit_range(n, groups, lo, hi);
     for (long long v0 = lo + threadIdx.x; v0 < hi; v0 += (long long)kMarkPer * kBlock) {
         unsigned int mk[kMarkPer];
         load_marks(vmark, v0, hi, mk);
@@ -4498,45 +4555,6 @@ __global__ __launch_bounds__(kBlock) void k_units_place(unsigned int *vmark, con
     }
 }
 
-// Append the lanes' values whose pred holds to list (one atomic per
-// wavefront; all lanes call it).
-__device__ __forceinline__ void wave_append(bool pred, int val, int32_t *list, unsigned long long *count) {
-    const int lane = threadIdx.x & 63;
-    const unsigned long long m = __ballot(pred);
-    if (!m) return;
-    unsigned long long first = 0;
-    if (lane == 0) first = atomicAdd(count, (unsigned long long)__popcll(m));
-    first = __shfl(first, 0);
-    if (pred) list[first + __popcll(m & ((1ull << lane) - 1ull))] = val;
-}
-
-// Flags -> the incremental launches' lists (indices of the full launches):
-// the flagged row blocks, and the score-hub chunks to rerun, each chunk of a
-// hub flagged whole and each chunk flagged by itself (the main list takes
-// the LDS-hub chunks, the big list the others).  Clears the row and chunk
-// flags; the hub flags are cleared by the score pass that follows.
-__global__ __launch_bounds__(kBlock) void k_unit_lists(uint8_t *rflag, int n_rows, uint8_t *cflag,
-                                                       const uint8_t *hflag, const int2 *hub_chunk, int n_chunks,
-                                                       int n_chunks_lds, int32_t *rlist, int32_t *slist,
-                                                       int32_t *hlist, unsigned long long *ictr) {
-    const int lane = threadIdx.x & 63;
-    const int top = max(n_rows, n_chunks);
-    for (int base = blockIdx.x * kBlock + (threadIdx.x & ~63); base < top; base += gridDim.x * kBlock) {
-        const int i = base + lane;
-        const bool r = i < n_rows && rflag[i] != 0;
-        if (r) rflag[i] = 0;
-        bool c = false;
-        if (i < n_chunks) {
-            const bool own = cflag[i] != 0;
-            if (own) cflag[i] = 0;
-            c = own || hflag[hub_chunk[i].x] != 0;
-        }
-        wave_append(r, i, rlist, &ictr[kIcRows]);
-        wave_append(c && i < n_chunks_lds, i, slist, &ictr[kIcMain]);
-        wave_append(c && i >= n_chunks_lds, i - n_chunks_lds, hlist, &ictr[kIcBig]);
-    }
-}
-
 template <typename OffT>
 static rs_status incremental_marks_t(rs_graph *g) {
     DeviceGraph &D = g->d;
@@ -4545,21 +4563,26 @@ static rs_status incremental_marks_t(rs_graph *g) {
     const int gn = grid_for(D.n, kBlock, 1024);
     hipLaunchKernelGGL(k_compact_rows<OffT>, dim3(gn), dim3(kBlock), 0, g->stream, off, D.deg, D.col, D.clab,
                        D.lab, D.goff, D.fcol, D.elist, &D.ictr[kIcChanged]);
-    hipLaunchKernelGGL(k_row_chunks, dim3(gn), dim3(kBlock), 0, g->stream, D.deg, D.elist, &D.ictr[kIcChanged],
-                       D.echunk, &D.ictr[kIcChunks]);
     hipLaunchKernelGGL(k_mark_link<OffT>, dim3(gn), dim3(kBlock), 0, g->stream, link_args<OffT>(g), D.vmark,
                        (const int32_t *)D.vscore, (const int32_t *)D.shub_first, D.cflag, D.elist, D.echunk,
                        &D.ictr[kIcChunks]);
     const int ug = grid_for(D.n, kBlock, kUnitGroups);
     hipLaunchKernelGGL(k_units_count, dim3(ug), dim3(kBlock), 0, g->stream, D.vmark, D.vrowb, D.vscore, D.goff,
                        (long long)D.n, D.rflag, D.hflag, D.ucnt);
-    hipLaunchKernelGGL(k_units_scan, dim3(1), dim3(kBlock), 0, g->stream, D.ucnt, ug, D.ictr, D.ctr);
-    hipLaunchKernelGGL(k_units_place, dim3(ug), dim3(kBlock), 0, g->stream, D.vmark, D.vscore, D.goff,
-                       (long long)D.n, D.ucnt, D.abin);
-    const int top = std::max(g->grid_rows, g->n_schunks);
-    hipLaunchKernelGGL(k_unit_lists, dim3(grid_for(top, kBlock, 4096)), dim3(kBlock), 0, g->stream, D.rflag,
-                       g->grid_rows, D.cflag, (const uint8_t *)D.hflag, (const int2 *)D.shub_chunk, g->n_schunks,
-                       g->n_schunks_lds, D.rlist, D.slist, D.hlist, D.ictr);
+    UnitLists U;
+    U.rflag = D.rflag;
+    U.cflag = D.cflag;
+    U.hflag = D.hflag;
+    U.hub_chunk = D.shub_chunk;
+    U.n_rows = g->grid_rows;
+    U.n_chunks = g->n_schunks;
+    U.n_chunks_lds = g->n_schunks_lds;
+    U.rlist = D.rlist;
+    U.slist = D.slist;
+    U.hlist = D.hlist;
+    const int lg = grid_for(std::max(g->grid_rows, g->n_schunks), kBlock, 4096);
+    hipLaunchKernelGGL(k_units_place, dim3(ug + lg), dim3(kBlock), 0, g->stream, D.vmark, D.vscore, D.goff,
+                       (long long)D.n, D.ucnt, ug, D.abin, U, D.ictr, D.ictr_next, D.ctr, g->rem_cnt_host);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? RS_OK : hip_fail(e, "incremental marks launch");
 }
