@@ -2340,17 +2340,15 @@ rs_status launch_load_slots(rs_graph *g, int32_t *count, long long *sums) {
     return e == hipSuccess ? RS_OK : hip_fail(e, "slot load launch");
 }
 
-template <typename OffT>
 struct LinkArgs {
-    const OffT *off;
-    const int32_t *deg, *col, *lab, *cstart;
+    const int32_t *lab, *cstart;
     const int32_t *goff, *fcol;
     const int64_t *oo;
     PairLink *plink;
     const int32_t *outl;        // out-lists (tombstones complemented)
     OutEnt *oe;                 // each out-list entry's leader slots
     const unsigned int *vmark;  // after removals: kRowChanged marks the rows that changed
-    const VMeta *meta;          // the last pass's own-run bounds [p, q) of the unchanged rows
+    const VMeta *meta;          // after removals: the rows' facts (ell: the last pass's)
 };
 
 // The last x in [0, n) with off[x] <= s.
@@ -2370,8 +2368,7 @@ __device__ __forceinline__ int owner_of(const T *off, long long n, long long s) 
 // Every slot's link (at load, when the lists are whole).  run_walk[0] gets
 // the sum of the slots' distances to their leaders: half the steps in which
 // the pairs would walk each other's runs.
-template <typename OffT>
-__global__ __launch_bounds__(kBlock) void k_links(LinkArgs<OffT> L, long long n, long long slots,
+__global__ __launch_bounds__(kBlock) void k_links(LinkArgs L, long long n, long long slots,
                                                   unsigned long long *run_walk) {
     unsigned long long walk = 0;
     for (long long s = (long long)blockIdx.x * kBlock + threadIdx.x; s < slots; s += (long long)gridDim.x * kBlock) {
@@ -2402,13 +2399,9 @@ __global__ __launch_bounds__(kBlock) void k_links(LinkArgs<OffT> L, long long n,
     }
 }
 
-template <typename OffT>
-static LinkArgs<OffT> link_args(rs_graph *g) {
+static LinkArgs link_args(rs_graph *g) {
     DeviceGraph &D = g->d;
-    LinkArgs<OffT> L;
-    L.off = (const OffT *)D.off;
-    L.deg = D.deg;
-    L.col = D.col;
+    LinkArgs L;
     L.lab = D.lab;
     L.cstart = D.cstart;
     L.goff = D.goff;
@@ -2422,19 +2415,14 @@ static LinkArgs<OffT> link_args(rs_graph *g) {
     return L;
 }
 
-template <typename OffT>
-static rs_status links_t(rs_graph *g, unsigned long long *run_walk) {
+rs_status launch_links(rs_graph *g, unsigned long long *run_walk) {
     DeviceGraph &D = g->d;
     const long long slots = 2 * g->n_out;  // each G' edge has one out-list entry and two slots
     if (slots == 0) return RS_OK;
-    hipLaunchKernelGGL(k_links<OffT>, dim3(grid_for(slots, kBlock, 4096)), dim3(kBlock), 0, g->stream,
-                       link_args<OffT>(g), (long long)D.n, slots, run_walk);
+    hipLaunchKernelGGL(k_links, dim3(grid_for(slots, kBlock, 4096)), dim3(kBlock), 0, g->stream, link_args(g),
+                       (long long)D.n, slots, run_walk);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? RS_OK : hip_fail(e, "link-slot launch");
-}
-
-rs_status launch_links(rs_graph *g, unsigned long long *d_run_walk) {
-    return g->d.off64 ? links_t<long long>(g, d_run_walk) : links_t<int32_t>(g, d_run_walk);
 }
 
 // The tile vertices' slots: each one's vertex, as its index in its score tile
@@ -2459,8 +2447,7 @@ rs_status launch_slot_owners(rs_graph *g) {
 
 // Each out-list entry x -> y (at load): the leader slots of C(y)'s run in x's
 // list and of C(x)'s run in y's list; the owner x is the last with oo[x] <= o.
-template <typename OffT>
-__global__ __launch_bounds__(kBlock) void k_out_entries(LinkArgs<OffT> L, long long n, long long n_out) {
+__global__ __launch_bounds__(kBlock) void k_out_entries(LinkArgs L, long long n, long long n_out) {
     for (long long o = (long long)blockIdx.x * kBlock + threadIdx.x; o < n_out; o += (long long)gridDim.x * kBlock) {
         const int x = owner_of(L.oo, n, o);
         const int y = out_id(L.outl[o]);
@@ -2477,19 +2464,14 @@ __global__ __launch_bounds__(kBlock) void k_out_entries(LinkArgs<OffT> L, long l
     }
 }
 
-template <typename OffT>
-static rs_status out_entries_t(rs_graph *g) {
+rs_status launch_out_entries(rs_graph *g) {
     DeviceGraph &D = g->d;
     const long long n_out = g->n_out;
     if (n_out == 0) return RS_OK;
-    hipLaunchKernelGGL(k_out_entries<OffT>, dim3(grid_for(n_out, kBlock, 65536)), dim3(kBlock), 0, g->stream,
-                       link_args<OffT>(g), (long long)D.n, n_out);
+    hipLaunchKernelGGL(k_out_entries, dim3(grid_for(n_out, kBlock, 65536)), dim3(kBlock), 0, g->stream, link_args(g),
+                       (long long)D.n, n_out);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? RS_OK : hip_fail(e, "out-entry launch");
-}
-
-rs_status launch_out_entries(rs_graph *g) {
-    return g->d.off64 ? out_entries_t<long long>(g) : out_entries_t<int32_t>(g);
 }
 
 // Each entry's neighbour community (once at load; compaction moves it with
@@ -3912,20 +3894,6 @@ struct OutLists {
     unsigned int *vmark;
 };
 
-// Tombstone y in out(x), if there; returns whether it was found.  Only the
-// request that deleted the edge gets here, so the store does not race.
-__device__ __forceinline__ bool out_drop(const OutLists &O, int x, int y) {
-    const long long o0 = O.oo[x];
-    const int32_t *row[1] = {O.outl + o0};
-    const int d[1] = {(int)(O.oo[x + 1] - o0)};
-    const int key[1] = {y};
-    int k[1];
-    lower_n<1, true>(row, d, key, k);
-    if (k[0] >= d[0] || O.outl[o0 + k[0]] != y) return false;
-    O.outl[o0 + k[0]] = ~y;
-    return true;
-}
-
 // Delete the undirected edge {a, b}; the entry in the row of min(a, b) is
 // the owner and decides which request wins.  Returns 1 if deleted here; nx
 // and ny tell whether the rows of min(a, b) and max(a, b) were marked changed
@@ -3935,28 +3903,34 @@ template <typename OffT>
 __device__ __forceinline__ int delete_edge(const OffT *off, const int32_t *deg, int32_t *col, const OutLists &O,
                                            int a, int b, bool &nx, bool &ny) {
     const int x = min(a, b), y = max(a, b);
-    // y in x's row and x in y's row, searched together (entries keep their
-    // places until the compaction, so the second position stays valid)
-    const long long xb = (long long)off[x], yb = (long long)off[y];
-    const int32_t *rows[2] = {col + xb, col + yb};
-    const int ds[2] = {deg[x], deg[y]};
-    const int keys[2] = {y, x};
-    int k[2];
-    lower_n<2, true>(rows, ds, keys, k);
+    // y in x's row and x in y's, and the same in the out-lists of an edge
+    // between communities, searched together (entries keep their places until
+    // the compaction, so the positions stay valid)
+    const long long xb = (long long)off[x], yb = (long long)off[y], xo = (long long)O.oo[x], yo = (long long)O.oo[y];
+    const bool foreign = O.lab[x] != O.lab[y];
+    const int32_t *rows[4] = {col + xb, col + yb, O.outl + xo, O.outl + yo};
+    const int ds[4] = {deg[x], deg[y], foreign ? (int)(O.oo[x + 1] - xo) : 0, foreign ? (int)(O.oo[y + 1] - yo) : 0};
+    const int keys[4] = {y, x, y, x};
+    int k[4];
+    lower_n<4, true>(rows, ds, keys, k);
     if (k[0] >= ds[0] || decode(col[xb + k[0]]) != y) return 0;
     if (atomicCAS(&col[xb + k[0]], y, ~y) != y) return 0;
+    // only the request that deleted the edge gets here
     if (k[1] < ds[1] && decode(col[yb + k[1]]) == x) col[yb + k[1]] = ~x;
     nx = (atomicOr(&O.vmark[x], kRowChanged) & kRowChanged) == 0u;
     ny = (atomicOr(&O.vmark[y], kRowChanged) & kRowChanged) == 0u;
-    if (O.lab[x] != O.lab[y] && !out_drop(O, x, y)) out_drop(O, y, x);
+    if (k[2] < ds[2] && O.outl[xo + k[2]] == y)
+        O.outl[xo + k[2]] = ~y;
+    else if (k[3] < ds[3] && O.outl[yo + k[3]] == x)
+        O.outl[yo + k[3]] = ~x;
     return 1;
 }
 
 // What the removals append to: the changed rows and, one by one, their chunks
-// of 64 entries (row's list index, chunk), at least one per row.  The chunks
-// count the row's length before; those beyond its new end are empty.
+// of 64 foreign entries (row's list index, chunk), at least one per row.  The
+// chunks count the row's slots; those beyond its foreign list are empty.
 struct ChangedRows {
-    const int32_t *deg;
+    const int32_t *deg, *goff;
     int32_t *list;
     int2 *chunks;
     unsigned long long *ictr;
@@ -3970,7 +3944,8 @@ __device__ __forceinline__ void append_changed(int x, bool nx, int y, bool ny, c
     const unsigned long long mx = __ballot(nx), my = __ballot(ny);
     const int tot = __popcll(mx) + __popcll(my);
     if (tot == 0) return;
-    const int cx = nx ? max(1, (C.deg[x] + 63) >> 6) : 0, cy = ny ? max(1, (C.deg[y] + 63) >> 6) : 0;
+    const int cx = nx ? max(1, (C.goff[x + 1] - C.goff[x] + 63) >> 6) : 0;
+    const int cy = ny ? max(1, (C.goff[y + 1] - C.goff[y] + 63) >> 6) : 0;
     int incl = cx + cy;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -4058,7 +4033,7 @@ rs_status launch_remove(rs_graph *g, const int32_t *src, const int32_t *dst, int
     DeviceGraph &D = g->d;
     const int eb = m > 0 ? grid_for(m, 256, 4096) : 0, vb = nv > 0 ? grid_for(nv, 4, 4096) : 0;
     if (eb + vb == 0) return RS_OK;
-    const ChangedRows C = {D.deg, D.elist, D.echunk, D.ictr};
+    const ChangedRows C = {D.deg, D.goff, D.elist, D.echunk, D.ictr};
     if (D.off64)
         hipLaunchKernelGGL(k_remove<long long>, dim3(eb + vb), dim3(256), 0, g->stream, (const long long *)D.off,
                            D.col, out_lists(g), D.alive, C, src, dst, (long long)m, eb, verts, (long long)nv);
@@ -4086,12 +4061,14 @@ rs_status launch_remove(rs_graph *g, const int32_t *src, const int32_t *dst, int
 // one wavefront per row, kCompactGroups groups of 64 entries loaded at once
 // (a hub's long row takes one round trip per 1,024 entries), each group
 // packed by a ballot and prefix (the foreign ones also into the row's slots);
-// the freed tail of the capacity is set to -1.
+// the freed tail of the capacity is set to -1.  The row's facts follow at
+// once, so the marks read every foreign list's length from them.
 constexpr int kCompactGroups = 16;
 template <typename OffT>
 __global__ __launch_bounds__(kBlock) void k_compact_rows(const OffT *off, int32_t *deg, int32_t *col, int32_t *clab,
                                                          const int32_t *lab, const int32_t *goff, int32_t *fcol,
-                                                         const int32_t *list, const unsigned long long *count) {
+                                                         VMeta *meta, const int32_t *list,
+                                                         const unsigned long long *count) {
     const long long nl = (long long)*count;
     const int lane = threadIdx.x & 63;
     for (long long i = ((long long)blockIdx.x * kBlock + threadIdx.x) >> 6; i < nl;
@@ -4100,7 +4077,7 @@ __global__ __launch_bounds__(kBlock) void k_compact_rows(const OffT *off, int32_
         const long long rb = (long long)off[v];
         const int d = deg[v];
         const int cv = lab[v], go = goff[v];
-        int w = 0, wf = 0;
+        int w = 0, wf = 0, p = 0;  // entries kept, foreign ones, those of them before the own run
         for (int j0 = 0; j0 < d; j0 += 64 * kCompactGroups) {  // groups of 64 entries loaded at once
             int x[kCompactGroups], c[kCompactGroups];
 #pragma unroll
@@ -4113,6 +4090,7 @@ __global__ __launch_bounds__(kBlock) void k_compact_rows(const OffT *off, int32_
             for (int t = 0; t < kCompactGroups; ++t) {
                 const unsigned long long m = __ballot(x[t] >= 0), mf = __ballot(x[t] >= 0 && c[t] != cv);
                 const unsigned long long lt = (1ull << lane) - 1ull;
+                p += __popcll(__ballot(x[t] >= 0 && c[t] != cv && x[t] < v));
                 if (x[t] >= 0) {
                     const long long to = rb + w + __popcll(m & lt);
                     col[to] = x[t];
@@ -4127,29 +4105,14 @@ __global__ __launch_bounds__(kBlock) void k_compact_rows(const OffT *off, int32_
             col[rb + j] = -1;
             clab[rb + j] = -1;
         }
-        if (lane == 0) deg[v] = w;
-    }
-}
-
-// The marks of the pair (x, w) of a member x of C(v) in the row of v's
-// foreign neighbour w (the pair sums a_v): a score hub whose row did not
-// change flags the chunk holding the pair (w's place in x's foreign list);
-// any other x is affected whole.
-template <typename OffT>
-__device__ __forceinline__ void mark_run_member(const LinkArgs<OffT> &L, unsigned int *vmark, const int32_t *vscore,
-                                                const int32_t *hub_first, uint8_t *cflag, int x, int w) {
-    const int sx = vscore[x];
-    if (sx < 0 && !(L.vmark[x] & kRowChanged)) {
-        const int32_t *row[1] = {L.col + L.off[x]};
-        const int d[1] = {L.deg[x]};
-        const int key[1] = {w};
-        int k[1];
-        lower_n<1, false>(row, d, key, k);
-        const VMeta m = L.meta[x];
-        const int kx = k[0] < m.p ? k[0] : k[0] - (m.q - m.p);
-        cflag[hub_first[-1 - sx] + kx / kScoreTileP] = 1;
-    } else {
-        atomicOr(&vmark[x], kAffected);
+        if (lane == 0) {
+            deg[v] = w;
+            VMeta m = meta[v];  // (ell comes with the row pass)
+            m.deg = w;
+            m.p = p;
+            m.q = p + w - wf;
+            meta[v] = m;
+        }
     }
 }
 
@@ -4172,9 +4135,8 @@ __device__ __forceinline__ int flat_owner(const int *pre, int g, int &idx) {
 // pair; a hub next to a longer changed row is rescored whole.
 constexpr int kTriRow = 512;
 
-// After removals, one wavefront per chunk of 64 entries of a changed
-// (compacted) row v (chunks: append_changed), for each entry (v, w) with w in
-// another community:
+// After removals, one wavefront per chunk of 64 entries (v, w) of a changed
+// (compacted) row v's foreign list (chunks: append_changed):
 // * links: v's link for the entry, and the leader and slot in v's list, which
 //   moved with v's row, in w's link back to v;
 // * marks: v is affected whole.  The pairs whose terms read v's row are
@@ -4186,11 +4148,15 @@ constexpr int kTriRow = 512;
 //   score hub whose own row did not change flags only the chunks holding the
 //   pairs (the others keep their partials), so a changed vertex next to a
 //   hub costs a few chunks, not the hub.
-// The long lists of (b) and (c) are worked by the whole wavefront (items
-// flattened over the lanes).  Only the kRowChanged bits, set by the
-// removals before, are read.
-template <typename OffT>
-__global__ __launch_bounds__(kBlock) void k_mark_link(LinkArgs<OffT> L, unsigned int *vmark, const int32_t *vscore,
+// Dependent loads bound it, so the searches run on the foreign lists (a tenth
+// of the rows at a mixing of 0.1, which also leaves fewer chunks) and the long
+// lists of (b) and (c) are worked by the whole wavefront, kMarkItems items a
+// lane at once (flattened over the lanes): 205 ids removed at n = 1 million
+// 21 us, 39 on whole rows one item at a time (1, 4 or 8 items, or searches of
+// four ways: the same there).  Only the kRowChanged bits, set by the removals
+// before, are read.
+constexpr int kMarkItems = 4;
+__global__ __launch_bounds__(kBlock) void k_mark_link(LinkArgs L, unsigned int *vmark, const int32_t *vscore,
                                                       const int32_t *hub_first, uint8_t *cflag, const int32_t *rows,
                                                       const int2 *chunks, const unsigned long long *n_chunks) {
     __shared__ int s_pre[kBlock / 64][64];
@@ -4202,85 +4168,58 @@ __global__ __launch_bounds__(kBlock) void k_mark_link(LinkArgs<OffT> L, unsigned
         const int2 it = chunks[q];
         const int v = rows[it.x];
         if (it.y == 0 && lane == 0) atomicOr(&vmark[v], kAffected);
-        const long long rb = (long long)L.off[v];
-        const int dv = L.deg[v];
-        const int cv = L.lab[v];
-        const int id0 = L.cstart[cv], id1 = L.cstart[cv + 1];
+        const VMeta mv = L.meta[v];
+        const int gv = L.goff[v], fv = L.goff[v + 1] - gv;  // fv: the load-time foreign degree
+        const int cv = L.lab[v], dfv = mv.deg - (mv.q - mv.p);
+        const int32_t *rowv = L.fcol + gv;
         const int j = it.y * 64 + lane;
-        int w = 0, cw = cv;
-        if (j < dv) {
-            w = L.col[rb + j];
-            cw = L.lab[w];
-        }
-        const bool fw = j < dv && cw != cv;
-        long long wb = 0;
-        int dw = 0, k0 = 0, k1 = 0, wh = 0, pw = 0, qw = 0;
+        if (it.y * 64 >= dfv) continue;
+        const int id0 = L.cstart[cv], id1 = L.cstart[cv + 1];
+        const bool in = j < dfv;
+        int w = 0, cw = cv, gw = 0, dfw = 0, k0 = 0, k1 = 0, wh = 0;
         bool whub = false;  // w: a score hub with its row unchanged
-        if (fw) {
-            wb = (long long)L.off[w];
-            dw = L.deg[w];
-            const int32_t *roww = L.col + wb;
-            // in w's row: C(v)'s run [k[0], k[1]) and the entry (w, v) at
-            // k[2]; in v's row: v's own run [k[3], k[4]) and the start of
-            // C(w)'s run at k[5]
-            const int32_t *rws[6] = {roww, roww, roww, L.col + rb, L.col + rb, L.col + rb};
-            const int ds[6] = {dw, dw, dw, dv, dv, dv};
-            const int keys[6] = {id0, id1, v, id0, id1, L.cstart[cw]};
-            int k[6];
-            lower_n<6, false>(rws, ds, keys, k);
+        if (in) {
+            w = rowv[j];
+            cw = L.lab[w];
+            gw = L.goff[w];
+            const int fw = L.goff[w + 1] - gw, sw = vscore[w];
+            const unsigned int mkw = L.vmark[w];
+            const VMeta mw = L.meta[w];
+            dfw = mw.deg - (mw.q - mw.p);
+            // the out-list entry of {v, w} is in the list of the lower rank:
+            // load-time foreign degree, then id
+            const bool v_low = fv < fw || (fv == fw && v < w);
+            const int a = v_low ? v : w, bkey = v_low ? w : v;
+            const long long o0 = L.oo[a], wo = v_low ? L.oo[w] : o0;
+            const int won = (int)(L.oo[w + 1] - wo), od = v_low ? (int)(L.oo[v + 1] - o0) : won;
+            // in w's foreign list: C(v)'s run [k[0], k[1]) and the entry
+            // (w, v) at k[2]; in v's: the start of C(w)'s run at k[3]; the
+            // out-list entry at k[4]
+            const int32_t *roww = L.fcol + gw;
+            const int32_t *rws[5] = {roww, roww, roww, rowv, L.outl + o0};
+            const int ds[5] = {dfw, dfw, dfw, dfv, od};
+            const int keys[5] = {id0, id1, v, L.cstart[cw], bkey};
+            int k[5];
+            lower_n<5, true>(rws, ds, keys, k);
             k0 = k[0];
             k1 = k[1];
-            const int ew = k[2], pv = k[3], hv = k[4] - k[3], lv = k[5];
-            const int gv = L.goff[v], gw = L.goff[w];
-            // w's own run is the last pass's when w's row did not change
-            const bool wch = (L.vmark[w] & kRowChanged) != 0u;
-            if (wch) {
-                const int32_t *rw2[2] = {roww, roww};
-                const int dw2[2] = {dw, dw};
-                const int kw2[2] = {L.cstart[cw], L.cstart[cw + 1]};
-                int pq[2];
-                lower_n<2, false>(rw2, dw2, kw2, pq);
-                pw = pq[0];
-                qw = pq[1];
-            } else {
-                const VMeta m = L.meta[w];
-                pw = m.p;
-                qw = m.q;
-            }
-            // the slots of (v, w) and (w, v), and the leaders of C(w)'s run
-            // in v's list and of C(v)'s run in w's
-            const int kw = ew < pw ? ew : ew - (qw - pw);
-            const int sv = gv + (j < pv ? j : j - hv), sw_ = gw + kw;
-            const int ldv = gv + (lv < pv ? lv : lv - hv), ldw = gw + (k0 < pw ? k0 : k0 - (qw - pw));
+            const int kw = k[2], sv = gv + j, sw_ = gw + kw;
+            const int ldv = gv + k[3], ldw = gw + k0;  // the runs' leaders
             PairLink pl;
             pl.lead = ldw;
             pl.slot = sw_;
-            pl.oo = (int)L.oo[w];
-            pl.on = (int)(L.oo[w + 1] - L.oo[w]);
+            pl.oo = (int)wo;
+            pl.on = won;
             L.plink[sv] = pl;
             L.plink[sw_].lead = ldv;
             L.plink[sw_].slot = sv;
-            {
-                // the out-list entry of {v, w} (in the list of the lower
-                // rank: load-time foreign degree, then id) gets both leaders
-                const int fv = L.goff[v + 1] - gv, fw = L.goff[w + 1] - gw;
-                const bool v_low = fv < fw || (fv == fw && v < w);
-                const int a = v_low ? v : w, bkey = v_low ? w : v;
-                const long long o0 = L.oo[a];
-                const int32_t *orow[1] = {L.outl + o0};
-                const int od[1] = {(int)(L.oo[a + 1] - o0)};
-                const int okey[1] = {bkey};
-                int ok[1];
-                lower_n<1, true>(orow, od, okey, ok);
-                if (ok[0] < od[0] && L.outl[o0 + ok[0]] == bkey) {
-                    OutEnt e;
-                    e.xy = v_low ? ldv : ldw;
-                    e.yx = v_low ? ldw : ldv;
-                    L.oe[o0 + ok[0]] = e;
-                }
+            if (k[4] < od && L.outl[o0 + k[4]] == bkey) {
+                OutEnt e;
+                e.xy = v_low ? ldv : ldw;
+                e.yx = v_low ? ldw : ldv;
+                L.oe[o0 + k[4]] = e;
             }
-            const int sw = vscore[w];
-            whub = sw < 0 && !wch;
+            whub = sw < 0 && !(mkw & kRowChanged);
             if (whub) {
                 wh = -1 - sw;
                 cflag[hub_first[wh] + kw / kScoreTileP] = 1;  // (a)
@@ -4288,9 +4227,11 @@ __global__ __launch_bounds__(kBlock) void k_mark_link(LinkArgs<OffT> L, unsigned
                 atomicOr(&vmark[w], kAffected);
             }
         }
-        // (c) the runs of C(v) in the foreign neighbours' rows
+        // (c) the runs of C(v) in the foreign neighbours' lists: a score hub
+        // whose row did not change flags the chunk holding the pair (x, w)
+        // (w's place in x's foreign list); any other x is affected whole
         {
-            const int cnt = fw ? k1 - k0 : 0;
+            const int cnt = k1 - k0;
             int incl = cnt;
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
@@ -4300,13 +4241,34 @@ __global__ __launch_bounds__(kBlock) void k_mark_link(LinkArgs<OffT> L, unsigned
             pre[lane] = incl;
             const int total = __shfl(incl, 63);
             wave_sync();
-            for (int g0 = 0; g0 < total; g0 += 64) {
-                const int g = g0 + lane;
-                int idx = 0, l = 0;
-                if (g < total) l = flat_owner(pre, g, idx);
-                const int wl = __shfl(w, l), kl = __shfl(k0, l);
-                const long long wbl = ((long long)__shfl((int)(wb >> 32), l) << 32) | (unsigned int)__shfl((int)wb, l);
-                if (g < total) mark_run_member(L, vmark, vscore, hub_first, cflag, L.col[wbl + kl + idx], wl);
+            for (int g0 = 0; g0 < total; g0 += 64 * kMarkItems) {
+                int x[kMarkItems], wx[kMarkItems], sx[kMarkItems];
+#pragma unroll
+                for (int t = 0; t < kMarkItems; ++t) {
+                    const int g = g0 + 64 * t + lane;
+                    int idx = 0, l = 0;
+                    if (g < total) l = flat_owner(pre, g, idx);
+                    const int at = __shfl(gw + k0, l);
+                    wx[t] = __shfl(w, l);
+                    x[t] = g < total ? L.fcol[at + idx] : -1;
+                }
+#pragma unroll
+                for (int t = 0; t < kMarkItems; ++t) sx[t] = x[t] >= 0 ? vscore[x[t]] : 0;
+#pragma unroll
+                for (int t = 0; t < kMarkItems; ++t) {
+                    if (x[t] < 0) continue;
+                    if (sx[t] < 0 && !(L.vmark[x[t]] & kRowChanged)) {
+                        const VMeta m = L.meta[x[t]];
+                        const int32_t *row[1] = {L.fcol + L.goff[x[t]]};
+                        const int d[1] = {m.deg - (m.q - m.p)};
+                        const int key[1] = {wx[t]};
+                        int kx[1];
+                        lower_n<1, false>(row, d, key, kx);
+                        cflag[hub_first[-1 - sx[t]] + kx[0] / kScoreTileP] = 1;
+                    } else {
+                        atomicOr(&vmark[x[t]], kAffected);
+                    }
+                }
             }
             wave_sync();
         }
@@ -4314,10 +4276,10 @@ __global__ __launch_bounds__(kBlock) void k_mark_link(LinkArgs<OffT> L, unsigned
         // (w, y) for the foreign neighbours y of v in a third community
         const unsigned long long hubs = __ballot(whub);
         if (hubs) {
-            if (dv > kTriRow) {  // too long to intersect: the hub reruns whole
+            if (mv.deg > kTriRow) {  // too long to intersect: the hub reruns whole
                 if (whub) atomicOr(&vmark[w], kAffected);
             } else {
-                const int cnt = whub ? dv : 0;
+                const int cnt = whub ? dfv : 0;
                 int incl = cnt;
 #pragma unroll
                 for (int o = 1; o < 64; o <<= 1) {
@@ -4327,29 +4289,27 @@ __global__ __launch_bounds__(kBlock) void k_mark_link(LinkArgs<OffT> L, unsigned
                 pre[lane] = incl;
                 const int total = __shfl(incl, 63);
                 wave_sync();
-                for (int g0 = 0; g0 < total; g0 += 64) {
-                    const int g = g0 + lane;
-                    int t = 0, l = 0;
-                    if (g < total) l = flat_owner(pre, g, t);
-                    const int cwl = __shfl(cw, l), hl = __shfl(wh, l), pwl = __shfl(pw, l), qwl = __shfl(qw, l),
-                              dwl = __shfl(dw, l);
-                    const long long wbl =
-                        ((long long)__shfl((int)(wb >> 32), l) << 32) | (unsigned int)__shfl((int)wb, l);
-                    if (g < total) {
-                        const int y = L.col[rb + t];
-                        const int cy = L.lab[y];
-                        if (cy != cv && cy != cwl) {
-                            const int32_t *row[1] = {L.col + wbl};
-                            const int d[1] = {dwl};
-                            const int key[1] = {y};
-                            int k[1];
-                            lower_n<1, false>(row, d, key, k);
-                            if (k[0] < dwl && L.col[wbl + k[0]] == y) {
-                                const int ky = k[0] < pwl ? k[0] : k[0] - (qwl - pwl);
-                                cflag[hub_first[hl] + ky / kScoreTileP] = 1;
-                            }
-                        }
+                for (int g0 = 0; g0 < total; g0 += 64 * kMarkItems) {
+                    const int32_t *row[kMarkItems];
+                    int d[kMarkItems], key[kMarkItems], hl[kMarkItems], k[kMarkItems], cwl[kMarkItems];
+#pragma unroll
+                    for (int t = 0; t < kMarkItems; ++t) {
+                        const int g = g0 + 64 * t + lane;
+                        int idx = 0, l = 0;
+                        if (g < total) l = flat_owner(pre, g, idx);
+                        cwl[t] = __shfl(cw, l);
+                        hl[t] = __shfl(wh, l);
+                        row[t] = L.fcol + __shfl(gw, l);
+                        d[t] = __shfl(dfw, l);
+                        key[t] = g < total ? rowv[idx] : -1;
                     }
+#pragma unroll
+                    for (int t = 0; t < kMarkItems; ++t)
+                        if (key[t] < 0 || L.lab[key[t]] == cwl[t]) d[t] = 0;
+                    lower_n<kMarkItems, false>(row, d, key, k);
+#pragma unroll
+                    for (int t = 0; t < kMarkItems; ++t)
+                        if (k[t] < d[t] && row[t][k[t]] == key[t]) cflag[hub_first[hl[t]] + k[t] / kScoreTileP] = 1;
                 }
                 wave_sync();
             }
@@ -4562,8 +4522,8 @@ static rs_status incremental_marks_t(rs_graph *g) {
     const OffT *off = (const OffT *)D.off;
     const int gn = grid_for(D.n, kBlock, 1024);
     hipLaunchKernelGGL(k_compact_rows<OffT>, dim3(gn), dim3(kBlock), 0, g->stream, off, D.deg, D.col, D.clab,
-                       D.lab, D.goff, D.fcol, D.elist, &D.ictr[kIcChanged]);
-    hipLaunchKernelGGL(k_mark_link<OffT>, dim3(gn), dim3(kBlock), 0, g->stream, link_args<OffT>(g), D.vmark,
+                       D.lab, D.goff, D.fcol, D.meta, D.elist, &D.ictr[kIcChanged]);
+    hipLaunchKernelGGL(k_mark_link, dim3(gn), dim3(kBlock), 0, g->stream, link_args(g), D.vmark,
                        (const int32_t *)D.vscore, (const int32_t *)D.shub_first, D.cflag, D.elist, D.echunk,
                        &D.ictr[kIcChunks]);
     const int ug = grid_for(D.n, kBlock, kUnitGroups);
