@@ -155,36 +155,78 @@ __device__ __forceinline__ void finish_row(const RowArgs<OffT> &A, int v, int d,
     }
 }
 
-__device__ void block_reduce_row(RowAcc acc, RowPart *out, unsigned long long *wmax_out) {
-    __shared__ unsigned long long s_u[5][kBlock / 64];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        acc.wmax = fmax(acc.wmax, __shfl_xor(acc.wmax, o));
-        acc.nb += __shfl_xor(acc.nb, o);
-        acc.dp += __shfl_xor(acc.dp, o);
-        acc.ell += __shfl_xor(acc.ell, o);
-        acc.ellx += __shfl_xor(acc.ellx, o);
-    }
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        s_u[0][w] = dbits(acc.wmax);
-        s_u[1][w] = acc.nb;
-        s_u[2][w] = acc.dp;
-        s_u[3][w] = acc.ell;
-        s_u[4][w] = acc.ellx;
+// Sum over a wavefront's lanes, and maximum of non-negative doubles, in lane 63
+// (row shifts and broadcasts: no LDS).
+template <int kCtrl, int kRows>
+__device__ __forceinline__ int dpp_or_zero(int x) {
+    return __builtin_amdgcn_update_dpp(0, x, kCtrl, kRows, 0xf, false);
+}
+template <int kCtrl, int kRows>
+__device__ __forceinline__ double dpp_max(double x) {
+    const unsigned long long b = dbits(x);
+    const unsigned int lo = (unsigned int)dpp_or_zero<kCtrl, kRows>((int)(unsigned int)b);
+    const unsigned int hi = (unsigned int)dpp_or_zero<kCtrl, kRows>((int)(unsigned int)(b >> 32));
+    return fmax(x, bitsd(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ unsigned int wave_sum_last(unsigned int v) {
+    int x = (int)v;
+    x += dpp_or_zero<0x111, 0xf>(x);  // row_shr:1, 2, 4, 8
+    x += dpp_or_zero<0x112, 0xf>(x);
+    x += dpp_or_zero<0x114, 0xf>(x);
+    x += dpp_or_zero<0x118, 0xf>(x);
+    x += dpp_or_zero<0x142, 0xa>(x);  // row_bcast:15, 31
+    x += dpp_or_zero<0x143, 0xc>(x);
+    return (unsigned int)x;
+}
+__device__ __forceinline__ double wave_max_last(double x) {
+    x = dpp_max<0x111, 0xf>(x);
+    x = dpp_max<0x112, 0xf>(x);
+    x = dpp_max<0x114, 0xf>(x);
+    x = dpp_max<0x118, 0xf>(x);
+    x = dpp_max<0x142, 0xa>(x);
+    return dpp_max<0x143, 0xc>(x);
+}
+
+// A row block's totals: a hub's are its first thread's already; a tile's
+// counts fit 16 bits each (kRowTile entries), so they are summed two to a
+// register (five 64-bit shuffled reductions took an eighth of the pass).
+__device__ __forceinline__ void store_row_part(const RowPart &p, RowPart *out, unsigned long long *wmax_out) {
+    *out = p;
+    *wmax_out = p.wmax_bits;
+}
+__device__ __forceinline__ void hub_row_part(const RowAcc &acc, RowPart *out, unsigned long long *wmax_out) {
+    if (threadIdx.x != 0) return;
+    RowPart p = {};
+    p.wmax_bits = dbits(acc.wmax);
+    p.n_border = acc.nb;
+    p.sum_dprime = acc.dp;
+    p.sum_ell = acc.ell;
+    p.sum_ell_x = acc.ellx;
+    store_row_part(p, out, wmax_out);
+}
+static_assert(kRowTile < 65536 && kRowTileV < 65536, "a tile's counts fit 16 bits");
+__device__ __forceinline__ void block_reduce_row(const RowAcc &acc, RowPart *out, unsigned long long *wmax_out) {
+    __shared__ double s_w[kBlock / 64];
+    __shared__ unsigned int s_u[2][kBlock / 64];
+    const double w = wave_max_last(acc.wmax);
+    const unsigned int a = wave_sum_last((unsigned int)acc.nb | (unsigned int)acc.dp << 16);
+    const unsigned int b = wave_sum_last((unsigned int)acc.ell | (unsigned int)acc.ellx << 16);
+    if ((threadIdx.x & 63) == 63) {
+        s_w[threadIdx.x >> 6] = w;
+        s_u[0][threadIdx.x >> 6] = a;
+        s_u[1][threadIdx.x >> 6] = b;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         RowPart p = {};
         for (int i = 0; i < kBlock / 64; ++i) {
-            p.wmax_bits = max(p.wmax_bits, s_u[0][i]);
-            p.n_border += s_u[1][i];
-            p.sum_dprime += s_u[2][i];
-            p.sum_ell += s_u[3][i];
-            p.sum_ell_x += s_u[4][i];
+            p.wmax_bits = max(p.wmax_bits, dbits(s_w[i]));
+            p.n_border += s_u[0][i] & 0xffffu;
+            p.sum_dprime += s_u[0][i] >> 16;
+            p.sum_ell += s_u[1][i] & 0xffffu;
+            p.sum_ell_x += s_u[1][i] >> 16;
         }
-        *out = p;
-        *wmax_out = p.wmax_bits;
+        store_row_part(p, out, wmax_out);
     }
 }
 
@@ -203,9 +245,16 @@ __device__ __forceinline__ int tile_of_block(int b, int n_hubs, int per_xcd) {
 //      the previous entry's (rows are community-sorted, so each run is one
 //      interaction-matrix record); run starts are ranked with wavefront
 //      ballots and a block prefix;
-//   3. one thread per vertex walks its runs in LDS: ell, X = sum f log2 f,
-//      the own community's run and the entries below it (p, q);
-//   4. the records' weights (Eq. H_optimal) are computed flat over runs.
+//   3. flat over the runs: the own community's run, or where it would be, and
+//      which runs are longer than one (a bit each);
+//   4. one thread per vertex adds X = sum f log2 f over those in run order (a
+//      run of one adds zero) and has ell, p, q from the run indices;
+//   5. the records' weights (Eq. H_optimal) are computed flat over runs.
+// One lane walking all of its vertex's runs held its wavefront for a third of
+// the kernel: a tile has some 75 to 110 vertices and ten times the runs.  With
+// the block totals below: n = 3 million, mean degree 30, 467 -> 376 us; n = 1
+// million, mean degree 20, 104 -> 87; n = 150,000, mean degree 71, 92 -> 73;
+// 128 graphs 150 -> 123 (1.9, 1.9, 1.1 and 1.4 TB/s of what has to move).
 // A removed entry is -1 (after compaction): such a tail forms a run that is
 // skipped.
 constexpr int kRowW = kBlock / 64;      // wavefronts per workgroup
@@ -226,14 +275,18 @@ struct HubSeg {
 struct RowTileShared {
     HubSeg hub;
     Tables tab;
-    unsigned int bm[kRowTile / 32];      // row-start bits
-    unsigned long long mask[kRowM];      // run-start bits
+    unsigned long long bm[kRowM];        // row-start bits
+    unsigned long long mask[kRowM];      // run-start bits; then, by run, those longer than one
     int mbase[kRowM];                    // run starts before each mask word
-    int wlast[kRowW], wcnt[kRowW];
+    unsigned short rbase[kRowM];         // row starts before each 64 entries
+    int wlast[kRowW], wcnt[kRowW], wrow[kRowW];
     unsigned short runpos[kRowTile + 1]; // tile-local entry of each run start (+ end)
-    unsigned short runv[kRowTile];       // tile-local vertex of each run
+    unsigned short runv[kRowTile];       // row of each run (the tile's rows with a capacity, in order)
     int runlab[kRowTile];                // label of each run (-1: removed tail)
-    double vX[kRowTileV];
+    union {  // by row
+        int vlab[2 * kRowTileV];  // its community, until X is known
+        double vX[kRowTileV];
+    };
     unsigned int vde[kRowTileV];     // degree and ell (16 bits each)
     short vslot[kRowTileV];          // tile slot of a foreign entry below the own community, minus its tile-local entry
     unsigned short vrun[kRowTileV];  // first run not below the own community, and kOwnRun when that is the own one
@@ -246,44 +299,27 @@ __device__ __forceinline__ int run_index(const RowTileShared &S, int e) {
     return S.mbase[e >> 6] + __popcll(S.mask[e >> 6] & ((1ull << (e & 63)) - 1ull));
 }
 
-// A wavefront's walk over the runs [rf, re) of one vertex (64 at a time), for
-// rows with more than kWalkRuns runs, where one lane's walk keeps the other 63
-// waiting.  X adds the runs in order, as the single lane does: a run of
-// length one adds zero, so only the longer ones take a step each.  Labels
-// ascend, so the runs below the own community are counted.  The totals go to
-// the lane that owns the vertex.
-constexpr int kWalkRuns = 20;
+// X of one row with the whole wavefront, for rows with many runs longer than
+// one, where one lane's sum keeps the other 63 waiting: the terms 64 runs at a
+// time, added in run order, as the single lane does.
+// (6, 12 or 24 as the limit: the same within 2 %.)
+constexpr int kWalkRuns = 12;
 __device__ __forceinline__ double lane_value(double x, int l) {
     const unsigned long long b = dbits(x);
     const unsigned int lo = __builtin_amdgcn_readlane((int)(unsigned int)b, l);
     const unsigned int hi = __builtin_amdgcn_readlane((int)(unsigned int)(b >> 32), l);
     return bitsd(((unsigned long long)hi << 32) | lo);
 }
-__device__ __forceinline__ void wave_walk(RowTileShared &S, int rf, int re, int cv, int i, int lane, bool mine,
-                                          double &X, int &ell, int &nbelow, bool &own) {
+__device__ __forceinline__ double wave_walk(const RowTileShared &S, int rf, int re, int lane) {
     double x = 0.0;
-    int n = 0, nb = 0;
-    bool o = false;
     for (int r0 = rf; r0 < re; r0 += 64) {
         const int r = r0 + lane;
-        int lb = -1, f = 0;
-        if (r < re) {
-            lb = S.runlab[r];
-            f = lb < 0 ? 0 : (int)S.runpos[r + 1] - (int)S.runpos[r];  // (a removed tail is the last run)
-            S.runv[r] = (unsigned short)i;
-        }
+        int f = 0;
+        if (r < re && ((S.mask[r >> 6] >> (r & 63)) & 1ull)) f = (int)S.runpos[r + 1] - (int)S.runpos[r];
         const double t = flogf_t(S.tab, f);
         for (unsigned long long m = __ballot(f > 1); m; m &= m - 1ull) x += lane_value(t, __ffsll((long long)m) - 1);
-        n += __popcll(__ballot(f > 0));
-        nb += __popcll(__ballot(f > 0 && lb < cv));
-        o |= __any(f > 0 && lb == cv);
     }
-    if (mine) {
-        X = x;
-        ell = n;
-        nbelow = nb;
-        own = o;
-    }
+    return x;
 }
 
 template <typename OffT>
@@ -295,7 +331,7 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
     const OffT e0 = (OffT)tl.e0;
     const int TE = tl.te;
     const int go0 = A.goff[v0];
-    for (int x = tid; x < kRowTile / 32; x += kBlock) S.bm[x] = 0u;
+    if (tid < kRowM) S.bm[tid] = 0ull;
     // the tile's entries and the facts of this thread's vertices, all
     // independent loads issued together (the tables are filled while they
     // are in flight)
@@ -325,28 +361,35 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kVU; ++j)
-        if (tid + j * kBlock < nv && vc[j] > 0) atomicOr(&S.bm[vo[j] >> 5], 1u << (vo[j] & 31));
+        if (tid + j * kBlock < nv && vc[j] > 0) atomicOr(&S.bm[vo[j] >> 6], 1ull << (vo[j] & 63));
     if (lane == 63) S.wlast[wave] = L[kRowU - 1];
     __syncthreads();
-    unsigned long long m[kRowU];
-    int cnt = 0;
+    unsigned long long m[kRowU], rows[kRowU];
+    int cnt = 0, nrow = 0;
 #pragma unroll
     for (int i = 0; i < kRowU; ++i) {
         const int e = wave * (kRowTile / kRowW) + i * 64 + lane;
         int lp = __shfl_up(L[i], 1);
         const int carry = i > 0 ? __shfl(L[i > 0 ? i - 1 : 0], 63) : (wave > 0 ? S.wlast[wave > 0 ? wave - 1 : 0] : INT_MIN);
         if (lane == 0) lp = carry;
-        const bool rs = (S.bm[e >> 5] >> (e & 31)) & 1u;
-        m[i] = __ballot(e < TE && (rs || L[i] != lp));
+        rows[i] = S.bm[e >> 6];
+        m[i] = __ballot(e < TE && (((rows[i] >> lane) & 1ull) || L[i] != lp));
         cnt += __popcll(m[i]);
+        nrow += __popcll(rows[i]);
     }
-    if (lane == 0) S.wcnt[wave] = cnt;
+    if (lane == 0) {
+        S.wcnt[wave] = cnt;
+        S.wrow[wave] = nrow;
+    }
     __syncthreads();
-    int base = 0, total = 0;
+    int base = 0, total = 0, row0 = 0;
 #pragma unroll
     for (int x = 0; x < kRowW; ++x) {
         const int c = S.wcnt[x];
-        if (x < wave) base += c;
+        if (x < wave) {
+            base += c;
+            row0 += S.wrow[x];
+        }
         total += c;
     }
     const unsigned long long lt = (1ull << lane) - 1ull;
@@ -356,56 +399,96 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
         if (lane == 0) {
             S.mask[e >> 6] = m[i];
             S.mbase[e >> 6] = base;
+            S.rbase[e >> 6] = (unsigned short)row0;
         }
         if ((m[i] >> lane) & 1ull) {
             const int r = base + __popcll(m[i] & lt);
             S.runpos[r] = (unsigned short)e;
             S.runlab[r] = L[i];
+            // (the tile's first entry starts a row, so the count is not 0)
+            S.runv[r] = (unsigned short)(row0 + __popcll(rows[i] & (lt << 1 | 1ull)) - 1);
         }
         base += __popcll(m[i]);
+        row0 += __popcll(rows[i]);
     }
     if (tid == 0) S.runpos[total] = (unsigned short)TE;
+    __syncthreads();
+    // each vertex's runs [rf, re) and its row; until a run says more, the own
+    // community's place is before them
+    int vrf[kVU], vre[kVU], vk[kVU];
+#pragma unroll
+    for (int j = 0; j < kVU; ++j) {
+        vrf[j] = vre[j] = vk[j] = 0;
+        if (tid + j * kBlock < nv && vc[j] > 0) {
+            const int o = vo[j], c = vc[j];
+            vrf[j] = run_index(S, o);
+            vre[j] = o + c >= TE ? total : run_index(S, o + c);
+            vk[j] = (int)S.rbase[o >> 6] + __popcll(S.bm[o >> 6] & ((1ull << (o & 63)) - 1ull));
+            S.vrun[vk[j]] = (unsigned short)vrf[j];
+            S.vlab[vk[j]] = vlab[j];
+        }
+    }
+    __syncthreads();
+    for (int r0 = wave * 64; r0 < total; r0 += kBlock) {
+        const int r = r0 + lane;
+        bool more = false;
+        if (r < total) {
+            const int lb = S.runlab[r], q = S.runv[r];
+            more = lb >= 0 && (int)S.runpos[r + 1] - (int)S.runpos[r] > 1;
+            const int cv = S.vlab[q];
+            if (lb == cv) {
+                S.vrun[q] = (unsigned short)(r | kOwnRun);
+            } else if (lb >= 0 && lb < cv) {  // the last run below the own community, if that has none
+                const int ln = r + 1 < total && S.runv[r + 1] == q ? S.runlab[r + 1] : -1;
+                if (ln < 0 || ln > cv) S.vrun[q] = (unsigned short)(r + 1);
+            }
+        }
+        const unsigned long long f1 = __ballot(more);
+        if (lane == 0) S.mask[r0 >> 6] = f1;
+    }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kVU; ++j) {
         if (__ballot(tid + j * kBlock < nv) == 0ull) break;  // no vertex in this wavefront
         const int i = tid + j * kBlock;
         const bool in = i < nv;
-        const int o = vo[j], c = in ? vc[j] : 0, d = vdeg[j], cv = vlab[j];
-        int rf = 0, re = 0;
-        if (c > 0) {
-            rf = run_index(S, o);
-            re = o + c >= TE ? total : run_index(S, o + c);
-        }
+        const int o = vo[j], c = in ? vc[j] : 0, d = vdeg[j], k = vk[j];
+        const int rf = vrf[j], re = vre[j];
         double X = 0.0;
-        int ell = 0, nbelow = 0;
-        bool own = false;
-        if (re - rf <= kWalkRuns) {
-            for (int r = rf; r < re; ++r) {
-                const int lb = S.runlab[r];
-                if (lb < 0) break;
-                const int f = (int)S.runpos[r + 1] - (int)S.runpos[r];
-                if (f > 1) X += flogf_t(S.tab, f);
-                ++ell;
-                S.runv[r] = (unsigned short)i;
-                nbelow += (int)(lb < cv);
-                own |= lb == cv;
+        int ell = 0, vr = 0;
+        bool own = false, far = false;
+        if (c > 0) {
+            ell = re - rf - (S.runlab[re - 1] < 0 ? 1 : 0);  // (a removed tail is the last run)
+            vr = S.vrun[k] & (kOwnRun - 1);
+            own = (S.vrun[k] & kOwnRun) != 0;
+            // at most 64 runs lie in two words
+            far = re - rf > 64;
+            if (!far) {
+                unsigned long long w0 = S.mask[rf >> 6] >> (rf & 63);
+                if ((rf & 63) != 0 && (rf >> 6) < (re - 1) >> 6) w0 |= S.mask[(rf >> 6) + 1] << (64 - (rf & 63));
+                if (re - rf < 64) w0 &= (1ull << (re - rf)) - 1ull;
+                far = __popcll(w0) > kWalkRuns;
+                if (!far)
+                    for (; w0; w0 &= w0 - 1ull) {
+                        const int r = rf + __ffsll((long long)w0) - 1;
+                        X += flogf_t(S.tab, (int)S.runpos[r + 1] - (int)S.runpos[r]);
+                    }
             }
         }
-        for (unsigned long long pend = __ballot(re - rf > kWalkRuns); pend; pend &= pend - 1ull) {
+        for (unsigned long long pend = __ballot(far); pend; pend &= pend - 1ull) {
             const int l = __ffsll((long long)pend) - 1;
-            wave_walk(S, __builtin_amdgcn_readlane(rf, l), __builtin_amdgcn_readlane(re, l),
-                      __builtin_amdgcn_readlane(cv, l), __builtin_amdgcn_readlane(i, l), lane, lane == l, X, ell,
-                      nbelow, own);
+            const double x = wave_walk(S, __builtin_amdgcn_readlane(rf, l), __builtin_amdgcn_readlane(re, l), lane);
+            if (lane == l) X = x;
         }
         if (!in) continue;
         // the runs below the own community come first
-        const int below = c > 0 ? (int)S.runpos[rf + nbelow] - o : 0;
-        const int fown = own ? (int)S.runpos[rf + nbelow + 1] - (int)S.runpos[rf + nbelow] : 0;
-        S.vX[i] = X;
-        S.vde[i] = (unsigned int)d | (unsigned int)ell << 16;
-        S.vslot[i] = (short)(vgo[j] - go0 - o);
-        S.vrun[i] = (unsigned short)((rf + nbelow) | (own ? kOwnRun : 0));
+        const int below = c > 0 ? (int)S.runpos[vr] - o : 0;
+        const int fown = own ? (int)S.runpos[vr + 1] - (int)S.runpos[vr] : 0;
+        if (c > 0) {
+            S.vX[k] = X;
+            S.vde[k] = (unsigned int)d | (unsigned int)ell << 16;
+            S.vslot[k] = (short)(vgo[j] - go0 - o);
+        }
         RowResult res;
         res.ell = ell;
         res.p = below;
@@ -702,11 +785,12 @@ __global__ __launch_bounds__(kBlock, 6) void k_rows(RowArgs<OffT> A) {
     const int b = (int)blockIdx.x;
     if (b < A.n_hubs) {
         hub_row(A, S, A.hubs[b], acc);
+        hub_row_part(acc, &A.part[b], &A.wmax_part[b]);
     } else {
         const int t = tile_of_block(b, A.n_hubs, A.tiles_per_xcd);
         if (t < A.n_tiles) row_tile(A, S, t, acc);
+        block_reduce_row(acc, &A.part[b], &A.wmax_part[b]);
     }
-    block_reduce_row(acc, &A.part[b], &A.wmax_part[b]);
 }
 
 // Whether an incremental pass runs every block of the full launches: its
@@ -736,11 +820,12 @@ __global__ __launch_bounds__(kBlock) void k_rows_inc(RowArgs<OffT> A, const unsi
         const int b = full ? (int)i : A.blist[i];
         if (b < A.n_hubs) {
             hub_row(A, S, A.hubs[b], acc);
+            hub_row_part(acc, &A.part[b], &A.wmax_part[b]);
         } else {
             const int t = tile_of_block(b, A.n_hubs, A.tiles_per_xcd);
             if (t < A.n_tiles) row_tile(A, S, t, acc);
+            block_reduce_row(acc, &A.part[b], &A.wmax_part[b]);
         }
-        block_reduce_row(acc, &A.part[b], &A.wmax_part[b]);
         __syncthreads();  // the next block's LDS
     }
 }
