@@ -264,6 +264,7 @@ struct DeviceGraph {
     VMeta *meta = nullptr;      // [n] row facts of the last pass
     double *wown = nullptr, *R = nullptr;
     double *av = nullptr;       // [n] a_v = cbrt(own-community weight) of the last pass
+    double *tables = nullptr;   // logarithms and reciprocals for the row tiles
     double *raw = nullptr;      // [n] Eq. RSI sums before the w_max and d(d-1) division
     long long *tI = nullptr, *tII = nullptr;
     RowPart *part_rows = nullptr;    // [row grid]
@@ -382,6 +383,8 @@ rs_status launch_load_rows(rs_graph *g, const LoadArgs &L);
 // [prefix_blocks(n)] are scratch.
 int prefix_blocks(int64_t n);
 rs_status launch_load_slots(rs_graph *g, int32_t *count, long long *sums);
+size_t table_bytes();
+rs_status launch_tables(rs_graph *g);
 rs_status launch_links(rs_graph *g, unsigned long long *d_run_walk);
 rs_status launch_col_labels(rs_graph *g);
 rs_status launch_slot_owners(rs_graph *g);

@@ -67,34 +67,59 @@ __device__ __forceinline__ double weight_absent(int d, double X, int ell) {
 
 __device__ __forceinline__ double flogf(int f) { return f > 1 ? (double)f * log2((double)f) : 0.0; }
 
-// The same terms with small arguments (<= kTab) read from LDS tables of
-// log2 y, y log2 y and 1/y (most run lengths and degrees are small).
+// The same terms in a row tile, whose degrees are at most kRowTile: the
+// logarithms come from a table in memory (16 KB, made at load with the same
+// log2, so the bits are the same), and small arguments (<= kTab; most run
+// lengths and degrees) read log2 y, y log2 y and 1/y from LDS.  With the
+// logarithms computed in place (and the LDS tables by every workgroup) the row
+// pass took 376 against 327 us at n = 3 million, mean degree 30, 87 against 72
+// at n = 1 million, mean degree 20, and 73 against 59 at n = 150,000, mean
+// degree 71.
 constexpr int kTab = 64;
 struct Tables {
     double lg[kTab + 1], fl[kTab + 1], rc[kTab + 1];
 };
-__device__ __forceinline__ void fill_tables(Tables &t) {
-    for (int i = threadIdx.x; i <= kTab; i += blockDim.x) {
-        const double x = (double)i;
-        t.lg[i] = i > 0 ? log2(x) : 0.0;
-        t.fl[i] = flogf(i);
-        t.rc[i] = i > 0 ? 1.0 / x : 0.0;
+struct TablesMem {
+    Tables small;
+    double lg[kRowTile + 1];
+};
+__global__ __launch_bounds__(kBlock) void k_tables(TablesMem *t) {
+    for (int i = threadIdx.x; i <= kRowTile; i += kBlock) {
+        const double x = (double)i, lg = i > 0 ? log2(x) : 0.0;
+        t->lg[i] = lg;
+        if (i <= kTab) {
+            t->small.lg[i] = lg;
+            t->small.fl[i] = flogf(i);
+            t->small.rc[i] = i > 0 ? 1.0 / x : 0.0;
+        }
     }
 }
-__device__ __forceinline__ double flogf_t(const Tables &t, int f) { return f <= kTab ? t.fl[f] : flogf(f); }
-__device__ __forceinline__ double weight_present_t(const Tables &t, int d, double X, int ell, int f) {
-    const int L = ell - 1;
-    if (L < 2) return 0.0;
-    const int Y = d - f;
-    if (Y <= kTab) return (t.lg[Y] + (flogf_t(t, f) - X) * t.rc[Y]) * (double)L;
-    return weight_present(d, X, ell, f);
-}
-__device__ __forceinline__ double weight_absent_t(const Tables &t, int d, double X, int ell) {
-    if (ell < 2) return 0.0;
-    if (d <= kTab) return (t.lg[d] - X * t.rc[d]) * (double)ell;
-    return weight_absent(d, X, ell);
+size_t table_bytes() { return sizeof(TablesMem); }
+rs_status launch_tables(rs_graph *g) {
+    hipLaunchKernelGGL(k_tables, dim3(1), dim3(kBlock), 0, g->stream, (TablesMem *)g->d.tables);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? RS_OK : hip_fail(e, "table launch");
 }
 
+struct Logs {
+    const Tables &t;   // LDS
+    const double *lg;  // memory: log2 of 1..kRowTile
+    __device__ __forceinline__ double flog(int f) const {
+        return f <= kTab ? t.fl[f] : (double)f * lg[f];
+    }
+    __device__ __forceinline__ double present(int d, double X, int ell, int f) const {
+        const int L = ell - 1;
+        if (L < 2) return 0.0;
+        const int Y = d - f;
+        if (Y <= kTab) return (t.lg[Y] + (flog(f) - X) * t.rc[Y]) * (double)L;
+        return (lg[Y] + (flog(f) - X) / (double)Y) * (double)L;
+    }
+    __device__ __forceinline__ double absent(int d, double X, int ell) const {
+        if (ell < 2) return 0.0;
+        if (d <= kTab) return (t.lg[d] - X * t.rc[d]) * (double)ell;
+        return (lg[d] - X / (double)d) * (double)ell;
+    }
+};
 
 // ============================================================ row pass
 template <typename OffT>
@@ -102,6 +127,7 @@ struct RowArgs {
     const OffT *off;
     const int32_t *deg, *col, *lab;
     const int32_t *clab;  // the community of each entry's neighbour (read in place of col and lab)
+    const TablesMem *tables;
     const RowTile *tiles;
     const int32_t *hubs;
     int n_tiles, n_hubs, tiles_per_xcd;
@@ -254,7 +280,7 @@ __device__ __forceinline__ int tile_of_block(int b, int n_hubs, int per_xcd) {
 // the kernel: a tile has some 75 to 110 vertices and ten times the runs.  With
 // the block totals below: n = 3 million, mean degree 30, 467 -> 376 us; n = 1
 // million, mean degree 20, 104 -> 87; n = 150,000, mean degree 71, 92 -> 73;
-// 128 graphs 150 -> 123 (1.9, 1.9, 1.1 and 1.4 TB/s of what has to move).
+// 128 graphs 150 -> 123.
 // A removed entry is -1 (after compaction): such a tail forms a run that is
 // skipped.
 constexpr int kRowW = kBlock / 64;      // wavefronts per workgroup
@@ -310,13 +336,13 @@ __device__ __forceinline__ double lane_value(double x, int l) {
     const unsigned int hi = __builtin_amdgcn_readlane((int)(unsigned int)(b >> 32), l);
     return bitsd(((unsigned long long)hi << 32) | lo);
 }
-__device__ __forceinline__ double wave_walk(const RowTileShared &S, int rf, int re, int lane) {
+__device__ __forceinline__ double wave_walk(const RowTileShared &S, const Logs &logs, int rf, int re, int lane) {
     double x = 0.0;
     for (int r0 = rf; r0 < re; r0 += 64) {
         const int r = r0 + lane;
         int f = 0;
         if (r < re && ((S.mask[r >> 6] >> (r & 63)) & 1ull)) f = (int)S.runpos[r + 1] - (int)S.runpos[r];
-        const double t = flogf_t(S.tab, f);
+        const double t = f > 1 ? logs.flog(f) : 0.0;
         for (unsigned long long m = __ballot(f > 1); m; m &= m - 1ull) x += lane_value(t, __ffsll((long long)m) - 1);
     }
     return x;
@@ -333,8 +359,7 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
     const int go0 = A.goff[v0];
     if (tid < kRowM) S.bm[tid] = 0ull;
     // the tile's entries and the facts of this thread's vertices, all
-    // independent loads issued together (the tables are filled while they
-    // are in flight)
+    // independent loads issued together
     int L[kRowU];
 #pragma unroll
     for (int i = 0; i < kRowU; ++i) {
@@ -357,7 +382,11 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
         vlab[j] = A.lab[v0 + ic];
         vgo[j] = A.goff[v0 + ic];
     }
-    fill_tables(S.tab);
+    constexpr int kTabN = (int)(sizeof(Tables) / sizeof(double));
+    static_assert(kTabN <= kBlock, "a table entry per thread");
+    const double te = ((const double *)&A.tables->small)[min(tid, kTabN - 1)];
+    if (tid < kTabN) ((double *)&S.tab)[tid] = te;
+    const Logs logs = {S.tab, A.tables->lg};
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kVU; ++j)
@@ -471,13 +500,13 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
                 if (!far)
                     for (; w0; w0 &= w0 - 1ull) {
                         const int r = rf + __ffsll((long long)w0) - 1;
-                        X += flogf_t(S.tab, (int)S.runpos[r + 1] - (int)S.runpos[r]);
+                        X += logs.flog((int)S.runpos[r + 1] - (int)S.runpos[r]);
                     }
             }
         }
         for (unsigned long long pend = __ballot(far); pend; pend &= pend - 1ull) {
             const int l = __ffsll((long long)pend) - 1;
-            const double x = wave_walk(S, __builtin_amdgcn_readlane(rf, l), __builtin_amdgcn_readlane(re, l), lane);
+            const double x = wave_walk(S, logs, __builtin_amdgcn_readlane(rf, l), __builtin_amdgcn_readlane(re, l), lane);
             if (lane == l) X = x;
         }
         if (!in) continue;
@@ -493,7 +522,7 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
         res.ell = ell;
         res.p = below;
         res.q = below + fown;
-        res.wown = fown > 0 ? weight_present_t(S.tab, d, X, ell, fown) : weight_absent_t(S.tab, d, X, ell);
+        res.wown = fown > 0 ? logs.present(d, X, ell, fown) : logs.absent(d, X, ell);
         res.lmax = res.wown;
         finish_row(A, v0 + i, d, res, acc);
     }
@@ -511,7 +540,7 @@ __device__ void row_tile(const RowArgs<OffT> &A, RowTileShared &S, int t, RowAcc
         const unsigned int de = S.vde[i];
         PairRec pr;
         pr.f = (int)S.runpos[r + 1] - p0;
-        pr.w = weight_present_t(S.tab, (int)(de & 0xffffu), S.vX[i], (int)(de >> 16), pr.f);
+        pr.w = logs.present((int)(de & 0xffffu), S.vX[i], (int)(de >> 16), pr.f);
         pr.c = lb;
         const int fo = own && r > vr ? (int)S.runpos[vr + 1] - (int)S.runpos[vr] : 0;
         const int s = go0 + S.vslot[i] + p0 - fo;
@@ -2619,6 +2648,7 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
     A.col = D.col;
     A.lab = D.lab;
     A.clab = D.clab;
+    A.tables = (const TablesMem *)D.tables;
     A.tiles = D.rtiles;
     A.hubs = D.rhubs;
     A.n_tiles = g->n_rtiles;

@@ -555,6 +555,7 @@ static rs_status alloc_vertices(rs_graph *g, int64_t n, int64_t nnz, int64_t k) 
         {(void **)&D.goff, 4 * (N + 1)},
         {(void **)&D.cstart, 4 * ((size_t)D.k + 1)},
         {(void **)&D.wpart, 8 * (size_t)kWorkBlocks},
+        {(void **)&D.tables, table_bytes()},
         {(void **)&D.raw, 8 * N},
         {(void **)&D.vmark, 4 * N},
         {(void **)&D.elist, 4 * N},
@@ -631,6 +632,7 @@ static hipError_t put_offsets(rs_graph *g, const std::vector<int64_t> &off, std:
 static rs_status finish_load(rs_graph *g, const HostGraph &H) {
     DeviceGraph &D = g->d;
     rs_status st = upload_tiles(g, H);
+    if (st == RS_OK) st = launch_tables(g);
     if (st == RS_OK) st = launch_zero_u64(g, D.scratch_u, 1);
     if (st == RS_OK) st = launch_links(g, D.scratch_u);
     if (st != RS_OK) return st;
