@@ -3078,61 +3078,75 @@ __global__ __launch_bounds__(kBlock) void k_list_hist(const TopkKey *list, const
 }
 
 // One block of 1024 threads: find the threshold digit of the current level,
-// record it, and clear the histogram for the next use.
+// record it, and clear the histogram for the next use.  The bins are read as
+// they lie (16 regions of 4,096, four bins a thread in each, coalesced); the
+// region where the count from the top reaches `take` is found from the regions'
+// sums, then the thread, then the bin.  With 64 consecutive bins a thread and a
+// scan by doubling in LDS a level took 26 us, now 11.
 __global__ __launch_bounds__(1024) void k_topk_find(unsigned int *hist, TopkState *st, int level) {
-    __shared__ long long s_scan[1024];
-    __shared__ long long s_total;
+    constexpr int kRegions = kTopkBins / 4096;
+    __shared__ unsigned int s_w[kRegions][16];
     if (refine_finished(st, level)) return;  // (uniform; the histogram is still clear)
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const long long need = st->take;
-    // thread t owns bins [base, base + 63]; bins descend with t
-    const int base = kTopkBins - 64 * (t + 1);
-    const uint4 *h4 = (const uint4 *)(hist + base);
-    long long mine = 0;
+    uint4 *h4 = (uint4 *)hist;
+    uint4 x[kRegions];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const uint4 x = h4[i];
-        mine += (long long)x.x + x.y + x.z + x.w;
+    for (int i = 0; i < kRegions; ++i) x[i] = h4[i * 1024 + t];
+#pragma unroll
+    for (int i = 0; i < kRegions; ++i) h4[i * 1024 + t] = make_uint4(0u, 0u, 0u, 0u);
+    // (a list holds at most n < 2^31 keys)
+#pragma unroll
+    for (int i = 0; i < kRegions; ++i) {
+        const unsigned int s = wave_sum_last(x[i].x + x[i].y + x[i].z + x[i].w);
+        if (lane == 63) s_w[i][wave] = s;
     }
-    s_scan[t] = mine;
     __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        const long long x = t >= o ? s_scan[t - o] : 0;
-        __syncthreads();
-        s_scan[t] += x;
-        __syncthreads();
+    // every thread walks the regions from the top, then the region's wavefronts
+    long long above = 0;
+    int reg = kRegions - 1, w = 15;
+    for (; reg >= 0; --reg) {
+        long long s = 0;
+        for (int i = 0; i < 16; ++i) s += s_w[reg][i];
+        if (above + s >= need) break;
+        above += s;
     }
-    const long long incl = s_scan[t];
-    const long long excl = incl - mine;
-    if (t == 1023) s_total = incl;
-    __syncthreads();
-    if (excl < need && need <= incl) {
-        long long cum = excl;
-        for (int i = 63; i >= 0; --i) {
-            const long long h = hist[base + i];
-            if (cum + h >= need) {
-                st->digit = (unsigned int)level;
-                st->thresh = (unsigned int)(base + i);
-                st->above += cum;
-                st->take = need - cum;
-                st->binsize = h;
-                st->done = (need - cum == h) ? 1u : 0u;
-                break;
-            }
-            cum += h;
+    if (reg < 0 || need <= 0) {  // cannot happen for need <= live keys: take all
+        if (t == 0) {
+            st->digit = (unsigned int)level;
+            st->thresh = 0;
+            st->take = 0;
+            st->binsize = 0;
+            st->done = 1u;
         }
+        return;
     }
-    __syncthreads();
-    if (t == 0 && !(need > 0 && s_total >= need)) {  // cannot happen for need <= live keys: take all
-        st->digit = (unsigned int)level;
-        st->thresh = 0;
-        st->take = 0;
-        st->binsize = 0;
-        st->done = 1u;
-    }
-    uint4 *w4 = (uint4 *)(hist + base);
+    for (; w > 0 && above + s_w[reg][w] < need; --w) above += s_w[reg][w];
+    if (wave != w) return;
+    uint4 b = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) w4[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int i = 0; i < kRegions; ++i)
+        if (i == reg) b = x[i];
+    const unsigned int mine = b.x + b.y + b.z + b.w;
+    unsigned int incl = mine;  // from this lane to the last: the counts of its bins and those above
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned int y = (unsigned int)__shfl_down((int)incl, o);
+        if (lane + o < 64) incl += y;
+    }
+    const long long before = above + (incl - mine);
+    if (before < need && need <= before + mine) {  // (one lane)
+        const unsigned int c[4] = {b.x, b.y, b.z, b.w};
+        long long cum = before;
+        int i = 3;
+        while (i > 0 && cum + c[i] < need) cum += c[i--];
+        st->digit = (unsigned int)level;
+        st->thresh = (unsigned int)(reg * 4096 + 4 * t + i);
+        st->above += cum;
+        st->take = need - cum;
+        st->binsize = c[i];
+        st->done = (need - cum == c[i]) ? 1u : 0u;
+    }
 }
 
 // Block-aggregated append of the flagged threads' keys to list[*counter...].
@@ -3225,6 +3239,32 @@ __global__ __launch_bounds__(kCollThreads) void k_topk_collect(const double *R, 
     __syncthreads();
     for (unsigned int i = threadIdx.x; i < cf; i += kCollThreads) fin[s_bf + i] = sf[i];
     for (unsigned int i = threadIdx.x; i < ct; i += kCollThreads) tie[s_bt + i] = stl[i];
+}
+
+// The tie class's largest score bits and the complement of its smallest (both
+// zero before).
+__global__ __launch_bounds__(kBlock) void k_tie_range(const TopkKey *tie, long long n, unsigned long long *range) {
+    unsigned long long a = 0ull, b = 0ull;
+    for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long long)gridDim.x * kBlock) {
+        const unsigned long long h = tie[i].hi;
+        a = max(a, h);
+        b = max(b, ~h);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        a = max(a, (unsigned long long)__shfl_xor((long long)a, o));
+        b = max(b, (unsigned long long)__shfl_xor((long long)b, o));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicMax(&range[0], a);
+        atomicMax(&range[1], b);
+    }
+}
+
+// The list sizes of the refine levels from `first` on: the tie class's, then
+// zeros.
+__global__ void k_refine_counts(unsigned long long *cnt, int first, long long n_tie) {
+    if ((int)threadIdx.x < 6) cnt[threadIdx.x] = (int)threadIdx.x == first - 1 ? (unsigned long long)n_tie : 0ull;
 }
 
 __global__ __launch_bounds__(kBlock) void k_list_collect(const TopkKey *list, const unsigned long long *count,
@@ -3439,7 +3479,10 @@ __global__ __launch_bounds__(kCountThreads) void k_topk_rank(const TopkState *st
     const long long nf = (long long)st->n_final;
     const long long n = nf + (st->done ? 0 : (long long)st->n_tie);
     const bool ok = n <= cap && n >= keff;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *flag = ok ? 1u : 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *flag = ok ? 1u : 0u;
+        ((unsigned long long *)flag)[1] = (unsigned long long)(n - nf);  // the tie class
+    }
     const long long base = (long long)blockIdx.x * kCountKeys;
     if (!ok || base >= n) return;  // uniform per workgroup
     const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
@@ -3509,12 +3552,6 @@ static rs_status final_order(rs_graph *g, long long keff) {
     return e == hipSuccess ? RS_OK : hip_fail(e, "top-k order launch");
 }
 
-static hipError_t copy_out(rs_graph *g, long long keff, int32_t *ids, double *scores) {
-    hipError_t e = hipMemcpyAsync(ids, g->d.tout_ids, 4 * (size_t)keff, hipMemcpyDeviceToHost, g->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(scores, g->d.tout_sc, 8 * (size_t)keff, hipMemcpyDeviceToHost, g->stream);
-    return e;
-}
-
 // The common path of top-k: the histogram, the collect (each block finds the
 // threshold itself), and the ranking of the candidates by counting across
 // workgroups into a compact device block [flag | ids | scores], copied once
@@ -3576,50 +3613,58 @@ rs_status launch_topk(rs_graph *g, int64_t k, int32_t *ids, double *scores, int6
         memcpy(scores, (const char *)g->hpin + sc_off, 8 * (size_t)keff);
         return RS_OK;
     }
-    TopkState st;
 
-    // General path: rank the tie class (by counting), then order the final list.
-    timing_begin(g, K_TOPK_TIE, &ev);
-    static_assert(kTieCap <= kRankMax, "a rankable tie class fits the counting ranker");
-    hipLaunchKernelGGL(k_count_rank, dim3(kTieCap / kCountKeys), dim3(kCountThreads), 0, g->stream,
-                       (const TopkKey *)D.ttie, D.tstate, 0, 0ll, D.tfinal, D.R, D.new2old, D.tout_ids, D.tout_sc);
-    timing_end(g, K_TOPK_TIE, ev);
-    rs_status rs_st = final_order(g, keff);
-    if (rs_st != RS_OK) return rs_st;
-    e = hipMemcpyAsync(&st, D.tstate, sizeof(st), hipMemcpyDeviceToHost, g->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
-    if (e != hipSuccess) return hip_fail(e, "top-k state read");
-    if (st.overflow) {
-        // A tie class larger than the pairwise ranker: refine it digit by
-        // digit.  The final list already holds the keys above the tie class.
-        // All levels are enqueued at once; the lists only shrink, so the
-        // tie count bounds every level's grid, and the levels after the one
-        // that finishes return at once.
-        unsigned long long *cnt = D.scratch_u;  // [0] current list size, [1] next list size
+    // General path: the tie class, by counting or digit by digit, then the
+    // order of the final list (which already holds the keys above the class).
+    const long long n_tie = (long long)((const unsigned long long *)g->hpin)[1];
+    if (n_tie <= kTieCap) {
+        timing_begin(g, K_TOPK_TIE, &ev);
+        static_assert(kTieCap <= kRankMax, "a rankable tie class fits the counting ranker");
+        hipLaunchKernelGGL(k_count_rank, dim3(kTieCap / kCountKeys), dim3(kCountThreads), 0, g->stream,
+                           (const TopkKey *)D.ttie, D.tstate, 0, 0ll, D.tfinal, D.R, D.new2old, D.tout_ids, D.tout_sc);
+        timing_end(g, K_TOPK_TIE, ev);
+    } else {
+        // A class larger than the pairwise ranker, as in a graph whose
+        // removals leave most scores equal: then the score digits are skipped
+        // and the ids' refined.  All levels are enqueued at once; the lists
+        // only shrink, so the class bounds every level's grid, and the levels
+        // after the one that finishes return at once.  (Three graphs of some
+        // 40,000 to 70,000 vertices, six requests: 1,112 us with all levels at 16
+        // keys a thread, the state read first and pageable copies; now 398.)
+        unsigned long long *cnt = D.scratch_u;  // list sizes: [j] what level j leaves; [6], [7] the score range
+        unsigned long long *range = (unsigned long long *)g->hpin;
         TopkKey *cur = D.ttie, *nxt = D.ttie2;
-        const int grid_l = grid_for((long long)st.n_tie, 16 * kBlock, 4096);
-        e = hipMemcpyAsync(cnt, &D.tstate->n_tie, sizeof(unsigned long long), hipMemcpyDeviceToDevice, g->stream);
-        for (int j = 1; j <= 5 && e == hipSuccess; ++j) {
+        const int grid_l = grid_for(n_tie, kBlock, 4096);
+        const rs_status zst = launch_zero_u64(g, cnt + 6, 2);
+        if (zst != RS_OK) return zst;
+        hipLaunchKernelGGL(k_tie_range, dim3(grid_for(n_tie, 4 * kBlock, 256)), dim3(kBlock), 0, g->stream, cur, n_tie,
+                           cnt + 6);
+        e = hipMemcpyAsync(range, cnt + 6, 16, hipMemcpyDeviceToHost, g->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
+        if (e != hipSuccess) return hip_fail(e, "top-k tie range");
+        const int first = range[0] == ~range[1] ? 4 : 1;
+        hipLaunchKernelGGL(k_refine_counts, dim3(1), dim3(64), 0, g->stream, cnt, first, n_tie);
+        for (int j = first; j <= 5; ++j) {
             timing_begin(g, K_TOPK_FIND, &ev);
-            hipLaunchKernelGGL(k_list_hist, dim3(grid_l), dim3(kBlock), 0, g->stream, cur, cnt, j, D.tstate, D.thist);
+            hipLaunchKernelGGL(k_list_hist, dim3(grid_l), dim3(kBlock), 0, g->stream, cur, cnt + j - 1, j, D.tstate,
+                               D.thist);
             hipLaunchKernelGGL(k_topk_find, dim3(1), dim3(1024), 0, g->stream, D.thist, D.tstate, j);
             timing_end(g, K_TOPK_FIND, ev);
-            hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, g->stream, cnt + 1, 1);
-            hipLaunchKernelGGL(k_list_collect, dim3(grid_l), dim3(kBlock), 0, g->stream, cur, cnt, j, D.tstate,
-                               D.tfinal, nxt, cnt + 1);
-            e = hipMemcpyAsync(cnt, cnt + 1, sizeof(unsigned long long), hipMemcpyDeviceToDevice, g->stream);
-            TopkKey *tmp = cur;
-            cur = nxt;
-            nxt = tmp;
+            hipLaunchKernelGGL(k_list_collect, dim3(grid_l), dim3(kBlock), 0, g->stream, cur, cnt + j - 1, j, D.tstate,
+                               D.tfinal, nxt, cnt + j);
+            std::swap(cur, nxt);
         }
-        if (e == hipSuccess) e = hipMemsetAsync(&D.tstate->overflow, 0, sizeof(unsigned int), g->stream);
-        if (e != hipSuccess) return hip_fail(e, "top-k refine");
-        rs_st = final_order(g, keff);
-        if (rs_st != RS_OK) return rs_st;
     }
-    e = copy_out(g, keff, ids, scores);
+    const rs_status rs_st = final_order(g, keff);
+    if (rs_st != RS_OK) return rs_st;
+    char *pin = (char *)g->hpin;
+    e = hipMemcpyAsync(pin + 16, D.tout_ids, 4 * (size_t)keff, hipMemcpyDeviceToHost, g->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(pin + sc_off, D.tout_sc, 8 * (size_t)keff, hipMemcpyDeviceToHost, g->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
-    return e == hipSuccess ? RS_OK : hip_fail(e, "top-k copy");
+    if (e != hipSuccess) return hip_fail(e, "top-k copy");
+    memcpy(ids, pin + 16, 4 * (size_t)keff);
+    memcpy(scores, pin + sc_off, 8 * (size_t)keff);
+    return RS_OK;
 }
 
 // ------------------------------------------------------------ batched top-k
