@@ -524,7 +524,7 @@ def bench_batch(args):
         return 1000.0 * ms / nl if nl else 0.0
     kb = kernel_bytes(counts, n_tot, 2 * m_tot, 8, K * G)
     avg_us = {"k_rows": avg("k_rows"),
-              "k_score": avg("k_mid") + avg("k_score") + avg("k_score_hub") + avg("k_hub_sum")}
+              "k_score": avg("k_mid") + avg("k_score") + avg("k_hub_sum")}
     dom = max(avg_us, key=avg_us.get)
     achieved = kb[dom] / (avg_us[dom] * 1e-6) / 1e9
     out = {
@@ -753,7 +753,7 @@ def main():
         return 1000.0 * ms / nl if nl else 0.0
 
     avg_us = {"k_rows": avg("k_rows"),
-              "k_score": avg("k_mid") + avg("k_score") + avg("k_score_hub") + avg("k_hub_sum")}
+              "k_score": avg("k_mid") + avg("k_score") + avg("k_hub_sum")}
     dom = max(avg_us, key=avg_us.get)
     achieved = kb[dom] / (avg_us[dom] * 1e-6) / 1e9
     gpu_ms = sum(v[0] for v in timings.values()) / args.steps

@@ -51,7 +51,6 @@ constexpr int kRowTile = 2048;       // row capacity (entries) covered by one ro
 constexpr int kRowTileV = 512;       // vertices of one row tile
 constexpr int kScoreTileP = 256;     // foreign entries (load-time bound) of one score tile (one per thread)
 constexpr int kScoreTileV = 256;     // vertices of one score tile (one per thread)
-constexpr int kHubKeys = 1024;       // score hubs with at most this many records keep their keys in LDS
 constexpr int kHubList = 1024;       // score hubs with at most this many foreign entries stage them in LDS
 constexpr int kFilterBits = 18;      // a big hub's neighbour filter: 2^18 bits (32 KB), one hash
 constexpr int kFilterWords = (1 << kFilterBits) / 32;
@@ -115,7 +114,6 @@ inline int tile_grid(int hubs, int tiles) { return hubs + 8 * ((tiles + 7) / 8);
 enum KernelId {
     K_ROWS = 0,
     K_MID,
-    K_SCORE_HUB,
     K_SCORE,
     K_TOPK_HIST,
     K_TOPK_FIND,

@@ -1,20 +1,20 @@
 // rs_kernels.hip -- HIP kernels of the robust-spanner scoring pass (gfx950, wave64).
 //
 // One pass (rs_score):
-//   k_rows   Algorithm 1 Steps 1-2 fused, per vertex: gather the labels of the
-//            neighbours, run-length count them into interaction-matrix records
+//   k_rows   Algorithm 1 Steps 1-2 fused, per vertex: run-length count the
+//            neighbours' communities into interaction-matrix records
 //            (rows are community-sorted, so every community is one run),
 //            detect the border vertex, compute every record's weight with
 //            Algorithm 2's shared terms (Eq. H_optimal) and the vertex's
 //            own-community weight, and a per-block maximum for w_max.
-//   k_wmax   reduce the per-block maxima to w_max (the other pass totals are
-//            reduced when a reader asks).
+//   k_mid    reduce the per-block maxima to w_max (per graph for a batch; the
+//            other totals are reduced when a reader asks), build the big hubs'
+//            neighbour filters and, where runs are long, the type-II values.
 //   k_score  Eq. RSI per border vertex u, one lane per pair (u, w) with w a
 //            foreign neighbour, in the per-(vertex, community) factorised form
 //            of Lemmas 1-2 (Section IV, Step 3).  One owner per vertex, fixed
-//            summation order, no floating-point atomics.  Hubs too large for
-//            LDS staging run in k_score_hub; k_hub_sum adds each hub's chunk
-//            partials.
+//            summation order, no floating-point atomics.  k_hub_sum adds each
+//            hub's chunk partials.
 // Top-k (Algorithm 1 Step 4) is an exact radix select on the 96-bit key
 // (score bits, complement of the caller id) with 16-bit digits.
 //
