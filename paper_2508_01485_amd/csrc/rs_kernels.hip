@@ -1762,13 +1762,17 @@ __device__ __forceinline__ void type2_tile(double *s_a, const PairRec *prec, con
         const int b = lead[j], e = lead[j] + f[j];
         double S = 0.0;
         if (b >= lo && e <= hi) {
-            for (int i = b; i < e; i += 8) {
+            // (whole groups read consecutive doubles without a bound each: at n =
+            // 3 million, mean degree 30, k_mid 135 -> 124 us)
+            int i = b;
+            for (; i + 8 <= e; i += 8) {
                 double x[8];
 #pragma unroll
-                for (int t = 0; t < 8; ++t) x[t] = i + t < e && i + t != s ? s_a[min(i + t, e - 1) - lo] : 0.0;
+                for (int t = 0; t < 8; ++t) x[t] = s_a[i - lo + t];
 #pragma unroll
-                for (int t = 0; t < 8; ++t) S += x[t];
+                for (int t = 0; t < 8; ++t) S += i + t != s ? x[t] : 0.0;
             }
+            for (; i < e; ++i) S += i != s ? s_a[i - lo] : 0.0;
         } else {
             for (int i = b; i < e; i += 8) {
                 int y[8];
