@@ -708,12 +708,12 @@ static rs_status upload(rs_graph *g, HostGraph &H, int64_t n, int64_t nnz, bool 
 // The vertices' renumbering: communities by ascending label, a stable counting
 // sort of the vertices by community (in chunks, one thread each, when there are
 // enough vertices for the communities), and the internal row offsets.
-// False: a negative label, bad offsets or a row that no simple graph has (the
-// host's checks say which).
+// False: a negative label, decreasing offsets or a row that no simple graph has
+// (the host's checks say which).
 template <class OffIn>
-static bool renumber(int64_t n, int64_t nnz, const OffIn *off, const int32_t *lab, HostGraph &H,
+static bool renumber(int64_t n, const OffIn *off, const int32_t *lab, HostGraph &H,
                      std::vector<int64_t> &cap) {
-    std::atomic<bool> ok{(int64_t)off[0] == 0 && (int64_t)off[n] == nnz};
+    std::atomic<bool> ok{true};
     std::atomic<int32_t> top{0};
     parallel_for(n, 1 << 16, [&](int64_t lo, int64_t hi) {
         int32_t m = 0;
@@ -822,6 +822,8 @@ static rs_status load_on_device(const rs_csr *csr, rs_graph *g, bool *done) {
         off = h_off.data();
         lab = h_lab.data();
     }
+    // nnz is trusted (the columns' size) only when the offsets agree
+    if ((int64_t)off[0] != 0 || (int64_t)off[n] != nnz) return RS_OK;
     HostGraph H;  // (these outlive the copies: the scratch's end waits for the stream)
     std::vector<int64_t> cap, fgn;
     std::vector<int32_t> off32, f32, hubs;
@@ -865,6 +867,8 @@ static rs_status load_on_device(const rs_csr *csr, rs_graph *g, bool *done) {
             ec = hipSetDevice(dev);
             if (ec == hipSuccess) ec = hipMemcpyAsync((void *)L.off, csr->row_offsets, b_off, hipMemcpyHostToDevice, s);
             if (ec == hipSuccess) ec = hipMemcpyAsync((void *)L.col, csr->col, b_col, hipMemcpyHostToDevice, s);
+            const hipError_t es = hipStreamSynchronize(s);  // (a per-thread stream is this thread's own)
+            if (ec == hipSuccess) ec = es;
         };
         try {
             copier = std::thread(copy);
@@ -878,7 +882,7 @@ static rs_status load_on_device(const rs_csr *csr, rs_graph *g, bool *done) {
             if (t.joinable()) t.join();
         }
     } join{copier};
-    const bool good = renumber<OffIn>(n, nnz, off, lab, H, cap);
+    const bool good = renumber<OffIn>(n, off, lab, H, cap);
     for (int64_t x = 0; good && x < n; ++x)
         if (cap[x] > load_hub_row()) hubs.push_back((int32_t)x);
     if (copier.joinable()) copier.join();
@@ -974,6 +978,7 @@ static rs_status load_t(const rs_csr *csr, rs_graph *g) {
         g->dev_bytes = 0;
         g->n_requests = 0;
         g->tile_slab = nullptr;
+        (void)hipGetLastError();  // a failed allocation is not the next launch's error
         clear_error();
     }
     const OffIn *off = (const OffIn *)csr->row_offsets;

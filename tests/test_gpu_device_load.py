@@ -99,6 +99,9 @@ def test_device_load_refuses(name):
     off = g.off.copy()
     off[5] = off[7] + 1
     refused(off, g.col, g.labels, rs.RS_ERR_GRAPH)
+    off = g.off.copy()
+    off[-1] -= 1  # the offsets end before the columns do
+    refused(off, g.col, g.labels, rs.RS_ERR_GRAPH)
     lab = g.labels.copy()
     lab[11] = -2
     refused(g.off, g.col, lab, rs.RS_ERR_GRAPH)
