@@ -388,8 +388,8 @@ def bench_served(args):
     # every graph resident (a budget above the whole footprint): the served
     # form against the plain baseline on the same request mix
     resident, mix = phase(int(est * 1.25))
-    # half the footprint: admission, eviction and reloads
-    budgeted, _ = phase(est // 2)
+    # half of what the resident phase held: admission, eviction and reloads
+    budgeted, _ = phase(resident["server"]["device_bytes"] // 2)
     log("plain baseline: a full pass per request")
     plain_ms = []
     for g in graphs:
