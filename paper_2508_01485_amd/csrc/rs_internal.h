@@ -154,6 +154,35 @@ struct __align__(16) PairLink {
     int on;
 };
 
+// The type-II values by slot (k_mid): a workgroup takes kT2Tile consecutive
+// slots and stages a_v for a window of kT2Win around them.  Positions are kept
+// relative to the tile's first slot: a graph may have 2^31 - 2 slots, so a sum
+// of a slot number and a tile or window does not fit 32 bits.
+constexpr int kT2Tile = 2048;
+constexpr int kT2Win = 4096;  // staged a_v (32 KB, the size of a filter)
+__host__ __device__ inline long long type2_first(int tile) { return (long long)tile * kT2Tile; }
+// Slots of the tile.
+__host__ __device__ inline int type2_count(int slots, int tile) {
+    const long long left = (long long)slots - type2_first(tile);
+    return left < kT2Tile ? (int)left : kT2Tile;
+}
+// The window [lo, hi): from the leader of the first slot's run (f_first: that
+// slot's f, the negated distance to its leader) to the end of the last slot's
+// run (leader l_last, length f_last), as far as it holds them.
+struct Type2Window {
+    int lo, hi;
+};
+__host__ __device__ inline Type2Window type2_window(int slots, int tile, int f_first, int l_last, int f_last) {
+    constexpr int kBefore = (kT2Win - kT2Tile) / 2;
+    const int left = (int)((long long)slots - type2_first(tile)), n = type2_count(slots, tile);
+    const int end = l_last + (f_last > 1 ? f_last : 1), top = end > n ? end : n;
+    Type2Window w;
+    w.lo = f_first >= 0 ? 0 : f_first > -kBefore ? f_first : -kBefore;
+    w.hi = top < left ? top : left;
+    if (w.hi > w.lo + kT2Win) w.hi = w.lo + kT2Win;
+    return w;
+}
+
 // A row tile: vertices [v0, v1) whose rows occupy entries [e0, e0 + te).
 struct __align__(16) RowTile {
     long long e0;

@@ -1727,38 +1727,38 @@ __device__ __forceinline__ void build_filter(uint32_t *f, const VMeta *meta, con
 // with the rest of the runs cut at both ends; runs too long for the window
 // are summed from memory.
 constexpr int kT2Per = 2;
-constexpr int kT2Tile = kT2Per * kMidThreads;
-constexpr int kT2Win = 4096;  // staged a_v (32 KB, the size of a filter)
+static_assert(kT2Tile == kT2Per * kMidThreads, "kT2Per slots per thread");
 __device__ __forceinline__ void type2_tile(double *s_a, const PairRec *prec, const int32_t *fcol, const double *av,
                                            double *val2, int slots, int tile) {
-    const int s0 = tile * kT2Tile, s1 = min(slots, s0 + kT2Tile);
+    // (positions below are relative to the tile's first slot)
+    prec += type2_first(tile);
+    fcol += type2_first(tile);
+    val2 += type2_first(tile);
+    const int n = type2_count(slots, tile), tid = (int)threadIdx.x;
     // slots beyond a list that removals shrank hold the runs of an earlier
     // pass: their values are never read, and their runs stay in range
     PairRec rec[kT2Per];
     int lead[kT2Per], f[kT2Per];
 #pragma unroll
-    for (int j = 0; j < kT2Per; ++j) rec[j] = prec[min(s0 + (int)threadIdx.x + j * kMidThreads, s1 - 1)];
-    const PairRec r0 = prec[s0], r1 = prec[s1 - 1];
-    const int l1 = r1.f < 0 ? s1 - 1 + r1.f : s1 - 1;
-    const int e1 = l1 + max(1, prec[l1].f);
-    // the window: from the leader of the first slot's run to the end of the
-    // last slot's, as far as it holds them
-    const int lo = r0.f < 0 ? max(s0 + r0.f, s0 - (kT2Win - kT2Tile) / 2) : s0;
-    const int hi = min(lo + kT2Win, min(slots, max(s1, e1)));
+    for (int j = 0; j < kT2Per; ++j) rec[j] = prec[min(tid + j * kMidThreads, n - 1)];
+    const PairRec r0 = prec[0], r1 = prec[n - 1];
+    const int l1 = r1.f < 0 ? n - 1 + r1.f : n - 1;
+    const Type2Window w = type2_window(slots, tile, r0.f, l1, prec[l1].f);
+    const int lo = w.lo, hi = w.hi;
 #pragma unroll
     for (int j = 0; j < kT2Per; ++j) {
-        const int s = s0 + (int)threadIdx.x + j * kMidThreads;
+        const int s = tid + j * kMidThreads;
         lead[j] = rec[j].f < 0 ? s + rec[j].f : s;
-        f[j] = s < s1 ? (rec[j].f < 0 ? prec[lead[j]].f : rec[j].f) : 0;
+        f[j] = s < n ? (rec[j].f < 0 ? prec[lead[j]].f : rec[j].f) : 0;
         if (f[j] > 1) s_a[s - lo] = av[fcol[s]];
     }
-    for (int s = lo + (int)threadIdx.x; s < s0; s += kMidThreads) s_a[s - lo] = av[fcol[s]];
-    for (int s = s1 + (int)threadIdx.x; s < hi; s += kMidThreads) s_a[s - lo] = av[fcol[s]];
+    for (int s = lo + tid; s < 0; s += kMidThreads) s_a[s - lo] = av[fcol[s]];
+    for (int s = n + tid; s < hi; s += kMidThreads) s_a[s - lo] = av[fcol[s]];
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kT2Per; ++j) {
         if (f[j] <= 1) continue;
-        const int s = s0 + (int)threadIdx.x + j * kMidThreads;
+        const int s = tid + j * kMidThreads;
         const int b = lead[j], e = lead[j] + f[j];
         double S = 0.0;
         if (b >= lo && e <= hi) {
