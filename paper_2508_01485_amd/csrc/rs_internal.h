@@ -183,6 +183,10 @@ __host__ __device__ inline Type2Window type2_window(int slots, int tile, int f_f
     return w;
 }
 
+// Whether the flattened entries of 64 rows (`total` of them) are counted in 32
+// bits: a wavefront's group of 64 goes at most 63 beyond the last one.
+__host__ __device__ inline bool flat_rows_fit(long long total) { return total <= (long long)INT32_MAX - 63; }
+
 // A row tile: vertices [v0, v1) whose rows occupy entries [e0, e0 + te).
 struct __align__(16) RowTile {
     long long e0;

@@ -4872,14 +4872,14 @@ __global__ __launch_bounds__(kBlock) void k_cc_hook(const OffT *off, const int32
             rb = (long long)off[v];
             cnt = deg[v];
         }
-        long long incl = cnt;  // (rows of hubs: the 64 may hold more than 2^31 entries)
+        long long incl = cnt;  // (the 64 rows may hold 2^31 entries and more)
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
             const long long y = __shfl_up(incl, o);
             if (lane >= o) incl += y;
         }
         const long long total = __shfl(incl, 63);
-        if (total <= (long long)INT_MAX) {
+        if (flat_rows_fit(total)) {
             pre[lane] = (int)incl;
             row[lane] = rb;
             wave_sync();

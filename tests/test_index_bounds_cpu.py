@@ -55,3 +55,15 @@ def test_type2_tiles_cover_the_slots(slots, tmp_path):
             }}
         }}
     }}""")
+
+
+@pytest.mark.parametrize("total", [0, 1, 64, 65, 2**31 - 129, 2**31 - 65, 2**31 - 64, 2**31 - 63, 2**31 - 2, 2**31 - 1,
+                                   2**31])
+def test_flattened_rows_are_counted_in_32_bits(total, tmp_path):
+    """Groups of 64 flattened entries: those counted in 32 bits end after the
+    last entry without a wrap, and all totals short of the wrap are."""
+    _run(tmp_path, f"""
+    const long long total = {total}ll, groups = (total + 63) / 64;
+    const bool fits = groups * 64 <= (long long)INT_MAX;  // the group that ends the loop
+    REQUIRE(!flat_rows_fit(total) || fits);
+    REQUIRE(flat_rows_fit(total) || total > (long long)INT_MAX - 64);""")
