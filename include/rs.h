@@ -288,12 +288,13 @@ rs_status rs_topk_batch(rs_graph *g, int64_t k, int32_t *ids, double *scores, in
  * kernels over vertices and edges; Section VI-C, the cost of skewed degrees).
  *
  * rs_get_tiling reads a graph's cut-offs.  rs_set_tiling re-cuts its schedule
- * (host work over n, and the schedule's device arrays are replaced); the
- * graph must then be scored again (RS_ERR_STATE from the readers until
- * rs_score).  Scores and counts do not depend on the cut-offs, except that
- * vertices that change between tile and hub sum their terms in another
- * order (the same values within rounding).  Errors: RS_ERR_ARG (a value out
- * of range).
+ * (host work over n, and the schedule's device arrays are replaced: the new
+ * ones are made before the old ones are freed); the graph must then be scored
+ * again (RS_ERR_STATE from the readers until rs_score).  Scores and counts do
+ * not depend on the cut-offs, except that vertices that change between tile and
+ * hub sum their terms in another order (the same values within rounding).
+ * Errors: RS_ERR_ARG (a value out of range), RS_ERR_NOMEM (no room for the new
+ * schedule beside the old one, which the graph then keeps).
  *
  * rs_autotune: the project's autotuner.  It cuts the schedule for each of the
  * n_cand candidates in turn, runs one untimed pass and then `reps` timed

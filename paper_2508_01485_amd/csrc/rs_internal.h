@@ -352,6 +352,7 @@ struct rs_graph {
     std::vector<std::pair<void *, size_t>> allocations;  // device buffers and their sizes
     long long n_requests = 0;                            // buffers asked for so far
     void *tile_slab = nullptr;                           // the schedule's arrays
+    void *gblk_slab = nullptr;                           // a batch's row blocks of each graph
     rs::Tiling tiling;
     // pinned staging of the readers' results (first use)
     char *read_host = nullptr;

@@ -71,13 +71,12 @@ struct DevReq {
 };
 // Buffers that live and die together share one device allocation (its base in
 // *slab, if wanted): a graph's sixty buffers cost 75 us each to free and 20 us
-// to allocate one by one.
+// to allocate one by one.  On an error no pointer is changed.
 static hipError_t dev_alloc_group(rs_graph *g, const DevReq *reqs, size_t n, void **slab = nullptr) {
     constexpr size_t kAlign = 256;
     const char *f = std::getenv("RS_FAULT_ALLOC");
     size_t total = 0;
     for (size_t i = 0; i < n; ++i) {
-        *reqs[i].p = nullptr;
         total += (std::max<size_t>(reqs[i].bytes, 16) + kAlign - 1) / kAlign * kAlign;
         if (f && std::atoll(f) == ++g->n_requests) return hipErrorOutOfMemory;
     }
@@ -471,27 +470,19 @@ static rs_status build_internal(int64_t n, int64_t nnz, const OffIn *off, const 
     return RS_OK;
 }
 
-// Allocate and fill the schedule's device arrays, freeing any earlier
-// ones: tiles and hubs, the per-block partials, the incremental re-score's
-// unit flags and lists, and each vertex's row block and score unit.  Leaves
-// the copies queued on the graph's stream.
+// Allocate and fill the schedule's device arrays: tiles and hubs, the
+// per-block partials, the incremental re-score's unit flags and lists, and each
+// vertex's row block and score unit.  Leaves the copies queued on the graph's
+// stream, and any earlier schedule's arrays to the caller.
 static rs_status upload_tiles(rs_graph *g, const HostTiles &H) {
     DeviceGraph &D = g->d;
-    dev_free(g, &g->tile_slab);
     const size_t N = (size_t)std::max<int64_t>(D.n, 1);
-    g->n_rtiles = (int)H.rtiles.size();
-    g->n_rhubs = (int)H.rhubs.size();
-    g->n_stiles = (int)H.stiles.size();
-    g->n_shubs = (int)H.shubs.size();
-    g->n_schunks = (int)H.schunk.size();
-    g->n_schunks_lds = H.n_chunks_lds;
-    g->n_shubs_lds = H.n_hubs_lds;
-    g->grid_rows = tile_grid(g->n_rhubs, g->n_rtiles);
-    g->grid_score = tile_grid(g->n_schunks, g->n_stiles);
     const size_t nch = std::max<size_t>(H.schunk.size(), 1);
     const size_t nrt = std::max<size_t>(H.rtiles.size(), 1), nrh = std::max<size_t>(H.rhubs.size(), 1);
     const size_t nst = std::max<size_t>(H.stiles.size(), 1), nsh = std::max<size_t>(H.shubs.size(), 1);
-    const size_t gr = (size_t)std::max(g->grid_rows, 1), gs = (size_t)std::max(g->grid_score, 1);
+    const int grid_rows = tile_grid((int)H.rhubs.size(), (int)H.rtiles.size());
+    const int grid_score = tile_grid((int)H.schunk.size(), (int)H.stiles.size());
+    const size_t gr = (size_t)std::max(grid_rows, 1), gs = (size_t)std::max(grid_score, 1);
     const DevReq reqs[] = {
         {(void **)&D.rtiles, sizeof(RowTile) * nrt},
         {(void **)&D.rhubs, 4 * nrh},
@@ -515,6 +506,15 @@ static rs_status upload_tiles(rs_graph *g, const HostTiles &H) {
     };
     hipError_t e = dev_alloc_group(g, reqs, sizeof(reqs) / sizeof(reqs[0]), &g->tile_slab);
     if (e != hipSuccess) return hip_fail(e, "device allocation");
+    g->n_rtiles = (int)H.rtiles.size();
+    g->n_rhubs = (int)H.rhubs.size();
+    g->n_stiles = (int)H.stiles.size();
+    g->n_shubs = (int)H.shubs.size();
+    g->n_schunks = (int)H.schunk.size();
+    g->n_schunks_lds = H.n_chunks_lds;
+    g->n_shubs_lds = H.n_hubs_lds;
+    g->grid_rows = grid_rows;
+    g->grid_score = grid_score;
     hipStream_t s = g->stream;
     auto put = [&](void *dst, const void *src, size_t bytes) {
         if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
@@ -1191,11 +1191,47 @@ static Tiling to_tiling(const rs_tiling *t) {
     return T;
 }
 
+// A graph's schedule while a new one is made.
+struct ScheduleState {
+    DeviceGraph d;
+    void *tile_slab, *gblk_slab;
+    int n_rtiles, n_rhubs, n_stiles, n_shubs, n_schunks, n_schunks_lds, n_shubs_lds, grid_rows, grid_score;
+    explicit ScheduleState(const rs_graph *g)
+        : d(g->d), tile_slab(g->tile_slab), gblk_slab(g->gblk_slab), n_rtiles(g->n_rtiles), n_rhubs(g->n_rhubs),
+          n_stiles(g->n_stiles), n_shubs(g->n_shubs), n_schunks(g->n_schunks), n_schunks_lds(g->n_schunks_lds),
+          n_shubs_lds(g->n_shubs_lds), grid_rows(g->grid_rows), grid_score(g->grid_score) {}
+    // The new one did not come about: free what there is of it, keep this one.
+    void restore(rs_graph *g) const {
+        if (g->tile_slab != tile_slab) dev_free(g, &g->tile_slab);
+        if (g->gblk_slab != gblk_slab) dev_free(g, &g->gblk_slab);
+        g->d = d;
+        g->tile_slab = tile_slab;
+        g->gblk_slab = gblk_slab;
+        g->n_rtiles = n_rtiles;
+        g->n_rhubs = n_rhubs;
+        g->n_stiles = n_stiles;
+        g->n_shubs = n_shubs;
+        g->n_schunks = n_schunks;
+        g->n_schunks_lds = n_schunks_lds;
+        g->n_shubs_lds = n_shubs_lds;
+        g->grid_rows = grid_rows;
+        g->grid_score = grid_score;
+    }
+    // The new one is in place: free this one (the stream is idle).
+    void drop(rs_graph *g) const {
+        void *p = tile_slab;
+        if (g->tile_slab != p) dev_free(g, &p);
+        p = gblk_slab;
+        if (g->gblk_slab != p) dev_free(g, &p);
+    }
+};
+
 // Re-cut the schedule of a resident graph for the tiling T.  The cut needs
 // each vertex's row capacity and load-time foreign degree, which the device
 // keeps as the capacity layout and the pair-slot offsets; the tiles are cut
 // on the host and the schedule's arrays replaced, and the graph must be scored
-// again.
+// again.  The old schedule goes once the new one is in place: on an error the
+// graph keeps it, its tiling and its results.
 static rs_status retile(rs_graph *g, const Tiling &T) {
     DeviceGraph &D = g->d;
     const int64_t n = D.n;
@@ -1226,23 +1262,31 @@ static rs_status retile(rs_graph *g, const Tiling &T) {
     } catch (const std::bad_alloc &) {
         return fail(RS_ERR_NOMEM, "host allocation failed while cutting tiles");
     }
+    const ScheduleState old(g);
     rs_status st = upload_tiles(g, X);
     if (st == RS_OK && g->n_graphs > 0) {  // a batch's row blocks of each graph
-        dev_free(g, (void **)&D.gblk_off);
-        dev_free(g, (void **)&D.gblk);
-        e = dev_alloc(g, (void **)&D.gblk_off, 4 * X.gblk_off.size());
-        if (e == hipSuccess) e = dev_alloc(g, (void **)&D.gblk, 4 * std::max<size_t>(X.gblk.size(), 1));
+        const DevReq reqs[] = {
+            {(void **)&D.gblk_off, 4 * X.gblk_off.size()},
+            {(void **)&D.gblk, 4 * std::max<size_t>(X.gblk.size(), 1)},
+        };
+        e = dev_alloc_group(g, reqs, 2, &g->gblk_slab);
         if (e == hipSuccess)
             e = hipMemcpyAsync(D.gblk_off, X.gblk_off.data(), 4 * X.gblk_off.size(), hipMemcpyHostToDevice, g->stream);
         if (e == hipSuccess && !X.gblk.empty())
             e = hipMemcpyAsync(D.gblk, X.gblk.data(), 4 * X.gblk.size(), hipMemcpyHostToDevice, g->stream);
         if (e != hipSuccess) st = hip_fail(e, "retile: batch row blocks");
+    }
+    e = hipStreamSynchronize(g->stream);  // (on an error too: the copies read this frame's arrays)
+    if (st == RS_OK && e != hipSuccess) st = hip_fail(e, "retile");
+    if (st != RS_OK) {
+        (void)hipGetLastError();  // a failed allocation is not the next launch's error
+        old.restore(g);
+        return st;
+    }
+    old.drop(g);
+    if (g->n_graphs > 0) {
         g->h_gblk_off.swap(X.gblk_off);
         g->h_gblk.swap(X.gblk);
-    }
-    if (st == RS_OK) {
-        e = hipStreamSynchronize(g->stream);
-        if (e != hipSuccess) st = hip_fail(e, "retile");
     }
     g->tiling = T;
     g->scored = false;
@@ -1378,8 +1422,11 @@ rs_status rs_load_batch(int32_t n_graphs, const int64_t *vertex_offsets, const r
     };
     hipError_t e = dev_alloc_group(g, reqs, sizeof(reqs) / sizeof(reqs[0]));
     // (replaced when the schedule is cut again)
-    if (e == hipSuccess) e = dev_alloc(g, (void **)&D.gblk_off, 4 * (G + 1));
-    if (e == hipSuccess) e = dev_alloc(g, (void **)&D.gblk, 4 * std::max<size_t>(g->h_gblk.size(), 1));
+    const DevReq blocks[] = {
+        {(void **)&D.gblk_off, 4 * (G + 1)},
+        {(void **)&D.gblk, 4 * std::max<size_t>(g->h_gblk.size(), 1)},
+    };
+    if (e == hipSuccess) e = dev_alloc_group(g, blocks, 2, &g->gblk_slab);
     if (e == hipSuccess) e = hipMemcpyAsync(D.vstart, vertex_offsets, 8 * (G + 1), hipMemcpyHostToDevice, g->stream);
     if (e == hipSuccess && n) e = hipMemcpyAsync(D.vgraph, vg.data(), 4 * n, hipMemcpyHostToDevice, g->stream);
     if (e == hipSuccess)
@@ -1773,6 +1820,7 @@ rs_status rs_autotune(rs_graph *g, int32_t n_cand, const rs_tiling *cand, int32_
         if (st != RS_OK) return st;
     }
     const bool was_scored = g->scored;
+    const Tiling before = g->tiling;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
@@ -1794,12 +1842,18 @@ rs_status rs_autotune(rs_graph *g, int32_t n_cand, const rs_tiling *cand, int32_
     }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
-    if (st != RS_OK) return st;
-    *best = b;
-    st = retile(g, to_tiling(&cand[b]));
-    if (st == RS_OK && was_scored) {
-        st = launch_score_pass(g);
-        if (st == RS_OK) g->scored = true;
+    if (st == RS_OK) st = retile(g, to_tiling(&cand[b]));
+    if (st == RS_OK) {
+        *best = b;
+    } else if (b >= 0) {  // back to the cut-offs before the first candidate
+        std::string keep = g_err;
+        if (retile(g, before) != RS_OK) return st;  // (g holds a candidate's, to be scored)
+        g_err = keep;
+    }
+    if (was_scored && !g->scored) {
+        const rs_status ss = launch_score_pass(g);
+        if (ss == RS_OK) g->scored = true;
+        if (st == RS_OK) st = ss;
     }
     return st;
 }
