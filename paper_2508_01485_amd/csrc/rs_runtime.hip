@@ -8,6 +8,7 @@
 // graph's stream (rs_kernels.hip); the host only marshals arguments, sizes
 // launches and copies results.
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cstdlib>
 #include <cstring>
@@ -69,15 +70,22 @@ struct DevReq {
     void **p;
     size_t bytes;
 };
+// Buffers are laid out at multiples of 256 bytes.
+static size_t slab_part(const DevReq &r) { return (std::max<size_t>(r.bytes, 16) + 255) / 256 * 256; }
+template <size_t N>
+static size_t group_bytes(const std::array<DevReq, N> &reqs) {
+    size_t total = 0;
+    for (const DevReq &r : reqs) total += slab_part(r);
+    return total;
+}
 // Buffers that live and die together share one device allocation (its base in
 // *slab, if wanted): a graph's sixty buffers cost 75 us each to free and 20 us
 // to allocate one by one.  On an error no pointer is changed.
 static hipError_t dev_alloc_group(rs_graph *g, const DevReq *reqs, size_t n, void **slab = nullptr) {
-    constexpr size_t kAlign = 256;
     const char *f = std::getenv("RS_FAULT_ALLOC");
     size_t total = 0;
     for (size_t i = 0; i < n; ++i) {
-        total += (std::max<size_t>(reqs[i].bytes, 16) + kAlign - 1) / kAlign * kAlign;
+        total += slab_part(reqs[i]);
         if (f && std::atoll(f) == ++g->n_requests) return hipErrorOutOfMemory;
     }
     char *base = nullptr;
@@ -93,7 +101,7 @@ static hipError_t dev_alloc_group(rs_graph *g, const DevReq *reqs, size_t n, voi
     if (slab) *slab = base;
     for (size_t i = 0; i < n; ++i) {
         *reqs[i].p = base;
-        base += (std::max<size_t>(reqs[i].bytes, 16) + kAlign - 1) / kAlign * kAlign;
+        base += slab_part(reqs[i]);
     }
     return e;
 }
@@ -470,41 +478,47 @@ static rs_status build_internal(int64_t n, int64_t nnz, const OffIn *off, const 
     return RS_OK;
 }
 
+static int rows_grid(const HostTiles &H) { return tile_grid((int)H.rhubs.size(), (int)H.rtiles.size()); }
+static int score_grid(const HostTiles &H) { return tile_grid((int)H.schunk.size(), (int)H.stiles.size()); }
+
+// The schedule's device arrays.
+static auto tile_reqs(DeviceGraph &D, int64_t n_out, const HostTiles &H) {
+    const size_t N = (size_t)std::max<int64_t>(D.n, 1);
+    const size_t nch = std::max<size_t>(H.schunk.size(), 1);
+    const size_t nrt = std::max<size_t>(H.rtiles.size(), 1), nrh = std::max<size_t>(H.rhubs.size(), 1);
+    const size_t nst = std::max<size_t>(H.stiles.size(), 1), nsh = std::max<size_t>(H.shubs.size(), 1);
+    const size_t gr = (size_t)std::max(rows_grid(H), 1), gs = (size_t)std::max(score_grid(H), 1);
+    return std::array{
+        DevReq{(void **)&D.rtiles, sizeof(RowTile) * nrt},
+        DevReq{(void **)&D.rhubs, 4 * nrh},
+        DevReq{(void **)&D.stiles, sizeof(int2) * nst},
+        DevReq{(void **)&D.shubs, 4 * nsh},
+        DevReq{(void **)&D.shub_first, 4 * (nsh + 1)},
+        DevReq{(void **)&D.shub_chunk, sizeof(int2) * nch},
+        DevReq{(void **)&D.hub_part, sizeof(HubPart) * nch},
+        DevReq{(void **)&D.rflag, gr},
+        DevReq{(void **)&D.cflag, nch},
+        DevReq{(void **)&D.hflag, nsh},
+        DevReq{(void **)&D.rlist, 4 * gr},
+        DevReq{(void **)&D.slist, 4 * gs},
+        DevReq{(void **)&D.hlist, 4 * nch},
+        DevReq{(void **)&D.part_rows, sizeof(RowPart) * gr},
+        DevReq{(void **)&D.wmax_part, 8 * gr},
+        DevReq{(void **)&D.vrowb, 4 * N},
+        DevReq{(void **)&D.vscore, 4 * N},
+        DevReq{(void **)&D.sown, (size_t)std::max<int64_t>(2 * n_out, 1)},
+        DevReq{(void **)&D.hfilter, 4 * (size_t)kFilterWords * std::max<size_t>(H.shubs.size() - H.n_hubs_lds, 1)}
+    };
+}
+
 // Allocate and fill the schedule's device arrays: tiles and hubs, the
 // per-block partials, the incremental re-score's unit flags and lists, and each
 // vertex's row block and score unit.  Leaves the copies queued on the graph's
 // stream, and any earlier schedule's arrays to the caller.
 static rs_status upload_tiles(rs_graph *g, const HostTiles &H) {
     DeviceGraph &D = g->d;
-    const size_t N = (size_t)std::max<int64_t>(D.n, 1);
-    const size_t nch = std::max<size_t>(H.schunk.size(), 1);
-    const size_t nrt = std::max<size_t>(H.rtiles.size(), 1), nrh = std::max<size_t>(H.rhubs.size(), 1);
-    const size_t nst = std::max<size_t>(H.stiles.size(), 1), nsh = std::max<size_t>(H.shubs.size(), 1);
-    const int grid_rows = tile_grid((int)H.rhubs.size(), (int)H.rtiles.size());
-    const int grid_score = tile_grid((int)H.schunk.size(), (int)H.stiles.size());
-    const size_t gr = (size_t)std::max(grid_rows, 1), gs = (size_t)std::max(grid_score, 1);
-    const DevReq reqs[] = {
-        {(void **)&D.rtiles, sizeof(RowTile) * nrt},
-        {(void **)&D.rhubs, 4 * nrh},
-        {(void **)&D.stiles, sizeof(int2) * nst},
-        {(void **)&D.shubs, 4 * nsh},
-        {(void **)&D.shub_first, 4 * (nsh + 1)},
-        {(void **)&D.shub_chunk, sizeof(int2) * nch},
-        {(void **)&D.hub_part, sizeof(HubPart) * nch},
-        {(void **)&D.rflag, gr},
-        {(void **)&D.cflag, nch},
-        {(void **)&D.hflag, nsh},
-        {(void **)&D.rlist, 4 * gr},
-        {(void **)&D.slist, 4 * gs},
-        {(void **)&D.hlist, 4 * nch},
-        {(void **)&D.part_rows, sizeof(RowPart) * gr},
-        {(void **)&D.wmax_part, 8 * gr},
-        {(void **)&D.vrowb, 4 * N},
-        {(void **)&D.vscore, 4 * N},
-        {(void **)&D.sown, (size_t)std::max<int64_t>(2 * g->n_out, 1)},
-        {(void **)&D.hfilter, 4 * (size_t)kFilterWords * std::max<size_t>(H.shubs.size() - H.n_hubs_lds, 1)},
-    };
-    hipError_t e = dev_alloc_group(g, reqs, sizeof(reqs) / sizeof(reqs[0]), &g->tile_slab);
+    const auto reqs = tile_reqs(D, g->n_out, H);
+    hipError_t e = dev_alloc_group(g, reqs.data(), reqs.size(), &g->tile_slab);
     if (e != hipSuccess) return hip_fail(e, "device allocation");
     g->n_rtiles = (int)H.rtiles.size();
     g->n_rhubs = (int)H.rhubs.size();
@@ -513,8 +527,8 @@ static rs_status upload_tiles(rs_graph *g, const HostTiles &H) {
     g->n_schunks = (int)H.schunk.size();
     g->n_schunks_lds = H.n_chunks_lds;
     g->n_shubs_lds = H.n_hubs_lds;
-    g->grid_rows = grid_rows;
-    g->grid_score = grid_score;
+    g->grid_rows = rows_grid(H);
+    g->grid_score = score_grid(H);
     hipStream_t s = g->stream;
     auto put = [&](void *dst, const void *src, size_t bytes) {
         if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
@@ -527,65 +541,84 @@ static rs_status upload_tiles(rs_graph *g, const HostTiles &H) {
     put(D.shub_chunk, H.schunk.data(), sizeof(int2) * H.schunk.size());
     put(D.vrowb, H.vrowb.data(), 4 * H.vrowb.size());
     put(D.vscore, H.vscore.data(), 4 * H.vscore.size());
-    if (e == hipSuccess) e = hipMemsetAsync(D.rflag, 0, gr, s);
-    if (e == hipSuccess) e = hipMemsetAsync(D.cflag, 0, nch, s);
-    if (e == hipSuccess) e = hipMemsetAsync(D.hflag, 0, nsh, s);
+    if (e == hipSuccess) e = hipMemsetAsync(D.rflag, 0, (size_t)std::max(g->grid_rows, 1), s);
+    if (e == hipSuccess) e = hipMemsetAsync(D.cflag, 0, std::max<size_t>(H.schunk.size(), 1), s);
+    if (e == hipSuccess) e = hipMemsetAsync(D.hflag, 0, std::max<size_t>(H.shubs.size(), 1), s);
     return e == hipSuccess ? launch_slot_owners(g) : hip_fail(e, "schedule upload");
 }
 
 // The graph's device arrays: those sized by its vertices and entries, cleared
 // where a pass expects it, and those sized by its slots (2 n_out).
-static rs_status alloc_vertices(rs_graph *g, int64_t n, int64_t nnz, int64_t k) {
-    DeviceGraph &D = g->d;
+static void set_sizes(DeviceGraph &D, int64_t n, int64_t nnz, int64_t k, bool wide) {
     D.n = n;
     D.nnz = nnz;
     D.k = (int32_t)k;
-    D.off64 = nnz > (int64_t)INT32_MAX || g->wide_offsets;
-    const size_t N = (size_t)std::max<int64_t>(n, 1), Z = (size_t)std::max<int64_t>(nnz, 1);
+    D.off64 = nnz > (int64_t)INT32_MAX || wide;
+}
+static auto vertex_reqs(DeviceGraph &D) {
+    const size_t N = (size_t)std::max<int64_t>(D.n, 1), Z = (size_t)std::max<int64_t>(D.nnz, 1);
     const size_t offb = D.off64 ? 8 : 4;
-    const DevReq reqs[] = {
-        {&D.off, offb * (N + 1)},
-        {(void **)&D.deg, 4 * N},
-        {(void **)&D.col, 4 * Z},
-        {(void **)&D.clab, 4 * Z},
-        {(void **)&D.lab, 4 * N},
-        {(void **)&D.new2old, 4 * N},
-        {(void **)&D.alive, N},
-        {(void **)&D.oo, 8 * (N + 1)},
-        {(void **)&D.goff, 4 * (N + 1)},
-        {(void **)&D.cstart, 4 * ((size_t)D.k + 1)},
-        {(void **)&D.wpart, 8 * (size_t)kWorkBlocks},
-        {(void **)&D.tables, table_bytes()},
-        {(void **)&D.raw, 8 * N},
-        {(void **)&D.vmark, 4 * N},
-        {(void **)&D.elist, 4 * N},
-        {(void **)&D.ucnt, 4 * (size_t)kUnitRows * kUnitGroups},
-        {(void **)&D.abin, 4 * N},
-        {(void **)&D.echunk, sizeof(int2) * (N + Z / 64 + 1)},
-        {(void **)&D.ictr, 8 * (size_t)kIcCount},
-        {(void **)&D.ictr_next, 8 * (size_t)kIcCount},
-        {(void **)&D.wblk, 8 * 64},
-        {(void **)&D.wticket, 8},
-        {(void **)&D.meta, sizeof(VMeta) * N},
-        {(void **)&D.wown, 8 * N},
-        {(void **)&D.av, 8 * N},
-        {(void **)&D.R, 8 * N},
-        {(void **)&D.tI, 8 * N},
-        {(void **)&D.tII, 8 * N},
-        {(void **)&D.ctr, sizeof(DevCounters)},
-        {(void **)&D.thist, 4 * (size_t)kTopkBins},
-        {(void **)&D.thist_c, 4 * 256},
-        {(void **)&D.tstate, sizeof(TopkState)},
-        {(void **)&D.tfinal, sizeof(TopkKey) * N},
-        {(void **)&D.ttie, sizeof(TopkKey) * N},
-        {(void **)&D.ttie2, sizeof(TopkKey) * N},
-        {(void **)&D.tout_ids, 4 * N},
-        {(void **)&D.tout_sc, 8 * N},
-        {(void **)&D.scratch_d, 8 * N},
-        {(void **)&D.tblk, 16 + 16 * N},
-        {(void **)&D.scratch_u, 8 * 8},
+    return std::array{
+        DevReq{&D.off, offb * (N + 1)},
+        DevReq{(void **)&D.deg, 4 * N},
+        DevReq{(void **)&D.col, 4 * Z},
+        DevReq{(void **)&D.clab, 4 * Z},
+        DevReq{(void **)&D.lab, 4 * N},
+        DevReq{(void **)&D.new2old, 4 * N},
+        DevReq{(void **)&D.alive, N},
+        DevReq{(void **)&D.oo, 8 * (N + 1)},
+        DevReq{(void **)&D.goff, 4 * (N + 1)},
+        DevReq{(void **)&D.cstart, 4 * ((size_t)D.k + 1)},
+        DevReq{(void **)&D.wpart, 8 * (size_t)kWorkBlocks},
+        DevReq{(void **)&D.tables, table_bytes()},
+        DevReq{(void **)&D.raw, 8 * N},
+        DevReq{(void **)&D.vmark, 4 * N},
+        DevReq{(void **)&D.elist, 4 * N},
+        DevReq{(void **)&D.ucnt, 4 * (size_t)kUnitRows * kUnitGroups},
+        DevReq{(void **)&D.abin, 4 * N},
+        DevReq{(void **)&D.echunk, sizeof(int2) * (N + Z / 64 + 1)},
+        DevReq{(void **)&D.ictr, 8 * (size_t)kIcCount},
+        DevReq{(void **)&D.ictr_next, 8 * (size_t)kIcCount},
+        DevReq{(void **)&D.wblk, 8 * 64},
+        DevReq{(void **)&D.wticket, 8},
+        DevReq{(void **)&D.meta, sizeof(VMeta) * N},
+        DevReq{(void **)&D.wown, 8 * N},
+        DevReq{(void **)&D.av, 8 * N},
+        DevReq{(void **)&D.R, 8 * N},
+        DevReq{(void **)&D.tI, 8 * N},
+        DevReq{(void **)&D.tII, 8 * N},
+        DevReq{(void **)&D.ctr, sizeof(DevCounters)},
+        DevReq{(void **)&D.thist, 4 * (size_t)kTopkBins},
+        DevReq{(void **)&D.thist_c, 4 * 256},
+        DevReq{(void **)&D.tstate, sizeof(TopkState)},
+        DevReq{(void **)&D.tfinal, sizeof(TopkKey) * N},
+        DevReq{(void **)&D.ttie, sizeof(TopkKey) * N},
+        DevReq{(void **)&D.ttie2, sizeof(TopkKey) * N},
+        DevReq{(void **)&D.tout_ids, 4 * N},
+        DevReq{(void **)&D.tout_sc, 8 * N},
+        DevReq{(void **)&D.scratch_d, 8 * N},
+        DevReq{(void **)&D.tblk, 16 + 16 * N},
+        DevReq{(void **)&D.scratch_u, 8 * 8}
     };
-    hipError_t e = dev_alloc_group(g, reqs, sizeof(reqs) / sizeof(reqs[0]));
+}
+static auto slot_reqs(DeviceGraph &D, int64_t n_out) {
+    const size_t NX = std::max<size_t>(2 * (size_t)n_out, 1), NO = std::max<size_t>((size_t)n_out, 1);
+    return std::array{
+        DevReq{(void **)&D.fcol, 4 * NX},
+        DevReq{(void **)&D.prec, sizeof(PairRec) * NX},
+        DevReq{(void **)&D.val2, 8 * NX},
+        DevReq{(void **)&D.plink, sizeof(PairLink) * NX},
+        DevReq{(void **)&D.outl, 4 * NO},
+        DevReq{(void **)&D.oe, sizeof(OutEnt) * NO}
+    };
+}
+
+static rs_status alloc_vertices(rs_graph *g, int64_t n, int64_t nnz, int64_t k) {
+    DeviceGraph &D = g->d;
+    set_sizes(D, n, nnz, k, g->wide_offsets);
+    const size_t N = (size_t)std::max<int64_t>(n, 1);
+    const auto reqs = vertex_reqs(D);
+    hipError_t e = dev_alloc_group(g, reqs.data(), reqs.size());
     if (e != hipSuccess) return hip_fail(e, "device allocation");
     hipStream_t s = g->stream;
     e = hipMemsetAsync(D.alive, 1, N, s);
@@ -601,18 +634,9 @@ static rs_status alloc_vertices(rs_graph *g, int64_t n, int64_t nnz, int64_t k) 
 }
 
 static rs_status alloc_slots(rs_graph *g, int64_t n_out) {
-    DeviceGraph &D = g->d;
     g->n_out = n_out;
-    const size_t NX = std::max<size_t>(2 * (size_t)n_out, 1), NO = std::max<size_t>((size_t)n_out, 1);
-    const DevReq reqs[] = {
-        {(void **)&D.fcol, 4 * NX},
-        {(void **)&D.prec, sizeof(PairRec) * NX},
-        {(void **)&D.val2, 8 * NX},
-        {(void **)&D.plink, sizeof(PairLink) * NX},
-        {(void **)&D.outl, 4 * NO},
-        {(void **)&D.oe, sizeof(OutEnt) * NO},
-    };
-    const hipError_t e = dev_alloc_group(g, reqs, sizeof(reqs) / sizeof(reqs[0]));
+    const auto reqs = slot_reqs(g->d, n_out);
+    const hipError_t e = dev_alloc_group(g, reqs.data(), reqs.size());
     return e == hipSuccess ? RS_OK : hip_fail(e, "device allocation");
 }
 
@@ -1072,6 +1096,16 @@ rs_status load_prebuilt(Prebuilt *P, void *hip_stream, rs_graph **out) {
 }
 
 void free_prebuilt(Prebuilt *P) { delete P; }
+
+// (From the lists that the load itself allocates from.)
+void prebuilt_allocations(const Prebuilt *P, size_t (&bytes)[3]) {
+    DeviceGraph D;
+    set_sizes(D, P->n, P->nnz, (int64_t)P->H.comm2orig.size(), false);
+    const int64_t n_out = (int64_t)P->H.outl.size();
+    bytes[0] = group_bytes(vertex_reqs(D));
+    bytes[1] = group_bytes(slot_reqs(D, n_out));
+    bytes[2] = group_bytes(tile_reqs(D, n_out, P->H));
+}
 
 template <class T>
 static hipError_t d2h(std::vector<T> &dst, const void *src, int64_t count);

@@ -35,9 +35,8 @@ struct ServedGraph {
     // removal history (caller ids): edges as (src, dst) pairs, vertices
     std::vector<int32_t> hist_src, hist_dst, hist_vert;
     rs_graph *h = nullptr;
-    rs::Prebuilt *pre = nullptr;  // validated, renumbered host form (built on the first load)
+    rs::Prebuilt *pre = nullptr;  // validated, renumbered host form (built by the first request)
     int64_t bytes = 0;     // device bytes counted in the budget while resident
-    int64_t estimate = 0;  // device bytes expected before the first load
     int64_t known = 0;     // device bytes measured at the last residency (0: never loaded)
     bool busy = false;
     int64_t last_use = 0;
@@ -56,23 +55,30 @@ struct Request {
     bool done = false;
 };
 
-// Device bytes of a graph before it is first loaded: an estimate from the
-// resident layout (per entry: col and its community; per vertex: offsets, row
-// facts, scores, top-k lists, marks; per G' entry: neighbour, record, link and
-// half an out-list entry), on the safe side for graphs whose edges mostly stay
-// inside their communities.
-int64_t estimate_bytes(int64_t n, int64_t nnz) {
-    return 48 * nnz + 360 * n + (8 << 20);
-}
-
 // Device bytes a resident graph is charged with.  The runtime hands out device
 // memory in chunks of 2 MiB and takes more for streams (25 MB and more with some
 // of the first): forty graphs whose own buffers hold 1.6 to 3.0 MB took 7.2 MB
 // of free device memory each.
-int64_t charged_bytes(const rs_graph *h) {
+int64_t charge(int64_t bytes) {
     constexpr int64_t kChunk = 2 << 20;
-    return (h->dev_bytes + kChunk - 1) / kChunk * kChunk + kChunk;
+    return (bytes + kChunk - 1) / kChunk * kChunk + kChunk;
 }
+int64_t charged_bytes(const rs_graph *h) { return charge(h->dev_bytes); }
+
+// What a graph is charged with before it was ever loaded, from the sizes of its
+// host form: the same allocations, so a load is neither refused nor let in on a
+// guess.
+int64_t charged_bytes(const rs::Prebuilt *P) {
+    size_t b[3];
+    rs::prebuilt_allocations(P, b);
+    return charge((int64_t)(b[0] + b[1] + b[2]));
+}
+
+// A first load finds this much more room, where the budget has it: the first
+// kernels on a new stream may take device memory for a hardware queue and its
+// scratch (eight handles took 148 MiB, of which 136 stayed with the process),
+// and the request adds its staging.
+constexpr int64_t kFirstLoadRoom = 16 << 20;
 
 }  // namespace
 
@@ -141,13 +147,22 @@ struct rs_server {
             sg.busy = true;
             r.info.t_start = now_ns();
             // residency: reserve the graph's bytes, evicting idle graphs
+            rs_status st = RS_OK;
             bool fresh = false;
-            if (!sg.h) {
-                const int64_t need = sg.known > 0 ? sg.known : sg.estimate;
-                if (budget > 0 && need > budget) {
-                    r.status = RS_ERR_NOMEM;
+            if (!sg.h && !sg.pre) {  // the host form first: it has the sizes
+                lk.unlock();
+                st = prebuild(sg);
+                if (st != RS_OK) r.error = rs_last_error();
+                lk.lock();
+            }
+            if (!sg.h && st == RS_OK) {
+                const int64_t own = sg.known > 0 ? sg.known : charged_bytes(sg.pre);
+                if (budget > 0 && own > budget) {
+                    st = RS_ERR_NOMEM;
                     r.error = "graph larger than the whole HBM budget";
                 } else {
+                    int64_t need = own;
+                    if (sg.known == 0) need = budget > 0 ? std::min(own + kFirstLoadRoom, budget) : own + kFirstLoadRoom;
                     cv_work.wait(lk, [&] { return make_room(need, r.gid); });
                     used += need;
                     sg.bytes = need;
@@ -158,14 +173,14 @@ struct rs_server {
             // its handle, and the handle is only published under mu
             rs_graph *h = sg.h;
             lk.unlock();
-            rs_status st = r.status;
             if (st == RS_OK && fresh) {
                 st = load(sg, &h);
                 if (st == RS_OK) {
                     lk.lock();
                     sg.h = h;
-                    // the reservation becomes the measured size; idle graphs
-                    // make way if the estimate was short, else the request fails
+                    // the reservation becomes the size held; idle graphs make
+                    // way if that is more (a reload whose removals staged more
+                    // than before), else the request fails
                     used += charged_bytes(h) - sg.bytes;
                     sg.bytes = sg.known = charged_bytes(h);
                     if (!make_room(0, r.gid)) {
@@ -206,29 +221,30 @@ struct rs_server {
         }
     }
 
-    // Load a graph and bring it to its current state: a full pass, then its
-    // removal history as one batch.  The first load validates and renumbers
-    // the host copy once and keeps that form (the copy itself is dropped);
-    // a reload after an eviction only uploads it.
+    // Validate and renumber a graph's host copy, once: that form is kept and
+    // the copy itself is dropped.
+    rs_status prebuild(ServedGraph &sg) {
+        rs_csr c;
+        c.n = sg.n;
+        c.nnz = sg.nnz;
+        c.offset_bytes = 8;
+        c.on_device = 0;
+        c.row_offsets = sg.off.data();
+        c.col = sg.col.data();
+        c.labels = sg.lab.data();
+        const rs_status st = rs::prebuild_graph(&c, &sg.pre);
+        if (st != RS_OK) return st;
+        std::vector<int64_t>().swap(sg.off);
+        std::vector<int32_t>().swap(sg.col);
+        std::vector<int32_t>().swap(sg.lab);
+        return RS_OK;
+    }
+
+    // Upload a graph's host form and bring it to its current state: a full
+    // pass, then its removal history as one batch.
     rs_status load(ServedGraph &sg, rs_graph **out) {
-        rs_status st = RS_OK;
-        if (!sg.pre) {
-            rs_csr c;
-            c.n = sg.n;
-            c.nnz = sg.nnz;
-            c.offset_bytes = 8;
-            c.on_device = 0;
-            c.row_offsets = sg.off.data();
-            c.col = sg.col.data();
-            c.labels = sg.lab.data();
-            st = rs::prebuild_graph(&c, &sg.pre);
-            if (st != RS_OK) return st;
-            std::vector<int64_t>().swap(sg.off);
-            std::vector<int32_t>().swap(sg.col);
-            std::vector<int32_t>().swap(sg.lab);
-        }
         rs_graph *h = nullptr;
-        st = rs::load_prebuilt(sg.pre, nullptr, &h);
+        rs_status st = rs::load_prebuilt(sg.pre, nullptr, &h);
         if (st == RS_OK) st = rs_score(h);
         if (st == RS_OK && (!sg.hist_src.empty() || !sg.hist_vert.empty())) {
             rs_removals b;
@@ -309,7 +325,6 @@ rs_status rs_server_add_graph(rs_server *s, const rs_csr *csr, int32_t *graph_id
     } catch (const std::bad_alloc &) {
         return rs::fail(RS_ERR_NOMEM, "host copy of the graph failed");
     }
-    sg.estimate = estimate_bytes(sg.n, sg.nnz);
     std::lock_guard<std::mutex> lk(s->mu);
     *graph_id = (int32_t)s->graphs.size();
     s->graphs.push_back(std::move(sg));
