@@ -327,7 +327,11 @@ void rs_free_graph(rs_graph *g);
  * applying the graph's batches one by one to a lone rs_graph.
  *
  *   rs_server_create      n_slots >= 1 workers; hbm_budget bytes of device
- *                         memory for resident graphs (<= 0: unlimited)
+ *                         memory for resident graphs (<= 0: unlimited): their
+ *                         buffers, those from 2 MiB on in whole 2 MiB as the
+ *                         device hands it out, and 1.07 MiB each for a stream;
+ *                         a graph's first load takes up to 16 MiB more until
+ *                         it is done
  *   rs_server_add_graph   copies the CSR (host arrays only) and returns its
  *                         id (0, 1, ...); nothing is loaded yet
  *   rs_server_submit      copies the batch; returns a request id at once
@@ -335,7 +339,8 @@ void rs_free_graph(rs_graph *g);
  *                         scores[k] receive its top-k (count of them), info
  *                         its timings (ns since the server started) and the
  *                         re-score's counts; the request is then forgotten
- *   rs_server_stats       loads, evictions, requests done, device bytes
+ *   rs_server_stats       loads, evictions, requests done, device bytes (as
+ *                         counted against the budget)
  * Errors: RS_ERR_ARG, RS_ERR_RANGE (graph id or vertex id), RS_ERR_GRAPH,
  * RS_ERR_NOMEM (a graph larger than the whole budget), RS_ERR_HIP; a failed
  * request reports its status through rs_server_wait.

@@ -436,8 +436,10 @@ struct Prebuilt;
 rs_status prebuild_graph(const rs_csr *csr, Prebuilt **out);
 rs_status load_prebuilt(Prebuilt *P, void *hip_stream, rs_graph **out);
 void free_prebuilt(Prebuilt *P);
-// The sizes of the device allocations that load_prebuilt makes.
+// The sizes of the device allocations that load_prebuilt makes, and the least
+// they are for any graph of n vertices and nnz entries.
 void prebuilt_allocations(const Prebuilt *P, size_t (&bytes)[3]);
+void least_allocations(int64_t n, int64_t nnz, size_t (&bytes)[3]);
 // counts[i] of source d_src[i] (internal ids; ns <= kMaxReachSources), with
 // comp [n], bits [ns * words] as scratch.
 rs_status launch_reach(rs_graph *g, const int32_t *d_src, int ns, int32_t *comp, unsigned int *bits, int words,

@@ -1098,13 +1098,19 @@ rs_status load_prebuilt(Prebuilt *P, void *hip_stream, rs_graph **out) {
 void free_prebuilt(Prebuilt *P) { delete P; }
 
 // (From the lists that the load itself allocates from.)
-void prebuilt_allocations(const Prebuilt *P, size_t (&bytes)[3]) {
+static void allocation_sizes(int64_t n, int64_t nnz, int64_t k, int64_t n_out, const HostTiles &H,
+                             size_t (&bytes)[3]) {
     DeviceGraph D;
-    set_sizes(D, P->n, P->nnz, (int64_t)P->H.comm2orig.size(), false);
-    const int64_t n_out = (int64_t)P->H.outl.size();
+    set_sizes(D, n, nnz, k, false);
     bytes[0] = group_bytes(vertex_reqs(D));
     bytes[1] = group_bytes(slot_reqs(D, n_out));
-    bytes[2] = group_bytes(tile_reqs(D, n_out, P->H));
+    bytes[2] = group_bytes(tile_reqs(D, n_out, H));
+}
+void prebuilt_allocations(const Prebuilt *P, size_t (&bytes)[3]) {
+    allocation_sizes(P->n, P->nnz, (int64_t)P->H.comm2orig.size(), (int64_t)P->H.outl.size(), P->H, bytes);
+}
+void least_allocations(int64_t n, int64_t nnz, size_t (&bytes)[3]) {
+    allocation_sizes(n, nnz, 1, 0, HostTiles(), bytes);
 }
 
 template <class T>

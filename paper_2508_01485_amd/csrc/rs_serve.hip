@@ -55,23 +55,39 @@ struct Request {
     bool done = false;
 };
 
-// Device bytes a resident graph is charged with.  The runtime hands out device
-// memory in chunks of 2 MiB and takes more for streams (25 MB and more with some
-// of the first): forty graphs whose own buffers hold 1.6 to 3.0 MB took 7.2 MB
-// of free device memory each.
-int64_t charge(int64_t bytes) {
-    constexpr int64_t kChunk = 2 << 20;
-    return (bytes + kChunk - 1) / kChunk * kChunk + kChunk;
+// Device bytes a resident graph is charged with: what its allocations and its
+// stream take of the device's free memory.  The runtime hands out 2 MiB at a
+// time: an allocation from 2 MiB on takes whole chunks, smaller ones share
+// chunks, and a stream takes 1.07 MiB.  48 handles each, taken per graph and
+// charged: n = 200 1.50 and 1.50 MiB, n = 3,000 3.00 and 2.72, n = 6,000 4.00 and
+// 4.02, n = 30,000 17.5 and 17.5, n = 100,000 50.9 and 50.3.  (Not counted: the 136
+// MiB that the process keeps for its first streams' queues and scratch.)
+constexpr int64_t kChunk = 2 << 20;
+constexpr int64_t kStreamBytes = 1096 << 10;
+int64_t charge(int64_t bytes) { return bytes < kChunk ? bytes : (bytes + kChunk - 1) / kChunk * kChunk; }
+int64_t charged_bytes(const rs_graph *h) {
+    int64_t b = kStreamBytes + charge(4 * h->rem_cap);
+    for (const auto &a : h->allocations) b += charge((int64_t)a.second);
+    return b;
 }
-int64_t charged_bytes(const rs_graph *h) { return charge(h->dev_bytes); }
 
-// What a graph is charged with before it was ever loaded, from the sizes of its
-// host form: the same allocations, so a load is neither refused nor let in on a
-// guess.
+// The same before the graph was ever loaded, from the sizes of its host form (the
+// same allocations, so a load is neither refused nor let in on a guess), and at
+// the least, before there is one.
+int64_t charge(const size_t (&sizes)[3]) {
+    int64_t b = kStreamBytes;
+    for (size_t s : sizes) b += charge((int64_t)s);
+    return b;
+}
 int64_t charged_bytes(const rs::Prebuilt *P) {
-    size_t b[3];
-    rs::prebuilt_allocations(P, b);
-    return charge((int64_t)(b[0] + b[1] + b[2]));
+    size_t sizes[3];
+    rs::prebuilt_allocations(P, sizes);
+    return charge(sizes);
+}
+int64_t least_charge(int64_t n, int64_t nnz) {
+    size_t sizes[3];
+    rs::least_allocations(n, nnz, sizes);
+    return charge(sizes);
 }
 
 // A first load finds this much more room, where the budget has it: the first
@@ -136,6 +152,41 @@ struct rs_server {
         return true;
     }
 
+    // Under mu: reserve `own` bytes for the graph of request r, and `room` more
+    // where the budget has it, in place of what it has reserved.
+    rs_status reserve(std::unique_lock<std::mutex> &lk, ServedGraph &sg, Request &r, int64_t own, int64_t room) {
+        if (budget > 0 && own > budget) {
+            r.error = "graph larger than the whole HBM budget";
+            return RS_ERR_NOMEM;
+        }
+        const int64_t need = budget > 0 ? std::min(own + room, budget) : own + room;
+        if (sg.bytes >= need) return RS_OK;
+        if (sg.bytes > 0) {  // (given back first: two that wait for more must not wait for each other)
+            used -= sg.bytes;
+            sg.bytes = 0;
+            cv_work.notify_all();
+        }
+        cv_work.wait(lk, [&] { return make_room(need, r.gid); });
+        used += need;
+        sg.bytes = need;
+        return RS_OK;
+    }
+
+    // Under mu: reserve device memory for a graph that is not resident.  Room is
+    // made when its turn comes, before its host form is built (by the first
+    // request); that form then has the sizes.
+    rs_status admit(std::unique_lock<std::mutex> &lk, ServedGraph &sg, Request &r) {
+        if (sg.known > 0) return reserve(lk, sg, r, sg.known, 0);
+        rs_status st = reserve(lk, sg, r, least_charge(sg.n, sg.nnz), kFirstLoadRoom);
+        if (st == RS_OK && !sg.pre) {
+            lk.unlock();
+            st = prebuild(sg);
+            if (st != RS_OK) r.error = rs_last_error();
+            lk.lock();
+        }
+        return st == RS_OK ? reserve(lk, sg, r, charged_bytes(sg.pre), kFirstLoadRoom) : st;
+    }
+
     void worker() {
         std::unique_lock<std::mutex> lk(mu);
         while (true) {
@@ -147,28 +198,8 @@ struct rs_server {
             sg.busy = true;
             r.info.t_start = now_ns();
             // residency: reserve the graph's bytes, evicting idle graphs
-            rs_status st = RS_OK;
-            bool fresh = false;
-            if (!sg.h && !sg.pre) {  // the host form first: it has the sizes
-                lk.unlock();
-                st = prebuild(sg);
-                if (st != RS_OK) r.error = rs_last_error();
-                lk.lock();
-            }
-            if (!sg.h && st == RS_OK) {
-                const int64_t own = sg.known > 0 ? sg.known : charged_bytes(sg.pre);
-                if (budget > 0 && own > budget) {
-                    st = RS_ERR_NOMEM;
-                    r.error = "graph larger than the whole HBM budget";
-                } else {
-                    int64_t need = own;
-                    if (sg.known == 0) need = budget > 0 ? std::min(own + kFirstLoadRoom, budget) : own + kFirstLoadRoom;
-                    cv_work.wait(lk, [&] { return make_room(need, r.gid); });
-                    used += need;
-                    sg.bytes = need;
-                    fresh = true;
-                }
-            }
+            const bool fresh = !sg.h;
+            rs_status st = fresh ? admit(lk, sg, r) : RS_OK;
             // sg is busy from here on: no other worker frees or replaces
             // its handle, and the handle is only published under mu
             rs_graph *h = sg.h;

@@ -42,3 +42,28 @@ def test_graphs_of_foreign_edges_wait_for_room():
     _compare(_alone(rs, graphs, reqs, 15), served)
     assert st["peak_device_bytes"] <= budget and st["evictions"] > 0, st
     print("[served budget] foreign edges", budget, st, flush=True)
+
+
+def test_small_graphs_stay_resident():
+    """Forty graphs of 200 vertices (half a MiB of buffers each) under 96 MiB:
+    none is evicted, and the budget's account is near what the device gave away."""
+    import torch
+
+    import paper_2508_01485_amd as rs
+    graphs = [lfr(200, 8.0, 50, 0.25, seed=i, cmin=10, cmax=60) for i in range(40)]
+    reqs = [(i % 40, None, np.array([i % 7])) for i in range(80)]
+    alone = _alone(rs, graphs, reqs, 10)  # (also the process's first streams)
+    srv = rs.RSServer(slots=2, hbm_budget=96 << 20)
+    try:
+        free = torch.cuda.mem_get_info()[0]
+        gids = [srv.add_graph(g.off, g.col, g.labels) for g in graphs]
+        rids = [srv.submit(gids[gi], 10, vertices=v) for gi, _, v in reqs]
+        served = [srv.wait(r) for r in rids]
+        taken, st = free - torch.cuda.mem_get_info()[0], srv.stats()
+    finally:
+        srv.free()
+    _compare(alone, served)
+    print("[served budget] small graphs", st, "device", taken, flush=True)
+    assert st["evictions"] == 0 and st["loads"] == 40, st
+    # 60 MiB; within a quarter and two chunks for sharing and the allocator's state
+    assert abs(st["device_bytes"] - taken) <= taken // 4 + (4 << 20), (st, taken)
