@@ -102,6 +102,7 @@ enum IncCounter {
     kIcVertices,                      // vertices removed
     kIcCount
 };
+constexpr int kPinK = 1024;  // top-k results that a handle's pinned memory holds from the load on
 // What rs_apply_removals reports, written by the device into pinned memory.
 struct RemovalCounts {
     unsigned long long edges, vertex_edges, vertices, affected;
@@ -357,16 +358,20 @@ struct rs_graph {
     // pinned staging of the readers' results (first use)
     char *read_host = nullptr;
     size_t read_cap = 0;
-    // pinned host buffer of the common top-k path: [flag | ids | scores]
+    // pinned host memory of the handle, made at load: the removals' counts, then
+    // the top-k's results [flag | ids | scores] for k up to kPinK (longer ones
+    // get a buffer of their own)
+    char *pin = nullptr;
     void *hpin = nullptr;
     int64_t hpin_cap = 0;
+    bool hpin_own = false;  // hpin is a buffer of its own
     // removal batches: device staging kept between calls (grown on demand),
     // pinned host staging of the batch and of the counts read back
     int32_t *rem_buf = nullptr;
     int64_t rem_cap = 0;
     int32_t *rem_host = nullptr;
     int64_t rem_host_cap = 0;
-    rs::RemovalCounts *rem_cnt_host = nullptr;       // pinned
+    rs::RemovalCounts *rem_cnt_host = nullptr;   // in pin
     bool ictr_dirty = false;                     // a re-score failed on its way: both counters need clearing
     hipEvent_t rem_ev = nullptr;                 // the removal counts have reached rem_cnt_host
 };

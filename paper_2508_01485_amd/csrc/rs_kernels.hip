@@ -3600,15 +3600,13 @@ rs_status launch_topk(rs_graph *g, int64_t k, int32_t *ids, double *scores, int6
     if (keff <= 0) return RS_OK;
     hipEvent_t ev;
     if (g->hpin_cap < keff) {
-        if (g->hpin) (void)hipHostFree(g->hpin);
-        g->hpin = nullptr;
-        g->hpin_cap = 0;
-        const hipError_t ea = hipHostMalloc(&g->hpin, 16 + 16 * (size_t)keff, hipHostMallocDefault);
-        if (ea != hipSuccess) {
-            g->hpin = nullptr;
-            return hip_fail(ea, "pinned top-k buffer");
-        }
+        void *p = nullptr;
+        const hipError_t ea = hipHostMalloc(&p, 16 + 16 * (size_t)keff, hipHostMallocDefault);
+        if (ea != hipSuccess) return hip_fail(ea, "pinned top-k buffer");
+        if (g->hpin_own) (void)hipHostFree(g->hpin);
+        g->hpin = p;
         g->hpin_cap = keff;
+        g->hpin_own = true;
     }
     const size_t sc_off = 16 + ((4 * (size_t)keff + 7) & ~(size_t)7);
     rs_status cst = topk_common(g, keff);

@@ -128,7 +128,10 @@ static void release(rs_graph *g) {
     if (g->stream) (void)hipStreamSynchronize(g->stream);
     for (auto &a : g->allocations) (void)hipFree(a.first);
     g->allocations.clear();
-    if (g->hpin) (void)hipHostFree(g->hpin);
+    if (g->hpin_own) (void)hipHostFree(g->hpin);
+    if (g->pin) (void)hipHostFree(g->pin);
+    g->hpin_own = false;
+    g->pin = nullptr;
     g->hpin = nullptr;
     g->hpin_cap = 0;
     if (g->bpin) (void)hipHostFree(g->bpin);
@@ -138,7 +141,6 @@ static void release(rs_graph *g) {
     g->read_cap = 0;
     if (g->rem_buf) (void)hipFree(g->rem_buf);
     if (g->rem_host) (void)hipHostFree(g->rem_host);
-    if (g->rem_cnt_host) (void)hipHostFree(g->rem_cnt_host);
     if (g->rem_ev) (void)hipEventDestroy(g->rem_ev);
     g->rem_ev = nullptr;
     if (g->reach_host) (void)hipHostFree(g->reach_host);
@@ -651,11 +653,39 @@ static hipError_t put_offsets(rs_graph *g, const std::vector<int64_t> &off, std:
     return hipMemcpyAsync(g->d.off, off32.data(), 4 * n1, hipMemcpyHostToDevice, g->stream);
 }
 
+// The handle's pinned memory and event, in one allocation (another 8 bytes or 16
+// KB cost 20 us to make and 250 to free).  A batch takes no removals and has its
+// own top-k.
+static rs_status alloc_pinned(rs_graph *g) {
+    constexpr size_t kCounts = 64;
+    static_assert(sizeof(RemovalCounts) <= kCounts, "the counts' place");
+    hipError_t e = hipSuccess;
+    if (!g->pin && g->n_graphs == 0) {
+        e = hipHostMalloc((void **)&g->pin, kCounts + 16 + 16 * (size_t)kPinK, hipHostMallocDefault);
+        if (e != hipSuccess) {
+            g->pin = nullptr;
+            return hip_fail(e, "pinned counters");
+        }
+        g->rem_cnt_host = (RemovalCounts *)g->pin;
+        g->hpin = g->pin + kCounts;
+        g->hpin_cap = kPinK;
+    }
+    if (!g->rem_ev && g->n_graphs == 0) {
+        e = hipEventCreateWithFlags(&g->rem_ev, hipEventDisableTiming);
+        if (e != hipSuccess) {
+            g->rem_ev = nullptr;
+            return hip_fail(e, "removal event");
+        }
+    }
+    return RS_OK;
+}
+
 // What follows once the rows, slots and out-lists are in place: the schedule
 // (cut in H), the links and the out-list entries' leaders.
 static rs_status finish_load(rs_graph *g, const HostGraph &H) {
     DeviceGraph &D = g->d;
-    rs_status st = upload_tiles(g, H);
+    rs_status st = alloc_pinned(g);
+    if (st == RS_OK) st = upload_tiles(g, H);
     if (st == RS_OK) st = launch_tables(g);
     if (st == RS_OK) st = launch_zero_u64(g, D.scratch_u, 1);
     if (st == RS_OK) st = launch_links(g, D.scratch_u);
@@ -1620,20 +1650,6 @@ rs_status rs_apply_removals(rs_graph *g, const rs_removals *b, rs_removal_result
     bool apart = m == 0 || nv == 0 || m <= kApartMax;  // no listed edge has a listed vertex
     for (int64_t i = 0; nv > 0 && apart && i < m; ++i)
         apart = !std::binary_search(vs.begin(), vs.end(), es[i]) && !std::binary_search(vs.begin(), vs.end(), ed[i]);
-    if (!g->rem_cnt_host) {  // (a graph that never loses an edge does without)
-        const hipError_t eh = hipHostMalloc((void **)&g->rem_cnt_host, sizeof(RemovalCounts), hipHostMallocDefault);
-        if (eh != hipSuccess) {
-            g->rem_cnt_host = nullptr;
-            return hip_fail(eh, "pinned counters");
-        }
-    }
-    if (!g->rem_ev) {
-        const hipError_t ee = hipEventCreateWithFlags(&g->rem_ev, hipEventDisableTiming);
-        if (ee != hipSuccess) {
-            g->rem_ev = nullptr;
-            return hip_fail(ee, "removal event");
-        }
-    }
     const int64_t need = std::max<int64_t>(2 * m + nv, 1);
     // staging kept between calls: grown (never shrunk) before anything is mutated
     if (need > g->rem_cap || need > g->rem_host_cap) {
