@@ -65,7 +65,8 @@ static void parallel_for(int64_t n, int64_t grain, F &&f) {
 
 // ------------------------------------------------------------ allocation
 // Optional fault injection for tests of the error paths: RS_FAULT_ALLOC=N
-// makes the N-th buffer asked for by every rs_load_graph call fail.
+// makes the N-th buffer that a handle asks for fail (a load counts from one),
+// RS_FAULT_ALLOC=load_scratch the scratch of a load on the device.
 struct DevReq {
     void **p;
     size_t bytes;
@@ -898,7 +899,8 @@ static rs_status load_on_device(const rs_csr *csr, rs_graph *g, bool *done) {
         }
     } tmp;
     tmp.s = s;
-    hipError_t e = hipMalloc((void **)&tmp.p, at[7]);
+    const char *f = std::getenv("RS_FAULT_ALLOC");
+    hipError_t e = f && std::strcmp(f, "load_scratch") == 0 ? hipErrorOutOfMemory : hipMalloc((void **)&tmp.p, at[7]);
     if (e != hipSuccess) {
         tmp.p = nullptr;
         return hip_fail(e, "load scratch");
