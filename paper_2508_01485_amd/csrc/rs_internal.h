@@ -236,7 +236,6 @@ struct TopkState {
     unsigned long long n_tie;    // tie-list fill counter
     unsigned int overflow;       // tie class too large for the pairwise ranker
     unsigned int done;           // threshold bin taken whole
-    unsigned int small;          // spare
 };
 
 struct DeviceGraph {

@@ -125,8 +125,8 @@ struct Logs {
 template <typename OffT>
 struct RowArgs {
     const OffT *off;
-    const int32_t *deg, *col, *lab;
-    const int32_t *clab;  // the community of each entry's neighbour (read in place of col and lab)
+    const int32_t *deg, *lab;
+    const int32_t *clab;  // the community of each entry's neighbour
     const TablesMem *tables;
     const RowTile *tiles;
     const int32_t *hubs;
@@ -951,7 +951,7 @@ struct ScoreArgs {
     const DevCounters *ctr;
 };
 
-// Sorted-range helpers on LDS arrays.
+// The first position in the sorted a[lo, hi) in LDS that holds x or more.
 __device__ __forceinline__ int lds_lower(const int *a, int lo, int hi, int x) {
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
@@ -961,10 +961,6 @@ __device__ __forceinline__ int lds_lower(const int *a, int lo, int hi, int x) {
             hi = mid;
     }
     return lo;
-}
-__device__ __forceinline__ bool lds_has(const int *a, int lo, int hi, int x) {
-    const int i = lds_lower(a, lo, hi, x);
-    return i < hi && a[i] == x;
 }
 
 // Out-lists keep removed entries complemented (~id) in place, so a list is
@@ -982,19 +978,6 @@ __device__ __forceinline__ int lds_find_out(const int *a, int n, int x) {
             hi = mid;
     }
     return lo < n && a[lo] == x ? lo : -1;
-}
-
-// Whether the n out-list entries a[0..n) in LDS hold the live id x.
-__device__ __forceinline__ bool lds_has_out(const int *a, int n, int x) {
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (out_id(a[mid]) < x)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    return lo < n && a[lo] == x;
 }
 
 // Position of the live id t in the sorted out-list outl[o0, o1) in HBM
@@ -1025,10 +1008,6 @@ __device__ __forceinline__ long long out_find(const int32_t *outl, long long o0,
     for (int j = 0; j < 16; ++j)
         if (lo + j < hi && y[j] == t) f = lo + j;
     return f;
-}
-
-__device__ __forceinline__ bool out_has(const int32_t *outl, long long o0, long long o1, int t) {
-    return out_find(outl, o0, o1, t) >= 0;
 }
 
 // The type-II terms of the pair (u, w), w a foreign neighbour of u (Lemma 2,
@@ -1646,7 +1625,7 @@ struct HubOutEdge {
     }
 };
 
-__device__ void score_hub_big(const ScoreArgs &A, ScoreHubBigShared &S, int hub, int chunk, double wmax) {
+__device__ void score_hub_big(const ScoreArgs &A, ScoreHubBigShared &S, int hub, int chunk) {
     const int tid = threadIdx.x;
     const int u = A.hubs[hub];
     const VMeta m = A.meta[u];
@@ -1863,7 +1842,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_score(ScoreArgs A) {
     int b = (int)blockIdx.x;
     if (b < n_big) {
         const int2 hc = A.hub_chunk[A.n_chunks_lds + b];
-        score_hub_big(A, S.h, hc.x, hc.y, wmax);
+        score_hub_big(A, S.h, hc.x, hc.y);
         return;
     }
     b -= n_big;
@@ -1910,7 +1889,7 @@ __global__ __launch_bounds__(kBlock) void k_score_inc(ScoreArgs A, const int32_t
         if (i < n_big) {
             const int c = full ? (int)i : big[i];
             const int2 hc = A.hub_chunk[A.n_chunks_lds + c];
-            score_hub_big(A, S.h, hc.x, hc.y, wmax);
+            score_hub_big(A, S.h, hc.x, hc.y);
         } else if (i < n_big + n_main) {
             const long long j = i - n_big;
             const int bl = full ? (int)j : main_[j];
@@ -2652,7 +2631,6 @@ static rs_status score_pass_t(rs_graph *g, bool inc) {
     RowArgs<OffT> A;
     A.off = (const OffT *)D.off;
     A.deg = D.deg;
-    A.col = D.col;
     A.lab = D.lab;
     A.clab = D.clab;
     A.tables = (const TablesMem *)D.tables;
