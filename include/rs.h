@@ -273,7 +273,6 @@ rs_status rs_load_batch(int32_t n_graphs, const int64_t *vertex_offsets, const r
                         uint32_t flags, rs_graph **out);
 rs_status rs_topk_batch(rs_graph *g, int64_t k, int32_t *ids, double *scores, int64_t *counts);
 
-/* rs_free_graph: release all device memory of g (NULL is ignored). */
 /*
  * The static schedule's cut-offs (the degree bins of the pass): a row tile
  * covers consecutive vertices with at most row_entries row entries and
@@ -310,6 +309,7 @@ rs_status rs_get_tiling(rs_graph *g, rs_tiling *t);
 rs_status rs_set_tiling(rs_graph *g, const rs_tiling *t);
 rs_status rs_autotune(rs_graph *g, int32_t n_cand, const rs_tiling *cand, int32_t reps, int32_t *best, double *ms);
 
+/* rs_free_graph: release all device memory of g (NULL is ignored). */
 void rs_free_graph(rs_graph *g);
 
 /*
@@ -318,7 +318,7 @@ void rs_free_graph(rs_graph *g);
  * host copy of each registered graph and loads it into device memory on its
  * first request, within an HBM budget: when a graph does not fit, idle graphs
  * are evicted least-recently-used first (an evicted graph is reloaded from
- * the validated, renumbered host form its first load built, with its removal
+ * the validated, renumbered host form its first request built, with its removal
  * history applied).  n_slots worker threads
  * take requests in submission order; requests on one graph run one at a time
  * in that order, requests on different graphs overlap on the device (each

@@ -32,8 +32,9 @@
 //   * Work is cut at load time into static tiles of consecutive vertices: row
 //     tiles bound the row capacity they cover, score tiles the number of
 //     foreign entries (removals only shrink both).  Vertices too large for a
-//     tile are hubs and get a workgroup of their own.  No kernel of a pass
-//     uses a same-address atomic; each workgroup writes its own partials.
+//     tile are hubs and get a workgroup of their own.  Each workgroup writes
+//     its own partials; the one same-address atomic of a pass is the ticket
+//     with which k_mid's up to 64 reducers of w_max finish.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -63,9 +64,9 @@ constexpr int kWorkBlocks = 1024;    // blocks (and partials) of the on-demand W
 constexpr int kMaxReachSources = 1024;  // sources per rs_reachable_communities call
 constexpr size_t kStaticScratchBytes = size_t(32) << 20;  // per-device array of rs_reachable_communities_static
 constexpr int kMaxDevices = 64;
-constexpr int kBatchK = 32;
+constexpr int kBatchK = 32;       // largest k of the per-graph top-k of a batch
 constexpr int kSegVerts = 1024;   // vertices per batched top-k segment (64 lanes x 16 keys)
-constexpr int kSegMax = 64;       // segments per graph merged by one wavefront          // largest k of the per-graph top-k of a batch
+constexpr int kSegMax = 64;       // segments per graph merged by one wavefront
 
 // An incremental re-score whose units exceed this many tenths of the full
 // pass's workgroups runs the full pass instead.

@@ -266,7 +266,7 @@ __device__ __forceinline__ int tile_of_block(int b, int n_hubs, int per_xcd) {
 // ------------------------------------------------------------ row tiles
 // A row tile is a run of consecutive vertices whose rows (capacity <=
 // kRowTile entries, a contiguous slice of col) are processed flat:
-//   1. every entry's neighbour label is gathered (coalesced col reads);
+//   1. every entry's neighbour community is read from clab (coalesced);
 //   2. an entry starts a run if it starts a row or its label differs from
 //      the previous entry's (rows are community-sorted, so each run is one
 //      interaction-matrix record); run starts are ranked with wavefront
@@ -1071,12 +1071,9 @@ __device__ __forceinline__ int block_excl_scan(int x, int *ws, int &total) {
     return base + incl - x;
 }
 
-// Store a hub chunk's partial; the chunk finishing last adds the partials
-// of the hub in chunk order and writes its score (one thread).
 // A hub chunk's partial (its pair terms and counts, summed over the block in a
-// fixed tree order) goes to its slot; k_hub_sum adds the chunks of each hub in
-// chunk order once the score kernels are done.  The chunk's counts also go to
-// the block totals.
+// fixed tree order) goes to its slot (one thread); k_hub_sum adds the chunks of
+// each hub in a fixed order once the score kernel is done.
 __device__ void hub_chunk_store(const ScoreArgs &A, const double *red, const long long (*ired)[kBlock / 64],
                                 int hub, int chunk) {
     HubPart hp;
@@ -1824,9 +1821,9 @@ union ScoreShared {
     ScoreUnitShared u;
     ScoreHubBigShared h;
 };
-// Six workgroups share a CU: with registers for seven the compiler spills 33 of
-// them (n = 3 million, mean degree 30: 1,413 against 1,362 us a pass; 128
-// graphs: 435 against 443).
+// Six workgroups share a CU, with 80 registers, 10 of them spilled (44 bytes a
+// lane): with registers for seven the compiler spills 33 of them (n = 3 million,
+// mean degree 30: 1,413 against 1,362 us a pass; 128 graphs: 435 against 443).
 static_assert(7 * sizeof(ScoreShared) <= 160 * 1024, "LDS for seven score workgroups per CU");
 
 // Algorithm 1 Step 3 (Eq. RSI) for every border vertex, in one launch: the
@@ -3067,7 +3064,8 @@ __global__ __launch_bounds__(kBlock) void k_list_hist(const TopkKey *list, const
 // they lie (16 regions of 4,096, four bins a thread in each, coalesced); the
 // region where the count from the top reaches `take` is found from the regions'
 // sums, then the thread, then the bin.  With 64 consecutive bins a thread and a
-// scan by doubling in LDS a level took 26 us, now 11.
+// scan by doubling in LDS a level took 26 us, now 11.  (The 16 quads of bins
+// take 96 registers and 32 bytes of scratch a lane.)
 __global__ __launch_bounds__(1024) void k_topk_find(unsigned int *hist, TopkState *st, int level) {
     constexpr int kRegions = kTopkBins / 4096;
     __shared__ unsigned int s_w[kRegions][16];
@@ -4814,7 +4812,11 @@ __global__ __launch_bounds__(kBlock) void k_cc_init(const OffT *off, const int32
 // kCcRounds of them (each flattened) the uniting sweep meets the same root
 // twice at nearly every edge.  Uniting from the start, where trees grow deep
 // while every lane climbs them, took 200 to 350 us at n = 10^5 with 4.6 edges
-// left a vertex (whole queries: one round 97 us, two 108, three 118).
+// left a vertex (whole queries: one round 97 us, two 108, three 118).  With five
+// live entries a vertex and more one round is the fastest or near it up to n =
+// 400,000 (n = 400,000, mean degree 12: 245, 289 and 328 us); sparser remainders
+// of large graphs would gain from more (n = 400,000 with 1.5: 1,741, 337 and 192;
+// n = 1 million with 5: 1,043, 403 and 446, with 2: 3,976, 890 and 294).
 constexpr int kCcRounds = 1;
 template <bool kUnite, typename OffT>
 __global__ __launch_bounds__(kBlock) void k_cc_hook(const OffT *off, const int32_t *deg, const int32_t *col,

@@ -3,10 +3,10 @@
 // rs_load_graph validates the caller's CSR (a simple undirected graph,
 // Section II), renumbers it so that every community is a contiguous id range
 // (labels ascending, caller ids ascending inside a community), re-sorts the
-// rows, bins the vertices by degree for the row kernel and uploads everything
-// to device memory owned by the handle.  All later calls run kernels on the
-// graph's stream (rs_kernels.hip); the host only marshals arguments, sizes
-// launches and copies results.
+// rows and cuts the schedule of tiles and hubs, into device memory owned by the
+// handle (large graphs: the rows are checked, renumbered and sorted on the
+// device).  All later calls run kernels on the graph's stream (rs_kernels.hip);
+// the host only marshals arguments, sizes launches and copies results.
 #include <algorithm>
 #include <array>
 #include <atomic>
@@ -698,13 +698,18 @@ static rs_status finish_load(rs_graph *g, const HostGraph &H) {
     if (st != RS_OK) return st;
     if (e == hipSuccess) e = es;
     if (e != hipSuccess) return hip_fail(e, "pair-slot map");
-    // The type-II values by slot cost each slot some 7 to 11 ps (its record
-    // and neighbour read once more); the pairs walking the runs themselves
-    // cost 14 to 41 ps a step.  With half the steps at 0.07 and 0.16 of the
-    // slots (n = 1 M, mean degree 20; 128 graphs of 200 to 50,000 vertices)
-    // the walks are faster (302 against 316 us a pass; 522 against 567), at
-    // 1.06 and 1.21 (n = 3 M, mean degree 30; n = 150 K, mean degree 71) the
-    // values by slot (1,818 against 2,675 us; 686 against 776).
+    // The type-II values by slot cost each slot its record and neighbour once
+    // more; the pairs walking the runs themselves cost a gather a step, by one
+    // lane.  Passes by slot against walks, with half the steps (walk) as a share
+    // of the slots: 0.07 164 against 156 us (n = 1 million, mean degree 20), 0.17
+    // 126 against 118 (n = 300,000), 0.22 387 against 372, 0.27 594 against 568
+    // (n = 1 million, mean degree 30, mixing 0.3), 0.39 99 against 95 (n =
+    // 100,000, mean degree 40), 0.43 340 against 383 (n = 1 million, hubs of
+    // 30,000), 0.48 246 against 256 (n = 300,000), and, with earlier kernels,
+    // 1.06 1,818 against 2,675 (n = 3 million, mean degree 30) and 1.21 686
+    // against 776 (n = 150,000, mean degree 71).  Below the line of a quarter
+    // the walks are faster; up to 0.4 the values by slot lose 4 to 6 %, but
+    // hubs' long runs are never left to one lane.
     g->type2_by_slot = 4 * walk >= 2 * (unsigned long long)g->n_out;
     g->n_alive = D.n;
     return RS_OK;
