@@ -654,9 +654,9 @@ static hipError_t put_offsets(rs_graph *g, const std::vector<int64_t> &off, std:
     return hipMemcpyAsync(g->d.off, off32.data(), 4 * n1, hipMemcpyHostToDevice, g->stream);
 }
 
-// The handle's pinned memory and event, in one allocation (another 8 bytes or 16
-// KB cost 20 us to make and 250 to free).  A batch takes no removals and has its
-// own top-k.
+// The handle's pinned memory, in one allocation (64 bytes or 16 KB: 12 us to make
+// and 12 to free), and its event.  A batch takes no removals and has its own
+// top-k.
 static rs_status alloc_pinned(rs_graph *g) {
     constexpr size_t kCounts = 64;
     static_assert(sizeof(RemovalCounts) <= kCounts, "the counts' place");
@@ -685,8 +685,7 @@ static rs_status alloc_pinned(rs_graph *g) {
 // (cut in H), the links and the out-list entries' leaders.
 static rs_status finish_load(rs_graph *g, const HostGraph &H) {
     DeviceGraph &D = g->d;
-    rs_status st = alloc_pinned(g);
-    if (st == RS_OK) st = upload_tiles(g, H);
+    rs_status st = upload_tiles(g, H);
     if (st == RS_OK) st = launch_tables(g);
     if (st == RS_OK) st = launch_zero_u64(g, D.scratch_u, 1);
     if (st == RS_OK) st = launch_links(g, D.scratch_u);
@@ -694,6 +693,7 @@ static rs_status finish_load(rs_graph *g, const HostGraph &H) {
     unsigned long long walk = 0;
     hipError_t e = hipMemcpyAsync(&walk, D.scratch_u, 8, hipMemcpyDeviceToHost, g->stream);
     if (e == hipSuccess) st = launch_out_entries(g);
+    if (st == RS_OK) st = alloc_pinned(g);                  // (while the device works)
     const hipError_t es = hipStreamSynchronize(g->stream);  // (on an error too: walk is this frame's)
     if (st != RS_OK) return st;
     if (e == hipSuccess) e = es;
